@@ -27,6 +27,12 @@ SQ_HD float div_by_reciprocal(float w, float s, float r) {
   return __builtin_fmaf(e0, r, q0);
 }
 
+// One step from an estimate r0 of 1 / s: r0 (2 - s r0), the residual 1 - s r0 in one FMA.
+SQ_HD float refine_reciprocal(float s, float r0) {
+  const float e = __builtin_fmaf(-s, r0, 1.0f);
+  return __builtin_fmaf(e, r0, r0);
+}
+
 SQ_HD int32_t imax2(int32_t a, int32_t b) { return a > b ? a : b; }
 SQ_HD int32_t imin2(int32_t a, int32_t b) { return a < b ? a : b; }
 SQ_HD int32_t imax3(int32_t a, int32_t b, int32_t c) { return imax2(imax2(a, b), c); }

@@ -85,6 +85,11 @@ __device__ __forceinline__ TensorDesc locate(const LaunchArgs& a, int g, int& m)
   return d;
 }
 
+// RN(1 / s) for 2^-100 < s < 2^100: the hardware's estimate is within one unit in the last
+// place of 1 / s, and one step from such an estimate gives the correctly rounded value
+// (checked for every significand and every such estimate by tests/host_reciprocal.cpp).
+__device__ __forceinline__ float reciprocal(float s) { return refine_reciprocal(s, __builtin_amdgcn_rcpf(s)); }
+
 __device__ __forceinline__ int sign_of(int64_t v) { return (v > 0) - (v < 0); }
 
 // k = round(|e|), an exact half rounded down (Algorithm 2, "k = round(|e|)").

@@ -390,12 +390,4 @@ __device__ __forceinline__ void generic_channel(const LaunchArgs& a, const Tenso
   emit_channel_bytes(code, L, d.out, m, s, a.out_format, tid, T);
 }
 
-__global__ void __launch_bounds__(1024) squant_channel_generic(LaunchArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ GenericShared gs;
-  int m;
-  const TensorDesc d = locate(a, blockIdx.x, m);
-  generic_channel(a, d, m, smem, gs);
-}
-
 }  // namespace squant

@@ -20,16 +20,14 @@
 
 #include "squant.h"
 
+#include "squant_act.h"
 #include "squant_common.h"
 #include "squant_generic.h"
-#include "squant_k9.h"
-#include "squant_ks.h"
-#include "squant_k1.h"
 #include "squant_k1_wave.h"
-#include "squant_mixed.h"
-#include "squant_stream.h"
-#include "squant_act.h"
+#include "squant_kernels.h"
+#include "squant_k9.h"
 #include "squant_plan.h"
+#include "squant_stream.h"
 
 namespace {
 
@@ -164,46 +162,6 @@ bool mixable(const Plan& p, size_t lds_cap) {
          p.lds <= lds_cap;
 }
 
-typedef void (*kernel_t)(LaunchArgs);
-
-// The small-kernel variant's instantiation for (K, kernels per thread), workgroup size and mode.
-template <int K, int KPT>
-kernel_t ks_kernel_of(int threads, int mode, bool largest) {
-#define SQ_KS_ROW(T)                                                                          \
-  {squant_channel_ks<T, SQUANT_MODE_E, K, KPT>, squant_channel_ks<T, SQUANT_MODE_EK, K, KPT>, \
-   squant_channel_ks<T, SQUANT_MODE_EKC, K, KPT>, squant_channel_ks<T, SQUANT_MODE_EC, K, KPT>}
-  static const kernel_t small[4] = SQ_KS_ROW(256);
-  if (threads <= 256 || !largest) return small[mode];
-  if constexpr (KPT == (1 << ks_max_kpt_log2(K))) {
-    static const kernel_t large[4] = SQ_KS_ROW(1024);
-    return large[mode];
-  }
-#undef SQ_KS_ROW
-  return small[mode];
-}
-template <int K>
-kernel_t ks_kernel_k(int kpt, int threads, int mode) {
-  const bool largest = kpt == (1 << ks_max_kpt_log2(K));
-  constexpr int top = 1 << ks_max_kpt_log2(K);
-  if (kpt == 1) return ks_kernel_of<K, 1>(threads, mode, largest);
-  if constexpr (top >= 2) if (kpt == 2) return ks_kernel_of<K, 2>(threads, mode, largest);
-  if constexpr (top >= 4) if (kpt == 4) return ks_kernel_of<K, 4>(threads, mode, largest);
-  if constexpr (top >= 8) if (kpt == 8) return ks_kernel_of<K, 8>(threads, mode, largest);
-  return nullptr;
-}
-kernel_t ks_kernel(int variant, int threads, int mode) {
-  const int kpt = ks_variant_kpt(variant);
-  switch (ks_variant_k(variant)) {
-    case 2: return ks_kernel_k<2>(kpt, threads, mode);
-    case 3: return ks_kernel_k<3>(kpt, threads, mode);
-    case 4: return ks_kernel_k<4>(kpt, threads, mode);
-    case 5: return ks_kernel_k<5>(kpt, threads, mode);
-    case 7: return ks_kernel_k<7>(kpt, threads, mode);
-    case 25: return ks_kernel_k<25>(kpt, threads, mode);
-    default: return nullptr;
-  }
-}
-
 // Launches tensors [begin, end) of a group (at most kInlineDescs of them) as one kernel.
 int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, int output, int wtype,
                 int wave_span, hipStream_t st) {
@@ -237,65 +195,22 @@ int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, in
   a.out_format = output;
   a.wtype = wtype;
   a.wave_span = wave_span;
-#define SQ_K9_ROW(T, KPT)                                                                     \
-  {squant_channel_k9<T, SQUANT_MODE_E, KPT>, squant_channel_k9<T, SQUANT_MODE_EK, KPT>,       \
-   squant_channel_k9<T, SQUANT_MODE_EKC, KPT>, squant_channel_k9<T, SQUANT_MODE_EC, KPT>}
-  static const kernel_t k9x1[4] = SQ_K9_ROW(256, 1);
-  static const kernel_t k9x2[4] = SQ_K9_ROW(256, 2);
-  static const kernel_t k9x4[4] = SQ_K9_ROW(256, 4);
-  static const kernel_t k9x4_large[4] = SQ_K9_ROW(1024, 4);
-#undef SQ_K9_ROW
-  // four kernels per thread in workgroups of exactly two waves (cin 260 .. 512) or one
-  // (cin 152 .. 256): weight type and wave count compiled in
-#define SQ_K9_ROW_X(WT, NWC)                                                                  \
-  {squant_channel_k9<256, SQUANT_MODE_E, 4, WT, NWC>, squant_channel_k9<256, SQUANT_MODE_EK, 4, WT, NWC>, \
-   squant_channel_k9<256, SQUANT_MODE_EKC, 4, WT, NWC>, squant_channel_k9<256, SQUANT_MODE_EC, 4, WT, NWC>}
-  static const kernel_t k9x4_two_waves[3][4] = {SQ_K9_ROW_X(SQUANT_W_F32, 2), SQ_K9_ROW_X(SQUANT_W_F16, 2),
-                                                SQ_K9_ROW_X(SQUANT_W_BF16, 2)};
-  static const kernel_t k9x4_one_wave[4] = SQ_K9_ROW_X(SQUANT_W_F32, 1);
-#undef SQ_K9_ROW_X
-#define SQ_K1_ROW(NV)                                                                         \
-  {squant_channel_k1<SQUANT_MODE_E, NV>, squant_channel_k1<SQUANT_MODE_E, NV>,                \
-   squant_channel_k1<SQUANT_MODE_EKC, NV>, squant_channel_k1<SQUANT_MODE_EKC, NV>}
-  // (for one-element kernels E&K equals E and E&C equals E&K&C)
-  static const kernel_t k1[8][4] = {SQ_K1_ROW(1), SQ_K1_ROW(2), SQ_K1_ROW(3), SQ_K1_ROW(4),
-                                    SQ_K1_ROW(5), SQ_K1_ROW(6), SQ_K1_ROW(7), SQ_K1_ROW(8)};
-  static const kernel_t k1x16[4] = SQ_K1_ROW(16);
-#define SQ_K1W_ROW(NV)                                                                        \
-  {squant_channel_k1_wave<SQUANT_MODE_E, NV>, squant_channel_k1_wave<SQUANT_MODE_E, NV>,      \
-   squant_channel_k1_wave<SQUANT_MODE_EKC, NV>, squant_channel_k1_wave<SQUANT_MODE_EKC, NV>}
-  static const kernel_t k1w[7][4] = {SQ_K1W_ROW(2), SQ_K1W_ROW(3), SQ_K1W_ROW(4), SQ_K1W_ROW(5),
-                                     SQ_K1W_ROW(6), SQ_K1W_ROW(7), SQ_K1W_ROW(8)};
-#undef SQ_K1W_ROW
-#undef SQ_K1_ROW
-  static const kernel_t k1s[4] = {squant_channel_k1_stream<SQUANT_MODE_E>, squant_channel_k1_stream<SQUANT_MODE_E>,
-                                  squant_channel_k1_stream<SQUANT_MODE_EKC>, squant_channel_k1_stream<SQUANT_MODE_EKC>};
-  static const kernel_t stream[4] = {squant_channel_stream<SQUANT_MODE_E>, squant_channel_stream<SQUANT_MODE_EK>,
-                                     squant_channel_stream<SQUANT_MODE_EKC>, squant_channel_stream<SQUANT_MODE_EC>};
-  static const kernel_t k1team[4] = {squant_channel_k1_team<SQUANT_MODE_E>, squant_channel_k1_team<SQUANT_MODE_E>,
-                                     squant_channel_k1_team<SQUANT_MODE_EKC>, squant_channel_k1_team<SQUANT_MODE_EKC>};
-  static const kernel_t dw9[4] = {squant_channel_dw9<SQUANT_MODE_E>, squant_channel_dw9<SQUANT_MODE_EK>,
-                                  squant_channel_dw9<SQUANT_MODE_EKC>, squant_channel_dw9<SQUANT_MODE_EC>};
-  static const kernel_t mixed[4] = {squant_channel_mixed<SQUANT_MODE_E>, squant_channel_mixed<SQUANT_MODE_EK>,
-                                    squant_channel_mixed<SQUANT_MODE_EKC>, squant_channel_mixed<SQUANT_MODE_EC>};
-  static const kernel_t ksmixed[4] = {squant_channel_ks_mixed<SQUANT_MODE_E>, squant_channel_ks_mixed<SQUANT_MODE_EK>,
-                                      squant_channel_ks_mixed<SQUANT_MODE_EKC>, squant_channel_ks_mixed<SQUANT_MODE_EC>};
-  const kernel_t kernel = is_ks(g.variant) ? ks_kernel(g.variant, g.threads, mode)
-                          : g.variant == kKsMixed ? ksmixed[mode]
-                          : (g.variant == kMixed || g.variant == kMixedWave) ? mixed[mode]
-                          : g.variant == kK1x16 ? k1x16[mode]
-                          : is_k1_wave(g.variant) ? k1w[g.variant - kK1Wave - 2][mode]
-                          : k1_variant_nv(g.variant) ? k1[k1_variant_nv(g.variant) - 1][mode]
-                          : g.variant == kK1Stream ? k1s[mode]
-                          : g.variant == kStream ? stream[mode]
-                          : g.variant == kDw9 ? dw9[mode]
-                          : g.variant == kK1Team ? k1team[mode]
-                          : g.variant == kK9x1 ? k9x1[mode]
-                          : g.variant == kK9x2 ? k9x2[mode]
-                          : g.variant == kK9x4 ? (g.threads == 2 * kWave ? k9x4_two_waves[wtype][mode]
-                                                  : g.threads == kWave && wtype == SQUANT_W_F32 ? k9x4_one_wave[mode]
-                                                  : g.threads <= 256 ? k9x4[mode] : k9x4_large[mode])
-                                               : squant_channel_generic;
+  const int nv = k1_variant_nv(g.variant);
+  bool tail = false;  // 1x1 / FC rows: any that is no whole number of 16-byte vectors
+  for (size_t i = begin; i < end; ++i) tail |= g.t[i].N % (wtype == SQUANT_W_F32 ? 4 : 8) != 0;
+  const kernel_t kernel = is_ks(g.variant) ? ks_kernel(ks_variant_k(g.variant), ks_variant_kpt(g.variant), g.threads, mode)
+                          : g.variant == kKsMixed ? ks_mixed_kernel(mode)
+                          : (g.variant == kMixed || g.variant == kMixedWave) ? mixed_kernel(mode, wtype)
+                          : is_k1_wave(g.variant) ? k1_wave_kernel(g.variant - kK1Wave, mode, wtype, tail)
+                          : nv ? k1_kernel(nv, mode, wtype, tail)
+                          : g.variant == kK1Stream ? k1_stream_kernel(mode)
+                          : g.variant == kStream ? stream_kernel(mode)
+                          : g.variant == kDw9 ? dw9_kernel(mode)
+                          : g.variant == kK1Team ? k1_team_kernel(mode)
+                          : g.variant == kK9x1 ? k9_kernel(1, g.threads, mode, wtype)
+                          : g.variant == kK9x2 ? k9_kernel(2, g.threads, mode, wtype)
+                          : g.variant == kK9x4 ? k9_kernel(4, g.threads, mode, wtype)
+                                               : generic_kernel();
   if (!kernel) return SQUANT_ERR_UNSUPPORTED;
   size_t lds = g.lds;
   if (g.wave_members) lds = std::max(lds, (size_t)(g.threads / kWave) * sizeof(K1WaveSel));

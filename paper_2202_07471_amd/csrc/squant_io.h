@@ -62,6 +62,49 @@ __device__ __forceinline__ void store_global_u16(void* p, uint16_t v) {
 #endif
 }
 
+// ---- buffer access: a descriptor of `bytes` bytes at p (uniform over the wave) ----
+// The hardware checks every dword (every unit of a narrower access) against the range: one that
+// does not lie inside as a whole reads as 0 and is not written, so rows of any length need no
+// bounds checks; any byte alignment is taken.  Offsets: per lane, and uniform.
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+__device__ __forceinline__ rsrc_t make_rsrc(const void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+constexpr int kNonTemporal = 2;  // the non-temporal bit of the cache policy: rows are touched once
+__device__ __forceinline__ vu4 buffer_load_u4_stream(rsrc_t r, uint32_t lane_off, uint32_t off) {
+  return __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)off, kNonTemporal);
+}
+__device__ __forceinline__ vu2 buffer_load_u2_stream(rsrc_t r, uint32_t lane_off, uint32_t off) {
+  return __builtin_amdgcn_raw_buffer_load_b64(r, (int)lane_off, (int)off, kNonTemporal);
+}
+// The uniform offset joins the lane's here and not the instruction's scalar operand: a 16-byte
+// store with one is still reading its data when the next instruction may write those registers,
+// and the compiler only keeps the two apart where there is none (first components of some lanes
+// came out as the next vector's).
+__device__ __forceinline__ void buffer_store_u4_stream(vu4 v, rsrc_t r, uint32_t lane_off, uint32_t off) {
+  __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)(lane_off + off), 0, kNonTemporal);
+}
+__device__ __forceinline__ void buffer_store_u2_stream(vu2 v, rsrc_t r, uint32_t lane_off, uint32_t off) {
+  __builtin_amdgcn_raw_buffer_store_b64(v, r, (int)lane_off, (int)off, kNonTemporal);
+}
+__device__ __forceinline__ void buffer_store_u1_stream(uint32_t v, rsrc_t r, uint32_t lane_off, uint32_t off) {
+  __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)lane_off, (int)off, kNonTemporal);
+}
+__device__ __forceinline__ void buffer_store_u16_stream(uint16_t v, rsrc_t r, uint32_t lane_off, uint32_t off) {
+  __builtin_amdgcn_raw_buffer_store_b16(v, r, (int)lane_off, (int)off, kNonTemporal);
+}
+#else  // the host pass only parses the kernels
+struct rsrc_t {};
+__device__ rsrc_t make_rsrc(const void*, uint32_t);
+__device__ vu4 buffer_load_u4_stream(rsrc_t, uint32_t, uint32_t);
+__device__ vu2 buffer_load_u2_stream(rsrc_t, uint32_t, uint32_t);
+__device__ void buffer_store_u4_stream(vu4, rsrc_t, uint32_t, uint32_t);
+__device__ void buffer_store_u2_stream(vu2, rsrc_t, uint32_t, uint32_t);
+__device__ void buffer_store_u1_stream(uint32_t, rsrc_t, uint32_t, uint32_t);
+__device__ void buffer_store_u16_stream(uint16_t, rsrc_t, uint32_t, uint32_t);
+#endif
+
 // ---- binary16 / bfloat16 weights: widened exactly to binary32 on load ----
 __device__ __forceinline__ float widen_f16(uint32_t bits) {  // low 16 bits
   return (float)__builtin_bit_cast(_Float16, (uint16_t)bits);

@@ -1,57 +1,54 @@
-// SQuant kernel for 1x1 convolutions and fully connected layers (K = kh*kw = 1).
+// SQuant kernels for 1x1 convolutions and fully connected layers (K = kh*kw = 1).
 //
 // With one element per kernel SQuant-K has nothing to do (k = round(|p|) = 0 for |p| <= 0.5,
 // Section 3.4), every element is its own kernel, and its rounding perturbation is its
-// SQuant-C candidate (Algorithm 3, "under SQuant" with k = 0).  One workgroup per output
-// channel; a thread takes NV 16-byte vectors of the channel, vector j of thread t being
-// vector t + j*T, so every load instruction of a wave reads 1 KB of consecutive weights.
-// SQuant-E runs in registers and leaves the codes there, four to a dword (rounding by a magic
-// addition leaves code + 128 in the sum's low byte, see squant_k9.h); SQuant-C is an LDS radix
-// select over the signed perturbations of all cin elements of the channel that marks the
-// elements to flip in a per-thread bit mask; the mask is applied to the packed codes and the
-// thread writes its own vectors out, so the codes never pass through LDS and the channel
-// needs no barrier after the selection.  The perturbations stay in the biased form the
-// conversion leaves them in (kQ23Bias + P): sums, bins and thresholds all work on that form.
+// SQuant-C candidate (Algorithm 3, "under SQuant" with k = 0).  A TEAM of threads owns an
+// output channel: a whole workgroup (squant_channel_k1) or, for channels of up to 2048
+// elements, a single wave (squant_k1_wave.h).  A thread holds NE elements in vectors of VE
+// (16 bytes: four binary32 or eight 16-bit weights; 8 bytes where an odd number of four-element
+// vectors is wanted): vector j of thread t is vector t + j*T of the channel, so every load
+// instruction of a wave reads 1 KB of consecutive weights.  The weights never touch LDS, the
+// codes never leave the registers until they are stored.
+//
+// The kernels are bound by the vector instructions issued per weight (a wave64 instruction
+// occupies its SIMD for two to four cycles), so everything per element is counted:
+//   * loads and stores are buffer instructions on a descriptor of the channel's row: one
+//     address register for all vectors, and the hardware's range check takes the place of the
+//     per-vector bounds checks (out-of-range dwords read as 0 and are not written);
+//   * SQuant-E is 9.75 instructions an element: three for the exact quotient, rounding by a
+//     magic addition that leaves code + 128 in the sum's low byte (squant_k9.h), the biased
+//     Q23 perturbation by one FMA.  The clamp to +-qmax can only move the element that set the
+//     scale, by one rounding, so it is left out and such elements are mended afterwards in the
+//     few channels that have one;
+//   * SQuant-C needs the `need` = round(|sum|) elements with the largest perturbation of one
+//     sign, a handful in thousands.  It is found by threshold search: two instructions an
+//     element (compare into the carry, add-with-carry) give a mask of the elements at or above
+//     a threshold, a population count says how many they are.  The first threshold comes from
+//     the density of evenly spread perturbations and aims a little below the need-th largest;
+//     on Gaussian or heavy-tailed weights it is the only one (1.0 to 1.1 passes on average at 3
+//     bits and more, about 2 where few weights are left outside the centre).  The elements
+//     between the best bounds found, at most kListCap, go to a list in LDS and are ranked there.
+// The version before counted every element into an LDS histogram (three instructions and an LDS
+// atomic), took two passes of two instructions over it and checked bounds per vector.  Vector
+// instructions per wave, before and after, and time:
+//   bfloat16 -> packed 4 bit, cin 4096, one wave of 64 elements a lane: 1958 -> 1352
+//     (six linear layers, 201 M weights: 254 -> 119 us, 2.0 -> 4.2 TB/s)
+//   binary16 -> int8, cin 512, four channels a wave: 1499 -> 1046
+//     (64 x [2048, 512], 67 M weights: 81 -> 59 us, 2.5 -> 3.4 TB/s)
 #pragma once
 
 #include <type_traits>
 
 #include "squant_common.h"
 #include "squant_io.h"
-#include "squant_k9.h"  // K9Shared, rounding constants, pack_low_bytes
+#include "squant_k9.h"  // rounding constants, pack_low_bytes
 #include "squant_select.h"
 
 namespace squant {
 
-__device__ __forceinline__ vf4 load_global_f4_stream(const float* p) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  return __builtin_nontemporal_load(
-      reinterpret_cast<const __attribute__((address_space(1))) vf4*>(reinterpret_cast<uintptr_t>(p)));
-#else
-  return *reinterpret_cast<const vf4*>(p);
-#endif
-}
-
-// ---------------------------------------------------------------------------
-// SQuant-C for one-element kernels.  Every element is a candidate and its candidate value is
-// its own rounding perturbation P (Q23, |P| <= 2^22), so the selection works on P directly:
-// the `need` elements with the largest |P| among those with the sign of the channel sum,
-// lowest index first on ties.  A radix select over the signed value:
-//   level 0  257 bins of P >> 15, counted into LDS before the channel sum (and with it the
-//            wanted sign) is known: negative P in bins 0..127, P >= 0 in bins 128..256.  The
-//            scan runs from the outside in over the wanted sign's bins only.
-//   below    u = P (sum > 0) or ~P (sum < 0) orders the wanted side "larger is better";
-//            bits 14..7 and 7..0 of u get a 256-bin pass each while the boundary bin still
-//            holds more keys than the ranking list takes.
-// A thread keeps the elements still undecided as a bit mask.  P = 0 is no candidate but
-// shares bin 128 with small positive P: when the scan ends in that bin the members are
-// counted again exactly.
-// ---------------------------------------------------------------------------
-// The routines below serve a whole workgroup on one channel (WAVE = false) or a single wave on
-// a channel of its own (WAVE = true, squant_k1_wave.h): then the "threads" are the wave's lanes
-// and a barrier only has to keep the compiler from moving LDS accesses across it (the LDS
-// handles a wave's instructions in order).  `Sel` is SelectShared or a structure with the same
-// members.
+// ---- what differs between a workgroup on one channel and a wave on a channel of its own ----
+// WAVE: the "threads" are the wave's lanes and a barrier only has to keep the compiler from
+// moving LDS accesses across it (the LDS handles a wave's instructions in order).
 template <bool WAVE>
 __device__ __forceinline__ int k1_tid() {
   if (!WAVE) return (int)threadIdx.x;
@@ -75,710 +72,530 @@ __device__ __forceinline__ void k1_sync() {
   }
 }
 
-__device__ __forceinline__ void k1_count(SelectShared& sh, int32_t P) {
-  atomicAdd(&sh.hist[(P >> 15) + 128], 1u);
-}
-// The same for a perturbation in biased form: bits 15..23 of kQ23Bias + P are 128 + (P >> 15)
-// (the bias has 128 there and zeros below, and the bin stays within 0..256).
-template <typename Sel>
-__device__ __forceinline__ void k1_count_biased(Sel& sh, uint32_t pb) {
-  static_assert(((kQ23Bias >> 15) & 511u) == 128u && (kQ23Bias & 0x7FFFu) == 0u, "bin taken from the biased bits");
-  atomicAdd(&sh.hist[(pb >> 15) & 511u], 1u);
-}
+// LDS of a team: the ranking list and, for a workgroup, what its waves exchange.
+struct alignas(16) K1List {
+  uint64_t list[kListCap + 8];  // padding: the ranking reads entries in eights
+};
+struct alignas(16) K1Shared : K1List {
+  float red_f[16];
+  int64_t red_i[16];
+  uint32_t cnt[2][16];  // counts per wave, two sets in turn
+  uint32_t list_count;
+};
 
-// Level 0 scan, by every wave on its own.  Returns the boundary bin in u units
-// (d = u >> 15 of the need-th best key, 0..128), or -1 when the wanted side holds fewer than
-// `need` keys; need_at = keys still wanted inside that bin, count_at = keys in it.
-__device__ __forceinline__ int k1_scan_top(const uint32_t* hist, int sgn, uint32_t need,
-                                           uint32_t& need_at, uint32_t& count_at) {
-  const int lane = threadIdx.x & (kWave - 1);
-  // traversal order: sum > 0 from bin 259 (padding) down to 128, sum < 0 from bin 0 up to 127
-  const bool on = sgn > 0 ? lane <= 32 : lane <= 31;
-  const int quad = sgn > 0 ? 64 - lane : lane;
-  uint4 h = make_uint4(0, 0, 0, 0);
-  if (on) h = reinterpret_cast<const uint4*>(hist)[quad];
-  const uint32_t a0 = sgn > 0 ? h.w : h.x, a1 = sgn > 0 ? h.z : h.y;
-  const uint32_t a2 = sgn > 0 ? h.y : h.z, a3 = sgn > 0 ? h.x : h.w;
-  const uint32_t mine = a0 + a1 + a2 + a3;
-  const uint32_t incl = wave_prefix_sum(mine);
-  const unsigned long long reach = __ballot(incl >= need);
-  if (reach == 0ull) { need_at = 0; count_at = 0; return -1; }
-  const int l = __builtin_ctzll(reach);
-  const uint32_t above = (uint32_t)__builtin_amdgcn_readlane((int)(incl - mine), l);
-  const uint32_t b0 = (uint32_t)__builtin_amdgcn_readlane((int)a0, l);
-  const uint32_t b1 = (uint32_t)__builtin_amdgcn_readlane((int)a1, l);
-  const uint32_t b2 = (uint32_t)__builtin_amdgcn_readlane((int)a2, l);
-  const uint32_t b3 = (uint32_t)__builtin_amdgcn_readlane((int)a3, l);
-  int t = 4 * l;  // position in traversal order
-  if (above + b0 >= need) { need_at = need - above; count_at = b0; }
-  else if (above + b0 + b1 >= need) { need_at = need - above - b0; count_at = b1; t += 1; }
-  else if (above + b0 + b1 + b2 >= need) { need_at = need - above - b0 - b1; count_at = b2; t += 2; }
-  else { need_at = need - above - b0 - b1 - b2; count_at = b3; t += 3; }
-  // bin index = 259 - t (sum > 0) or t (sum < 0); u >> 15 = bin - 128 resp. ~(bin - 128)
-  return (sgn > 0 ? 131 : 127) - t;
-}
-
-// Ranks the `count` (key, index) pairs of the list against each other: larger key first, then
-// lower index; the first `need` flip.  Four lanes share a pair, each comparing it with every
-// fourth group of four list entries (two 16-byte LDS reads per group), and add their counts
-// up inside the quad.  Slots past `count` hold (0, 0xFFFFFFFF), which ranks below every pair.
-// After a barrier that follows the last push.
-__device__ __forceinline__ void k1_rank_list(SelectShared& sh, uint32_t count, uint32_t need, int sgn,
-                                             uint32_t* code32) {
-  const uint32_t sub = threadIdx.x & 3u, groups = (count + 3u) >> 2;
-  const uint4* key4 = reinterpret_cast<const uint4*>(sh.list_key);
-  const uint4* n4 = reinterpret_cast<const uint4*>(sh.list_n);
-  for (uint32_t i = threadIdx.x >> 2; i < count; i += blockDim.x >> 2) {
-    const uint32_t key = sh.list_key[i], n = sh.list_n[i];
-    int rank = 0;
-    for (uint32_t g = sub; g < groups; g += 4) {
-      const uint4 ek = key4[g], en = n4[g];
-      rank += (ek.x > key || (ek.x == key && en.x < n)) ? 1 : 0;
-      rank += (ek.y > key || (ek.y == key && en.y < n)) ? 1 : 0;
-      rank += (ek.z > key || (ek.z == key && en.z < n)) ? 1 : 0;
-      rank += (ek.w > key || (ek.w == key && en.w < n)) ? 1 : 0;
+// ---------------------------------------------------------------------------
+// loads
+// ---------------------------------------------------------------------------
+// The raw dwords of a thread's vectors.  N elements from `src`; HALF: 16-bit elements, where
+// the last dword of an odd row is only half inside and reads as 0: `tail` takes its element.
+// TAIL: N need not be a multiple of VE.
+template <int NE, int VE, bool HALF, bool TAIL>
+__device__ __forceinline__ void k1_load(const void* src, int N, int tid, int T,
+                                        uint32_t (&raw)[HALF ? NE / 2 : NE], uint32_t& tail) {
+  constexpr int NL = NE / VE;
+  const rsrc_t row = make_rsrc(src, HALF ? 2u * ((uint32_t)N & ~1u) : 4u * (uint32_t)N);
+  constexpr int kBytes = VE * (HALF ? 2 : 4);
+  const uint32_t at = (uint32_t)tid * kBytes;
+#pragma unroll
+  for (int j = 0; j < NL; ++j) {
+    const uint32_t step = (uint32_t)(j * kBytes) * (uint32_t)T;
+    if (kBytes == 16) {
+      const vu4 v = buffer_load_u4_stream(row, at, step);
+      raw[4 * j] = v.x; raw[4 * j + 1] = v.y; raw[4 * j + 2] = v.z; raw[4 * j + 3] = v.w;
+    } else {
+      const vu2 v = buffer_load_u2_stream(row, at, step);
+      raw[2 * j] = v.x; raw[2 * j + 1] = v.y;
     }
-    rank += __builtin_amdgcn_update_dpp(0, rank, 0xB1, 0xf, 0xf, true);  // quad_perm [1,0,3,2]
-    rank += __builtin_amdgcn_update_dpp(0, rank, 0x4E, 0xf, 0xf, true);  // quad_perm [2,3,0,1]
-    if (sub == 0 && (uint32_t)rank < need) flip_code(code32, (int)n, sgn);
+  }
+  tail = 0;
+  if (HALF && TAIL && (N & 1)) tail = static_cast<const uint16_t*>(src)[N - 1];
+}
+
+// Vector and thread that hold element n (uniform).
+struct K1Place { int j, thread; };
+template <int VE>
+__device__ __forceinline__ K1Place k1_place(int n, int T) {
+  const int v = n / VE, j = v / T;
+  return {j, v - j * T};
+}
+
+// The raw dwords as binary32 weights.
+template <int NE, int VE, bool HALF, bool TAIL>
+__device__ __forceinline__ void k1_widen(uint32_t (&raw)[HALF ? NE / 2 : NE], uint32_t tail, bool bf16, int N,
+                                         int tid, int T, float (&w)[NE]) {
+  if (!HALF) {
+#pragma unroll
+    for (int q = 0; q < NE; ++q) w[q] = __uint_as_float(raw[q]);
+    return;
+  }
+  if (TAIL && (N & 1)) {
+    const K1Place p = k1_place<VE>(N - 1, T);
+    const int at = p.j * (VE / 2) + ((N - 1) % VE) / 2;
+#pragma unroll
+    for (int r = 0; r < NE / 2; ++r)
+      if (r == at) raw[r] = tid == p.thread ? tail : raw[r];
+  }
+  if (bf16) {
+#pragma unroll
+    for (int r = 0; r < NE / 2; ++r) widen_pair(raw[r], true, w[2 * r], w[2 * r + 1]);
+  } else {
+#pragma unroll
+    for (int r = 0; r < NE / 2; ++r) widen_pair(raw[r], false, w[2 * r], w[2 * r + 1]);
   }
 }
 
-// The same ranking for the kernel that keeps its codes in registers: the lanes that rank an
-// entry are not the thread that owns the element, so the list carries, in place of the index
-// n = 4 * (t + j * T) + e, the word (j << 12) | (t << 2) | e, which orders the elements as n
-// does and names the owner: the entries picked set bit 4 * j + e of the owner's mask, and
-// after a barrier every thread reads its own.  The mask of thread t is owner_mask[t], with
-// bits 32..63 (vectors 8..15) in owner_mask[T + t]; the words were zeroed before the barrier
-// that precedes the pushes.  Returns the mask of this thread's
-// picked elements.
-constexpr int kK1MaxThreads = 1024;  // the owner word has ten bits for the thread
-__device__ __forceinline__ uint32_t k1_owner_word(int tid, int q) {
-  return ((uint32_t)(q >> 2) << 12) | ((uint32_t)tid << 2) | (uint32_t)(q & 3);
+// ---------------------------------------------------------------------------
+// SQuant-E
+// ---------------------------------------------------------------------------
+// x = w / s for the NE elements of a thread: the packed biased codes (code + 128, four to a
+// dword) and, WITH_P, the Q23 perturbations in biased form (kQ23Bias + P).  `over` (uniform):
+// the quotient of the absmax element exceeds qmax.  Returns the sum of the P.
+template <int NE, bool WITH_P>
+__device__ __forceinline__ int32_t k1_round_all(const float (&w)[NE], float s, float rs, float qmaxf,
+                                                float xmax, uint32_t (&code)[NE / 4], uint32_t (&B)[NE]) {
+  uint32_t biased = 0;
+#pragma unroll
+  for (int i = 0; i < NE / 4; ++i) {
+    uint32_t tb[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float x = div_by_reciprocal(w[4 * i + e], s, rs);  // the IEEE quotient
+      const float t = x + kRoundMagic;  // round half to even; code + 128 in the low byte
+      tb[e] = __float_as_uint(t);
+      if (WITH_P) {
+        const float c = t - kRoundMagic;
+        const float p = c - x;  // exact
+        const uint32_t pb = __float_as_uint(__builtin_fmaf(p, 8388608.0f, kQ23Magic));
+        biased += pb;
+        B[4 * i + e] = pb;
+      }
+    }
+    code[i] = pack_low_bytes(tb[0], tb[1], tb[2], tb[3]);
+    // keeps the scheduler from interleaving the vectors of the thread, which costs tens of
+    // registers and with them occupancy
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  if (WITH_P && xmax > qmaxf) {
+    // The clamp (Section 2.2), after the fact: an element whose quotient is +-xmax rounded to
+    // +-qmax all the same, but its perturbation is that of +-qmax itself, 0.  No other element
+    // with that code has the perturbation of xmax.
+    const uint32_t d = __float_as_uint(__builtin_fmaf(qmaxf - xmax, 8388608.0f, kQ23Magic));  // P of +xmax
+    const uint32_t top = 128u + (uint32_t)qmaxf, bottom = 128u - (uint32_t)qmaxf;
+#pragma unroll
+    for (int q = 0; q < NE; ++q) {
+      const uint32_t c = (code[q / 4] >> (8 * (q & 3))) & 255u;
+      const bool hit = (c == top && B[q] == d) || (c == bottom && B[q] == 2u * kQ23Bias - d);
+      biased += hit ? kQ23Bias - B[q] : 0u;
+      B[q] = hit ? kQ23Bias : B[q];
+    }
+  }
+  return (int32_t)(biased - (uint32_t)NE * kQ23Bias);
 }
-template <typename MaskT, bool WAVE = false, typename Sel>
-__device__ __forceinline__ MaskT k1_rank_list_owner(Sel& sh, uint32_t* owner_mask, uint32_t count,
-                                                    uint32_t need) {
+
+// ---------------------------------------------------------------------------
+// SQuant-C: among the elements whose P has the sign of the channel sum, the `need` with the
+// largest |P|, lowest index first on ties (Algorithm 2 on the channel, Eq. 7).  u = P (sum > 0)
+// or ~P (sum < 0) orders the wanted side "larger is better": its elements are those with u > 0
+// resp. u >= 0.  Elements past the channel's end hold P = 0 and are on neither side.
+// ---------------------------------------------------------------------------
+// Order within the channel, and the owner, of element q of thread t: vector, thread, element.
+template <int VE>
+__device__ __forceinline__ uint32_t k1_owner_word(int tid, int q) {
+  return ((uint32_t)(q / VE) << 13) | ((uint32_t)tid << 3) | (uint32_t)(q % VE);
+}
+
+// Ranks the entries (order of u above ~owner word, so all different and not 0) of the list and
+// sets the bits of the `need` largest in their owners' masks: bit q % 32 of word
+// owner[(q / 32) * T + thread].  Four threads share an entry, each comparing it with every fourth
+// pair; the eight entries after the last are 0.  After a barrier that follows the last push;
+// another must follow before the masks are read.
+template <bool WAVE, int VE>
+__device__ __forceinline__ void k1_rank(const uint64_t* list, uint32_t* owner, uint32_t count, uint32_t need) {
   const uint32_t tid = (uint32_t)k1_tid<WAVE>(), T = (uint32_t)k1_team<WAVE>();
-  const uint32_t sub = tid & 3u, groups = (count + 3u) >> 2;
-  const uint4* key4 = reinterpret_cast<const uint4*>(sh.list_key);
-  const uint4* n4 = reinterpret_cast<const uint4*>(sh.list_n);
-  for (uint32_t i = tid >> 2; i < count; i += T >> 2) {
-    const uint32_t key = sh.list_key[i], n = sh.list_n[i];
+  const uint32_t sub = tid & 3u;
+  for (uint32_t i0 = 0; i0 < count; i0 += T >> 2) {
+    const uint32_t i = umin2(i0 + (tid >> 2), count);  // past the end: an entry of 0, never picked
+    const uint64_t own = list[i];
     int rank = 0;
-    for (uint32_t g = sub; g < groups; g += 4) {
-      const uint4 ek = key4[g], en = n4[g];
-      rank += (ek.x > key || (ek.x == key && en.x < n)) ? 1 : 0;
-      rank += (ek.y > key || (ek.y == key && en.y < n)) ? 1 : 0;
-      rank += (ek.z > key || (ek.z == key && en.z < n)) ? 1 : 0;
-      rank += (ek.w > key || (ek.w == key && en.w < n)) ? 1 : 0;
+    for (uint32_t g = 0; g < count; g += 8) {
+      const ulonglong2 two = *reinterpret_cast<const ulonglong2*>(list + (g + 2 * sub));
+      rank += two.x > own ? 1 : 0;
+      rank += two.y > own ? 1 : 0;
     }
     rank += __builtin_amdgcn_update_dpp(0, rank, 0xB1, 0xf, 0xf, true);  // quad_perm [1,0,3,2]
     rank += __builtin_amdgcn_update_dpp(0, rank, 0x4E, 0xf, 0xf, true);  // quad_perm [2,3,0,1]
     if (sub == 0 && (uint32_t)rank < need) {
-      const uint32_t j = n >> 12, t = (n >> 2) & (uint32_t)(kK1MaxThreads - 1);
-      atomicOr(&owner_mask[(j >> 3) * T + t], 1u << (4u * (j & 7u) + (n & 3u)));
+      const uint32_t n = ~(uint32_t)own;
+      const uint32_t q = (n >> 13) * VE + (n & 7u), t = (n >> 3) & 1023u;
+      atomicOr(&owner[(q >> 5) * T + t], 1u << (q & 31u));
     }
   }
-  k1_sync<WAVE>();
-  MaskT mine = owner_mask[tid];
-  if (sizeof(MaskT) > 4) mine |= (MaskT)owner_mask[T + tid] << (8 * sizeof(MaskT) - 32);
-  return mine;
 }
 
-// Empties the ranking list (see k1_rank_list); with select_reset, before the first barrier.
-template <bool WAVE = false, typename Sel>
-__device__ __forceinline__ void k1_list_reset(Sel& sh) {
-  for (int b = k1_tid<WAVE>(); b < kListCap / 4; b += k1_team<WAVE>()) {
-    reinterpret_cast<uint4*>(sh.list_key)[b] = make_uint4(0, 0, 0, 0);
-    reinterpret_cast<uint4*>(sh.list_n)[b] = make_uint4(~0u, ~0u, ~0u, ~0u);
+// Sum over the team of one count per wave (uniform over the wave); one barrier, for callers that
+// alternate `set`.
+template <bool WAVE, typename Sh>
+__device__ __forceinline__ uint32_t k1_team_count(Sh& sh, uint32_t wave_total, int set) {
+  if constexpr (WAVE) {
+    return wave_total;
+  } else {
+    const int wid = threadIdx.x / kWave, nw = (blockDim.x + kWave - 1) / kWave;
+    if ((threadIdx.x & (kWave - 1)) == 0) sh.cnt[set][wid] = wave_total;
+    __syncthreads();
+    uint32_t r = 0;
+    for (int i = 0; i < nw; ++i) r += sh.cnt[set][i];
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)r);
   }
 }
 
-template <typename Sel>
-__device__ __forceinline__ void k1_push(Sel& sh, uint32_t key, int n) {
-  const uint32_t slot = atomicAdd(&sh.list_count, 1u);
-  sh.list_key[slot] = key;
-  sh.list_n[slot] = (uint32_t)n;
+// Shifts the four results b[i] >= t (AT_LEAST) or b[i] <= t into m, b[3] first, so that b[0]
+// ends up in bit 0: four compares and four additions with carry.  Ordered so that at least two
+// instructions lie between a compare and the addition that reads its result, which this
+// hardware asks for where the compiler does not see the pair.
+template <bool AT_LEAST>
+__device__ __forceinline__ void push_compares(uint32_t& m, uint32_t t, const uint32_t* b) {
+  uint64_t c0, c1, c2, c3;
+#define SQ_PUSH(CMP)                                  \
+  asm(CMP " %1, %5, %9\n\t"                           \
+      CMP " %2, %5, %8\n\t"                           \
+      CMP " %3, %5, %7\n\t"                           \
+      "v_addc_co_u32_e64 %0, %1, %0, %0, %1\n\t"      \
+      CMP " %4, %5, %6\n\t"                           \
+      "v_addc_co_u32_e64 %0, %2, %0, %0, %2\n\t"      \
+      "v_addc_co_u32_e64 %0, %3, %0, %0, %3\n\t"      \
+      "v_addc_co_u32_e64 %0, %4, %0, %0, %4"          \
+      : "+v"(m), "=&s"(c0), "=&s"(c1), "=&s"(c2), "=&s"(c3) \
+      : "s"(t), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]))
+  if (AT_LEAST) SQ_PUSH("v_cmp_le_u32_e64");
+  else SQ_PUSH("v_cmp_ge_u32_e64");
+#undef SQ_PUSH
 }
 
-// B[q] = kQ23Bias + P of element 4 * (tid + (q / 4) * T) + (q % 4) of the channel; elements
-// past the channel's end hold P = 0.  All threads of the workgroup call this after the barrier
-// that follows the last k1_count_biased.  Returns the mask of this thread's elements that flip
-// (bit q).  The common case costs four instructions an element: with u = P (sum > 0) or ~P
-// (sum < 0), u >= thr is P >= thr resp. P <= ~thr, a compare on the biased value whose result
-// is shifted into a mask.
-template <int NE, typename MaskT, bool WAVE = false, typename Sel>
-__device__ __forceinline__ MaskT k1_channel_stage(const uint32_t (&B)[NE], int sgn, uint32_t need,
-                                                  Sel& sh, uint32_t* owner_mask) {
+// B[q] = kQ23Bias + P; sm: 0 for a positive channel sum, -1 for a negative one.  All threads of the team call this; the owners' masks are zero, and the
+// list counter, and a barrier has passed since.  Returns the mask of this thread's elements that
+// flip (bit q).
+template <int NE, int VE, bool WAVE, typename MaskT, typename Sh>
+__device__ __forceinline__ MaskT k1_channel_stage(const uint32_t (&B)[NE], int32_t sm, uint32_t need, int N, Sh& sh,
+                                                  uint32_t* owner) {
   static_assert(NE <= 8 * (int)sizeof(MaskT), "one mask bit per element");
   const int T = k1_team<WAVE>(), tid = k1_tid<WAVE>();
-  const int32_t smask = sgn < 0 ? -1 : 0;
-  auto bit = [](int q) { return (MaskT)1 << q; };
-  // mask of the elements with u >= thr: a compare into the carry and an add-with-carry that
-  // shifts it into the mask, as one unit so that no element needs a temporary register
+  // mask of the elements with u >= thr, bit q for element q
   auto at_least = [&](int32_t thr) {
     MaskT all = 0;
 #pragma unroll
     for (int base = (NE - 1) / 32 * 32; base >= 0; base -= 32) {  // 32 elements to a mask word
       uint32_t m = 0;
-      if (sgn > 0) {
-        const uint32_t t = kQ23Bias + (uint32_t)thr;  // P >= thr
+      const uint32_t t = kQ23Bias + (uint32_t)(thr ^ sm);  // P >= thr resp. P <= ~thr
+      if (sm == 0) {
 #pragma unroll
-        for (int q = (NE - base < 32 ? NE - base : 32) - 1; q >= 0; --q)
-          asm("v_cmp_le_u32_e32 vcc, %2, %1\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc"
-              : "+v"(m) : "v"(B[base + q]), "s"(t) : "vcc");
+        for (int q = (NE - base < 32 ? NE - base : 32) - 4; q >= 0; q -= 4) push_compares<true>(m, t, &B[base + q]);
       } else {
-        const uint32_t t = kQ23Bias + (uint32_t)~thr;  // P <= ~thr
 #pragma unroll
-        for (int q = (NE - base < 32 ? NE - base : 32) - 1; q >= 0; --q)
-          asm("v_cmp_ge_u32_e32 vcc, %2, %1\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc"
-              : "+v"(m) : "v"(B[base + q]), "s"(t) : "vcc");
+        for (int q = (NE - base < 32 ? NE - base : 32) - 4; q >= 0; q -= 4) push_compares<false>(m, t, &B[base + q]);
       }
       all |= (MaskT)m << (base & (8 * (int)sizeof(MaskT) - 1));
     }
     return all;
   };
+  auto population = [](MaskT m) {
+    return (uint32_t)__popc((uint32_t)m) + (sizeof(MaskT) > 4 ? (uint32_t)__popc((uint32_t)((uint64_t)m >> 32)) : 0u);
+  };
 
-  uint32_t count = 0, need_at = 0;
-  const int d = k1_scan_top(sh.hist, sgn, need, need_at, count);
-  // u >= thr_flip flips outright; thr_member <= u < thr_flip is the boundary bin
-  int32_t thr_flip, thr_member;
-  if (d < 0) {  // fewer candidates of the wanted sign than flips wanted: all of them flip
-    thr_flip = thr_member = sgn > 0 ? 1 : 0;  // P > 0 resp. ~P >= 0
-  } else {
-    need = need_at;
-    thr_member = d << 15;
-    thr_flip = (d + 1) << 15;
-    // every member of the boundary bin flips (the bin that P = 0 shares needs its real count)
-    if (count == need && !(sgn > 0 && d == 0)) thr_flip = thr_member;
+  // ---- threshold search ----
+  // Bounds: fewer than `need` elements have u >= hi (n_hi of them, mask m_hi); at least `need`
+  // have u >= lo (n_lo, mask m_lo) once `found`.  The interval shrinks with every pass, and every
+  // fourth pass halves it, so it ends after at most 4 * 23 passes whatever the distribution.
+  // the step of u per element when the perturbations are spread evenly
+  const int32_t step = __builtin_amdgcn_readfirstlane((int32_t)(8388608.0f * __builtin_amdgcn_rcpf((float)N)));
+  int32_t lo = 1 + sm, hi = (1 << 22) + 1;
+  uint32_t n_lo = 0, n_hi = 0, incl = 0;
+  MaskT m_lo = 0, m_hi = 0;
+  bool found = false;
+  // elements wanted at or above the first threshold
+  const uint32_t aim = umin2(need + (need >> 2) + 4u, need + kListCap / 4);
+  int32_t thr = (1 << 22) - (int32_t)aim * step;
+  for (int pass = 1;; ++pass) {
+    thr = thr < lo ? lo : thr > hi - 1 ? hi - 1 : thr;
+    const MaskT m = at_least(thr);
+    const uint32_t run = wave_prefix_sum(population(m));
+    const uint32_t n = k1_team_count<WAVE>(sh, (uint32_t)__builtin_amdgcn_readlane((int)run, kWave - 1), pass & 1);
+    if (n >= need) {
+      lo = thr; n_lo = n; m_lo = m; incl = run; found = true;
+      if (n == need) return m;
+    } else {
+      if (thr == lo && !found) return m;  // fewer candidates of the wanted sign than flips: all flip
+      hi = thr; n_hi = n; m_hi = m;
+    }
+    if (found) {
+      if (n_lo - n_hi <= (uint32_t)kListCap || hi - lo == 1) break;
+      if ((pass & 3) == 0) {
+        thr = lo + ((hi - lo) >> 1);
+      } else {
+        // interpolate between the bounds; once the lower one is close, from the other side of `need`
+        float want = n_lo - need > (uint32_t)kListCap / 2 ? (float)need + 0.125f * kListCap
+                                                          : (float)need - 0.25f * kListCap;
+        if (want <= (float)n_hi + 0.5f) want = 0.5f * (float)(n_hi + need);
+        const float part = (want - (float)n_hi) * __builtin_amdgcn_rcpf((float)(n_lo - n_hi));
+        thr = __builtin_amdgcn_readfirstlane(hi - (int32_t)(part * (float)(hi - lo)));
+        thr = thr <= lo ? lo + 1 : thr;
+      }
+    } else {  // too few: widen the distance from the top in proportion
+      const float wider = ((float)need * 1.25f + 4.0f) * __builtin_amdgcn_rcpf(fmaxf((float)n, 0.5f));
+      thr = (1 << 22) - (int32_t)fminf((float)((1 << 22) + 1 - thr) * wider, 4194304.0f);
+      thr = __builtin_amdgcn_readfirstlane(thr);
+    }
   }
-  MaskT flip = at_least(thr_flip);
-  if (thr_flip == thr_member) return flip;
-  MaskT live = at_least(thr_member) & ~flip;  // this thread's members of the boundary bin
-
-  // u of element q, for the rare sides below: (B ^ m) - ((bias ^ m) - m) with m the sign mask.
-  // Every phase takes the mask through a register move that the compiler cannot see through: it
-  // then recomputes u where it is used instead of keeping one more register per element alive
-  // across the whole selection, which does not fit.
-  auto opaque = [](int32_t v) { int32_t r; asm volatile("s_mov_b32 %0, %1" : "=s"(r) : "s"(v)); return r; };
-  auto u_of = [&](int q, int32_t m) { return (int32_t)((B[q] ^ (uint32_t)m) - ((kQ23Bias ^ (uint32_t)m) - (uint32_t)m)); };
+  // those with u >= hi flip; `want` of the `count` with lo <= u < hi
+  const MaskT live = m_lo & (MaskT)~m_hi;
+  const uint32_t count = n_lo - n_hi, want = need - n_hi;
 
   if (count <= (uint32_t)kListCap) {
-    // the usual case: the boundary bin's members go straight to the ranking list
-    if (live) {
-      const int32_t sm = opaque(smask);
+    if (n_hi != 0) incl = wave_prefix_sum(population(live));
+    uint32_t slot = incl - population(live);
+    if constexpr (!WAVE) {  // the order within the list does not matter
+      uint32_t base = 0;
+      if ((tid & (kWave - 1)) == kWave - 1 && incl != 0) base = atomicAdd(&sh.list_count, incl);
+      slot += (uint32_t)__builtin_amdgcn_readlane((int)base, kWave - 1);
+    }
+    if (tid < 8) sh.list[count + tid] = 0;
+    uint64_t* put = sh.list + slot;
+    const uint32_t me = ~((uint32_t)tid << 3);  // ~k1_owner_word(tid, q) = me - k1_owner_word(0, q)
 #pragma unroll
-      for (int j = 0; j < NE / 4; ++j) {
-        if (((uint32_t)(live >> (4 * j)) & 15u) == 0) continue;  // few vectors hold a member
+    for (int j = NE / 4 - 1; j >= 0; --j) {
+      uint32_t bits = (uint32_t)(live >> (4 * j)) << 28;  // the vector's four, in the top bits
+      if (__ballot(bits != 0) == 0ull) continue;  // few vectors hold a member
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int q = 4 * j + e;
-          if (live & bit(q)) {
-            const int32_t u = u_of(q, sm);
-            if (u > 0 || sm != 0) k1_push(sh, (uint32_t)u, k1_owner_word(tid, q));  // P = 0 is no candidate
-          }
-        }
+      for (int e = 3; e >= 0; --e) {
+        const int q = 4 * j + e;
+        if (__builtin_add_overflow(bits, bits, &bits))
+          *put++ = ((uint64_t)(B[q] ^ (uint32_t)sm) << 32) | (me - k1_owner_word<VE>(0, q));
       }
     }
     k1_sync<WAVE>();
-    count = sh.list_count;  // exact: without the P = 0 elements that bin 128 also counts
-    return flip | k1_rank_list_owner<MaskT, WAVE>(sh, owner_mask, count, need < count ? need : count);
+    k1_rank<WAVE, VE>(sh.list, owner, count, want);
+    k1_sync<WAVE>();
+    MaskT mine = owner[tid];
+    if (sizeof(MaskT) > 4) mine |= (MaskT)owner[T + tid] << (8 * sizeof(MaskT) - 32);
+    return m_hi | mine;
   }
 
-  // ---- a crowded bin: histogram passes over bits 14..7, then 7..0 of u ----
-  int32_t sm = opaque(smask);
-  if (sgn > 0 && d == 0) {  // the bin that P = 0 shares: drop those, count its real members
-#pragma unroll
-    for (int q = 0; q < NE; ++q)
-      if (B[q] == kQ23Bias) live &= ~bit(q);
-    k1_sync<WAVE>();
-    if (tid == 0) sh.wave_cnt[16] = 0;
-    k1_sync<WAVE>();
-    if (live) atomicAdd(&sh.wave_cnt[16], (uint32_t)__popcll((unsigned long long)live));
-    k1_sync<WAVE>();
-    count = sh.wave_cnt[16];
-    if (count < need) need = count;
-    if (count == 0) return flip;
-  }
-  int shift = 15;
-  while (count > (uint32_t)kListCap && count != need && shift > 0) {
-    shift = shift == 15 ? 7 : 0;
-    k1_sync<WAVE>();  // every wave has finished reading the histogram
-    for (int b = tid; b < 256; b += T) sh.hist[b] = 0;
-    k1_sync<WAVE>();
-    sm = opaque(smask);
-#pragma unroll
-    for (int q = 0; q < NE; ++q)
-      if (live & bit(q)) atomicAdd(&sh.hist[((uint32_t)u_of(q, sm) >> shift) & 255u], 1u);
-    k1_sync<WAVE>();
-    const uint32_t d2 = scan_histogram_top(sh.hist, need, need_at, count);
-    need = need_at;
-    sm = opaque(smask);
-#pragma unroll
-    for (int q = 0; q < NE; ++q) {
-      if (!(live & bit(q))) continue;
-      const uint32_t dq = ((uint32_t)u_of(q, sm) >> shift) & 255u;
-      if (dq > d2) flip |= bit(q);
-      if (dq != d2) live &= ~bit(q);
-    }
-  }
-
-  // `count` elements are still live (equal down to bit `shift`); `need` of them flip
-  if (count == need) return flip | live;
-  if (count <= (uint32_t)kListCap) {
-    sm = opaque(smask);
-#pragma unroll
-    for (int q = 0; q < NE; ++q)
-      if (live & bit(q)) k1_push(sh, (uint32_t)u_of(q, sm), k1_owner_word(tid, q));
-    k1_sync<WAVE>();
-    return flip | k1_rank_list_owner<MaskT, WAVE>(sh, owner_mask, count, need);
-  }
-  // more than kListCap elements equal in all their bits: the lowest indices flip.  The four
-  // elements of a vector are consecutive and vectors ascend with the thread, so inside round
-  // j an exclusive prefix count over the threads ranks them; the rounds follow each other.
-  const int lane = tid & (kWave - 1), wid = tid / kWave;
-  const int nw = (T + kWave - 1) / kWave;
+  // more than kListCap elements with the same u: the lowest indices flip.  The VE elements of a
+  // vector are consecutive and vectors ascend with the thread, so inside round j an exclusive
+  // prefix count over the threads ranks them; the rounds follow each other.
+  MaskT flip = m_hi;
   uint32_t done = 0;
 #pragma unroll 1
-  for (int round = 0; round < NE / 4; ++round) {
-    const uint32_t bits = (uint32_t)(live >> (4 * round)) & 15u;
+  for (int round = 0; round < NE / VE && done < want; ++round) {
+    const uint32_t bits = (uint32_t)(live >> (VE * round)) & ((1u << VE) - 1u);
     const uint32_t mine = (uint32_t)__popc(bits);
-    const uint32_t incl = wave_prefix_sum(mine);
-    k1_sync<WAVE>();
-    if (lane == kWave - 1) sh.wave_cnt[wid] = incl;
-    k1_sync<WAVE>();
-    uint32_t base = done + incl - mine, total = 0;
-    for (int w = 0; w < nw; ++w) {
-      const uint32_t c = sh.wave_cnt[w];
-      if (w < wid) base += c;
-      total += c;
+    const uint32_t run = wave_prefix_sum(mine);
+    uint32_t rank = done + run - mine, total = (uint32_t)__builtin_amdgcn_readlane((int)run, kWave - 1);
+    if constexpr (!WAVE) {
+      const int wid = tid / kWave, nw = (T + kWave - 1) / kWave;
+      __syncthreads();
+      if ((tid & (kWave - 1)) == 0) sh.cnt[0][wid] = total;
+      __syncthreads();
+      total = 0;
+      for (int w = 0; w < nw; ++w) {
+        const uint32_t c = sh.cnt[0][w];
+        if (w < wid) rank += c;
+        total += c;
+      }
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
+    for (int e = 0; e < VE; ++e)
       if (bits & (1u << e)) {
-        if (base < need) flip |= bit(4 * round + e);
-        ++base;
+        if (rank < want) flip |= (MaskT)1 << (VE * round + e);
+        ++rank;
       }
     done += total;
   }
   return flip;
 }
 
-// SQuant-E for the NV vectors of a thread: the packed biased codes (code + 128, four to a
-// dword) and, WITH_P, the Q23 perturbations in biased form (kQ23Bias + P).  One body for every
-// channel, so that the values have one home in the registers: `prescale` (uniform over the
-// workgroup, almost never set) multiplies the weights by f1 * f2 first.
-template <int NV, bool WITH_P>
-__device__ __forceinline__ void k1_round_all(const float (&w)[4 * NV], float s, float rs, float qmaxf,
-                                             bool prescale, float f1, float f2, uint32_t (&code)[NV],
-                                             uint32_t (&B)[4 * NV], int32_t& esum) {
-  uint32_t biased = 0;
-#pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    // A branch that is always taken (s is finite) but that the compiler cannot fold: every
-    // vector becomes a basic block of its own, which keeps the scheduler from interleaving
-    // all the vectors of the thread (that costs tens of registers, and with them occupancy).
-    code[j] = 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) B[4 * j + e] = 0;
-    if (__float_as_uint(s) + (uint32_t)j == 0xFFFFFFF0u) continue;
-    float wv[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) wv[e] = w[4 * j + e];
-    if (prescale) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) wv[e] = wv[e] * f1 * f2;
-    }
-    uint32_t tb[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float x = div_by_reciprocal(wv[e], s, rs);  // the IEEE quotient
-      // (leaving the clamp out for the channels that do not need it, as the 3x3 kernel does, was
-      // measured to cost more instructions here than the clamp itself)
-      const float xc = __builtin_amdgcn_fmed3f(x, -qmaxf, qmaxf);
-      const float t = xc + kRoundMagic;  // round half to even; code + 128 in the low byte
-      tb[e] = __float_as_uint(t);
-      if (WITH_P) {
-        const float c = t - kRoundMagic;
-        const float p = c - xc;  // exact
-        const uint32_t pb = __float_as_uint(__builtin_fmaf(p, 8388608.0f, kQ23Magic));
-        biased += pb;
-        B[4 * j + e] = pb;
-      }
-    }
-    code[j] = pack_low_bytes(tb[0], tb[1], tb[2], tb[3]);
-  }
-  esum = (int32_t)(biased - (uint32_t)(4 * NV) * kQ23Bias);
+// ---------------------------------------------------------------------------
+// The whole solve of one channel whose weights are in w: scale, codes.  Returns the scale.
+// ---------------------------------------------------------------------------
+// Sum over a wave of per-thread sums of NE perturbations each.
+template <int NE>
+__device__ __forceinline__ int64_t k1_wave_sum(int32_t v) {
+  return NE < 32 ? wave_sum_rows(v) : wave_sum_dpp(v);  // a row of 16 lanes: 16 * NE * 2^22 < 2^31
 }
 
-// Writes vector `idx` of output channel m (its four biased codes in c) in the requested
-// format (squant_output_t): one coalesced store per thread.
-__device__ __forceinline__ void k1_emit_vector(uint32_t c, int idx, void* out_base, int m, int N, float s,
-                                               int format) {
-  if (format == SQUANT_OUT_INT8) {
-    store_global_u1(static_cast<uint8_t*>(out_base) + (size_t)m * N + 4 * (size_t)idx, c ^ 0x80808080u);
-  } else if (format == SQUANT_OUT_INT4) {
-    store_global_u16(static_cast<uint8_t*>(out_base) + (size_t)m * (N / 2) + 2 * (size_t)idx,
-                     (uint16_t)pack_nibbles4(c));
-  } else if (format == SQUANT_OUT_BF16) {
-    uint16_t* out = static_cast<uint16_t*>(out_base) + (size_t)m * N + 4 * (size_t)idx;
-    const vf4 v = dequant4(c, s);
-    if ((reinterpret_cast<uintptr_t>(out) & 7u) == 0) {
-      vu2 o;
-      o.x = bf16_bits(v.x) | (bf16_bits(v.y) << 16);
-      o.y = bf16_bits(v.z) | (bf16_bits(v.w) << 16);
-      store_global_u2(out, o);
-    } else {
-      out[0] = (uint16_t)bf16_bits(v.x); out[1] = (uint16_t)bf16_bits(v.y);
-      out[2] = (uint16_t)bf16_bits(v.z); out[3] = (uint16_t)bf16_bits(v.w);
-    }
-  } else {  // SQUANT_OUT_F32
-    float* out = static_cast<float*>(out_base) + (size_t)m * N + 4 * (size_t)idx;
-    const vf4 v = dequant4(c, s);
-    if ((reinterpret_cast<uintptr_t>(out) & 15u) == 0) {
-      store_global_f4(out, v);
-    } else {
-      out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
-    }
-  }
-}
-
-template <int MODE, int NV>
-__device__ __forceinline__ void k1_channel(const LaunchArgs& a, const TensorDesc& d, int m,
-                                           unsigned char* smem, K9Shared& sh) {
+template <int MODE, int NE, int VE, bool WAVE, typename Sh>
+__device__ __forceinline__ float k1_solve(float (&w)[NE], int N, float qmaxf, Sh& sh, uint32_t* owner,
+                                          uint32_t (&code)[NE / 4]) {
   constexpr bool kChannelStage = MODE == SQUANT_MODE_EKC || MODE == SQUANT_MODE_EC;
-  constexpr int NE = 4 * NV;  // elements per thread
   typedef typename std::conditional<(NE > 32), uint64_t, uint32_t>::type MaskT;
-  const int T = blockDim.x, tid = threadIdx.x;
-  const float qmaxf = (float)a.qmax;
-  uint32_t* owner_mask = reinterpret_cast<uint32_t*>(smem);  // see k1_rank_list_owner
-
-  const int N = d.N, nvec = N >> 2;  // cin % 4 == 0
-  float w[NE];
-  if (a.wtype == SQUANT_W_F32) {
-    const float* src = static_cast<const float*>(d.w) + (size_t)m * N;
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      const int idx = tid + j * T;
-      vf4 v = {0.0f, 0.0f, 0.0f, 0.0f};
-      if (idx < nvec) v = load_global_f4_stream(src + 4 * idx);
-      w[4 * j] = v.x; w[4 * j + 1] = v.y; w[4 * j + 2] = v.z; w[4 * j + 3] = v.w;
-    }
-  } else {  // 16-bit weights: the same four elements per vector, 8 bytes
-    const uint16_t* src = static_cast<const uint16_t*>(d.w) + (size_t)m * N;
-    const bool bf16 = a.wtype == SQUANT_W_BF16;
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      const int idx = tid + j * T;
-      vu2 v = {0u, 0u};
-      if (idx < nvec) v = load_global_u2_stream(src + 4 * idx);
-      widen_pair(v.x, bf16, w[4 * j], w[4 * j + 1]);
-      widen_pair(v.y, bf16, w[4 * j + 2], w[4 * j + 3]);
-    }
+  const int T = k1_team<WAVE>(), tid = k1_tid<WAVE>();
+  if (kChannelStage) {  // before the first barrier
+    owner[tid] = 0;
+    if (NE > 32) owner[T + tid] = 0;
+    if constexpr (!WAVE)
+      if (tid == 0) sh.list_count = 0;
   }
-  if (kChannelStage) { select_reset(sh.sel); k1_list_reset(sh.sel); owner_mask[tid] = 0; if (NE > 32) owner_mask[T + tid] = 0; }  // before the first barrier
-
   float amax = 0.0f;
 #pragma unroll
-  for (int e = 0; e < NE; e += 2) amax = fmaxf(fmaxf(amax, fabsf(w[e])), fabsf(w[e + 1]));
-  amax = block_max_dpp1(amax, sh.red_f);
-  const float s = amax > 0.0f ? amax / qmaxf : 1.0f;
-  if (tid == 0) d.scales[m] = s;
+  for (int q = 0; q < NE; q += 2) amax = fmaxf(fmaxf(amax, fabsf(w[q])), fabsf(w[q + 1]));
+  if constexpr (WAVE) amax = wave_max_dpp(amax);
+  else amax = block_max_dpp1(amax, sh.red_f);
 
-  // ---- SQuant-E (Algorithm 1): codes and perturbations in registers ----
   // The quotients go through the reciprocal of s, which is proven exact for an absmax within
   // [2^-60, 2^60]; a channel outside is first scaled by a power of two (see squant_k9.h).
-  int32_t esum = 0;
-  uint32_t B[NE];
-  uint32_t code[NV];
-  {
-    const bool prescale = !(amax <= 0x1p60f && (amax >= 0x1p-60f || amax == 0.0f));
-    const float f1 = !prescale ? 1.0f : amax < 1.0f ? 0x1p64f : 0x1p-64f;
+  float s = div_by_reciprocal(amax, qmaxf, 1.0f / qmaxf);  // 1 / qmax does not depend on the channel
+  float s2 = s;
+  if (!(amax >= 0x1p-60f && amax <= 0x1p60f)) {
+    s = amax > 0.0f ? amax / qmaxf : 1.0f;
+    const float f1 = amax >= 1.0f ? 0x1p-64f : amax > 0.0f ? 0x1p64f : 1.0f;
     const float a1 = amax * f1;
-    const float f2 = !prescale ? 1.0f : a1 < 0x1p-60f ? 0x1p64f : a1 > 0x1p60f ? 0x1p-64f : 1.0f;
-    const float s2 = s * f1 * f2;
-    k1_round_all<NV, kChannelStage>(w, s2, 1.0f / s2, qmaxf, prescale, f1, f2, code, B, esum);
+    const float f2 = a1 > 0x1p60f ? 0x1p-64f : a1 < 0x1p-60f && amax > 0.0f ? 0x1p64f : 1.0f;
+#pragma unroll
+    for (int q = 0; q < NE; ++q) w[q] = w[q] * f1 * f2;
+    s2 = s * f1 * f2;
+    amax = a1 * f2;
   }
+  const float rs = reciprocal(s2);
+  uint32_t B[NE];
+  const int32_t esum = k1_round_all<NE, kChannelStage>(w, s2, rs, qmaxf, div_by_reciprocal(amax, s2, rs), code, B);
 
   if (kChannelStage) {
-    // elements past the channel's end were loaded as 0, so their P is 0: no candidate.  They
-    // are kept out of the histogram all the same: a wave's worth of them would land in one
-    // bin, and LDS atomics on one address run one lane at a time.
-#pragma unroll
-    for (int j = 0; j < NV; ++j)
-      if (tid + j * T < nvec) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) k1_count_biased(sh.sel, B[4 * j + e]);
-      }
-    const int64_t ec = block_sum_dpp1(esum, sh.red_i);  // its barrier publishes the histogram
-    const int sgn = sign_of(ec);
-    const int64_t kc = flips_for(ec < 0 ? -ec : ec);
+    int64_t ec = k1_wave_sum<NE>(esum);
+    if constexpr (!WAVE) {
+      const int nw = (T + kWave - 1) / kWave;
+      if ((tid & (kWave - 1)) == 0) sh.red_i[tid / kWave] = ec;
+      __syncthreads();
+      ec = 0;
+      for (int i = 0; i < nw; ++i) ec += sh.red_i[i];
+      ec = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(ec >> 32)) << 32) |
+                     (uint32_t)__builtin_amdgcn_readfirstlane((int)ec));
+    }
+    // scalar arithmetic throughout; |ec| <= 2^16 * 2^22
+    const int32_t sm = (int32_t)(ec >> 63);
+    const uint32_t kc = (uint32_t)(((uint64_t)((ec ^ sm) - sm) + (uint64_t)(kHalf - 1)) >> 23);  // flips_for(|ec|)
     if (kc > 0) {
-      const MaskT flip = k1_channel_stage<NE, MaskT>(B, sgn, (uint32_t)(kc > N ? N : kc), sh.sel, owner_mask);
+      if (WAVE) k1_sync<true>();  // the owners' masks are reset
+      const MaskT flip = k1_channel_stage<NE, VE, WAVE, MaskT>(B, sm, umin2(kc, (uint32_t)N), N, sh, owner);
       // one step against the channel sum for the marked elements: on the biased bytes a +-1
       // never carries into the neighbouring code
-      const uint32_t sm = sgn < 0 ? ~0u : 0u;
 #pragma unroll
-      for (int j = 0; j < NV; ++j) {
-        const uint32_t f4 = (uint32_t)(flip >> (4 * j)) & 15u;
+      for (int i = 0; i < NE / 4; ++i) {
+        const uint32_t f4 = (uint32_t)(flip >> (4 * i)) & 15u;
         const uint32_t b = (f4 * 0x204081u) & 0x01010101u;  // bit e to byte e
-        code[j] -= (b ^ sm) - sm;
+        code[i] -= (b ^ (uint32_t)sm) - (uint32_t)sm;
       }
     }
   }
-
-  // the format is chosen once, outside the loop over the vectors
-  auto emit_all = [&](int format) {
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      const int idx = tid + j * T;
-      if (idx < nvec) k1_emit_vector(code[j], idx, d.out, m, N, s, format);
-    }
-  };
-  if (a.out_format == SQUANT_OUT_INT8) emit_all(SQUANT_OUT_INT8);
-  else if (a.out_format == SQUANT_OUT_INT4) emit_all(SQUANT_OUT_INT4);
-  else if (a.out_format == SQUANT_OUT_BF16) emit_all(SQUANT_OUT_BF16);
-  else emit_all(SQUANT_OUT_F32);
+  return s;
 }
 
-// One kernel per vector count serves every workgroup size.  Up to six vectors per thread fit
-// the 64 VGPRs of eight waves per SIMD, seven and eight the 80 of six, sixteen (workgroups of
-// up to 512 threads) the 128 of four.  The steps matter because
+// ---------------------------------------------------------------------------
+// stores
+// ---------------------------------------------------------------------------
+// The row of output channel m in one format (squant_output_t): whole vectors by buffer stores
+// whose range ends with the last of them, the VE - 1 or fewer elements after it one by one.
+template <int NE, int VE, bool TAIL, int FORMAT>
+__device__ __forceinline__ void k1_emit(const uint32_t (&code)[NE / 4], void* out_base, int m, int N, float s,
+                                        int tid, int T) {
+  constexpr int kUnit = FORMAT == SQUANT_OUT_INT8 ? VE : FORMAT == SQUANT_OUT_INT4 ? VE / 2
+                        : FORMAT == SQUANT_OUT_BF16 ? 2 * VE : 4 * VE;  // bytes of a vector
+  const int full = N / VE, rem = N % VE;
+  const size_t row_bytes = FORMAT == SQUANT_OUT_INT8 ? (size_t)N : FORMAT == SQUANT_OUT_INT4 ? (size_t)(N + 1) / 2
+                           : FORMAT == SQUANT_OUT_BF16 ? 2 * (size_t)N : 4 * (size_t)N;
+  uint8_t* out = static_cast<uint8_t*>(out_base) + (size_t)m * row_bytes;
+  const rsrc_t row = make_rsrc(out, (uint32_t)full * kUnit);
+  const uint32_t at = (uint32_t)tid * kUnit;
+#pragma unroll
+  for (int j = 0; j < NE / VE; ++j) {
+    const uint32_t step = (uint32_t)(j * kUnit) * (uint32_t)T;
+    const uint32_t c0 = code[j * VE / 4], c1 = code[j * VE / 4 + VE / 4 - 1];
+    if (FORMAT == SQUANT_OUT_INT8) {
+      if (VE == 4) buffer_store_u1_stream(c0 ^ 0x80808080u, row, at, step);
+      else buffer_store_u2_stream(vu2{c0 ^ 0x80808080u, c1 ^ 0x80808080u}, row, at, step);
+    } else if (FORMAT == SQUANT_OUT_INT4) {
+      if (VE == 4) buffer_store_u16_stream((uint16_t)pack_nibbles4(c0), row, at, step);
+      else buffer_store_u1_stream(pack_nibbles8(c0, c1), row, at, step);
+    } else if (FORMAT == SQUANT_OUT_BF16) {
+      const vf4 v = dequant4(c0, s);
+      const uint32_t o0 = bf16_bits(v.x) | (bf16_bits(v.y) << 16), o1 = bf16_bits(v.z) | (bf16_bits(v.w) << 16);
+      if (VE == 4) {
+        buffer_store_u2_stream(vu2{o0, o1}, row, at, step);
+      } else {
+        const vf4 u = dequant4(c1, s);
+        buffer_store_u4_stream(vu4{o0, o1, bf16_bits(u.x) | (bf16_bits(u.y) << 16),
+                                   bf16_bits(u.z) | (bf16_bits(u.w) << 16)}, row, at, step);
+      }
+    } else {
+      buffer_store_u4_stream(__builtin_bit_cast(vu4, dequant4(c0, s)), row, at, step);
+      if (VE == 8) buffer_store_u4_stream(__builtin_bit_cast(vu4, dequant4(c1, s)), row, at + 16u, step);
+    }
+  }
+  if (!TAIL || rem == 0) return;
+  const K1Place p = k1_place<VE>(full * VE, T);
+  uint32_t c[VE / 4] = {};
+#pragma unroll
+  for (int j = 0; j < NE / VE; ++j)
+    if (j == p.j) {
+#pragma unroll
+      for (int i = 0; i < VE / 4; ++i) c[i] = code[j * VE / 4 + i];
+    }
+  if (tid != p.thread) return;
+  uint8_t* end = out + (size_t)full * kUnit;
+#pragma unroll
+  for (int e = 0; e < VE - 1; ++e) {
+    if (e >= rem) break;
+    const uint32_t byte = (c[e / 4] >> (8 * (e & 3))) & 255u;
+    const float v = ((float)byte - 128.0f) * s;
+    if (FORMAT == SQUANT_OUT_INT8) end[e] = (uint8_t)(byte ^ 0x80u);
+    else if (FORMAT == SQUANT_OUT_BF16) reinterpret_cast<uint16_t*>(end)[e] = (uint16_t)bf16_bits(v);
+    else if (FORMAT == SQUANT_OUT_F32) reinterpret_cast<float*>(end)[e] = v;
+    else if ((e & 1) == 0) {  // the next element's nibble: past the end its code is 0
+      const uint32_t next = e + 1 < VE ? (c[(e + 1) / 4] >> (8 * ((e + 1) & 3))) & 15u : 0u;
+      end[e / 2] = (uint8_t)((byte & 15u) | (next << 4));
+    }
+  }
+}
+
+template <int NE, int VE, bool TAIL>
+__device__ __forceinline__ void k1_emit_as(int format, const uint32_t (&code)[NE / 4], void* out_base, int m, int N,
+                                           float s, int tid, int T) {
+  // the format is chosen once, outside the loop over the vectors
+  if (format == SQUANT_OUT_INT8) k1_emit<NE, VE, TAIL, SQUANT_OUT_INT8>(code, out_base, m, N, s, tid, T);
+  else if (format == SQUANT_OUT_INT4) k1_emit<NE, VE, TAIL, SQUANT_OUT_INT4>(code, out_base, m, N, s, tid, T);
+  else if (format == SQUANT_OUT_BF16) k1_emit<NE, VE, TAIL, SQUANT_OUT_BF16>(code, out_base, m, N, s, tid, T);
+  else k1_emit<NE, VE, TAIL, SQUANT_OUT_F32>(code, out_base, m, N, s, tid, T);
+}
+
+// Elements per vector with NV four-element vectors per thread.
+template <int NV, bool HALF>
+constexpr int k1_ve() { return HALF && NV % 2 == 0 ? 8 : 4; }
+
+template <int MODE, int NV, int VE, bool HALF, bool TAIL>
+__device__ __forceinline__ void k1_channel(const LaunchArgs& a, const TensorDesc& d, int m, unsigned char* smem,
+                                           K1Shared& sh) {
+  constexpr int NE = 4 * NV;
+  const int T = blockDim.x, tid = threadIdx.x, N = d.N;
+  uint32_t raw[HALF ? NE / 2 : NE], tail, code[NE / 4];
+  k1_load<NE, VE, HALF, TAIL>(static_cast<const uint8_t*>(d.w) + (size_t)m * N * (HALF ? 2 : 4), N, tid, T, raw, tail);
+  float w[NE];
+  k1_widen<NE, VE, HALF, TAIL>(raw, tail, a.wtype == SQUANT_W_BF16, N, tid, T, w);
+  const float s = k1_solve<MODE, NE, VE, false>(w, N, (float)a.qmax, sh, reinterpret_cast<uint32_t*>(smem), code);
+  if (tid == 0) d.scales[m] = s;
+  k1_emit_as<NE, VE, TAIL>(a.out_format, code, d.out, m, N, s, tid, T);
+}
+
+// One kernel per vector count serves every workgroup size.  Up to seven vectors per thread fit
+// the 64 VGPRs of eight waves per SIMD, eight the 72 of seven, sixteen (workgroups of up to 512
+// threads) the 128 of four.  The steps matter because
 // whole workgroups must fit: at 64 VGPRs a compute unit has 32 wave slots, so two workgroups of
 // 1024 threads or eight of 256 run side by side; at 80 it has 24.
-template <int MODE, int NV>
-__global__ void __launch_bounds__(NV <= 8 ? 1024 : 512) __attribute__((amdgpu_waves_per_eu(NV <= 6 ? 8 : NV <= 8 ? 6 : 4)))
+template <int MODE, int NV, bool HALF, bool TAIL>
+__global__ void __launch_bounds__(NV <= 8 ? 1024 : 512) __attribute__((amdgpu_waves_per_eu(NV <= 7 ? 8 : NV <= 8 ? 7 : 4)))
     squant_channel_k1(LaunchArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];  // the owners' masks
-  __shared__ K9Shared sh;
+  __shared__ K1Shared sh;
   int m;
   const TensorDesc d = locate(a, blockIdx.x, m);
-  k1_channel<MODE, NV>(a, d, m, smem, sh);
-}
-
-// ---------------------------------------------------------------------------
-// Streaming variant for channels too long for the register-resident kernel above
-// (cin > 32768, e.g. the input side of a very wide fully connected layer).  Only the
-// channel's codes live on chip (cin bytes of LDS); the weights are walked three times or
-// more - absmax, SQuant-E with the histogram, then every step of the selection - and each
-// walk recomputes the element's perturbation from the weight, which gives the same bits
-// every time.  The re-reads come from the caches (one channel is a few hundred KB).
-// Same selection as k1_channel_stage, with "the elements still undecided" expressed as a
-// prefix of u = P or ~P instead of a per-thread bit mask.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ int32_t k1_round(float wv, float s, float rs, bool fast, float qmaxf,
-                                            float& c) {
-  const float x = fast ? div_by_reciprocal(wv, s, rs) : wv / s;  // the IEEE quotient either way
-  const float xc = __builtin_amdgcn_fmed3f(x, -qmaxf, qmaxf);
-  c = rintf(xc);
-  const float p = c - xc;  // exact
-  return __float_as_int(__builtin_fmaf(p, 8388608.0f, 12582912.0f)) - 0x4B400000;
-}
-
-// Sum of one count per thread over the workgroup (LDS counter, three barriers).
-__device__ __forceinline__ uint32_t block_count(SelectShared& sh, uint32_t mine) {
-  __syncthreads();
-  if (threadIdx.x == 0) sh.wave_cnt[16] = 0;
-  __syncthreads();
-  if (mine) atomicAdd(&sh.wave_cnt[16], mine);
-  __syncthreads();
-  return sh.wave_cnt[16];
-}
-
-template <int MODE>
-__device__ __forceinline__ void k1_stream_channel(const LaunchArgs& a, const TensorDesc& d, int m,
-                                                  unsigned char* smem, K9Shared& sh) {
-  constexpr bool kChannelStage = MODE == SQUANT_MODE_EKC || MODE == SQUANT_MODE_EC;
-  const int T = blockDim.x, tid = threadIdx.x;
-  const float qmaxf = (float)a.qmax;
-  uint32_t* code32 = reinterpret_cast<uint32_t*>(smem);
-  const int N = d.N, nvec = N >> 2;  // cin % 4 == 0
-  const int wtype = a.wtype;
-  const void* wbase = d.w;
-  const size_t chan = (size_t)m * N;
-  auto load4 = [&](int idx, float (&w)[4]) {
-    if (wtype == SQUANT_W_F32) {
-      const vf4 v = load_global_f4(static_cast<const float*>(wbase) + chan + 4 * (size_t)idx);
-      w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
-    } else {
-      const uint32_t* p = reinterpret_cast<const uint32_t*>(static_cast<const uint16_t*>(wbase) + chan +
-                                                            4 * (size_t)idx);
-      const bool bf16 = wtype == SQUANT_W_BF16;
-      widen_pair(load_global_u1(p), bf16, w[0], w[1]);
-      widen_pair(load_global_u1(p + 1), bf16, w[2], w[3]);
-    }
-  };
-
-  if (kChannelStage) { select_reset(sh.sel); k1_list_reset(sh.sel); }  // before the first barrier
-  float amax = 0.0f;
-  for (int idx = tid; idx < nvec; idx += T) {
-    float w[4];
-    load4(idx, w);
-    amax = fmaxf(fmaxf(fmaxf(amax, fabsf(w[0])), fabsf(w[1])), fmaxf(fabsf(w[2]), fabsf(w[3])));
-  }
-  amax = block_max_dpp1(amax, sh.red_f);
-  const float s = amax > 0.0f ? amax / qmaxf : 1.0f;
-  if (tid == 0) d.scales[m] = s;
-  const bool fast = amax >= 0x1p-60f && amax <= 0x1p60f;  // uniform over the workgroup
-  const float rs = 1.0f / s;
-
-  // ---- SQuant-E: codes to LDS, perturbations into the level-0 histogram ----
-  int64_t esum = 0;
-  for (int idx = tid; idx < nvec; idx += T) {
-    float w[4];
-    load4(idx, w);
-    uint32_t packed = 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      float c;
-      const int32_t P = k1_round(w[e], s, rs, fast, qmaxf, c);
-      packed = __builtin_amdgcn_cvt_pk_u8_f32(c + 128.0f, e, packed);
-      if (kChannelStage) { k1_count(sh.sel, P); esum += P; }
-    }
-    code32[idx] = packed;
-  }
-
-  if (kChannelStage) {
-    const int64_t ec = block_sum(esum, sh.red_i);  // its barriers publish codes and histogram
-    const int sgn = sign_of(ec);
-    const int64_t kc = flips_for(ec < 0 ? -ec : ec);
-    uint32_t need = (uint32_t)(kc > N ? N : kc);
-    const int32_t smask = sgn < 0 ? -1 : 0;
-    // f(u, n) for every element n of the channel, u = P (sum > 0) or ~P (sum < 0): the wanted
-    // side has u > 0 resp. u >= 0, larger u is the better candidate
-    auto for_each = [&](auto&& f) {
-      for (int idx = tid; idx < nvec; idx += T) {
-        float w[4];
-        load4(idx, w);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          float c;
-          f(k1_round(w[e], s, rs, fast, qmaxf, c) ^ smask, 4 * idx + e);
-        }
-      }
-    };
-    auto eligible = [&](int32_t u) { return u > 0 || (smask != 0 && u == 0); };
-    do {  // once; `break` leaves the selection
-      if (kc <= 0) break;
-      uint32_t count = 0, need_at = 0;
-      const int dtop = k1_scan_top(sh.sel.hist, sgn, need, need_at, count);
-      if (dtop < 0) {  // fewer candidates of the wanted sign than flips wanted: all of them flip
-        for_each([&](int32_t u, int n) { if (eligible(u)) flip_code(code32, n, sgn); });
-        break;
-      }
-      need = need_at;
-      const int32_t thr_member = dtop << 15, thr_flip = (dtop + 1) << 15;
-      if (sgn > 0 && dtop == 0) {  // the bin that P = 0 shares: count its real members
-        uint32_t mine = 0;
-        for_each([&](int32_t u, int) { mine += (u > 0 && u < thr_flip) ? 1u : 0u; });
-        count = block_count(sh.sel, mine);
-        if (count < need) need = count;
-      }
-      if (count == need) {  // everything from the boundary bin up flips
-        for_each([&](int32_t u, int n) { if (u >= thr_member && eligible(u)) flip_code(code32, n, sgn); });
-        break;
-      }
-      if (count <= (uint32_t)kListCap) {
-        for_each([&](int32_t u, int n) {
-          if (u >= thr_member) {
-            if (u >= thr_flip) flip_code(code32, n, sgn);
-            else if (eligible(u)) k1_push(sh.sel, (uint32_t)u, n);
-          }
-        });
-        __syncthreads();
-        k1_rank_list(sh.sel, count, need, sgn, code32);
-        break;
-      }
-      // a crowded bin: flip what lies above it, then histogram passes over the lower bits.
-      // Members are the eligible elements with (u >> pshift) == prefix.
-      for_each([&](int32_t u, int n) { if (u >= thr_flip) flip_code(code32, n, sgn); });
-      int32_t prefix = dtop;
-      int pshift = 15;
-      while (count > (uint32_t)kListCap && count != need && pshift > 0) {
-        const int shift = pshift == 15 ? 7 : 0;
-        __syncthreads();  // every wave has finished reading the histogram
-        for (int b = tid; b < 256; b += T) sh.sel.hist[b] = 0;
-        __syncthreads();
-        for_each([&](int32_t u, int) {
-          if ((u >> pshift) == prefix && eligible(u)) atomicAdd(&sh.sel.hist[((uint32_t)u >> shift) & 255u], 1u);
-        });
-        __syncthreads();
-        const uint32_t d2 = scan_histogram_top(sh.sel.hist, need, need_at, count);
-        need = need_at;
-        for_each([&](int32_t u, int n) {
-          if ((u >> pshift) == prefix && eligible(u) && (((uint32_t)u >> shift) & 255u) > d2)
-            flip_code(code32, n, sgn);
-        });
-        // bits 14..7 join the prefix; the last pass (bits 7..0, bit 7 shared) pins u itself
-        prefix = shift == 7 ? (prefix << 8) | (int32_t)d2 : ((prefix >> 1) << 8) | (int32_t)d2;
-        pshift = shift;
-      }
-      if (count == need) {
-        for_each([&](int32_t u, int n) {
-          if ((u >> pshift) == prefix && eligible(u)) flip_code(code32, n, sgn);
-        });
-        break;
-      }
-      if (count <= (uint32_t)kListCap) {
-        for_each([&](int32_t u, int n) {
-          if ((u >> pshift) == prefix && eligible(u)) k1_push(sh.sel, (uint32_t)u, n);
-        });
-        __syncthreads();
-        k1_rank_list(sh.sel, count, need, sgn, code32);
-        break;
-      }
-      // more than kListCap elements equal in all their bits: the lowest indices flip.  Within
-      // one step of the walk, element order is thread order.
-      const int lane = tid & (kWave - 1), wid = tid / kWave;
-      const int nw = (T + kWave - 1) / kWave;
-      uint32_t done = 0;
-      for (int base = 0; base < nvec && done < need; base += T) {
-        const int idx = base + tid;
-        uint32_t bits = 0;
-        if (idx < nvec) {
-          float w[4];
-          load4(idx, w);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            float c;
-            const int32_t u = k1_round(w[e], s, rs, fast, qmaxf, c) ^ smask;
-            bits |= ((u >> pshift) == prefix && eligible(u)) ? 1u << e : 0u;
-          }
-        }
-        const uint32_t mine = (uint32_t)__popc(bits);
-        const uint32_t incl = wave_prefix_sum(mine);
-        __syncthreads();
-        if (lane == kWave - 1) sh.sel.wave_cnt[wid] = incl;
-        __syncthreads();
-        uint32_t rank = done + incl - mine, total = 0;
-        for (int w2 = 0; w2 < nw; ++w2) {
-          const uint32_t c = sh.sel.wave_cnt[w2];
-          if (w2 < wid) rank += c;
-          total += c;
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (bits & (1u << e)) {
-            if (rank < need) flip_code(code32, 4 * idx + e, sgn);
-            ++rank;
-          }
-        done += total;
-      }
-    } while (false);
-  }
-  __syncthreads();
-
-  emit_channel(code32, nvec, d.out, m, s, a.out_format, tid, T);
-}
-
-template <int MODE>
-__global__ void __launch_bounds__(1024) squant_channel_k1_stream(LaunchArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];  // N bytes of biased codes
-  __shared__ K9Shared sh;
-  int m;
-  const TensorDesc d = locate(a, blockIdx.x, m);
-  k1_stream_channel<MODE>(a, d, m, smem, sh);
+  k1_channel<MODE, NV, k1_ve<NV, HALF>(), HALF, TAIL>(a, d, m, smem, sh);
 }
 
 }  // namespace squant

@@ -1,0 +1,41 @@
+// 1x1 / FC kernels: a wave per channel, and several channels per wave.
+#include "squant_kernels.h"
+
+#include "squant_k1_team.h"
+#include "squant_k1_wave.h"
+
+namespace squant {
+namespace {
+
+template <int NV>
+kernel_t k1_wave_of(bool channel_stage, bool half, bool tail) {
+  static const kernel_t k[2][2][2] = {
+      {{squant_channel_k1_wave<SQUANT_MODE_E, NV, false, false>, squant_channel_k1_wave<SQUANT_MODE_E, NV, false, true>},
+       {squant_channel_k1_wave<SQUANT_MODE_E, NV, true, false>, squant_channel_k1_wave<SQUANT_MODE_E, NV, true, true>}},
+      {{squant_channel_k1_wave<SQUANT_MODE_EKC, NV, false, false>, squant_channel_k1_wave<SQUANT_MODE_EKC, NV, false, true>},
+       {squant_channel_k1_wave<SQUANT_MODE_EKC, NV, true, false>, squant_channel_k1_wave<SQUANT_MODE_EKC, NV, true, true>}}};
+  return k[channel_stage][half][tail];
+}
+
+}  // namespace
+
+kernel_t k1_wave_kernel(int nv, int mode, int wtype, bool tail) {
+  const bool stage = mode == SQUANT_MODE_EKC || mode == SQUANT_MODE_EC, half = wtype != SQUANT_W_F32;
+  switch (nv) {
+    case 2: return k1_wave_of<2>(stage, half, tail);
+    case 3: return k1_wave_of<3>(stage, half, tail);
+    case 4: return k1_wave_of<4>(stage, half, tail);
+    case 5: return k1_wave_of<5>(stage, half, tail);
+    case 6: return k1_wave_of<6>(stage, half, tail);
+    case 7: return k1_wave_of<7>(stage, half, tail);
+    case 8: return k1_wave_of<8>(stage, half, tail);
+    default: return nullptr;
+  }
+}
+
+kernel_t k1_team_kernel(int mode) {
+  return mode == SQUANT_MODE_EKC || mode == SQUANT_MODE_EC ? squant_channel_k1_team<SQUANT_MODE_EKC>
+                                                           : squant_channel_k1_team<SQUANT_MODE_E>;
+}
+
+}  // namespace squant

@@ -6,7 +6,6 @@
 #pragma once
 
 #include "squant_generic.h"
-#include "squant_k1.h"
 #include "squant_k1_team.h"
 #include "squant_k1_wave.h"
 #include "squant_k9.h"
@@ -14,20 +13,23 @@
 
 namespace squant {
 
-constexpr int kMixedMaxThreads = 256;
-
 // Compiled for five waves per SIMD (at most 96 VGPRs, what the four-kernel 3x3 routine needs):
 // these launches live on the number of resident workgroups.  Measured 2-4 % faster on the
 // ResNet-50 and MobileNetV2 sets; eight waves spill in the 3x3 routine and cost ResNet-18 24 %.
-template <int MODE>
+// HALF: 16-bit weights.
+template <int MODE, bool HALF>
 __global__ void __launch_bounds__(kMixedMaxThreads)
     __attribute__((amdgpu_waves_per_eu(5))) squant_channel_mixed(LaunchArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ K9Shared sh;
-  __shared__ GenericShared gs;
+  // one area for whichever routine the workgroup takes
+  constexpr size_t kArea = sizeof(K9Shared) > sizeof(K1Shared) ? sizeof(K9Shared) : sizeof(K1Shared);
+  __shared__ __align__(16) unsigned char shared[kArea > sizeof(GenericShared) ? kArea : sizeof(GenericShared)];
+  K9Shared& sh = *reinterpret_cast<K9Shared*>(shared);
+  GenericShared& gs = *reinterpret_cast<GenericShared*>(shared);
   // one-element kernels: E&K is E and E&C is E&K&C (SQuant-K has nothing to do, Section 3.4)
   constexpr int M1 = (MODE == SQUANT_MODE_EK) ? SQUANT_MODE_E
                      : (MODE == SQUANT_MODE_EC) ? SQUANT_MODE_EKC : MODE;
+  constexpr int kWeights = HALF ? -1 : SQUANT_W_F32;
   int m;
   const TensorDesc d = locate(a, blockIdx.x, m);
   // Per-thread work is chosen from the launch's workgroup size T, not from the variant the
@@ -36,21 +38,22 @@ __global__ void __launch_bounds__(kMixedMaxThreads)
   const int T = blockDim.x;
   const int family = choose_family(d.N, d.K, pointers_aligned(d.w, d.out));
   if (family == 9) {
-    if (d.N <= T) k9_channel<MODE, 1>(a, d, m, smem, sh);
-    else if (d.N <= 2 * T) k9_channel<MODE, 2>(a, d, m, smem, sh);
-    else k9_channel<MODE, 4>(a, d, m, smem, sh);
+    if (d.N <= T) k9_channel<MODE, 1, kWeights>(a, d, m, smem, sh);
+    else if (d.N <= 2 * T) k9_channel<MODE, 2, kWeights>(a, d, m, smem, sh);
+    else k9_channel<MODE, 4, kWeights>(a, d, m, smem, sh);
   } else if (family == 1) {
+    K1Shared& sh1 = *reinterpret_cast<K1Shared*>(shared);
     const int nvec = d.N >> 2;
-    if (nvec <= T) k1_channel<M1, 1>(a, d, m, smem, sh);
-    else if (nvec <= 2 * T) k1_channel<M1, 2>(a, d, m, smem, sh);
-    else if (nvec <= 3 * T) k1_channel<M1, 3>(a, d, m, smem, sh);
-    else k1_channel<M1, 4>(a, d, m, smem, sh);
+    if (nvec <= T) k1_channel<M1, 1, 4, HALF, false>(a, d, m, smem, sh1);
+    else if (nvec <= 2 * T) k1_channel<M1, 2, 4, HALF, false>(a, d, m, smem, sh1);
+    else if (nvec <= 3 * T) k1_channel<M1, 3, 4, HALF, false>(a, d, m, smem, sh1);
+    else k1_channel<M1, 4, 4, HALF, false>(a, d, m, smem, sh1);
   } else if (family == 3) {
     dw9_channels<MODE>(a, d, m);
   } else if (family == 4) {
     k1_team_dispatch<M1>(a, d, m);
   } else if (family == 6) {
-    k1_wave_dispatch<M1>(a, d, m, smem);
+    k1_wave_dispatch<M1, HALF>(a, d, m, smem);
   } else {
     generic_channel(a, d, m, smem, gs);
   }

@@ -29,6 +29,7 @@ constexpr int kMaxTeamCin = 256;  // 1x1 channels this short share a wave
 constexpr int kMaxWaveCin = 2048; // 1x1 channels up to here take a wave each (at most 8 vectors per lane)
 constexpr int kK1WaveSpan = 4;    // consecutive channels a wave of that kernel walks in a large launch (1 in others)
 constexpr int kK1WaveThreads = 256;  // its workgroup in a launch of its own
+constexpr int kMixedMaxThreads = 256;  // largest workgroup of a mixed launch
 
 SQ_HD int64_t round_up64(int64_t v) { return (v + 63) / 64 * 64; }
 

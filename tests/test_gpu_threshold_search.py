@@ -1,0 +1,114 @@
+"""GPU parity for the threshold search of the 1x1 / FC kernels: channel lengths at the edges of the
+vectors per lane and of the workgroup sizes, and values for which the search takes another way
+than its first guess: ties by the thousand, nearly empty tails, one-sided sums, quotients that the
+clamp moves, a scale whose reciprocal is the hardest to round."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def sq():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2202_07471_amd as sq
+    sq.binding.lib()
+    return sq
+
+
+def overshooting_absmax(qmax, rng):
+    """Absolute maxima whose quotient by their own scale exceeds qmax, so that the clamp acts."""
+    a = rng.uniform(0.5, 1.0, 200000).astype(np.float32)
+    s = a / np.float32(qmax)
+    return a[a / s > np.float32(qmax)]
+
+
+def values(kind, shape, bits, rng):
+    qmax = 2 ** (bits - 1) - 1
+    m, n = shape
+    if kind == "normal":
+        w = rng.standard_normal(shape) * 0.05
+    elif kind == "grid":        # quotients on a coarse grid: hundreds of equal perturbations, exact halves
+        w = rng.integers(-4 * qmax, 4 * qmax + 1, shape) / 4.0
+        w[:, 0] = qmax
+    elif kind == "one_sided":   # every perturbation has the channel's sign and most of them are equal
+        w = rng.integers(-qmax, qmax, shape) + 0.3 + 0.1 * (rng.random(shape) < 0.01)
+        w[:, 0] = qmax
+        w[1::2] *= -1
+    elif kind == "centre":      # a few large weights, the rest far below half a step
+        w = rng.standard_normal(shape) * 1e-3
+        w[:, ::97] = rng.standard_normal(w[:, ::97].shape)
+    else:                       # "clamp": absmax elements of both signs with an overshooting quotient
+        w = rng.uniform(-0.5, 0.5, shape)
+        top = overshooting_absmax(qmax, rng)
+        if len(top):
+            w[:, 1] = top[:m]
+            w[:, -1] = -top[:m]
+    return w.astype(np.float32)
+
+
+# around one vector more per lane, the wave / workgroup border, one, two, four, eight and more waves
+CINS = [260, 512, 516, 1028, 2044, 2048, 2052, 3072, 4096, 6148, 8192, 16384, 24580, 32768]
+
+
+@pytest.mark.parametrize("cin", CINS)
+@pytest.mark.parametrize("bits", [2, 4, 8])
+def test_matches_the_reference(sq, cin, bits):
+    rng = np.random.default_rng(1000 * bits + cin)
+    for kind in ("normal", "grid", "one_sided", "centre", "clamp"):
+        w = values(kind, (4, cin), bits, rng)
+        for dtype, name in ((torch.float32, None), (torch.float16, "f16"), (torch.bfloat16, "bf16")):
+            d = torch.from_numpy(w).to(dtype).cuda()
+            ref = w if name is None else oracle.widen(
+                d.cpu().view(torch.int16).numpy().view(np.uint16).reshape(4, cin, 1, 1), name)
+            codes, scales = sq.squant_quantize_ex(d, bits, sq.MODE_EKC)
+            want, want_s = oracle.quantize(ref.reshape(4, cin, 1, 1), bits, sq.MODE_EKC)
+            what = f"{kind} cin={cin} bits={bits} {dtype}"
+            assert np.array_equal(scales.cpu().numpy(), want_s), what
+            assert np.array_equal(codes.cpu().numpy().reshape(want.shape), want), what
+
+
+@pytest.mark.parametrize("cin", [64, 512, 4096])
+def test_scale_just_below_a_power_of_two(sq, cin):
+    """Scales with an all-ones significand: the reciprocal lies next to a midpoint."""
+    rng = np.random.default_rng(cin)
+    w = rng.standard_normal((6, cin)).astype(np.float32)
+    w = (np.clip(w, -3, 3) / 3).astype(np.float32)
+    one = np.float32(2) - np.float32(2) ** -23          # bits = 2: the scale is the absmax itself
+    w[:, 0] = one * np.float32(2) ** np.array([0, 1, -20, 30, -40, 50], dtype=np.float32)
+    w[:, 1:] *= w[:, :1]
+    d = torch.from_numpy(w).cuda()
+    codes, scales = sq.squant_quantize(d, 2)
+    want, want_s = oracle.quantize(w.reshape(6, cin, 1, 1), 2, sq.MODE_EKC)
+    assert np.array_equal(scales.cpu().numpy(), want_s)
+    assert np.array_equal(codes.cpu().numpy().reshape(want.shape), want)
+
+
+@pytest.mark.parametrize("output", ["int8", "int4", "f32", "bf16"])
+@pytest.mark.parametrize("wtype", [torch.float32, torch.float16, torch.bfloat16])
+def test_every_output_format(sq, wtype, output):
+    """Whole rows in each format, one tensor at a time and as members of a mixed launch; enough
+    channels that every store of a row meets the next one's data in flight."""
+    rng = np.random.default_rng(7)
+    ws = [torch.from_numpy(rng.standard_normal((256, cin)).astype(np.float32) * 0.05).to(wtype).cuda()
+          for cin in (288, 516, 768, 1280, 2048, 2056, 4096, 16384)]
+    fmt = sq.OUTPUTS[output]
+    single = [sq.squant_quantize_ex(w, 4, sq.MODE_EKC, fmt) for w in ws]
+    together, scales = sq.squant_quantize_batched_ex(ws, 4, sq.MODE_EKC, fmt)
+    for w, (out, s), batched, batched_s in zip(ws, single, together, scales):
+        shape = (*w.shape, 1, 1)
+        ref = w.cpu().numpy().reshape(shape) if wtype == torch.float32 else oracle.widen(
+            w.cpu().view(torch.int16).numpy().view(np.uint16).reshape(shape), "f16" if wtype == torch.float16 else "bf16")
+        codes, want_s = oracle.quantize(ref, 4, sq.MODE_EKC, threads=8)
+        codes = codes.reshape(w.shape)
+        value = torch.from_numpy(codes.astype(np.float32) * want_s[:, None])
+        want = {"int8": torch.from_numpy(codes), "int4": torch.from_numpy(oracle.pack_int4(codes.reshape(shape))),
+                "f32": value, "bf16": value.to(torch.bfloat16)}[output]
+        for got, got_s in ((out, s), (batched, batched_s)):
+            assert np.array_equal(got_s.cpu().numpy(), want_s)
+            assert torch.equal(got.cpu().reshape(want.shape), want), (tuple(w.shape), output, wtype)

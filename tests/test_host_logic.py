@@ -29,6 +29,18 @@ def test_reciprocal_division_is_exact_on_every_near_midpoint_case(tmp_path):
     assert cases > 60_000_000
 
 
+def test_reciprocal_from_the_hardware_estimate(tmp_path):
+    """One refinement step from any estimate within one unit in the last place is the correctly
+    rounded reciprocal, for every significand."""
+    exe = str(tmp_path / "host_reciprocal")
+    subprocess.check_call(["g++", "-std=c++17", "-O2", "-mfma", "-ffp-contract=off",
+                           "-I", os.path.join(ROOT, "paper_2202_07471_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "host_reciprocal.cpp"), "-o", exe])
+    out = subprocess.run([exe], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout + out.stderr
+    assert "reciprocal_mismatches=0" in out.stdout
+
+
 def test_variant_choice_covers_every_shape(tmp_path):
     exe = str(tmp_path / "host_plan_check")
     subprocess.check_call(["g++", "-std=c++17", "-O2",
