@@ -116,20 +116,20 @@ Plan stream_plan(int64_t N) {
 
 // Picks the kernel variant and launch shape for one tensor (every tensor fits one).
 Plan plan_tensor(const void* w, const void* out, int64_t N, int64_t K, int lds_limit) {
-  const int variant = choose_variant(N, K, pointers_aligned(w, out));
+  const int variant = route_variant(N, K, pointers_aligned(w, out));
   // LDS: a selection area per wave of the launch's workgroup, added when the launch goes out
   if (is_k1_wave(variant)) return Plan{variant, kK1WaveThreads, 16, kWave};
   switch (variant) {
     case kK9x1: case kK9x2: case kK9x4: {
       const int kpt = variant == kK9x4 ? 4 : variant == kK9x2 ? 2 : 1;
-      // LDS: the channel's int8 codes
-      const int th = (int)round_up64(N / kpt);
-      return Plan{variant, th, round_up((size_t)9 * N, 16), th};
+      // LDS: the channel's int8 codes, one more, whole chunks of 32
+      const int th = (int)round_up64((N + kpt - 1) / kpt);
+      return Plan{variant, th, round_up((size_t)9 * N + 1, 32), th};
     }
     case kK1x1: case kK1x2: case kK1x3: case kK1x4: case kK1x5: case kK1x6: case kK1x7: case kK1x8:
     case kK1x16: {
       const int nv = k1_variant_nv(variant);
-      const int64_t nvec = N / 4;
+      const int64_t nvec = (N + 3) / 4;
       const int th = (int)k1_threads(nvec, nv);
       // the mixed kernel carries the routines of up to four vectors per thread
       const int mix = nv <= 4 ? th : nvec <= 4 * kMixedMaxThreads ? (int)round_up64((nvec + 3) / 4) : 0;
@@ -147,8 +147,10 @@ Plan plan_tensor(const void* w, const void* out, int64_t N, int64_t K, int lds_l
     }
     default: break;
   }
-  if (is_ks(variant))  // LDS: the channel's int8 codes
-    return Plan{variant, (int)round_up64(N / ks_variant_kpt(variant)), round_up((size_t)K * N, 16), 0};
+  if (is_ks(variant)) {  // LDS: as for 3x3
+    const int64_t kpt = ks_variant_kpt(variant);
+    return Plan{variant, (int)round_up64((N + kpt - 1) / kpt), round_up((size_t)K * N + 1, 32), 0};
+  }
   const size_t lds = generic_lds_bytes(N, K);
   if (lds + kStaticLds > (size_t)lds_limit) return stream_plan(N);
   const int th = generic_threads(N, K);
@@ -169,7 +171,7 @@ int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, in
   int64_t total = 0;
   bool uniform = true;
   auto items_of = [&](const TensorDesc& t) {
-    return work_items(t.M, t.N, t.K, g.threads, choose_family(t.N, t.K, pointers_aligned(t.w, t.out)),
+    return work_items(t.M, t.N, t.K, g.threads, route_family(t.N, t.K, pointers_aligned(t.w, t.out)),
                       wave_span);
   };
   const int64_t items0 = items_of(g.t[begin]);
@@ -197,7 +199,12 @@ int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, in
   a.wave_span = wave_span;
   const int nv = k1_variant_nv(g.variant);
   bool tail = false;  // 1x1 / FC rows: any that is no whole number of 16-byte vectors
-  for (size_t i = begin; i < end; ++i) tail |= g.t[i].N % (wtype == SQUANT_W_F32 ? 4 : 8) != 0;
+  bool any = false;   // 3x3: any off the common channel counts and alignments
+  for (size_t i = begin; i < end; ++i) {
+    const TensorDesc& t = g.t[i];
+    tail |= t.N % (wtype == SQUANT_W_F32 ? 4 : 8) != 0;
+    any |= k9_any(t.N, pointers_aligned(t.w, t.out));
+  }
   const kernel_t kernel = is_ks(g.variant) ? ks_kernel(ks_variant_k(g.variant), ks_variant_kpt(g.variant), g.threads, mode)
                           : g.variant == kKsMixed ? ks_mixed_kernel(mode)
                           : (g.variant == kMixed || g.variant == kMixedWave) ? mixed_kernel(mode, wtype)
@@ -207,9 +214,9 @@ int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, in
                           : g.variant == kStream ? stream_kernel(mode)
                           : g.variant == kDw9 ? dw9_kernel(mode)
                           : g.variant == kK1Team ? k1_team_kernel(mode)
-                          : g.variant == kK9x1 ? k9_kernel(1, g.threads, mode, wtype)
-                          : g.variant == kK9x2 ? k9_kernel(2, g.threads, mode, wtype)
-                          : g.variant == kK9x4 ? k9_kernel(4, g.threads, mode, wtype)
+                          : g.variant == kK9x1 ? k9_kernel(1, g.threads, mode, wtype, any)
+                          : g.variant == kK9x2 ? k9_kernel(2, g.threads, mode, wtype, any)
+                          : g.variant == kK9x4 ? k9_kernel(4, g.threads, mode, wtype, any)
                                                : generic_kernel();
   if (!kernel) return SQUANT_ERR_UNSUPPORTED;
   size_t lds = g.lds;

@@ -10,6 +10,7 @@ typedef float vf3 __attribute__((ext_vector_type(3)));
 typedef float vf4 __attribute__((ext_vector_type(4)));
 typedef uint32_t vu4 __attribute__((ext_vector_type(4)));
 typedef uint32_t vu2 __attribute__((ext_vector_type(2)));
+typedef uint32_t vu3 __attribute__((ext_vector_type(3)));
 
 // 16-byte load / store through the global (not flat) address space
 __device__ __forceinline__ vf4 load_global_f4(const float* p) {
@@ -75,6 +76,21 @@ constexpr int kNonTemporal = 2;  // the non-temporal bit of the cache policy: ro
 __device__ __forceinline__ vu4 buffer_load_u4_stream(rsrc_t r, uint32_t lane_off, uint32_t off) {
   return __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)off, kNonTemporal);
 }
+__device__ __forceinline__ uint32_t buffer_load_u1(rsrc_t r, uint32_t lane_off, uint32_t off) {
+  return __builtin_amdgcn_raw_buffer_load_b32(r, (int)lane_off, (int)off, 0);
+}
+__device__ __forceinline__ vu2 buffer_load_u2(rsrc_t r, uint32_t lane_off, uint32_t off) {
+  return __builtin_amdgcn_raw_buffer_load_b64(r, (int)lane_off, (int)off, 0);
+}
+__device__ __forceinline__ vu3 buffer_load_u3(rsrc_t r, uint32_t lane_off, uint32_t off) {
+  return __builtin_amdgcn_raw_buffer_load_b96(r, (int)lane_off, (int)off, 0);
+}
+__device__ __forceinline__ vu4 buffer_load_u4(rsrc_t r, uint32_t lane_off, uint32_t off) {
+  return __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)off, 0);
+}
+__device__ __forceinline__ uint32_t buffer_load_u16(rsrc_t r, uint32_t lane_off, uint32_t off) {
+  return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)lane_off, (int)off, 0);
+}
 __device__ __forceinline__ vu2 buffer_load_u2_stream(rsrc_t r, uint32_t lane_off, uint32_t off) {
   return __builtin_amdgcn_raw_buffer_load_b64(r, (int)lane_off, (int)off, kNonTemporal);
 }
@@ -97,6 +113,11 @@ __device__ __forceinline__ void buffer_store_u16_stream(uint16_t v, rsrc_t r, ui
 #else  // the host pass only parses the kernels
 struct rsrc_t {};
 __device__ rsrc_t make_rsrc(const void*, uint32_t);
+__device__ uint32_t buffer_load_u1(rsrc_t, uint32_t, uint32_t);
+__device__ vu2 buffer_load_u2(rsrc_t, uint32_t, uint32_t);
+__device__ vu3 buffer_load_u3(rsrc_t, uint32_t, uint32_t);
+__device__ vu4 buffer_load_u4(rsrc_t, uint32_t, uint32_t);
+__device__ uint32_t buffer_load_u16(rsrc_t, uint32_t, uint32_t);
 __device__ vu4 buffer_load_u4_stream(rsrc_t, uint32_t, uint32_t);
 __device__ vu2 buffer_load_u2_stream(rsrc_t, uint32_t, uint32_t);
 __device__ void buffer_store_u4_stream(vu4, rsrc_t, uint32_t, uint32_t);
@@ -237,6 +258,50 @@ __device__ __forceinline__ void emit_channel(const uint32_t* code32, int nvec, v
         out[4 * j] = v.x; out[4 * j + 1] = v.y; out[4 * j + 2] = v.z; out[4 * j + 3] = v.w;
       }
     }
+  }
+}
+
+// The same for a channel of any length L whose row starts anywhere: 16 (8 for bfloat16) bytes a
+// store, whatever their alignment; the range of the row's descriptor cuts the last one at a whole
+// dword, and the up to three bytes after it go one by one.  The codes' area is a multiple of 32
+// bytes and holds 128 (code 0) in the byte behind an odd channel.
+__device__ __forceinline__ void emit_row(const uint8_t* code8, int L, void* out_base, int m, float s, int format,
+                                         int tid, int T) {
+  const uint32_t* code32 = reinterpret_cast<const uint32_t*>(code8);
+  const vu4* src4 = reinterpret_cast<const vu4*>(code8);
+  if (format == SQUANT_OUT_INT8) {
+    uint8_t* out = static_cast<uint8_t*>(out_base) + (size_t)m * L;
+    const int whole = L & ~3;
+    const rsrc_t row = make_rsrc(out, (uint32_t)whole);
+    for (int j = tid; 16 * j < whole; j += T) buffer_store_u4_stream(src4[j] ^ 0x80808080u, row, 16u * j, 0);
+    if (tid < L - whole) out[whole + tid] = code8[whole + tid] ^ 0x80u;
+  } else if (format == SQUANT_OUT_INT4) {
+    const int bytes = (L + 1) >> 1, whole = bytes & ~3;
+    uint8_t* out = static_cast<uint8_t*>(out_base) + (size_t)m * bytes;
+    const rsrc_t row = make_rsrc(out, (uint32_t)whole);
+    for (int j = tid; 16 * j < whole; j += T) {
+      const vu4 a = src4[2 * j], b = src4[2 * j + 1];
+      const vu4 o = {pack_nibbles8(a.x, a.y), pack_nibbles8(a.z, a.w), pack_nibbles8(b.x, b.y), pack_nibbles8(b.z, b.w)};
+      buffer_store_u4_stream(o, row, 16u * j, 0);
+    }
+    if (tid < bytes - whole) {
+      const int e = 2 * (whole + tid);
+      out[whole + tid] = (uint8_t)((code8[e] & 15u) | (code8[e + 1] << 4));
+    }
+  } else if (format == SQUANT_OUT_BF16) {
+    uint16_t* out = static_cast<uint16_t*>(out_base) + (size_t)m * L;
+    const rsrc_t row = make_rsrc(out, 2u * (uint32_t)(L & ~1));
+    for (int j = tid; 4 * j < L; j += T) {
+      const vf4 v = dequant4(code32[j], s);
+      const vu2 o = {bf16_bits(v.x) | (bf16_bits(v.y) << 16), bf16_bits(v.z) | (bf16_bits(v.w) << 16)};
+      buffer_store_u2_stream(o, row, 8u * j, 0);
+    }
+    if ((L & 1) && tid == 0) out[L - 1] = (uint16_t)bf16_bits(((float)code8[L - 1] - 128.0f) * s);
+  } else {  // SQUANT_OUT_F32
+    float* out = static_cast<float*>(out_base) + (size_t)m * L;
+    const rsrc_t row = make_rsrc(out, 4u * (uint32_t)L);
+    for (int j = tid; 4 * j < L; j += T)
+      buffer_store_u4_stream(__builtin_bit_cast(vu4, dequant4(code32[j], s)), row, 16u * j, 0);
   }
 }
 

@@ -493,12 +493,12 @@ __device__ __forceinline__ float k1_solve(float (&w)[NE], int N, float qmaxf, Sh
 // ---------------------------------------------------------------------------
 // The row of output channel m in one format (squant_output_t): whole vectors by buffer stores
 // whose range ends with the last of them, the VE - 1 or fewer elements after it one by one.
-template <int NE, int VE, bool TAIL, int FORMAT>
+template <int NE, int VE, int FORMAT>
 __device__ __forceinline__ void k1_emit(const uint32_t (&code)[NE / 4], void* out_base, int m, int N, float s,
                                         int tid, int T) {
   constexpr int kUnit = FORMAT == SQUANT_OUT_INT8 ? VE : FORMAT == SQUANT_OUT_INT4 ? VE / 2
                         : FORMAT == SQUANT_OUT_BF16 ? 2 * VE : 4 * VE;  // bytes of a vector
-  const int full = N / VE, rem = N % VE;
+  const int full = N / VE;
   const size_t row_bytes = FORMAT == SQUANT_OUT_INT8 ? (size_t)N : FORMAT == SQUANT_OUT_INT4 ? (size_t)(N + 1) / 2
                            : FORMAT == SQUANT_OUT_BF16 ? 2 * (size_t)N : 4 * (size_t)N;
   uint8_t* out = static_cast<uint8_t*>(out_base) + (size_t)m * row_bytes;
@@ -529,8 +529,14 @@ __device__ __forceinline__ void k1_emit(const uint32_t (&code)[NE / 4], void* ou
       if (VE == 8) buffer_store_u4_stream(__builtin_bit_cast(vu4, dequant4(c1, s)), row, at + 16u, step);
     }
   }
-  if (!TAIL || rem == 0) return;
-  const K1Place p = k1_place<VE>(full * VE, T);
+}
+
+// The elements after the last whole vector, one by one.
+template <int NE, int VE>
+__device__ __forceinline__ void k1_emit_tail(int format, const uint32_t (&code)[NE / 4], void* out_base, int m, int N,
+                                             float s, int tid, int T) {
+  const int rem = N % VE, first = N - rem;
+  const K1Place p = k1_place<VE>(first, T);
   uint32_t c[VE / 4] = {};
 #pragma unroll
   for (int j = 0; j < NE / VE; ++j)
@@ -539,19 +545,19 @@ __device__ __forceinline__ void k1_emit(const uint32_t (&code)[NE / 4], void* ou
       for (int i = 0; i < VE / 4; ++i) c[i] = code[j * VE / 4 + i];
     }
   if (tid != p.thread) return;
-  uint8_t* end = out + (size_t)full * kUnit;
-#pragma unroll
-  for (int e = 0; e < VE - 1; ++e) {
-    if (e >= rem) break;
-    const uint32_t byte = (c[e / 4] >> (8 * (e & 3))) & 255u;
+#pragma unroll 1
+  for (int e = 0; e < rem; ++e) {
+    const uint32_t byte = c[0] & 255u;
     const float v = ((float)byte - 128.0f) * s;
-    if (FORMAT == SQUANT_OUT_INT8) end[e] = (uint8_t)(byte ^ 0x80u);
-    else if (FORMAT == SQUANT_OUT_BF16) reinterpret_cast<uint16_t*>(end)[e] = (uint16_t)bf16_bits(v);
-    else if (FORMAT == SQUANT_OUT_F32) reinterpret_cast<float*>(end)[e] = v;
-    else if ((e & 1) == 0) {  // the next element's nibble: past the end its code is 0
-      const uint32_t next = e + 1 < VE ? (c[(e + 1) / 4] >> (8 * ((e + 1) & 3))) & 15u : 0u;
-      end[e / 2] = (uint8_t)((byte & 15u) | (next << 4));
-    }
+    c[0] = VE == 4 ? c[0] >> 8 : __builtin_amdgcn_alignbit(c[VE / 4 - 1], c[0], 8);
+    if (VE == 8) c[VE / 4 - 1] >>= 8;
+    const size_t at = (size_t)m * N + first + e;
+    if (format == SQUANT_OUT_INT8) static_cast<uint8_t*>(out_base)[at] = (uint8_t)(byte ^ 0x80u);
+    else if (format == SQUANT_OUT_BF16) static_cast<uint16_t*>(out_base)[at] = (uint16_t)bf16_bits(v);
+    else if (format == SQUANT_OUT_F32) static_cast<float*>(out_base)[at] = v;
+    else if ((e & 1) == 0)  // with the next element's nibble: past the end its code is 0
+      static_cast<uint8_t*>(out_base)[(size_t)m * ((N + 1) / 2) + (first + e) / 2] =
+          (uint8_t)((byte & 15u) | (c[0] << 4));
   }
 }
 
@@ -559,10 +565,11 @@ template <int NE, int VE, bool TAIL>
 __device__ __forceinline__ void k1_emit_as(int format, const uint32_t (&code)[NE / 4], void* out_base, int m, int N,
                                            float s, int tid, int T) {
   // the format is chosen once, outside the loop over the vectors
-  if (format == SQUANT_OUT_INT8) k1_emit<NE, VE, TAIL, SQUANT_OUT_INT8>(code, out_base, m, N, s, tid, T);
-  else if (format == SQUANT_OUT_INT4) k1_emit<NE, VE, TAIL, SQUANT_OUT_INT4>(code, out_base, m, N, s, tid, T);
-  else if (format == SQUANT_OUT_BF16) k1_emit<NE, VE, TAIL, SQUANT_OUT_BF16>(code, out_base, m, N, s, tid, T);
-  else k1_emit<NE, VE, TAIL, SQUANT_OUT_F32>(code, out_base, m, N, s, tid, T);
+  if (format == SQUANT_OUT_INT8) k1_emit<NE, VE, SQUANT_OUT_INT8>(code, out_base, m, N, s, tid, T);
+  else if (format == SQUANT_OUT_INT4) k1_emit<NE, VE, SQUANT_OUT_INT4>(code, out_base, m, N, s, tid, T);
+  else if (format == SQUANT_OUT_BF16) k1_emit<NE, VE, SQUANT_OUT_BF16>(code, out_base, m, N, s, tid, T);
+  else k1_emit<NE, VE, SQUANT_OUT_F32>(code, out_base, m, N, s, tid, T);
+  if (TAIL && N % VE != 0) k1_emit_tail<NE, VE>(format, code, out_base, m, N, s, tid, T);
 }
 
 // Elements per vector with NV four-element vectors per thread.

@@ -237,28 +237,28 @@ __device__ __forceinline__ void k9_load_kernel(float (&w)[NW], int q, const floa
   }
 }
 
-// The same for 16-bit weights (binary16 or bfloat16).  Kernel n starts at half-word 9n of
-// the channel, which is dword aligned for even n only, so five aligned dwords starting at
-// half-word 9n - (n & 1) are read and shifted down by one half-word for odd n.  chan32 is the
-// channel's first dword (the channel has 9 * cin half-words, cin % 4 == 0, so it is dword
-// aligned and ends with the last kernel's last half-word: no load reaches past it).
+// The same through a descriptor of the channel: kernel q of a thread starts `off` bytes after the
+// kernel at lane_off, at any dword.  A kernel behind the channel's end reads as 0.
 template <int NW>
-__device__ __forceinline__ void k9_load_kernel16(float (&w)[NW], int q, const uint32_t* chan32,
-                                                 uint32_t n, bool bf16) {
-  const uint32_t h0 = 9u * n;
-  const uint32_t sh = (h0 & 1u) << 4;
-  const uint32_t* p = chan32 + (h0 >> 1);
-  uint32_t d[5];
+__device__ __forceinline__ void k9_load_kernel_row(float (&w)[NW], int q, rsrc_t row, uint32_t lane_off, uint32_t off) {
 #pragma unroll
-  for (int j = 0; j < 5; ++j) d[j] = load_global_u1(p + j);
-  uint32_t u[5];
+  for (int j = 0; j < 3; ++j) {
+    const vu3 v = buffer_load_u3(row, lane_off + 12u * j, off);
+    w[9 * q + 3 * j] = __uint_as_float(v.x); w[9 * q + 3 * j + 1] = __uint_as_float(v.y);
+    w[9 * q + 3 * j + 2] = __uint_as_float(v.z);
+  }
+}
+
+// The same for 16-bit weights (binary16 or bfloat16): nine half-words, 16 bytes and two, at any
+// half-word (five aligned dwords shifted into place cost ten vector instructions a kernel more).
+template <int NW>
+__device__ __forceinline__ void k9_load_kernel16(float (&w)[NW], int q, rsrc_t row, uint32_t lane_off, uint32_t off,
+                                                 bool bf16) {
+  const vu4 v = buffer_load_u4(row, lane_off, off);
+  const uint32_t last = buffer_load_u16(row, lane_off + 16u, off);
 #pragma unroll
-  for (int j = 0; j < 4; ++j) u[j] = __builtin_amdgcn_alignbit(d[j + 1], d[j], sh);
-  u[4] = d[4] >> sh;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) widen_pair(u[j], bf16, w[9 * q + 2 * j], w[9 * q + 2 * j + 1]);
-  float unused;
-  widen_pair(u[4], bf16, w[9 * q + 8], unused);
+  for (int j = 0; j < 4; ++j) widen_pair(v[j], bf16, w[9 * q + 2 * j], w[9 * q + 2 * j + 1]);
+  w[9 * q + 8] = bf16 ? widen_bf16(last) : widen_f16(last);
 }
 
 // Sum over the wave of values with |v| <= 2^25 (the 16 lanes of a row add up to at most 2^29).
@@ -320,7 +320,7 @@ __device__ __forceinline__ void k9_select_reset(SelectShared& sel) {
 // decisions.
 template <int KPT>
 __device__ __forceinline__ void k9_channel_flip(K9Kernel (&kk)[KPT], int64_t ec, int N, int t, int G,
-                                                bool active, uint32_t* list, SelectShared& sel) {
+                                                uint32_t owned, uint32_t* list, SelectShared& sel) {
   const int64_t a = ec < 0 ? -ec : ec;
   int64_t kc = flips_for(a);
   if (kc <= 0) return;
@@ -342,6 +342,7 @@ __device__ __forceinline__ void k9_channel_flip(K9Kernel (&kk)[KPT], int64_t ec,
   for (int q = 0; q < KPT; ++q) {
     const uint32_t bin = kk[q].cand >> 15;
     const bool above = bin - lo - 1u < span;
+    const bool active = (owned >> q) & 1u;
     at[q] = rank && active && bin == lo;
     if (above && active) kk[q].flips ^= kk[q].cand_bit;
   }
@@ -377,10 +378,11 @@ __device__ __forceinline__ void k9_channel_flip(K9Kernel (&kk)[KPT], int64_t ec,
 // SQuant-E and SQuant-K on all the kernels of a thread.
 //   PRESCALE  the weights are first multiplied by the powers of two f1 and f2 (and s, rs are
 //             those of the scaled channel): see k9_channel
+//   owned     bit q: the thread has a kernel q (others hold zeros and leave no trace)
 template <int MODE, int KPT, bool PRESCALE, bool CLAMP>
 __device__ __forceinline__ void k9_solve_all(const float (&w)[9 * KPT], float s, float rs, float qmaxf,
                                              float f1, float f2, K9Kernel (&kk)[KPT], int32_t& esum,
-                                             uint32_t& amin) {
+                                             uint32_t& amin, uint32_t owned = ~0u) {
 #pragma unroll
   for (int q = 0; q < KPT; ++q) {
     // A branch that is always taken (s is finite) but that the compiler cannot fold: it makes
@@ -398,7 +400,8 @@ __device__ __forceinline__ void k9_solve_all(const float (&w)[9 * KPT], float s,
     uint32_t pb[9];
     k9_round<true, CLAMP>(x, s, rs, qmaxf, kk[q], pb);
     if (MODE != SQUANT_MODE_E) {
-      amin = umin2(amin, k9_flip<MODE>(pb, kk[q], esum));
+      const uint32_t sum = k9_flip<MODE>(pb, kk[q], esum);
+      amin = umin2(amin, (owned >> q) & 1u ? sum : ~0u);
       if (MODE == SQUANT_MODE_EK) k9_apply_flips(kk[q]);
     }
   }
@@ -409,7 +412,10 @@ __device__ __forceinline__ void k9_solve_all(const float (&w)[9 * KPT], float s,
 // stay full.
 //   WT   the weight type when it is known at compile time (squant_wtype_t), -1: the launch's
 //   NWC  the waves per workgroup when known at compile time, 0: the launch's
-template <int MODE, int KPT, int WT = -1, int NWC = 0>
+//   ANY  any cin and any alignment: G = ceil(cin / KPT), the kernels past the channel's end read
+//        as zeros through the range of the row's descriptor, and the row is written through one.
+//        (Otherwise cin is a multiple of four, weights start on 16 bytes and codes on four.)
+template <int MODE, int KPT, int WT = -1, int NWC = 0, bool ANY = false>
 __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc& d, int m,
                                            unsigned char* smem, K9Shared& sh) {
   constexpr bool kChannelStage = MODE == SQUANT_MODE_EKC || MODE == SQUANT_MODE_EC;
@@ -418,21 +424,30 @@ __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc
   const float qmaxf = (float)a.qmax;
   uint8_t* code8 = reinterpret_cast<uint8_t*>(smem);  // biased codes: code + 128
 
-  const int N = d.N, G = N / KPT;
+  const int N = d.N, G = ANY ? (N + KPT - 1) / KPT : N / KPT;
   const int L = 9 * N, nvec = L >> 2;  // dwords of codes (cin % 4 == 0)
   const bool active = tid < G;
   const int t = active ? tid : 0;  // idle threads shadow thread 0's loads and write nothing
+  uint32_t owned = active ? ~0u : 0u;  // bit q: kernel t + q * G exists and is this thread's
+  if (ANY && active) {
+#pragma unroll
+    for (int q = 1; q < KPT; ++q) owned &= tid + q * G < N ? ~0u : ~(1u << q);
+  }
   float w[9 * KPT];
-  if (wtype == SQUANT_W_F32) {
+  if (wtype == SQUANT_W_F32 && !ANY) {
     const float* src = static_cast<const float*>(d.w) + (size_t)m * L;
 #pragma unroll
     for (int q = 0; q < KPT; ++q) k9_load_kernel(w, q, src + (size_t)q * (9 * G), 9u * (uint32_t)t);
   } else {
-    const uint32_t* chan32 =
-        reinterpret_cast<const uint32_t*>(static_cast<const uint16_t*>(d.w) + (size_t)m * L);
+    const uint32_t each = wtype == SQUANT_W_F32 ? 36u : 18u;  // bytes of a kernel
+    const rsrc_t row = make_rsrc(static_cast<const uint8_t*>(d.w) + (size_t)m * N * each, each * (uint32_t)N);
+    const uint32_t lane_off = active ? each * (uint32_t)tid : 0x40000000u;  // idle threads: out of range
     const bool bf16 = wtype == SQUANT_W_BF16;
 #pragma unroll
-    for (int q = 0; q < KPT; ++q) k9_load_kernel16(w, q, chan32, (uint32_t)(t + q * G), bf16);
+    for (int q = 0; q < KPT; ++q) {
+      if (wtype == SQUANT_W_F32) k9_load_kernel_row(w, q, row, lane_off, each * (uint32_t)(q * G));
+      else k9_load_kernel16(w, q, row, lane_off, each * (uint32_t)(q * G), bf16);
+    }
   }
   if (kChannelStage) k9_select_reset<NWC>(sh.sel);  // before the first barrier
 
@@ -456,20 +471,21 @@ __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc
   if (amax <= 0x1p60f && (amax >= 0x1p-60f || amax == 0.0f)) {
     const float rs = 1.0f / s;
     // the largest quotient of the channel: no element needs the clamp unless this one does
-    if (div_by_reciprocal(amax, s, rs) <= qmaxf) k9_solve_all<MODE, KPT, false, false>(w, s, rs, qmaxf, 1.0f, 1.0f, kk, esum, amin);
-    else k9_solve_all<MODE, KPT, false, true>(w, s, rs, qmaxf, 1.0f, 1.0f, kk, esum, amin);
+    if (div_by_reciprocal(amax, s, rs) <= qmaxf) k9_solve_all<MODE, KPT, false, false>(w, s, rs, qmaxf, 1.0f, 1.0f, kk, esum, amin, ANY ? owned : ~0u);
+    else k9_solve_all<MODE, KPT, false, true>(w, s, rs, qmaxf, 1.0f, 1.0f, kk, esum, amin, ANY ? owned : ~0u);
   } else {
     const float f1 = amax < 1.0f ? 0x1p64f : 0x1p-64f;
     const float a1 = amax * f1;
     const float f2 = a1 < 0x1p-60f ? 0x1p64f : a1 > 0x1p60f ? 0x1p-64f : 1.0f;
     const float s2 = s * f1 * f2;
-    k9_solve_all<MODE, KPT, true, true>(w, s2, 1.0f / s2, qmaxf, f1, f2, kk, esum, amin);
+    k9_solve_all<MODE, KPT, true, true>(w, s2, 1.0f / s2, qmaxf, f1, f2, kk, esum, amin, ANY ? owned : ~0u);
   }
 
   if (kChannelStage) {
     if (amin == 0u && active) {
 #pragma unroll
       for (int q = 0; q < KPT; ++q) {
+        if (ANY && !((owned >> q) & 1u)) continue;
         const int3 z = k9_recheck_kernel(d.w, (size_t)m * L + 9 * (t + q * G), wtype, s, qmaxf);
         if (z.x) k9_set_zero_sum_candidate(kk[q], z.y, z.z);
       }
@@ -478,13 +494,14 @@ __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc
     // publishes the partial sums and the histogram
     if (active) {
 #pragma unroll
-      for (int q = 0; q < KPT; ++q) count_candidate(sh.sel, kk[q].cand);
+      for (int q = 0; q < KPT; ++q)
+        if (!ANY || ((owned >> q) & 1u)) count_candidate(sh.sel, kk[q].cand);
     }
     // after SQuant-K a kernel's sum is at most a half; without it (mode E&C) up to 4.5
     const int64_t ws = MODE == SQUANT_MODE_EC ? wave_sum_dpp(active ? esum : 0)
                                               : wave_sum_rows(active ? esum : 0);
     const int64_t ec = k9_block_sum<NWC>(ws, sh.red_i);
-    k9_channel_flip<KPT>(kk, ec, N, t, G, active, reinterpret_cast<uint32_t*>(smem), sh.sel);
+    k9_channel_flip<KPT>(kk, ec, N, t, G, owned, reinterpret_cast<uint32_t*>(smem), sh.sel);
 #pragma unroll
     for (int q = 0; q < KPT; ++q) k9_apply_flips(kk[q]);
   }
@@ -492,27 +509,30 @@ __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc
   if (active) {
 #pragma unroll
     for (int q = 0; q < KPT; ++q) {
+      if (ANY && !((owned >> q) & 1u)) continue;
       uint8_t* dst = code8 + 9 * (t + q * G);
       const uint64_t lo = (uint64_t)kk[q].d0 | ((uint64_t)kk[q].d1 << 32);
       __builtin_memcpy(dst, &lo, 8);
       dst[8] = (uint8_t)kk[q].d2;
     }
   }
+  if (ANY && tid == 0) code8[L] = 128;  // the element a packed row of odd length is short of
   __syncthreads();
 
-  emit_channel(reinterpret_cast<const uint32_t*>(smem), nvec, d.out, m, s, a.out_format, tid, T);
+  if (ANY) emit_row(code8, L, d.out, m, s, a.out_format, tid, T);
+  else emit_channel(reinterpret_cast<const uint32_t*>(smem), nvec, d.out, m, s, a.out_format, tid, T);
 }
 
 // Compiled for five waves per SIMD (at most 102 VGPRs): left alone, the scheduler interleaves
 // the four kernels of a thread further than the register file pays for.
-template <int MAX_THREADS, int MODE, int KPT, int WT = -1, int NWC = 0>
+template <int MAX_THREADS, int MODE, int KPT, int WT = -1, int NWC = 0, bool ANY = false>
 __global__ void __launch_bounds__(MAX_THREADS) __attribute__((amdgpu_waves_per_eu(5)))
     squant_channel_k9(LaunchArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];  // 9*N bytes of codes
   __shared__ K9Shared sh;
   int m;
   const TensorDesc d = locate(a, blockIdx.x, m);
-  k9_channel<MODE, KPT, WT, NWC>(a, d, m, smem, sh);
+  k9_channel<MODE, KPT, WT, NWC, ANY>(a, d, m, smem, sh);
 }
 
 // ---------------------------------------------------------------------------

@@ -11,8 +11,10 @@ namespace squant {
 typedef void (*kernel_t)(LaunchArgs);
 
 // mode: squant_mode_t, wtype: squant_wtype_t, threads: of the workgroup, tail: some channel is
-// no whole number of 16-byte vectors.
-kernel_t k9_kernel(int kpt, int threads, int mode, int wtype);
+// no whole number of 16-byte vectors, any: some channel count is no multiple of four or some
+// buffer off its alignment.
+kernel_t k9_kernel(int kpt, int threads, int mode, int wtype, bool any);
+kernel_t k9_any_kernel(int kpt, int threads, int mode);
 kernel_t dw9_kernel(int mode);
 kernel_t ks_kernel(int K, int kpt, int threads, int mode);
 kernel_t ks_mixed_kernel(int mode);

@@ -22,6 +22,7 @@ kernel_t k1_wave_of(bool channel_stage, bool half, bool tail) {
 kernel_t k1_wave_kernel(int nv, int mode, int wtype, bool tail) {
   const bool stage = mode == SQUANT_MODE_EKC || mode == SQUANT_MODE_EC, half = wtype != SQUANT_W_F32;
   switch (nv) {
+    case 1: return k1_wave_of<1>(stage, half, tail);
     case 2: return k1_wave_of<2>(stage, half, tail);
     case 3: return k1_wave_of<3>(stage, half, tail);
     case 4: return k1_wave_of<4>(stage, half, tail);

@@ -5,7 +5,8 @@
 
 namespace squant {
 
-kernel_t k9_kernel(int kpt, int threads, int mode, int wtype) {
+kernel_t k9_kernel(int kpt, int threads, int mode, int wtype, bool any) {
+  if (any) return k9_any_kernel(kpt, threads, mode);
 #define SQ_K9_ROW(T, KPT)                                                                     \
   {squant_channel_k9<T, SQUANT_MODE_E, KPT>, squant_channel_k9<T, SQUANT_MODE_EK, KPT>,       \
    squant_channel_k9<T, SQUANT_MODE_EKC, KPT>, squant_channel_k9<T, SQUANT_MODE_EC, KPT>}

@@ -19,31 +19,50 @@
 
 namespace squant {
 
-typedef float vf2 __attribute__((ext_vector_type(2)));
-// kernels start on 4-byte boundaries only
-typedef vf4 vf4_dword __attribute__((aligned(4)));
-typedef vf3 vf3_dword __attribute__((aligned(4)));
-typedef vf2 vf2_dword __attribute__((aligned(4)));
-
-// K consecutive floats at p (4-byte aligned) into w[K*q .. K*q+K-1], in 16-byte pieces and
-// one shorter piece.
+// K consecutive weights (binary32 or 16-bit, at any alignment) into w[K*q .. K*q+K-1], in 16-byte
+// pieces and shorter ones; a kernel behind the channel's end reads as zeros.
 template <int K, int NW>
-__device__ __forceinline__ void ks_load_kernel(float (&w)[NW], int q, const float* p) {
-  const uintptr_t a = reinterpret_cast<uintptr_t>(p);
+__device__ __forceinline__ void ks_load_kernel(float (&w)[NW], int q, rsrc_t row, uint32_t lane_off, uint32_t off) {
   constexpr int V4 = K / 4, R = K % 4;
 #pragma unroll
   for (int j = 0; j < V4; ++j) {
-    const vf4 v = *reinterpret_cast<const __attribute__((address_space(1))) vf4_dword*>(a + 16 * j);
-    w[K * q + 4 * j] = v.x; w[K * q + 4 * j + 1] = v.y; w[K * q + 4 * j + 2] = v.z; w[K * q + 4 * j + 3] = v.w;
+    const vu4 v = buffer_load_u4(row, lane_off + 16u * j, off);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[K * q + 4 * j + e] = __uint_as_float(v[e]);
   }
   if (R == 3) {
-    const vf3 v = *reinterpret_cast<const __attribute__((address_space(1))) vf3_dword*>(a + 16 * V4);
-    w[K * q + 4 * V4] = v.x; w[K * q + 4 * V4 + 1] = v.y; w[K * q + 4 * V4 + 2] = v.z;
+    const vu3 v = buffer_load_u3(row, lane_off + 16u * V4, off);
+#pragma unroll
+    for (int e = 0; e < 3; ++e) w[K * q + 4 * V4 + e] = __uint_as_float(v[e]);
   } else if (R == 2) {
-    const vf2 v = *reinterpret_cast<const __attribute__((address_space(1))) vf2_dword*>(a + 16 * V4);
-    w[K * q + 4 * V4] = v.x; w[K * q + 4 * V4 + 1] = v.y;
+    const vu2 v = buffer_load_u2(row, lane_off + 16u * V4, off);
+    w[K * q + 4 * V4] = __uint_as_float(v.x); w[K * q + 4 * V4 + 1] = __uint_as_float(v.y);
   } else if (R == 1) {
-    w[K * q + 4 * V4] = *reinterpret_cast<const __attribute__((address_space(1))) float*>(a + 16 * V4);
+    w[K * q + 4 * V4] = __uint_as_float(buffer_load_u1(row, lane_off + 16u * V4, off));
+  }
+}
+template <int K, int NW>
+__device__ __forceinline__ void ks_load_kernel16(float (&w)[NW], int q, rsrc_t row, uint32_t lane_off, uint32_t off,
+                                                 bool bf16) {
+  constexpr int V8 = K / 8;
+  uint32_t d[(K + 1) / 2];
+#pragma unroll
+  for (int j = 0; j < V8; ++j) {
+    const vu4 v = buffer_load_u4(row, lane_off + 16u * j, off);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) d[4 * j + e] = v[e];
+  }
+  if (K & 4) {
+    const vu2 v = buffer_load_u2(row, lane_off + 16u * V8, off);
+    d[4 * V8] = v.x; d[4 * V8 + 1] = v.y;
+  }
+  if (K & 2) d[(K & ~3) / 2] = buffer_load_u1(row, lane_off + 2u * (K & ~3), off);
+  if (K & 1) d[K / 2] = buffer_load_u16(row, lane_off + 2u * (K - 1), off);
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    float lo, hi;
+    widen_pair(d[i / 2], bf16, lo, hi);
+    w[K * q + i] = i & 1 ? hi : lo;
   }
 }
 
@@ -141,10 +160,11 @@ __device__ __noinline__ int2 ks_zero_sum_candidate(const void* w, size_t first, 
 
 template <int K, int KPT, bool FAST, int MODE>
 __device__ __forceinline__ void ks_solve_all(const float (&w)[K * KPT], float s, float rs, float qmaxf,
-                                             uint8_t* code8, int t, int G, int32_t& esum,
+                                             uint8_t* code8, int t, int G, uint32_t owned, int32_t& esum,
                                              uint32_t (&cv)[KPT], int (&ci)[KPT], uint32_t& zero) {
 #pragma unroll
   for (int q = 0; q < KPT; ++q) {
+    if (!((owned >> q) & 1u)) continue;
     float cf[K];
     ks_solve<K, K * KPT, FAST, MODE>(w, q, s, rs, qmaxf, cf, esum, cv[q], ci[q], zero);
     const int n = t + q * G;
@@ -153,7 +173,8 @@ __device__ __forceinline__ void ks_solve_all(const float (&w)[K * KPT], float s,
   }
 }
 
-// One workgroup per output channel of N = KPT * G kernels, N * K a multiple of 4.
+// One workgroup per output channel of N kernels, any N and any alignment; thread t takes kernels
+// t, t + G, ..., G = ceil(N / KPT).
 template <int MODE, int K, int KPT>
 __device__ __forceinline__ void ks_channel(const LaunchArgs& a, const TensorDesc& d, int m,
                                            unsigned char* smem, K9Shared& sh) {
@@ -162,22 +183,25 @@ __device__ __forceinline__ void ks_channel(const LaunchArgs& a, const TensorDesc
   const float qmaxf = (float)a.qmax;
   uint8_t* code8 = reinterpret_cast<uint8_t*>(smem);  // biased codes: code + 128
 
-  const int N = d.N, G = N / KPT;
-  const int L = K * N, nvec = L >> 2;
+  const int N = d.N, G = (N + KPT - 1) / KPT;
+  const int L = K * N;
   const bool active = tid < G;
-  const int t = active ? tid : 0;  // idle threads shadow thread 0's loads and write nothing
+  const int t = tid;
+  uint32_t owned = active ? ~0u : 0u;  // bit q: kernel t + q * G exists and is this thread's
+  if (active) {
+#pragma unroll
+    for (int q = 1; q < KPT; ++q) owned &= t + q * G < N ? ~0u : ~(1u << q);
+  }
   float w[K * KPT];
-  if (a.wtype == SQUANT_W_F32) {
-    const float* src = static_cast<const float*>(d.w) + (size_t)m * L;
+  {
+    const uint32_t each = K * (a.wtype == SQUANT_W_F32 ? 4u : 2u);  // bytes of a kernel
+    const rsrc_t row = make_rsrc(static_cast<const uint8_t*>(d.w) + (size_t)m * N * each, each * (uint32_t)N);
+    const uint32_t lane_off = active ? each * (uint32_t)t : 0x40000000u;  // idle threads: out of range
 #pragma unroll
-    for (int q = 0; q < KPT; ++q) ks_load_kernel<K>(w, q, src + (size_t)K * (size_t)(t + q * G));
-  } else {
-    const size_t first = (size_t)m * L;
-#pragma unroll
-    for (int q = 0; q < KPT; ++q)
-#pragma unroll
-      for (int i = 0; i < K; ++i)
-        w[K * q + i] = load_weight(d.w, first + (size_t)K * (size_t)(t + q * G) + i, a.wtype);
+    for (int q = 0; q < KPT; ++q) {
+      if (a.wtype == SQUANT_W_F32) ks_load_kernel<K>(w, q, row, lane_off, each * (uint32_t)(q * G));
+      else ks_load_kernel16<K>(w, q, row, lane_off, each * (uint32_t)(q * G), a.wtype == SQUANT_W_BF16);
+    }
   }
   if (kChannelStage) select_reset(sh.sel);  // before the first barrier
 
@@ -196,9 +220,9 @@ __device__ __forceinline__ void ks_channel(const LaunchArgs& a, const TensorDesc
   uint32_t zero = 0;
   if (active) {
     if (amax >= 0x1p-60f && amax <= 0x1p60f) {  // uniform over the workgroup
-      ks_solve_all<K, KPT, true, MODE>(w, s, 1.0f / s, qmaxf, code8, t, G, esum, cv, ci, zero);
+      ks_solve_all<K, KPT, true, MODE>(w, s, 1.0f / s, qmaxf, code8, t, G, owned, esum, cv, ci, zero);
     } else {
-      ks_solve_all<K, KPT, false, MODE>(w, s, 0.0f, qmaxf, code8, t, G, esum, cv, ci, zero);
+      ks_solve_all<K, KPT, false, MODE>(w, s, 0.0f, qmaxf, code8, t, G, owned, esum, cv, ci, zero);
     }
     if (kChannelStage && zero != 0) {
 #pragma unroll
@@ -214,7 +238,8 @@ __device__ __forceinline__ void ks_channel(const LaunchArgs& a, const TensorDesc
   if (kChannelStage) {
     if (active) {
 #pragma unroll
-      for (int q = 0; q < KPT; ++q) count_candidate(sh.sel, cv[q]);
+      for (int q = 0; q < KPT; ++q)
+        if ((owned >> q) & 1u) count_candidate(sh.sel, cv[q]);
     }
     const int64_t ec = block_sum_dpp1(esum, sh.red_i);
     const int sgn = sign_of(ec);
@@ -227,9 +252,10 @@ __device__ __forceinline__ void ks_channel(const LaunchArgs& a, const TensorDesc
                             reinterpret_cast<uint32_t*>(smem), sh.sel);
     }
   }
+  if (tid == 0) code8[L] = 128;  // the element a packed row of odd length is short of
   __syncthreads();
 
-  emit_channel(reinterpret_cast<const uint32_t*>(smem), nvec, d.out, m, s, a.out_format, tid, T);
+  emit_row(code8, L, d.out, m, s, a.out_format, tid, T);
 }
 
 // Up to 256 threads: compiled for five waves per SIMD (measured 1-3.5 % faster than the
@@ -257,7 +283,7 @@ __global__ void __launch_bounds__(256)
   __shared__ K9Shared sh;
   int m;
   const TensorDesc d = locate(a, blockIdx.x, m);
-  switch (4 * d.K + ks_kpt_log2(d.N, d.K)) {
+  switch (4 * d.K + ks_kpt_log2_any(d.N, d.K, pointers_aligned(d.w, d.out))) {
 #define SQ_KS_CASE(K, LG) \
     case 4 * K + LG: ks_channel<MODE, K, (1 << LG)>(a, d, m, smem, sh); break;
     SQ_KS_CASE(2, 0) SQ_KS_CASE(2, 1) SQ_KS_CASE(2, 2) SQ_KS_CASE(2, 3)

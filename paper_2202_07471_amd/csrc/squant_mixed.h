@@ -36,24 +36,25 @@ __global__ void __launch_bounds__(kMixedMaxThreads)
   // tensor would get in a launch of its own: as few kernels / vectors per thread as T allows.
   // The host only admits tensors with cin <= 4T (3x3) or cin <= 16T (1x1).
   const int T = blockDim.x;
-  const int family = choose_family(d.N, d.K, pointers_aligned(d.w, d.out));
+  const int family = route_family(d.N, d.K, pointers_aligned(d.w, d.out));
   if (family == 9) {
-    if (d.N <= T) k9_channel<MODE, 1, kWeights>(a, d, m, smem, sh);
-    else if (d.N <= 2 * T) k9_channel<MODE, 2, kWeights>(a, d, m, smem, sh);
-    else k9_channel<MODE, 4, kWeights>(a, d, m, smem, sh);
+    if (d.N <= T) k9_channel<MODE, 1, kWeights, 0, true>(a, d, m, smem, sh);
+    else if (d.N <= 2 * T) k9_channel<MODE, 2, kWeights, 0, true>(a, d, m, smem, sh);
+    else k9_channel<MODE, 4, kWeights, 0, true>(a, d, m, smem, sh);
   } else if (family == 1) {
     K1Shared& sh1 = *reinterpret_cast<K1Shared*>(shared);
-    const int nvec = d.N >> 2;
-    if (nvec <= T) k1_channel<M1, 1, 4, HALF, false>(a, d, m, smem, sh1);
-    else if (nvec <= 2 * T) k1_channel<M1, 2, 4, HALF, false>(a, d, m, smem, sh1);
-    else if (nvec <= 3 * T) k1_channel<M1, 3, 4, HALF, false>(a, d, m, smem, sh1);
-    else k1_channel<M1, 4, 4, HALF, false>(a, d, m, smem, sh1);
+    const int nvec = (d.N + 3) >> 2;
+    if (nvec <= T) k1_channel<M1, 1, 4, HALF, true>(a, d, m, smem, sh1);
+    else if (nvec <= 2 * T) k1_channel<M1, 2, 4, HALF, true>(a, d, m, smem, sh1);
+    else if (nvec <= 3 * T) k1_channel<M1, 3, 4, HALF, true>(a, d, m, smem, sh1);
+    else k1_channel<M1, 4, 4, HALF, true>(a, d, m, smem, sh1);
   } else if (family == 3) {
     dw9_channels<MODE>(a, d, m);
   } else if (family == 4) {
     k1_team_dispatch<M1>(a, d, m);
   } else if (family == 6) {
-    k1_wave_dispatch<M1, HALF>(a, d, m, smem);
+    if ((d.N & 3) == 0 && d.N > kMaxTeamCin) k1_wave_dispatch<M1, HALF, false>(a, d, m, smem);
+    else k1_wave_dispatch<M1, HALF, true>(a, d, m, smem);
   } else {
     generic_channel(a, d, m, smem, gs);
   }

@@ -81,7 +81,7 @@ SQ_HD int64_t k1_threads(int64_t nvec, int nv) {
 
 // The wave-per-channel 1x1 / FC kernel: 16-byte vectors per lane of a channel of N elements.
 SQ_HD int k1_wave_nv(int64_t N) { return (int)((N / 4 + 63) / 64); }
-SQ_HD bool is_k1_wave(int variant) { return variant >= kK1Wave + 2 && variant <= kK1Wave + 8; }
+SQ_HD bool is_k1_wave(int variant) { return variant >= kK1Wave + 1 && variant <= kK1Wave + 8; }
 
 // 16-byte vectors per thread of a 1x1 / FC variant (0: not one), and back.
 SQ_HD int k1_variant_nv(int variant) {
@@ -172,6 +172,65 @@ SQ_HD int choose_variant(int64_t N, int64_t K, bool aligned) {
   if (family == 6) return kK1Wave + k1_wave_nv(N);
   if (family == 5) return ks_variant(K, ks_kpt_log2(N, K));
   return kGeneric;
+}
+
+// ---- shapes and alignments the choices above leave to the generic kernel ----
+// A channel count that is no multiple of four (a pruned network) and weights or codes that start
+// anywhere (a checkpoint in one buffer without padding) go through the same register kernels,
+// which read and write rows by descriptors whose range check stands in for both conditions
+// (the generic kernel took 120 us for a ResNet-50-shaped network with such channel counts, nine
+// times the time of its bytes).
+
+// log2 of the small kernels per thread for any N: the measured choice where that applies, else the
+// same rule with the kernels spread over ceil(N / c) threads.  -1: none fits.
+SQ_HD int ks_kpt_log2_any(int64_t N, int64_t K, bool aligned) {
+  if (!ks_has(K)) return -1;
+  const int pinned = aligned ? ks_kpt_log2(N, K) : -1;
+  if (pinned >= 0) return pinned;
+  const int top = ks_max_kpt_log2(K);
+  int best = -1;
+  int64_t best_num = 0, best_den = 1;
+  for (int lg = top; lg >= 0; --lg) {
+    const int64_t used = (N + ((int64_t)1 << lg) - 1) >> lg, th = round_up64(used);
+    if (th > 1024 || (th > 256 && lg != top)) continue;
+    if (th == 64 && used * 10 >= th * 6) return lg;
+    if (used * best_den > best_num * th) { best_num = used; best_den = th; best = lg; }
+  }
+  return best;
+}
+
+// choose_family with those shapes: 3x3 up to kMaxK9Cin, other small kernels, one-element rows
+// (a wave each up to kMaxWaveCin, a workgroup up to kMaxK1Cin).
+SQ_HD int route_family(int64_t N, int64_t K, bool aligned) {
+  const int family = choose_family(N, K, aligned);
+  if (family != 0) return family;
+  if (K == 9 && N > 1 && N <= kMaxK9Cin) return 9;
+  if (K == 1 && N <= kMaxWaveCin) return 6;
+  if (K == 1 && N <= kMaxK1Cin) return 1;
+  if (N > 1 && ks_kpt_log2_any(N, K, aligned) >= 0) return 5;
+  return 0;
+}
+
+// Whether a 3x3 channel needs the routine for any cin and alignment.
+SQ_HD bool k9_any(int64_t N, bool aligned) { return (N & 3) != 0 || !aligned; }
+
+SQ_HD int route_variant(int64_t N, int64_t K, bool aligned) {
+  const int family = route_family(N, K, aligned);
+  if (family == choose_family(N, K, aligned)) return choose_variant(N, K, aligned);
+  if (family == 9) {  // kernels per thread by the rule of choose_variant
+    int best_c = 4;
+    int64_t best_num = 0, best_den = 1;
+    for (int c = 4; c >= 1; c >>= 1) {
+      const int64_t used = (N + c - 1) / c, th = round_up64(used);
+      if (th > 256 && c != 4) continue;
+      if (th == 64 && used * 10 >= th * 6) { best_c = c; break; }
+      if (used * best_den > best_num * th) { best_num = used; best_den = th; best_c = c; }
+    }
+    return best_c == 4 ? kK9x4 : best_c == 2 ? kK9x2 : kK9x1;
+  }
+  if (family == 6) return kK1Wave + k1_wave_nv(N + 3);
+  if (family == 1) return k1_variant_of(k1_nv_for((N + 3) / 4));
+  return ks_variant(K, ks_kpt_log2_any(N, K, aligned));
 }
 
 // Lanes that share a short 1x1 channel (see squant_k1_team.h).
