@@ -25,23 +25,21 @@ struct BnArgs {
   BnDesc layer[kInlineBn];
 };
 
-__global__ void __launch_bounds__(256) squant_activation_range_kernel(BnArgs a) {
-  __shared__ float red_lo[16], red_hi[16];
-  const BnDesc d = a.layer[blockIdx.x];
-  const float n_sigma = a.n_sigma;
-  const int32_t levels_minus_1 = a.levels_minus_1;
-  squant_act_range_t* out = a.out;
+// One layer by one workgroup of any number of whole waves up to 16.
+__device__ __forceinline__ void activation_range(const float* gamma, const float* beta, int channels, bool relu,
+                                                 float n_sigma, int32_t levels_minus_1, squant_act_range_t* out,
+                                                 float* red_lo, float* red_hi) {
   float lo = INFINITY, hi = -INFINITY;
-  for (int c = threadIdx.x; c < d.channels; c += blockDim.x) {
-    const float t = n_sigma * fabsf(d.gamma[c]);
-    const float b = d.beta[c];
+  for (int c = threadIdx.x; c < channels; c += blockDim.x) {
+    const float t = n_sigma * fabsf(gamma[c]);
+    const float b = beta[c];
     lo = fminf(lo, b - t);
     hi = fmaxf(hi, b + t);
   }
   lo = -block_max(-lo, red_lo);
   hi = block_max(hi, red_hi);
   if (threadIdx.x == 0) {
-    if (d.relu) { lo = fmaxf(lo, 0.0f); hi = fmaxf(hi, 0.0f); }
+    if (relu) { lo = fmaxf(lo, 0.0f); hi = fmaxf(hi, 0.0f); }
     lo += 0.0f;  // a zero bound is +0
     hi += 0.0f;
     squant_act_range_t r;
@@ -53,7 +51,7 @@ __global__ void __launch_bounds__(256) squant_activation_range_kernel(BnArgs a) 
     float z = rintf(-lo / r.scale);
     z = fminf(fmaxf(z, 0.0f), q);
     r.zero_point = (int32_t)z;
-    out[d.out_index] = r;
+    *out = r;
   }
 }
 

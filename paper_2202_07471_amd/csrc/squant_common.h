@@ -16,6 +16,8 @@ constexpr int32_t kHalf = 1 << 22;  // 0.5 in Q23
 constexpr int kWave = 64;
 constexpr int kXcdRun = 64;  // consecutive channels one XCD takes at a time (see locate)
 
+// In a mixed launch a descriptor with K = 0 stands for a batch norm instead: w its gammas, scales
+// its betas, M their number, N whether a ReLU follows, out the squant_act_range_t to write.
 struct TensorDesc {
   const void* w;  // weights, in the launch's weight type
   void* out;      // codes or dequantised weights, in the launch's output format
@@ -38,6 +40,9 @@ struct LaunchArgs {
   int32_t out_format;       // squant_output_t
   int32_t wtype;            // squant_wtype_t
   int32_t wave_span;        // channels a wave of the wave-per-channel 1x1 routine walks
+  float n_sigma;            // for the activation ranges of a mixed launch: see TensorDesc
+  int32_t act_levels_minus_1;
+  int32_t first[kInlineDescs];  // the tables' `first` side by side: locate reads a few lines of them
   TensorDesc table[kInlineDescs];
 };
 
@@ -72,7 +77,7 @@ __device__ __forceinline__ TensorDesc locate(const LaunchArgs& a, int g, int& m)
       int below = 0;
       for (int base = 0; base < a.n_tensors; base += kWave) {
         const int i = base + lane;
-        const int first = i < a.n_tensors ? a.table[i].first : 0x7fffffff;
+        const int first = i < a.n_tensors ? a.first[i] : 0x7fffffff;
         const int cnt = __popcll(__ballot(first <= g));
         below += cnt;
         if (cnt < kWave) break;

@@ -89,8 +89,15 @@ int check_shape(int32_t cout, int32_t cin, int32_t kh, int32_t kw) {
 
 constexpr int kMixed = 100;      // Group::variant of a launch of squant_channel_mixed
 constexpr int kMixedWave = 101;  // the same for the tensors whose channels take one wave each
-constexpr int kKsMixed = 102;    // Group::variant of a launch of squant_channel_ks_mixed
-constexpr int kKsMixedMaxThreads = 128;
+constexpr size_t kMixedMaxLds = 16 * 1024;  // a member that wants more LDS than this stays out of it
+
+// Threads a register-kernel tensor of N kernels, up to `top` per thread, takes as a member of a
+// mixed launch: its own workgroup (`own` threads) up to two waves, else two waves where more
+// kernels per thread make it fit (a member of three waves would send every one-wave member to a
+// launch of its own: InceptionV3-style and pruned ResNet-50 sets).
+int mixed_threads(int own, int64_t N, int top) {
+  return own <= 2 * kWave || (N + top - 1) / top > 2 * kWave ? own : 2 * kWave;
+}
 
 struct Group {
   int variant;
@@ -98,6 +105,8 @@ struct Group {
   size_t lds;
   std::vector<TensorDesc> t;
   bool fixed_threads = false;  // mixed launch: a non-generic member has set the workgroup size
+  float n_sigma = 0.0f;        // of the batch norms among the members
+  int32_t act_levels_minus_1 = 0;
   bool wave_members = false;   // holds wave-per-channel 1x1 tensors: LDS for a selection area per wave
 };
 
@@ -124,7 +133,7 @@ Plan plan_tensor(const void* w, const void* out, int64_t N, int64_t K, int lds_l
       const int kpt = variant == kK9x4 ? 4 : variant == kK9x2 ? 2 : 1;
       // LDS: the channel's int8 codes, one more, whole chunks of 32
       const int th = (int)round_up64((N + kpt - 1) / kpt);
-      return Plan{variant, th, round_up((size_t)9 * N + 1, 32), th};
+      return Plan{variant, th, round_up((size_t)9 * N + 1, 32), mixed_threads(th, N, 4)};
     }
     case kK1x1: case kK1x2: case kK1x3: case kK1x4: case kK1x5: case kK1x6: case kK1x7: case kK1x8:
     case kK1x16: {
@@ -149,7 +158,8 @@ Plan plan_tensor(const void* w, const void* out, int64_t N, int64_t K, int lds_l
   }
   if (is_ks(variant)) {  // LDS: as for 3x3
     const int64_t kpt = ks_variant_kpt(variant);
-    return Plan{variant, (int)round_up64((N + kpt - 1) / kpt), round_up((size_t)K * N + 1, 32), 0};
+    const int th = (int)round_up64((N + kpt - 1) / kpt);
+    return Plan{variant, th, round_up((size_t)K * N + 1, 32), mixed_threads(th, N, 1 << ks_max_kpt_log2(K))};
   }
   const size_t lds = generic_lds_bytes(N, K);
   if (lds + kStaticLds > (size_t)lds_limit) return stream_plan(N);
@@ -160,17 +170,19 @@ Plan plan_tensor(const void* w, const void* out, int64_t N, int64_t K, int lds_l
 // Whether a tensor may join a launch of the mixed kernel: the mixed kernel carries a routine
 // for it that fits its workgroup size and LDS.
 bool mixable(const Plan& p, size_t lds_cap) {
-  return p.mix_threads > 0 && p.mix_threads <= kMixedMaxThreads &&
-         p.lds <= lds_cap;
+  return p.mix_threads > 0 && p.mix_threads <= kMixedMaxThreads && p.lds <= std::min(kMixedMaxLds, lds_cap);
 }
 
 // Launches tensors [begin, end) of a group (at most kInlineDescs of them) as one kernel.
 int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, int output, int wtype,
                 int wave_span, hipStream_t st) {
   LaunchArgs a{};
+  a.n_sigma = g.n_sigma;
+  a.act_levels_minus_1 = g.act_levels_minus_1;
   int64_t total = 0;
   bool uniform = true;
   auto items_of = [&](const TensorDesc& t) {
+    if (t.K == 0) return (int64_t)1;  // a batch norm
     return work_items(t.M, t.N, t.K, g.threads, route_family(t.N, t.K, pointers_aligned(t.w, t.out)),
                       wave_span);
   };
@@ -179,7 +191,7 @@ int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, in
     const TensorDesc& t = g.t[i];
     const int64_t items = items_of(t);
     a.table[i - begin] = t;
-    a.table[i - begin].first = (int32_t)total;  // first workgroup within this launch
+    a.table[i - begin].first = a.first[i - begin] = (int32_t)total;  // first workgroup within this launch
     total += items;
     uniform &= items == items0;
     if (total > 0x7fffffff) return SQUANT_ERR_SHAPE;
@@ -199,15 +211,17 @@ int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, in
   a.wave_span = wave_span;
   const int nv = k1_variant_nv(g.variant);
   bool tail = false;  // 1x1 / FC rows: any that is no whole number of 16-byte vectors
-  bool any = false;   // 3x3: any off the common channel counts and alignments
+  bool any = false;   // any off the common channel counts and alignments (mixed: or another small kernel)
   for (size_t i = begin; i < end; ++i) {
     const TensorDesc& t = g.t[i];
+    if (t.K == 0) continue;
+    const bool aligned = pointers_aligned(t.w, t.out);
     tail |= t.N % (wtype == SQUANT_W_F32 ? 4 : 8) != 0;
-    any |= k9_any(t.N, pointers_aligned(t.w, t.out));
+    any |= route_family(t.N, t.K, aligned) != choose_family(t.N, t.K, aligned) ||
+           (choose_family(t.N, t.K, aligned) == 5 && !is_ks(g.variant));
   }
   const kernel_t kernel = is_ks(g.variant) ? ks_kernel(ks_variant_k(g.variant), ks_variant_kpt(g.variant), g.threads, mode)
-                          : g.variant == kKsMixed ? ks_mixed_kernel(mode)
-                          : (g.variant == kMixed || g.variant == kMixedWave) ? mixed_kernel(mode, wtype)
+                          : (g.variant == kMixed || g.variant == kMixedWave) ? mixed_kernel(mode, wtype, any)
                           : is_k1_wave(g.variant) ? k1_wave_kernel(g.variant - kK1Wave, mode, wtype, tail)
                           : nv ? k1_kernel(nv, mode, wtype, tail)
                           : g.variant == kK1Stream ? k1_stream_kernel(mode)
@@ -248,6 +262,113 @@ int launch_group(const Group& g, int qmax, int mode, int output, int wtype, hipS
     const size_t end = std::min(g.t.size(), begin + (size_t)kInlineDescs);
     if (int rc = launch_part(g, begin, end, qmax, mode, output, wtype, wave_span, st)) return rc;
   }
+  return SQUANT_OK;
+}
+
+// What squant_quantize_network adds to a batched call.
+struct ActArgs {
+  float n_sigma;
+  int32_t bits;
+  squant_act_range_t* ranges;
+};
+
+// The batched call.  bns: batch norms whose ranges join the mixed launch if there is one (a launch
+// of their own takes 5 us, mostly its start and end); *bns is empty afterwards if they did.
+int quantize_batched(const squant_tensor_t* h_tensors, int32_t n_tensors, squant_wtype_t wtype, int32_t bits,
+                     squant_mode_t mode, squant_output_t output, void* d_workspace, size_t workspace_bytes,
+                     std::vector<BnDesc>* bns, const ActArgs* act, hipStream_t st) {
+  if (n_tensors < 0) return SQUANT_ERR_SHAPE;
+  if (n_tensors == 0) return SQUANT_OK;
+  if (!h_tensors) return SQUANT_ERR_NULL;
+  if (int rc = check_common(bits, (int)mode)) return rc;
+  for (int32_t i = 0; i < n_tensors; ++i) {
+    const squant_tensor_t& t = h_tensors[i];
+    if (!t.w || !t.codes || !t.scales) return SQUANT_ERR_NULL;
+    if (int rc = check_shape(t.cout, t.cin, t.kh, t.kw)) return rc;
+    if (int rc = check_format((int)wtype, (int)output, bits, t.w, t.codes)) return rc;
+  }
+  if (!d_workspace && workspace_bytes != 0) return SQUANT_ERR_WORKSPACE;
+  const DeviceLimits lim = device_limits();
+  if (!lim.ok) { (void)hipGetLastError(); return SQUANT_ERR_DEVICE; }
+
+  // Group tensors by launch configuration.  Tensors whose variant runs in workgroups of at
+  // most kMixedMaxThreads threads share ONE launch of the mixed kernel when they differ in
+  // variant or launch shape (the layers of a network); a uniform set keeps its own kernel.
+  std::vector<Plan> plans((size_t)n_tensors);
+  const size_t lds_cap = (size_t)lim.lds_bytes - kStaticLds - sizeof(K9Shared) - sizeof(GenericShared);
+  int small_kinds = 0;
+  Plan small_first{};
+  for (int32_t i = 0; i < n_tensors; ++i) {
+    const squant_tensor_t& t = h_tensors[i];
+    Plan p = plan_tensor(t.w, t.codes, t.cin, (int64_t)t.kh * t.kw, lim.lds_bytes);
+    if (p.lds == 0) return SQUANT_ERR_UNSUPPORTED;
+    // LDS size classes: next power of two >= 2 KB keeps the number of launches small
+    size_t cls = 2048;
+    while (cls < p.lds) cls <<= 1;
+    p.lds = std::max(std::min(cls, lds_cap), p.lds);
+    plans[(size_t)i] = p;
+    if (mixable(p, lds_cap)) {
+      if (small_kinds == 0) { small_first = p; small_kinds = 1; }
+      else if (p.variant != small_first.variant || p.threads != small_first.threads ||
+               p.lds != small_first.lds) small_kinds = 2;
+    }
+  }
+  const bool use_mixed = small_kinds > 1;
+  // One mixed launch while its workgroups stay at 128 threads (measured: ResNet-18 set 27 %,
+  // MobileNetV2 set 12 % faster than two launches, ResNet-50 set the same).  When a member
+  // needs 256 threads, the channels that take one wave get a launch of one-wave workgroups of
+  // their own: four times as many of them fit a compute unit.
+  int widest = 0;
+  for (int32_t i = 0; i < n_tensors; ++i) {
+    const Plan& p = plans[(size_t)i];
+    if (use_mixed && mixable(p, lds_cap) && p.variant != kGeneric) widest = std::max(widest, p.mix_threads);
+  }
+  const bool two_classes = widest > 2 * kWave;
+  std::vector<Group> groups;
+  for (int32_t i = 0; i < n_tensors; ++i) {
+    const squant_tensor_t& t = h_tensors[i];
+    const Plan& p = plans[(size_t)i];
+    const bool in_mixed = use_mixed && mixable(p, lds_cap);
+    const int need_threads = p.mix_threads;
+    const int mixed_kind = two_classes && need_threads <= kWave ? kMixedWave : kMixed;
+    Group* g = nullptr;
+    for (auto& c : groups) {
+      if (in_mixed ? c.variant == mixed_kind
+                   : (c.variant == p.variant && c.threads == p.threads && c.lds == p.lds)) { g = &c; break; }
+    }
+    if (!g) {
+      groups.push_back(Group{in_mixed ? mixed_kind : p.variant, in_mixed ? need_threads : p.threads, p.lds, {}});
+      g = &groups.back();
+    }
+    if (in_mixed) {
+      // the workgroup size follows the specialised routines (their kernels / vectors per thread
+      // depend on it); the generic routine strides by whatever size it is given, so a generic
+      // member only sets the size of a launch that has no other kind of member
+      if (p.variant != kGeneric) {
+        g->threads = g->fixed_threads ? std::max(g->threads, need_threads) : need_threads;
+        g->fixed_threads = true;
+      } else if (!g->fixed_threads) {
+        g->threads = std::max(g->threads, need_threads);
+      }
+      g->lds = std::max(g->lds, p.lds);
+    }
+    g->t.push_back(TensorDesc{t.w, t.codes, t.scales, t.cout, t.cin, (int32_t)((int64_t)t.kh * t.kw), 0});
+    g->wave_members |= is_k1_wave(p.variant);
+  }
+  if (bns && !bns->empty()) {
+    for (auto& g : groups) {
+      if (g.variant != kMixed && g.variant != kMixedWave) continue;
+      g.n_sigma = act->n_sigma;
+      g.act_levels_minus_1 = (int32_t)((1 << act->bits) - 1);
+      for (const BnDesc& b : *bns)
+        g.t.push_back(TensorDesc{b.gamma, act->ranges + b.out_index, const_cast<float*>(b.beta), b.channels, b.relu, 0, 0});
+      bns->clear();
+      break;
+    }
+  }
+  const int qmax = (1 << (bits - 1)) - 1;
+  for (const auto& g : groups)
+    if (int rc = launch_group(g, qmax, (int)mode, (int)output, (int)wtype, st)) return rc;
   return SQUANT_OK;
 }
 
@@ -308,101 +429,8 @@ int squant_quantize_batched_ex(const squant_tensor_t* h_tensors, int32_t n_tenso
                                squant_wtype_t wtype, int32_t bits, squant_mode_t mode,
                                squant_output_t output, void* d_workspace, size_t workspace_bytes,
                                void* stream) {
-  if (n_tensors < 0) return SQUANT_ERR_SHAPE;
-  if (n_tensors == 0) return SQUANT_OK;
-  if (!h_tensors) return SQUANT_ERR_NULL;
-  if (int rc = check_common(bits, (int)mode)) return rc;
-  for (int32_t i = 0; i < n_tensors; ++i) {
-    const squant_tensor_t& t = h_tensors[i];
-    if (!t.w || !t.codes || !t.scales) return SQUANT_ERR_NULL;
-    if (int rc = check_shape(t.cout, t.cin, t.kh, t.kw)) return rc;
-    if (int rc = check_format((int)wtype, (int)output, bits, t.w, t.codes)) return rc;
-  }
-  if (!d_workspace && workspace_bytes != 0) return SQUANT_ERR_WORKSPACE;
-  const DeviceLimits lim = device_limits();
-  if (!lim.ok) { (void)hipGetLastError(); return SQUANT_ERR_DEVICE; }
-
-  // Group tensors by launch configuration.  Tensors whose variant runs in workgroups of at
-  // most kMixedMaxThreads threads share ONE launch of the mixed kernel when they differ in
-  // variant or launch shape (the layers of a network); a uniform set keeps its own kernel.
-  std::vector<Plan> plans((size_t)n_tensors);
-  const size_t lds_cap = (size_t)lim.lds_bytes - kStaticLds - sizeof(K9Shared) - sizeof(GenericShared);
-  int small_kinds = 0;
-  Plan small_first{};
-  for (int32_t i = 0; i < n_tensors; ++i) {
-    const squant_tensor_t& t = h_tensors[i];
-    Plan p = plan_tensor(t.w, t.codes, t.cin, (int64_t)t.kh * t.kw, lim.lds_bytes);
-    if (p.lds == 0) return SQUANT_ERR_UNSUPPORTED;
-    // LDS size classes: next power of two >= 2 KB keeps the number of launches small
-    size_t cls = 2048;
-    while (cls < p.lds) cls <<= 1;
-    p.lds = std::max(std::min(cls, lds_cap), p.lds);
-    plans[(size_t)i] = p;
-    if (mixable(p, lds_cap)) {
-      if (small_kinds == 0) { small_first = p; small_kinds = 1; }
-      else if (p.variant != small_first.variant || p.threads != small_first.threads ||
-               p.lds != small_first.lds) small_kinds = 2;
-    }
-  }
-  const bool use_mixed = small_kinds > 1;
-  // Likewise the small-kernel tensors of up to kKsMixedMaxThreads threads per channel share one
-  // launch when they differ in kernel size, kernels per thread or launch shape.
-  int ks_kinds = 0;
-  Plan ks_first{};
-  for (int32_t i = 0; i < n_tensors; ++i) {
-    const Plan& p = plans[(size_t)i];
-    if (!is_ks(p.variant) || p.threads > kKsMixedMaxThreads) continue;
-    if (ks_kinds == 0) { ks_first = p; ks_kinds = 1; }
-    else if (p.variant != ks_first.variant || p.threads != ks_first.threads || p.lds != ks_first.lds) ks_kinds = 2;
-  }
-  const bool use_ks_mixed = ks_kinds > 1;
-  // One mixed launch while its workgroups stay at 128 threads (measured: ResNet-18 set 27 %,
-  // MobileNetV2 set 12 % faster than two launches, ResNet-50 set the same).  When a member
-  // needs 256 threads, the channels that take one wave get a launch of one-wave workgroups of
-  // their own: four times as many of them fit a compute unit.
-  int widest = 0;
-  for (int32_t i = 0; i < n_tensors; ++i) {
-    const Plan& p = plans[(size_t)i];
-    if (use_mixed && mixable(p, lds_cap) && p.variant != kGeneric) widest = std::max(widest, p.mix_threads);
-  }
-  const bool two_classes = widest > 2 * kWave;
-  std::vector<Group> groups;
-  for (int32_t i = 0; i < n_tensors; ++i) {
-    const squant_tensor_t& t = h_tensors[i];
-    const Plan& p = plans[(size_t)i];
-    const bool in_ks_mixed = use_ks_mixed && is_ks(p.variant) && p.threads <= kKsMixedMaxThreads;
-    const bool in_mixed = in_ks_mixed || (use_mixed && mixable(p, lds_cap));
-    const int need_threads = in_ks_mixed ? p.threads : p.mix_threads;
-    const int mixed_kind = in_ks_mixed ? kKsMixed : (two_classes && need_threads <= kWave) ? kMixedWave : kMixed;
-    Group* g = nullptr;
-    for (auto& c : groups) {
-      if (in_mixed ? c.variant == mixed_kind
-                   : (c.variant == p.variant && c.threads == p.threads && c.lds == p.lds)) { g = &c; break; }
-    }
-    if (!g) {
-      groups.push_back(Group{in_mixed ? mixed_kind : p.variant, in_mixed ? need_threads : p.threads, p.lds, {}});
-      g = &groups.back();
-    }
-    if (in_mixed) {
-      // the workgroup size follows the specialised routines (their kernels / vectors per thread
-      // depend on it); the generic routine strides by whatever size it is given, so a generic
-      // member only sets the size of a launch that has no other kind of member
-      if (p.variant != kGeneric) {
-        g->threads = g->fixed_threads ? std::max(g->threads, need_threads) : need_threads;
-        g->fixed_threads = true;
-      } else if (!g->fixed_threads) {
-        g->threads = std::max(g->threads, need_threads);
-      }
-      g->lds = std::max(g->lds, p.lds);
-    }
-    g->t.push_back(TensorDesc{t.w, t.codes, t.scales, t.cout, t.cin, (int32_t)((int64_t)t.kh * t.kw), 0});
-    g->wave_members |= is_k1_wave(p.variant);
-  }
-  hipStream_t st = (hipStream_t)stream;
-  const int qmax = (1 << (bits - 1)) - 1;
-  for (const auto& g : groups)
-    if (int rc = launch_group(g, qmax, (int)mode, (int)output, (int)wtype, st)) return rc;
-  return SQUANT_OK;
+  return quantize_batched(h_tensors, n_tensors, wtype, bits, mode, output, d_workspace, workspace_bytes,
+                          nullptr, nullptr, (hipStream_t)stream);
 }
 
 size_t squant_activation_workspace_bytes(int32_t) { return 0; }
@@ -419,7 +447,7 @@ int launch_activation_ranges(const std::vector<BnDesc>& layers, float n_sigma, i
     a.n_sigma = n_sigma;
     a.levels_minus_1 = (int32_t)((1 << bits) - 1);
     a.out = d_ranges;
-    hipLaunchKernelGGL(squant_activation_range_kernel, dim3((unsigned)cnt), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(activation_range_kernel(), dim3((unsigned)cnt), dim3(256), 0, st, a);
     if (hipGetLastError() != hipSuccess) return SQUANT_ERR_DEVICE;
   }
   return SQUANT_OK;
@@ -472,7 +500,9 @@ int squant_quantize_network(const squant_layer_t* h_layers, int32_t n_layers, in
     bns.push_back(BnDesc{l.gamma, l.beta, l.channels, l.relu, i, 0});
   }
   if (!d_workspace && workspace_bytes != 0) return SQUANT_ERR_WORKSPACE;
-  if (int rc = squant_quantize_batched(weights.data(), n_layers, weight_bits, mode, nullptr, 0, stream))
+  const ActArgs act{n_sigma, act_bits, d_ranges};
+  if (int rc = quantize_batched(weights.data(), n_layers, SQUANT_W_F32, weight_bits, mode, SQUANT_OUT_INT8, nullptr, 0,
+                                &bns, &act, (hipStream_t)stream))
     return rc;
   if (bns.empty()) return SQUANT_OK;
   return launch_activation_ranges(bns, n_sigma, act_bits, d_ranges, (hipStream_t)stream);

@@ -212,6 +212,11 @@ __device__ __forceinline__ uint32_t k1_owner_word(int tid, int q) {
 template <bool WAVE, int VE>
 __device__ __forceinline__ void k1_rank(const uint64_t* list, uint32_t* owner, uint32_t count, uint32_t need) {
   const uint32_t tid = (uint32_t)k1_tid<WAVE>(), T = (uint32_t)k1_team<WAVE>();
+  auto pick = [&](uint64_t entry) {
+    const uint32_t n = ~(uint32_t)entry;
+    const uint32_t q = (n >> 13) * VE + (n & 7u), t = (n >> 3) & 1023u;
+    atomicOr(&owner[(q >> 5) * T + t], 1u << (q & 31u));
+  };
   const uint32_t sub = tid & 3u;
   for (uint32_t i0 = 0; i0 < count; i0 += T >> 2) {
     const uint32_t i = umin2(i0 + (tid >> 2), count);  // past the end: an entry of 0, never picked
@@ -224,11 +229,7 @@ __device__ __forceinline__ void k1_rank(const uint64_t* list, uint32_t* owner, u
     }
     rank += __builtin_amdgcn_update_dpp(0, rank, 0xB1, 0xf, 0xf, true);  // quad_perm [1,0,3,2]
     rank += __builtin_amdgcn_update_dpp(0, rank, 0x4E, 0xf, 0xf, true);  // quad_perm [2,3,0,1]
-    if (sub == 0 && (uint32_t)rank < need) {
-      const uint32_t n = ~(uint32_t)own;
-      const uint32_t q = (n >> 13) * VE + (n & 7u), t = (n >> 3) & 1023u;
-      atomicOr(&owner[(q >> 5) * T + t], 1u << (q & 31u));
-    }
+    if (sub == 0 && (uint32_t)rank < need) pick(own);
   }
 }
 
@@ -307,6 +308,12 @@ __device__ __forceinline__ MaskT k1_channel_stage(const uint32_t (&B)[NE], int32
   // fourth pass halves it, so it ends after at most 4 * 23 passes whatever the distribution.
   // the step of u per element when the perturbations are spread evenly
   const int32_t step = __builtin_amdgcn_readfirstlane((int32_t)(8388608.0f * __builtin_amdgcn_rcpf((float)N)));
+  // The list is ranked in steps of T / 4 entries by eight, each a round trip to LDS, so the search
+  // goes on until the bounds hold a list of a few steps: with lists of up to 128 entries ranked by
+  // a wave the slowest channels of a launch took 3 us longer than the others (1x1 layers of the
+  // MobileNetV2 set 10.6 -> 8.6 us).  With 64 elements a thread a pass costs more than it saves
+  // (six linear layers 119 -> 139 us).
+  const uint32_t cap = NE > 32 ? kListCap : umin2(16u + (uint32_t)T / 8u, kListCap);
   int32_t lo = 1 + sm, hi = (1 << 22) + 1;
   uint32_t n_lo = 0, n_hi = 0, incl = 0;
   MaskT m_lo = 0, m_hi = 0;
@@ -327,13 +334,13 @@ __device__ __forceinline__ MaskT k1_channel_stage(const uint32_t (&B)[NE], int32
       hi = thr; n_hi = n; m_hi = m;
     }
     if (found) {
-      if (n_lo - n_hi <= (uint32_t)kListCap || hi - lo == 1) break;
+      if (n_lo - n_hi <= cap || hi - lo == 1) break;
       if ((pass & 3) == 0) {
         thr = lo + ((hi - lo) >> 1);
       } else {
         // interpolate between the bounds; once the lower one is close, from the other side of `need`
-        float want = n_lo - need > (uint32_t)kListCap / 2 ? (float)need + 0.125f * kListCap
-                                                          : (float)need - 0.25f * kListCap;
+        float want = n_lo - need > cap - (cap >> 2) - 2u ? (float)need + 0.125f * (float)cap
+                                                         : (float)need - 0.25f * (float)cap;
         if (want <= (float)n_hi + 0.5f) want = 0.5f * (float)(n_hi + need);
         const float part = (want - (float)n_hi) * __builtin_amdgcn_rcpf((float)(n_lo - n_hi));
         thr = __builtin_amdgcn_readfirstlane(hi - (int32_t)(part * (float)(hi - lo)));

@@ -318,7 +318,7 @@ __device__ __forceinline__ void k9_select_reset(SelectShared& sel) {
 // LDS room for one dword per kernel of the channel (the place the codes go afterwards).
 // Uniform control flow: every wave scans the histogram for itself and reaches the same
 // decisions.
-template <int KPT>
+template <int KPT, bool ANY>
 __device__ __forceinline__ void k9_channel_flip(K9Kernel (&kk)[KPT], int64_t ec, int N, int t, int G,
                                                 uint32_t owned, uint32_t* list, SelectShared& sel) {
   const int64_t a = ec < 0 ? -ec : ec;
@@ -342,7 +342,7 @@ __device__ __forceinline__ void k9_channel_flip(K9Kernel (&kk)[KPT], int64_t ec,
   for (int q = 0; q < KPT; ++q) {
     const uint32_t bin = kk[q].cand >> 15;
     const bool above = bin - lo - 1u < span;
-    const bool active = (owned >> q) & 1u;
+    const bool active = ANY ? (owned >> q) & 1u : owned != 0;
     at[q] = rank && active && bin == lo;
     if (above && active) kk[q].flips ^= kk[q].cand_bit;
   }
@@ -501,7 +501,7 @@ __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc
     const int64_t ws = MODE == SQUANT_MODE_EC ? wave_sum_dpp(active ? esum : 0)
                                               : wave_sum_rows(active ? esum : 0);
     const int64_t ec = k9_block_sum<NWC>(ws, sh.red_i);
-    k9_channel_flip<KPT>(kk, ec, N, t, G, owned, reinterpret_cast<uint32_t*>(smem), sh.sel);
+    k9_channel_flip<KPT, ANY>(kk, ec, N, t, G, owned, reinterpret_cast<uint32_t*>(smem), sh.sel);
 #pragma unroll
     for (int q = 0; q < KPT; ++q) k9_apply_flips(kk[q]);
   }

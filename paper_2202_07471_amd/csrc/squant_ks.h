@@ -5,7 +5,7 @@
 // arithmetic, LDS only holds the channel's biased codes for SQuant-C and the write-out.
 //
 // The k largest same-sign perturbations of a kernel (Algorithm 2's top-k, k <= K/2) are found
-// by ranking: with unique integer keys (|p| in Q23 above an "index from the end" tie-break,
+// by ranking (up to nine elements; larger kernels step through their keys from the top): with unique integer keys (|p| in Q23 above an "index from the end" tie-break,
 // elements of the other sign below all same-sign ones) the rank of an element is the number of
 // larger keys, K(K-1)/2 comparisons in all; an element flips when its rank is below k, and the
 // candidate is the element of rank k-1 (over SQuant) or k (under SQuant).
@@ -107,33 +107,56 @@ __device__ __forceinline__ void ks_solve(const float (&w)[NW], int q, float s, f
 
   // unique keys: 2^IB |p| + (IM - i) >= 2^IB for the elements with the sign of the sum, below
   // 2^IB for all others; |P| <= 2^22 fits the 24-bit multiply
-  int32_t key[K], rank[K];
+  int32_t key[K];
 #pragma unroll
-  for (int i = 0; i < K; ++i) {
-    key[i] = __mul24(P[i], smask ? -(1 << IB) : (1 << IB)) + (IM - i);
-    rank[i] = i;  // rank = #{larger keys}: i counts the pairs (j < i), corrected below
-  }
+  for (int i = 0; i < K; ++i) key[i] = __mul24(P[i], smask ? -(1 << IB) : (1 << IB)) + (IM - i);
+  const bool over = r < 0;
+  const int32_t want = over ? k - 1 : k;  // the candidate's rank: last flipped resp. first un-flipped (k <= K/2 < K)
+  const float flip = smask ? 129.0f : 127.0f;  // code -= sign(E)
+  int32_t ck = 0;  // the candidate's key
+  if constexpr (K <= 9) {
+    // rank = #{larger keys}, by all pairs
+    int32_t rank[K];
 #pragma unroll
-  for (int i = 0; i < K; ++i)
+    for (int i = 0; i < K; ++i) rank[i] = i;  // i counts the pairs (j < i), corrected below
 #pragma unroll
-    for (int j = i + 1; j < K; ++j) {
-      const int32_t gt = key[j] > key[i] ? 1 : 0;
-      rank[i] += gt;
-      rank[j] -= gt;
+    for (int i = 0; i < K; ++i)
+#pragma unroll
+      for (int j = i + 1; j < K; ++j) {
+        const int32_t gt = key[j] > key[i] ? 1 : 0;
+        rank[i] += gt;
+        rank[j] -= gt;
+      }
+#pragma unroll
+    for (int i = 0; i < K; ++i) cf[i] = c[i] + (rank[i] < k ? flip : 128.0f);
+    if (MODE == SQUANT_MODE_EK) return;
+#pragma unroll
+    for (int i = 0; i < K; ++i) ck |= rank[i] == want ? key[i] : 0;
+  } else {
+    // The keys in descending order, as far as any kernel of the wave needs them (k is rarely above
+    // three): with keys within 2^30 of each other, key - m wraps to a huge number for the keys
+    // below m and to a small one for the others, so the largest difference names the next key.
+    // 1.5 instructions an element and step; all pairs of 25 elements took 900 and spilled.
+    int32_t m = key[0];
+#pragma unroll
+    for (int i = 1; i < K; ++i) m = imax2(m, key[i]);
+    int32_t last = 0x7fffffff;  // the k-th largest key
+#pragma unroll 1
+    for (int32_t rank = 0;; ++rank) {
+      if (rank == k - 1) last = m;
+      if (rank == want) ck = m;
+      if (__ballot(rank < want) == 0ull) break;
+      uint32_t z = 0;
+#pragma unroll
+      for (int i = 0; i < K; ++i) z = umax2(z, (uint32_t)key[i] - (uint32_t)m);
+      m = (int32_t)((uint32_t)m + z);
     }
-
-  // flip the k largest: code -= sign(E)
-  const float flip = smask ? 129.0f : 127.0f;
 #pragma unroll
-  for (int i = 0; i < K; ++i) cf[i] = c[i] + (rank[i] < k ? flip : 128.0f);
-  if (MODE == SQUANT_MODE_EK) return;
+    for (int i = 0; i < K; ++i) cf[i] = c[i] + (key[i] >= last ? flip : 128.0f);
+    if (MODE == SQUANT_MODE_EK) return;
+  }
 
   // ---- perturbation update (Algorithm 3): the kernel's candidate for SQuant-C ----
-  const bool over = r < 0;
-  const int32_t want = over ? k - 1 : k;  // over: last flipped; under: first un-flipped (k <= K/2 < K)
-  int32_t ck = 0;
-#pragma unroll
-  for (int i = 0; i < K; ++i) ck |= rank[i] == want ? key[i] : 0;
   const uint32_t mag = (uint32_t)ck >> IB;  // |p| of that element before any flip (if same-sign)
   const uint32_t absv = over ? (uint32_t)kOne - mag : mag;
   const uint32_t neg = (over ? ~(uint32_t)smask : (uint32_t)smask) & (1u << 23);
@@ -164,7 +187,7 @@ __device__ __forceinline__ void ks_solve_all(const float (&w)[K * KPT], float s,
                                              uint32_t (&cv)[KPT], int (&ci)[KPT], uint32_t& zero) {
 #pragma unroll
   for (int q = 0; q < KPT; ++q) {
-    if (!((owned >> q) & 1u)) continue;
+    if (KPT > 1 && !((owned >> q) & 1u)) continue;
     float cf[K];
     ks_solve<K, K * KPT, FAST, MODE>(w, q, s, rs, qmaxf, cf, esum, cv[q], ci[q], zero);
     const int n = t + q * G;
@@ -270,30 +293,33 @@ __global__ void __launch_bounds__(MAX_THREADS)
   ks_channel<MODE, K, KPT>(a, d, m, smem, sh);
 }
 
-// One launch for tensors of different small-kernel shapes (the factorised 1x7 / 7x1 / 1x3 / 3x1
-// and 5x5 layers of a network): every workgroup looks up its tensor and takes the routine for
-// its kernel size and kernels per thread.  The workgroup may be larger than a member needs;
-// its extra threads idle.
-// Compiled for four waves per SIMD (the 5x5 routine alone would take 130 VGPRs and leave three;
-// measured 3 % faster on the InceptionV3-style set, five and six waves are no better).
+// The routine for a channel of N kernels of K elements in a workgroup of T threads: as few kernels
+// per thread as T allows.
+template <int MODE, int K>
+__device__ __forceinline__ void ks_channel_fit(const LaunchArgs& a, const TensorDesc& d, int m, unsigned char* smem,
+                                               K9Shared& sh) {
+  constexpr int top = ks_max_kpt_log2(K);
+  const int N = d.N, T = blockDim.x;
+  if (N <= T || top < 1) { ks_channel<MODE, K, 1>(a, d, m, smem, sh); return; }
+  if constexpr (top >= 1)
+    if (N <= 2 * T) { ks_channel<MODE, K, 2>(a, d, m, smem, sh); return; }
+  if constexpr (top >= 2)
+    if (N <= 4 * T) { ks_channel<MODE, K, 4>(a, d, m, smem, sh); return; }
+  if constexpr (top >= 3) ks_channel<MODE, K, 8>(a, d, m, smem, sh);
+}
+
+// For the mixed kernel.
 template <int MODE>
-__global__ void __launch_bounds__(256)
-    __attribute__((amdgpu_waves_per_eu(4))) squant_channel_ks_mixed(LaunchArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ K9Shared sh;
-  int m;
-  const TensorDesc d = locate(a, blockIdx.x, m);
-  switch (4 * d.K + ks_kpt_log2_any(d.N, d.K, pointers_aligned(d.w, d.out))) {
-#define SQ_KS_CASE(K, LG) \
-    case 4 * K + LG: ks_channel<MODE, K, (1 << LG)>(a, d, m, smem, sh); break;
-    SQ_KS_CASE(2, 0) SQ_KS_CASE(2, 1) SQ_KS_CASE(2, 2) SQ_KS_CASE(2, 3)
-    SQ_KS_CASE(3, 0) SQ_KS_CASE(3, 1) SQ_KS_CASE(3, 2) SQ_KS_CASE(3, 3)
-    SQ_KS_CASE(4, 0) SQ_KS_CASE(4, 1) SQ_KS_CASE(4, 2) SQ_KS_CASE(4, 3)
-    SQ_KS_CASE(5, 0) SQ_KS_CASE(5, 1) SQ_KS_CASE(5, 2)
-    SQ_KS_CASE(7, 0) SQ_KS_CASE(7, 1) SQ_KS_CASE(7, 2)
-    SQ_KS_CASE(25, 0)
-#undef SQ_KS_CASE
-    default: break;  // the host puts no other tensor into this launch
+__device__ __forceinline__ void ks_dispatch(const LaunchArgs& a, const TensorDesc& d, int m, unsigned char* smem,
+                                            K9Shared& sh) {
+  switch (d.K) {
+    case 2: ks_channel_fit<MODE, 2>(a, d, m, smem, sh); break;
+    case 3: ks_channel_fit<MODE, 3>(a, d, m, smem, sh); break;
+    case 4: ks_channel_fit<MODE, 4>(a, d, m, smem, sh); break;
+    case 5: ks_channel_fit<MODE, 5>(a, d, m, smem, sh); break;
+    case 7: ks_channel_fit<MODE, 7>(a, d, m, smem, sh); break;
+    case 25: ks_channel_fit<MODE, 25>(a, d, m, smem, sh); break;
+    default: break;  // the host puts no other tensor here
   }
 }
 

@@ -5,10 +5,12 @@
 // needs (at most 256); the routines let surplus threads idle.
 #pragma once
 
+#include "squant_act.h"
 #include "squant_generic.h"
 #include "squant_k1_team.h"
 #include "squant_k1_wave.h"
 #include "squant_k9.h"
+#include "squant_ks.h"
 #include "squant_plan.h"
 
 namespace squant {
@@ -16,8 +18,10 @@ namespace squant {
 // Compiled for five waves per SIMD (at most 96 VGPRs, what the four-kernel 3x3 routine needs):
 // these launches live on the number of resident workgroups.  Measured 2-4 % faster on the
 // ResNet-50 and MobileNetV2 sets; eight waves spill in the 3x3 routine and cost ResNet-18 24 %.
-// HALF: 16-bit weights.
-template <int MODE, bool HALF>
+// HALF: 16-bit weights.  ANY: carries the routines for other small kernels, for channel counts that
+// are no multiple of four and for buffers off their alignment; a launch without such members takes
+// the leaner kernel (ResNet-18 and MobileNetV2 sets 5 % faster in it).
+template <int MODE, bool HALF, bool ANY>
 __global__ void __launch_bounds__(kMixedMaxThreads)
     __attribute__((amdgpu_waves_per_eu(5))) squant_channel_mixed(LaunchArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -36,25 +40,30 @@ __global__ void __launch_bounds__(kMixedMaxThreads)
   // tensor would get in a launch of its own: as few kernels / vectors per thread as T allows.
   // The host only admits tensors with cin <= 4T (3x3) or cin <= 16T (1x1).
   const int T = blockDim.x;
-  const int family = route_family(d.N, d.K, pointers_aligned(d.w, d.out));
+  const bool aligned = pointers_aligned(d.w, d.out);
+  const int family = ANY ? route_family(d.N, d.K, aligned) : choose_family(d.N, d.K, aligned);
   if (family == 9) {
-    if (d.N <= T) k9_channel<MODE, 1, kWeights, 0, true>(a, d, m, smem, sh);
-    else if (d.N <= 2 * T) k9_channel<MODE, 2, kWeights, 0, true>(a, d, m, smem, sh);
-    else k9_channel<MODE, 4, kWeights, 0, true>(a, d, m, smem, sh);
+    if (d.N <= T) k9_channel<MODE, 1, kWeights, 0, ANY>(a, d, m, smem, sh);
+    else if (d.N <= 2 * T) k9_channel<MODE, 2, kWeights, 0, ANY>(a, d, m, smem, sh);
+    else k9_channel<MODE, 4, kWeights, 0, ANY>(a, d, m, smem, sh);
   } else if (family == 1) {
     K1Shared& sh1 = *reinterpret_cast<K1Shared*>(shared);
     const int nvec = (d.N + 3) >> 2;
-    if (nvec <= T) k1_channel<M1, 1, 4, HALF, true>(a, d, m, smem, sh1);
-    else if (nvec <= 2 * T) k1_channel<M1, 2, 4, HALF, true>(a, d, m, smem, sh1);
-    else if (nvec <= 3 * T) k1_channel<M1, 3, 4, HALF, true>(a, d, m, smem, sh1);
-    else k1_channel<M1, 4, 4, HALF, true>(a, d, m, smem, sh1);
+    if (nvec <= T) k1_channel<M1, 1, 4, HALF, ANY>(a, d, m, smem, sh1);
+    else if (nvec <= 2 * T) k1_channel<M1, 2, 4, HALF, ANY>(a, d, m, smem, sh1);
+    else if (nvec <= 3 * T) k1_channel<M1, 3, 4, HALF, ANY>(a, d, m, smem, sh1);
+    else k1_channel<M1, 4, 4, HALF, ANY>(a, d, m, smem, sh1);
   } else if (family == 3) {
     dw9_channels<MODE>(a, d, m);
   } else if (family == 4) {
     k1_team_dispatch<M1>(a, d, m);
+  } else if (ANY && family == 5) {
+    ks_dispatch<MODE>(a, d, m, smem, sh);
   } else if (family == 6) {
-    if ((d.N & 3) == 0 && d.N > kMaxTeamCin) k1_wave_dispatch<M1, HALF, false>(a, d, m, smem);
-    else k1_wave_dispatch<M1, HALF, true>(a, d, m, smem);
+    k1_wave_dispatch<M1, HALF, ANY>(a, d, m, smem);
+  } else if (d.K == 0) {  // a batch norm (see TensorDesc)
+    activation_range(static_cast<const float*>(d.w), d.scales, d.M, d.N != 0, a.n_sigma, a.act_levels_minus_1,
+                     static_cast<squant_act_range_t*>(d.out), sh.red_f, reinterpret_cast<float*>(sh.red_i));
   } else {
     generic_channel(a, d, m, smem, gs);
   }

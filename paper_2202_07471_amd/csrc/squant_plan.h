@@ -211,9 +211,6 @@ SQ_HD int route_family(int64_t N, int64_t K, bool aligned) {
   return 0;
 }
 
-// Whether a 3x3 channel needs the routine for any cin and alignment.
-SQ_HD bool k9_any(int64_t N, bool aligned) { return (N & 3) != 0 || !aligned; }
-
 SQ_HD int route_variant(int64_t N, int64_t K, bool aligned) {
   const int family = route_family(N, K, aligned);
   if (family == choose_family(N, K, aligned)) return choose_variant(N, K, aligned);
