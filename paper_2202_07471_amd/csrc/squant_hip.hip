@@ -128,6 +128,10 @@ Plan plan_tensor(const void* w, const void* out, int64_t N, int64_t K, int lds_l
   const int variant = route_variant(N, K, pointers_aligned(w, out));
   // LDS: a selection area per wave of the launch's workgroup, added when the launch goes out
   if (is_k1_wave(variant)) return Plan{variant, kK1WaveThreads, 16, kWave};
+  if (is_k1_wide(variant)) {  // LDS: the owners' masks, two words per thread
+    const int th = (int)round_up64(((N + 3) / 4 + k1_variant_nv(variant) - 1) / k1_variant_nv(variant));
+    return Plan{variant, th, (size_t)8 * th, 0};
+  }
   switch (variant) {
     case kK9x1: case kK9x2: case kK9x4: {
       const int kpt = variant == kK9x4 ? 4 : variant == kK9x2 ? 2 : 1;

@@ -598,12 +598,12 @@ __device__ __forceinline__ void k1_channel(const LaunchArgs& a, const TensorDesc
 }
 
 // One kernel per vector count serves every workgroup size.  Up to seven vectors per thread fit
-// the 64 VGPRs of eight waves per SIMD, eight the 72 of seven, sixteen (workgroups of up to 512
-// threads) the 128 of four.  The steps matter because
+// the 64 VGPRs of eight waves per SIMD, eight the 72 of seven, ten to sixteen the 128 of
+// four.  The steps matter because
 // whole workgroups must fit: at 64 VGPRs a compute unit has 32 wave slots, so two workgroups of
 // 1024 threads or eight of 256 run side by side; at 80 it has 24.
 template <int MODE, int NV, bool HALF, bool TAIL>
-__global__ void __launch_bounds__(NV <= 8 ? 1024 : 512) __attribute__((amdgpu_waves_per_eu(NV <= 7 ? 8 : NV <= 8 ? 7 : 4)))
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(NV <= 7 ? 8 : NV <= 8 ? 7 : 4)))
     squant_channel_k1(LaunchArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];  // the owners' masks
   __shared__ K1Shared sh;

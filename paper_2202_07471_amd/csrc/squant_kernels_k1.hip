@@ -31,6 +31,9 @@ kernel_t k1_kernel(int nv, int mode, int wtype, bool tail) {
     case 6: return k1_of<6>(stage, half, tail);
     case 7: return k1_of<7>(stage, half, tail);
     case 8: return k1_of<8>(stage, half, tail);
+    case 10: return k1_of<10>(stage, half, tail);
+    case 12: return k1_of<12>(stage, half, tail);
+    case 14: return k1_of<14>(stage, half, tail);
     case 16: return k1_of<16>(stage, half, tail);
     default: return nullptr;
   }

@@ -20,11 +20,13 @@ enum Variant {
   kStream = 15,                                // any shape: nothing kept on chip, weights walked repeatedly
   kK1x16 = 16,                                 // 1x1 / FC: 16 vectors per thread
   kK1Wave = 32,                                // 1x1 / FC up to kMaxWaveCin, a wave per channel: kK1Wave + vectors per lane (2..8)
+  kK1Wide = 48,                                // 1x1 / FC beyond kMaxK1Cin in one workgroup: kK1Wide + vectors per thread (10, 12, 14, 16)
   kKs = 1024                                   // small kernels in registers: kKs + 4 * K + log2(kernels per thread)
 };
 
 constexpr int kMaxK9Cin = 4096;   // 3x3 variant: cin % 4 == 0 up to here
 constexpr int kMaxK1Cin = 32768;  // 1x1 variant: cin % 4 == 0 up to here
+constexpr int kMaxWideCin = 65536;  // 1x1 / FC rows held in one workgroup of 1024 threads
 constexpr int kMaxTeamCin = 256;  // 1x1 channels this short share a wave
 constexpr int kMaxWaveCin = 2048; // 1x1 channels up to here take a wave each (at most 8 vectors per lane)
 constexpr int kK1WaveSpan = 4;    // consecutive channels a wave of that kernel walks in a large launch (1 in others)
@@ -84,7 +86,9 @@ SQ_HD int k1_wave_nv(int64_t N) { return (int)((N / 4 + 63) / 64); }
 SQ_HD bool is_k1_wave(int variant) { return variant >= kK1Wave + 1 && variant <= kK1Wave + 8; }
 
 // 16-byte vectors per thread of a 1x1 / FC variant (0: not one), and back.
+SQ_HD bool is_k1_wide(int variant) { return variant > kK1Wide && variant <= kK1Wide + 16; }
 SQ_HD int k1_variant_nv(int variant) {
+  if (is_k1_wide(variant)) return variant - kK1Wide;
   switch (variant) {
     case kK1x1: return 1; case kK1x2: return 2; case kK1x3: return 3; case kK1x4: return 4;
     case kK1x5: return 5; case kK1x6: return 6; case kK1x7: return 7; case kK1x8: return 8;
@@ -201,12 +205,16 @@ SQ_HD int ks_kpt_log2_any(int64_t N, int64_t K, bool aligned) {
 
 // choose_family with those shapes: 3x3 up to kMaxK9Cin, other small kernels, one-element rows
 // (a wave each up to kMaxWaveCin, a workgroup up to kMaxK1Cin).
+// Rows of up to kMaxWideCin elements are held in one workgroup too: walking the weights three times
+// and more instead took 175 us for a [1024, 50176] layer of binary32 weights (18 % of the HBM
+// roofline).
 SQ_HD int route_family(int64_t N, int64_t K, bool aligned) {
   const int family = choose_family(N, K, aligned);
+  if (family == 2 && N <= kMaxWideCin) return 1;
   if (family != 0) return family;
   if (K == 9 && N > 1 && N <= kMaxK9Cin) return 9;
   if (K == 1 && N <= kMaxWaveCin) return 6;
-  if (K == 1 && N <= kMaxK1Cin) return 1;
+  if (K == 1 && N <= kMaxWideCin) return 1;
   if (N > 1 && ks_kpt_log2_any(N, K, aligned) >= 0) return 5;
   return 0;
 }
@@ -226,7 +234,11 @@ SQ_HD int route_variant(int64_t N, int64_t K, bool aligned) {
     return best_c == 4 ? kK9x4 : best_c == 2 ? kK9x2 : kK9x1;
   }
   if (family == 6) return kK1Wave + k1_wave_nv(N + 3);
-  if (family == 1) return k1_variant_of(k1_nv_for((N + 3) / 4));
+  if (family == 1 && N <= kMaxK1Cin) return k1_variant_of(k1_nv_for((N + 3) / 4));
+  if (family == 1) {  // the fewest vectors per thread, in steps of two, that 1024 threads hold the row with
+    const int64_t nv = ((N + 3) / 4 + 1023) / 1024;
+    return kK1Wide + (int)(nv <= 10 ? 10 : (nv + 1) / 2 * 2);
+  }
   return ks_variant(K, ks_kpt_log2_any(N, K, aligned));
 }
 

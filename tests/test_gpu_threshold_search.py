@@ -52,8 +52,10 @@ def values(kind, shape, bits, rng):
     return w.astype(np.float32)
 
 
-# around one vector more per lane, the wave / workgroup border, one, two, four, eight and more waves
-CINS = [260, 512, 516, 1028, 2044, 2048, 2052, 3072, 4096, 6148, 8192, 16384, 24580, 32768]
+# around one vector more per lane, the wave / workgroup border, one, two, four, eight and more waves,
+# and the workgroup of 1024 threads with ten to sixteen vectors each
+CINS = [260, 512, 516, 1028, 2044, 2048, 2052, 3072, 4096, 6148, 8192, 16384, 24580, 32768,
+        33000, 50176, 57347, 65536]
 
 
 @pytest.mark.parametrize("cin", CINS)
