@@ -124,8 +124,8 @@ Plan stream_plan(int64_t N) {
 }
 
 // Picks the kernel variant and launch shape for one tensor (every tensor fits one).
-Plan plan_tensor(const void* w, const void* out, int64_t N, int64_t K, int lds_limit) {
-  const int variant = route_variant(N, K, pointers_aligned(w, out));
+Plan plan_tensor(const void* w, const void* out, int64_t M, int64_t N, int64_t K, int lds_limit) {
+  const int variant = route_variant(M, N, K, pointers_aligned(w, out));
   // LDS: a selection area per wave of the launch's workgroup, added when the launch goes out
   if (is_k1_wave(variant)) return Plan{variant, kK1WaveThreads, 16, kWave};
   if (is_k1_wide(variant)) {  // LDS: the owners' masks, two words per thread
@@ -152,6 +152,7 @@ Plan plan_tensor(const void* w, const void* out, int64_t N, int64_t K, int lds_l
       return Plan{variant, th, lds, mix};
     }
     case kDw9: return Plan{kDw9, kWave, 16, kWave};     // no LDS; 16 stands for "fits"
+    case kDwTeam: return Plan{kDwTeam, kWave, 16, kWave};
     case kK1Team: return Plan{kK1Team, kWave, 16, kWave};
     case kK1Stream: {
       const size_t lds = round_up((size_t)N, 16);  // the channel's int8 codes
@@ -187,8 +188,8 @@ int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, in
   bool uniform = true;
   auto items_of = [&](const TensorDesc& t) {
     if (t.K == 0) return (int64_t)1;  // a batch norm
-    return work_items(t.M, t.N, t.K, g.threads, route_family(t.N, t.K, pointers_aligned(t.w, t.out)),
-                      wave_span);
+    return route_work_items(t.M, t.N, t.K, g.threads, route_family(t.M, t.N, t.K, pointers_aligned(t.w, t.out)),
+                            wave_span);
   };
   const int64_t items0 = items_of(g.t[begin]);
   for (size_t i = begin; i < end; ++i) {
@@ -221,8 +222,8 @@ int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, in
     if (t.K == 0) continue;
     const bool aligned = pointers_aligned(t.w, t.out);
     tail |= t.N % (wtype == SQUANT_W_F32 ? 4 : 8) != 0;
-    any |= route_family(t.N, t.K, aligned) != choose_family(t.N, t.K, aligned) ||
-           (choose_family(t.N, t.K, aligned) == 5 && !is_ks(g.variant));
+    const int family = route_family(t.M, t.N, t.K, aligned);
+    any |= family != 7 && (family != choose_family(t.N, t.K, aligned) || (family == 5 && !is_ks(g.variant)));
   }
   const kernel_t kernel = is_ks(g.variant) ? ks_kernel(ks_variant_k(g.variant), ks_variant_kpt(g.variant), g.threads, mode)
                           : (g.variant == kMixed || g.variant == kMixedWave) ? mixed_kernel(mode, wtype, any)
@@ -231,6 +232,7 @@ int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, in
                           : g.variant == kK1Stream ? k1_stream_kernel(mode)
                           : g.variant == kStream ? stream_kernel(mode)
                           : g.variant == kDw9 ? dw9_kernel(mode)
+                          : g.variant == kDwTeam ? dw_team_kernel(mode)
                           : g.variant == kK1Team ? k1_team_kernel(mode)
                           : g.variant == kK9x1 ? k9_kernel(1, g.threads, mode, wtype, any)
                           : g.variant == kK9x2 ? k9_kernel(2, g.threads, mode, wtype, any)
@@ -304,7 +306,7 @@ int quantize_batched(const squant_tensor_t* h_tensors, int32_t n_tensors, squant
   Plan small_first{};
   for (int32_t i = 0; i < n_tensors; ++i) {
     const squant_tensor_t& t = h_tensors[i];
-    Plan p = plan_tensor(t.w, t.codes, t.cin, (int64_t)t.kh * t.kw, lim.lds_bytes);
+    Plan p = plan_tensor(t.w, t.codes, t.cout, t.cin, (int64_t)t.kh * t.kw, lim.lds_bytes);
     if (p.lds == 0) return SQUANT_ERR_UNSUPPORTED;
     // LDS size classes: next power of two >= 2 KB keeps the number of launches small
     size_t cls = 2048;
@@ -390,7 +392,7 @@ int squant_quantize_ex(const void* d_w, squant_wtype_t wtype, int32_t cout, int3
   const DeviceLimits lim = device_limits();
   if (!lim.ok) { (void)hipGetLastError(); return SQUANT_ERR_DEVICE; }
   const int64_t K = (int64_t)kh * kw;
-  const Plan p = plan_tensor(d_w, d_out, cin, K, lim.lds_bytes);
+  const Plan p = plan_tensor(d_w, d_out, cout, cin, K, lim.lds_bytes);
   if (p.lds == 0) return SQUANT_ERR_UNSUPPORTED;
   Group g{p.variant, p.threads, p.lds, {}};
   g.t.push_back(TensorDesc{d_w, d_out, d_scales, cout, cin, (int32_t)K, 0});

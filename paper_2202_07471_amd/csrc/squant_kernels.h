@@ -17,6 +17,7 @@ typedef void (*kernel_t)(LaunchArgs);
 kernel_t k9_kernel(int kpt, int threads, int mode, int wtype, bool any);
 kernel_t k9_any_kernel(int kpt, int threads, int mode);
 kernel_t dw9_kernel(int mode);
+kernel_t dw_team_kernel(int mode);
 kernel_t ks_kernel(int K, int kpt, int threads, int mode);
 kernel_t k1_kernel(int nv, int mode, int wtype, bool tail);
 kernel_t k1_wave_kernel(int nv, int mode, int wtype, bool tail);

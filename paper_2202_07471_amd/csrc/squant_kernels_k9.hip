@@ -1,6 +1,7 @@
-// 3x3 kernels.
+// 3x3 kernels and depthwise ones.
 #include "squant_kernels.h"
 
+#include "squant_dw.h"
 #include "squant_k9.h"
 
 namespace squant {
@@ -35,6 +36,12 @@ kernel_t dw9_kernel(int mode) {
   static const kernel_t dw9[4] = {squant_channel_dw9<SQUANT_MODE_E>, squant_channel_dw9<SQUANT_MODE_EK>,
                                   squant_channel_dw9<SQUANT_MODE_EKC>, squant_channel_dw9<SQUANT_MODE_EC>};
   return dw9[mode];
+}
+
+kernel_t dw_team_kernel(int mode) {
+  static const kernel_t k[4] = {squant_channel_dw_team<SQUANT_MODE_E>, squant_channel_dw_team<SQUANT_MODE_EK>,
+                                squant_channel_dw_team<SQUANT_MODE_EKC>, squant_channel_dw_team<SQUANT_MODE_EC>};
+  return k[mode];
 }
 
 }  // namespace squant

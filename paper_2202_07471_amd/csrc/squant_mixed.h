@@ -6,6 +6,7 @@
 #pragma once
 
 #include "squant_act.h"
+#include "squant_dw.h"
 #include "squant_generic.h"
 #include "squant_k1_team.h"
 #include "squant_k1_wave.h"
@@ -41,7 +42,7 @@ __global__ void __launch_bounds__(kMixedMaxThreads)
   // The host only admits tensors with cin <= 4T (3x3) or cin <= 16T (1x1).
   const int T = blockDim.x;
   const bool aligned = pointers_aligned(d.w, d.out);
-  const int family = ANY ? route_family(d.N, d.K, aligned) : choose_family(d.N, d.K, aligned);
+  const int family = ANY ? route_family(d.M, d.N, d.K, aligned) : choose_family(d.N, d.K, aligned);
   if (family == 9) {
     if (d.N <= T) k9_channel<MODE, 1, kWeights, 0, ANY>(a, d, m, smem, sh);
     else if (d.N <= 2 * T) k9_channel<MODE, 2, kWeights, 0, ANY>(a, d, m, smem, sh);
@@ -61,6 +62,8 @@ __global__ void __launch_bounds__(kMixedMaxThreads)
     ks_dispatch<MODE>(a, d, m, smem, sh);
   } else if (family == 6) {
     k1_wave_dispatch<M1, HALF, ANY>(a, d, m, smem);
+  } else if (d.N == 1 && d.K > 1 && d.K <= kMaxDwK) {  // family 7
+    dw_team_dispatch<MODE>(a, d, m);
   } else if (d.K == 0) {  // a batch norm (see TensorDesc)
     activation_range(static_cast<const float*>(d.w), d.scales, d.M, d.N != 0, a.n_sigma, a.act_levels_minus_1,
                      static_cast<squant_act_range_t*>(d.out), sh.red_f, reinterpret_cast<float*>(sh.red_i));

@@ -20,6 +20,7 @@ enum Variant {
   kStream = 15,                                // any shape: nothing kept on chip, weights walked repeatedly
   kK1x16 = 16,                                 // 1x1 / FC: 16 vectors per thread
   kK1Wave = 32,                                // 1x1 / FC up to kMaxWaveCin, a wave per channel: kK1Wave + vectors per lane (2..8)
+  kDwTeam = 41,                                // depthwise, up to 64 elements a kernel: a team of lanes per channel
   kK1Wide = 48,                                // 1x1 / FC beyond kMaxK1Cin in one workgroup: kK1Wide + vectors per thread (10, 12, 14, 16)
   kKs = 1024                                   // small kernels in registers: kKs + 4 * K + log2(kernels per thread)
 };
@@ -203,13 +204,23 @@ SQ_HD int ks_kpt_log2_any(int64_t N, int64_t K, bool aligned) {
   return best;
 }
 
-// choose_family with those shapes: 3x3 up to kMaxK9Cin, other small kernels, one-element rows
+// Depthwise kernels other than 3x3 (squant_dw.h): lanes per channel.
+constexpr int kMaxDwK = 64;
+SQ_HD int dw_team_lanes(int64_t K) { return K <= 16 ? 16 : K <= 32 ? 32 : 64; }
+
+// Tensors this small (a stem with three input channels) stay with the generic routine: one of them
+// among the common shapes would otherwise send a whole network to the larger mixed kernel.
+constexpr int64_t kSmallTensor = 16384;
+
+// choose_family with those shapes, 7 = depthwise with a team of lanes per channel: 3x3 up to kMaxK9Cin, other small kernels, one-element rows
 // (a wave each up to kMaxWaveCin, a workgroup up to kMaxK1Cin).
 // Rows of up to kMaxWideCin elements are held in one workgroup too: walking the weights three times
 // and more instead took 175 us for a [1024, 50176] layer of binary32 weights (18 % of the HBM
 // roofline).
-SQ_HD int route_family(int64_t N, int64_t K, bool aligned) {
+SQ_HD int route_family(int64_t M, int64_t N, int64_t K, bool aligned) {
   const int family = choose_family(N, K, aligned);
+  if (family == 0 && N == 1 && K > 1 && K <= kMaxDwK) return 7;
+  if (family == 0 && M * N * K < kSmallTensor) return 0;
   if (family == 2 && N <= kMaxWideCin) return 1;
   if (family != 0) return family;
   if (K == 9 && N > 1 && N <= kMaxK9Cin) return 9;
@@ -219,8 +230,9 @@ SQ_HD int route_family(int64_t N, int64_t K, bool aligned) {
   return 0;
 }
 
-SQ_HD int route_variant(int64_t N, int64_t K, bool aligned) {
-  const int family = route_family(N, K, aligned);
+SQ_HD int route_variant(int64_t M, int64_t N, int64_t K, bool aligned) {
+  const int family = route_family(M, N, K, aligned);
+  if (family == 7) return kDwTeam;
   if (family == choose_family(N, K, aligned)) return choose_variant(N, K, aligned);
   if (family == 9) {  // kernels per thread by the rule of choose_variant
     int best_c = 4;
@@ -254,6 +266,12 @@ SQ_HD int64_t work_items(int64_t M, int64_t N, int64_t K, int64_t T, int family,
   if (family == 6) { const int64_t per = T / 64 * wave_span; return (M + per - 1) / per; }
   (void)K;
   return M;
+}
+
+// The same for every family.
+SQ_HD int64_t route_work_items(int64_t M, int64_t N, int64_t K, int64_t T, int family, int wave_span) {
+  if (family == 7) { const int64_t per = T / dw_team_lanes(K); return (M + per - 1) / per; }
+  return work_items(M, N, K, T, family, wave_span);
 }
 
 SQ_HD bool pointers_aligned(const void* w, const void* out) {

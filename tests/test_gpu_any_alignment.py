@@ -67,6 +67,7 @@ def oracle_mode(mode):
     return {"E": 0, "EK": 1, "EKC": 2, "EC": 3}[mode]
 
 
+# the small-kernel cases carry enough channels not to count as a small tensor (those stay generic)
 CASES = ([(3, 3, n) for n in (2, 3, 5, 31, 63, 65, 66, 127, 130, 153, 255, 257, 511, 514, 1023, 1025, 4095)] +
          [(1, 1, n) for n in (1, 2, 3, 5, 63, 255, 257, 511, 514, 1023, 2047, 2049, 4095, 9001, 32766)] +
          [(1, 3, 2), (3, 1, 85), (1, 7, 33), (7, 1, 129), (2, 2, 63), (2, 2, 514), (1, 5, 67), (5, 5, 3), (5, 5, 65),
@@ -80,7 +81,8 @@ def test_odd_channel_counts(sq, kh, kw, cin):
     for wtype in (torch.float32, torch.float16, torch.bfloat16):
         for output, bits, mode in (("int8", 4, "EKC"), ("int4", 4, "EKC"), ("f32", 3, "EK"), ("bf16", 8, "EKC"),
                                    ("int8", 8, "EC"), ("int4", 2, "E")):
-            w = weights((4, cin, kh, kw), rng, "grid" if lead % 2 else "normal")
+            w = weights((max(4, -(-16384 // (cin * kh * kw))) if cin < 400 else 4, cin, kh, kw), rng,
+                        "grid" if lead % 2 else "normal")
             lead = (lead + 1) % 8
             got, got_s, codes, want_s = run_off_alignment(sq, w, wtype, bits, mode, output, lead)
             what = (kh, kw, cin, wtype, output, bits, mode, lead)
@@ -110,3 +112,20 @@ def test_packed_checkpoint_in_one_call(sq, wtype, mode):
         codes, want_s = oracle.quantize(w, 4, oracle_mode(mode), threads=4)
         assert np.array_equal(s.cpu().numpy(), want_s), tuple(v.shape)
         assert np.array_equal(out.cpu().numpy(), oracle.pack_int4(codes)), tuple(v.shape)
+
+
+@pytest.mark.parametrize("kh,kw", [(1, 2), (2, 2), (1, 7), (4, 4), (1, 17), (5, 5), (4, 8), (3, 11), (7, 7), (8, 8), (5, 13)])
+def test_depthwise_kernels(sq, kh, kw):
+    """One kernel per channel: teams of 16, 32 and 64 lanes at their edges (65 elements: the generic kernel)."""
+    rng = np.random.default_rng(kh * 100 + kw)
+    for lead, (wtype, output, bits, mode) in enumerate([
+            (torch.float32, "int8", 4, "EKC"), (torch.float16, "int4", 4, "EK"), (torch.bfloat16, "f32", 8, "EC"),
+            (torch.float32, "bf16", 2, "EC"), (torch.float32, "int4", 3, "EC"), (torch.bfloat16, "int8", 5, "E")]):
+        for kind in ("grid", "normal"):
+            w = weights((67, 1, kh, kw), rng, kind)
+            got, got_s, codes, want_s = run_off_alignment(sq, w, wtype, bits, mode, output, lead)
+            what = (kh, kw, wtype, output, bits, mode, kind)
+            assert np.array_equal(got_s, want_s), what
+            want = expected(codes, want_s, output).reshape(-1)
+            assert torch.equal(got.view(torch.int16) if output == "bf16" else got,
+                               want.view(torch.int16) if output == "bf16" else want), what
