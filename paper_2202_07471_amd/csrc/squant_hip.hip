@@ -233,7 +233,7 @@ int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, in
                           : g.variant == kStream ? stream_kernel(mode)
                           : g.variant == kDw9 ? dw9_kernel(mode)
                           : g.variant == kDwTeam ? dw_team_kernel(mode)
-                          : g.variant == kK1Team ? k1_team_kernel(mode)
+                          : g.variant == kK1Team ? k1_team_kernel(mode, any)
                           : g.variant == kK9x1 ? k9_kernel(1, g.threads, mode, wtype, any)
                           : g.variant == kK9x2 ? k9_kernel(2, g.threads, mode, wtype, any)
                           : g.variant == kK9x4 ? k9_kernel(4, g.threads, mode, wtype, any)

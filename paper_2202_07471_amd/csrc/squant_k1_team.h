@@ -53,8 +53,14 @@ __device__ __forceinline__ int32_t team_sum_i32(int32_t v) {  // |sum| < 2^31: c
   return v;
 }
 
+typedef uint32_t u32_byte __attribute__((aligned(1)));
+typedef uint16_t u16_byte __attribute__((aligned(1)));
+
 // `item` is the workgroup's index within the tensor: it covers blockDim.x / TEAM channels.
-template <int MODE, int TEAM, int NV>
+//   TAIL  any cin and any alignment: rows are read through the descriptor of the workgroup's
+//         channels, the elements behind a row's end (the next row's) are dropped, and the last,
+//         partial vector of a row is stored element by element
+template <int MODE, int TEAM, int NV, bool TAIL>
 __device__ __forceinline__ void k1_team_channels(const LaunchArgs& a, const TensorDesc& d, int item) {
   constexpr bool kChannelStage = MODE == SQUANT_MODE_EKC || MODE == SQUANT_MODE_EC;
   constexpr int NE = 4 * NV;
@@ -64,27 +70,51 @@ __device__ __forceinline__ void k1_team_channels(const LaunchArgs& a, const Tens
   const int channel = item * per_group + tid / TEAM;
   const bool live = channel < d.M;
   const int c = live ? channel : d.M - 1;  // surplus teams shadow the last channel, store nothing
-  const int N = d.N, nvec = N >> 2;
+  const int N = d.N;
   const float qmaxf = (float)a.qmax;
 
+  const int nvec = TAIL ? (N + 3) >> 2 : N >> 2;
   float w[NE];
+  if (TAIL) {
+    const int first = item * per_group, rows = imin2(per_group, d.M - first);
+    const uint32_t each = a.wtype == SQUANT_W_F32 ? 4u : 2u;
+    const rsrc_t range = make_rsrc(static_cast<const uint8_t*>(d.w) + (size_t)first * N * each, (uint32_t)rows * N * each);
 #pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    const int idx = l + j * TEAM;
-    const bool in = idx < nvec;
-    const size_t at = (size_t)c * N + 4 * (size_t)(in ? idx : 0);
-    float v0, v1, v2, v3;
-    if (a.wtype == SQUANT_W_F32) {
-      const vf4 v = load_global_f4(static_cast<const float*>(d.w) + at);
-      v0 = v.x; v1 = v.y; v2 = v.z; v3 = v.w;
-    } else {
-      const uint32_t* p = reinterpret_cast<const uint32_t*>(static_cast<const uint16_t*>(d.w) + at);
-      const bool bf16 = a.wtype == SQUANT_W_BF16;
-      widen_pair(load_global_u1(p), bf16, v0, v1);
-      widen_pair(load_global_u1(p + 1), bf16, v2, v3);
+    for (int j = 0; j < NV; ++j) {
+      const int n = 4 * (l + j * TEAM);  // first element of this vector
+      const uint32_t at = each * (uint32_t)((c - first) * N + n);
+      if (a.wtype == SQUANT_W_F32) {
+        const vu4 v = buffer_load_u4(range, at, 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[4 * j + e] = n + e < N ? __uint_as_float(v[e]) : 0.0f;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t h = buffer_load_u16(range, at + 2u * e, 0);
+          const float v = a.wtype == SQUANT_W_BF16 ? widen_bf16(h) : widen_f16(h);
+          w[4 * j + e] = n + e < N ? v : 0.0f;
+        }
+      }
     }
-    w[4 * j] = in ? v0 : 0.0f; w[4 * j + 1] = in ? v1 : 0.0f;
-    w[4 * j + 2] = in ? v2 : 0.0f; w[4 * j + 3] = in ? v3 : 0.0f;
+  } else {
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      const int idx = l + j * TEAM;
+      const bool in = idx < nvec;
+      const size_t at = (size_t)c * N + 4 * (size_t)(in ? idx : 0);
+      float v0, v1, v2, v3;
+      if (a.wtype == SQUANT_W_F32) {
+        const vf4 v = load_global_f4(static_cast<const float*>(d.w) + at);
+        v0 = v.x; v1 = v.y; v2 = v.z; v3 = v.w;
+      } else {
+        const uint32_t* p = reinterpret_cast<const uint32_t*>(static_cast<const uint16_t*>(d.w) + at);
+        const bool bf16 = a.wtype == SQUANT_W_BF16;
+        widen_pair(load_global_u1(p), bf16, v0, v1);
+        widen_pair(load_global_u1(p + 1), bf16, v2, v3);
+      }
+      w[4 * j] = in ? v0 : 0.0f; w[4 * j + 1] = in ? v1 : 0.0f;
+      w[4 * j + 2] = in ? v2 : 0.0f; w[4 * j + 3] = in ? v3 : 0.0f;
+    }
   }
 
   float amax = 0.0f;
@@ -150,48 +180,58 @@ __device__ __forceinline__ void k1_team_channels(const LaunchArgs& a, const Tens
     const int idx = l + j * TEAM;
     if (idx >= nvec) continue;
     const size_t at = (size_t)channel * N + 4 * (size_t)idx;  // first element of this vector
+    const int left = TAIL ? N - 4 * idx : 4;                  // elements of it inside the row
     if (a.out_format == SQUANT_OUT_INT8) {
       uint32_t packed = 0;
 #pragma unroll
       for (int e = 0; e < 4; ++e) packed = __builtin_amdgcn_cvt_pk_u8_f32(cf[4 * j + e] + 128.0f, e, packed);
-      store_global_u1(static_cast<int8_t*>(d.out) + at, packed ^ 0x80808080u);
+      packed ^= 0x80808080u;
+      int8_t* out = static_cast<int8_t*>(d.out) + at;
+      if (!TAIL) store_global_u1(out, packed);
+      else if (left >= 4) *reinterpret_cast<u32_byte*>(out) = packed;
+      else
+        for (int e = 0; e < left; ++e) out[e] = (int8_t)(packed >> (8 * e));
     } else if (a.out_format == SQUANT_OUT_INT4) {
       uint32_t packed = 0;
 #pragma unroll
       for (int e = 0; e < 4; ++e) packed |= ((uint32_t)(int)cf[4 * j + e] & 0xFu) << (4 * e);
-      store_global_u16(static_cast<uint8_t*>(d.out) + (size_t)channel * (N / 2) + 2 * (size_t)idx,
-                       (uint16_t)packed);
+      uint8_t* out = static_cast<uint8_t*>(d.out) + (size_t)channel * ((N + 1) / 2) + 2 * (size_t)idx;
+      if (!TAIL) store_global_u16(out, (uint16_t)packed);
+      else if (left >= 3) *reinterpret_cast<u16_byte*>(out) = (uint16_t)packed;
+      else out[0] = (uint8_t)packed;
     } else if (a.out_format == SQUANT_OUT_BF16) {
       uint16_t* out = static_cast<uint16_t*>(d.out) + at;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) out[e] = (uint16_t)bf16_bits((cf[4 * j + e] + 0.0f) * s);  // code -0 is 0
+      for (int e = 0; e < 4; ++e)
+        if (!TAIL || e < left) out[e] = (uint16_t)bf16_bits((cf[4 * j + e] + 0.0f) * s);  // code -0 is 0
     } else {  // SQUANT_OUT_F32
       float* out = static_cast<float*>(d.out) + at;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) out[e] = (cf[4 * j + e] + 0.0f) * s;  // code -0 is 0
+      for (int e = 0; e < 4; ++e)
+        if (!TAIL || e < left) out[e] = (cf[4 * j + e] + 0.0f) * s;  // code -0 is 0
     }
   }
 }
 
 // Picks TEAM and NV from cin (<= kMaxTeamCin): the smallest team whose lanes hold the channel
 // with one vector each, then 16 lanes with two or four vectors.
-template <int MODE>
+template <int MODE, bool TAIL>
 __device__ __forceinline__ void k1_team_dispatch(const LaunchArgs& a, const TensorDesc& d, int item) {
   const int N = d.N;
-  if (N <= 16) k1_team_channels<MODE, 4, 1>(a, d, item);
-  else if (N <= 32) k1_team_channels<MODE, 8, 1>(a, d, item);
-  else if (N <= 64) k1_team_channels<MODE, 16, 1>(a, d, item);
-  else if (N <= 128) k1_team_channels<MODE, 16, 2>(a, d, item);
-  else k1_team_channels<MODE, 16, 4>(a, d, item);
+  if (N <= 16) k1_team_channels<MODE, 4, 1, TAIL>(a, d, item);
+  else if (N <= 32) k1_team_channels<MODE, 8, 1, TAIL>(a, d, item);
+  else if (N <= 64) k1_team_channels<MODE, 16, 1, TAIL>(a, d, item);
+  else if (N <= 128) k1_team_channels<MODE, 16, 2, TAIL>(a, d, item);
+  else k1_team_channels<MODE, 16, 4, TAIL>(a, d, item);
 }
 
 // Compiled for eight waves per SIMD (64 VGPRs instead of 66: measured 1-4 % faster).
-template <int MODE>
+template <int MODE, bool TAIL>
 __global__ void __launch_bounds__(256)
     __attribute__((amdgpu_waves_per_eu(8))) squant_channel_k1_team(LaunchArgs a) {
   int m;
   const TensorDesc d = locate(a, blockIdx.x, m);
-  k1_team_dispatch<MODE>(a, d, m);
+  k1_team_dispatch<MODE, TAIL>(a, d, m);
 }
 
 }  // namespace squant

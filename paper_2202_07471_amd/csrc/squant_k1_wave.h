@@ -62,15 +62,12 @@ __device__ __forceinline__ void k1_wave_item(const LaunchArgs& a, const TensorDe
   k1_wave_channels<MODE, NV, VE, HALF, TAIL, PREFETCH>(a, d, c0, c1, reinterpret_cast<K1WaveSel*>(smem)[wave]);
 }
 
-// For the mixed kernel: vectors per lane from the channel's length, 1 to 8; without the
+// For the mixed kernel: vectors per lane from the channel's length, 2 to 8; without the
 // prefetch, whose registers that kernel does not have.
 template <int MODE, bool HALF, bool TAIL>
 __device__ __forceinline__ void k1_wave_dispatch(const LaunchArgs& a, const TensorDesc& d, int item,
                                                  unsigned char* smem) {
   switch (k1_wave_nv(d.N + 3)) {
-    case 1:
-      if (TAIL) k1_wave_item<MODE, 1, 4, HALF, TAIL, false>(a, d, item, smem);  // whole ones share a wave
-      break;
     case 2: k1_wave_item<MODE, 2, 4, HALF, TAIL, false>(a, d, item, smem); break;
     case 3: k1_wave_item<MODE, 3, 4, HALF, TAIL, false>(a, d, item, smem); break;
     case 4: k1_wave_item<MODE, 4, 4, HALF, TAIL, false>(a, d, item, smem); break;

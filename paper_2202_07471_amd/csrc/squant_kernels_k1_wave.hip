@@ -22,7 +22,6 @@ kernel_t k1_wave_of(bool channel_stage, bool half, bool tail) {
 kernel_t k1_wave_kernel(int nv, int mode, int wtype, bool tail) {
   const bool stage = mode == SQUANT_MODE_EKC || mode == SQUANT_MODE_EC, half = wtype != SQUANT_W_F32;
   switch (nv) {
-    case 1: return k1_wave_of<1>(stage, half, tail);
     case 2: return k1_wave_of<2>(stage, half, tail);
     case 3: return k1_wave_of<3>(stage, half, tail);
     case 4: return k1_wave_of<4>(stage, half, tail);
@@ -34,9 +33,10 @@ kernel_t k1_wave_kernel(int nv, int mode, int wtype, bool tail) {
   }
 }
 
-kernel_t k1_team_kernel(int mode) {
-  return mode == SQUANT_MODE_EKC || mode == SQUANT_MODE_EC ? squant_channel_k1_team<SQUANT_MODE_EKC>
-                                                           : squant_channel_k1_team<SQUANT_MODE_E>;
+kernel_t k1_team_kernel(int mode, bool any) {
+  if (mode == SQUANT_MODE_EKC || mode == SQUANT_MODE_EC)
+    return any ? squant_channel_k1_team<SQUANT_MODE_EKC, true> : squant_channel_k1_team<SQUANT_MODE_EKC, false>;
+  return any ? squant_channel_k1_team<SQUANT_MODE_E, true> : squant_channel_k1_team<SQUANT_MODE_E, false>;
 }
 
 }  // namespace squant

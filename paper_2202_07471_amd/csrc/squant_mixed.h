@@ -57,7 +57,7 @@ __global__ void __launch_bounds__(kMixedMaxThreads)
   } else if (family == 3) {
     dw9_channels<MODE>(a, d, m);
   } else if (family == 4) {
-    k1_team_dispatch<M1>(a, d, m);
+    k1_team_dispatch<M1, ANY>(a, d, m);
   } else if (ANY && family == 5) {
     ks_dispatch<MODE>(a, d, m, smem, sh);
   } else if (family == 6) {

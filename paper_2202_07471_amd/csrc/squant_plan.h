@@ -84,7 +84,7 @@ SQ_HD int64_t k1_threads(int64_t nvec, int nv) {
 
 // The wave-per-channel 1x1 / FC kernel: 16-byte vectors per lane of a channel of N elements.
 SQ_HD int k1_wave_nv(int64_t N) { return (int)((N / 4 + 63) / 64); }
-SQ_HD bool is_k1_wave(int variant) { return variant >= kK1Wave + 1 && variant <= kK1Wave + 8; }
+SQ_HD bool is_k1_wave(int variant) { return variant >= kK1Wave + 2 && variant <= kK1Wave + 8; }
 
 // 16-byte vectors per thread of a 1x1 / FC variant (0: not one), and back.
 SQ_HD bool is_k1_wide(int variant) { return variant > kK1Wide && variant <= kK1Wide + 16; }
@@ -213,7 +213,7 @@ SQ_HD int dw_team_lanes(int64_t K) { return K <= 16 ? 16 : K <= 32 ? 32 : 64; }
 constexpr int64_t kSmallTensor = 16384;
 
 // choose_family with those shapes, 7 = depthwise with a team of lanes per channel: 3x3 up to kMaxK9Cin, other small kernels, one-element rows
-// (a wave each up to kMaxWaveCin, a workgroup up to kMaxK1Cin).
+// (a team of lanes up to kMaxTeamCin, a wave up to kMaxWaveCin, a workgroup up to kMaxWideCin).
 // Rows of up to kMaxWideCin elements are held in one workgroup too: walking the weights three times
 // and more instead took 175 us for a [1024, 50176] layer of binary32 weights (18 % of the HBM
 // roofline).
@@ -224,6 +224,7 @@ SQ_HD int route_family(int64_t M, int64_t N, int64_t K, bool aligned) {
   if (family == 2 && N <= kMaxWideCin) return 1;
   if (family != 0) return family;
   if (K == 9 && N > 1 && N <= kMaxK9Cin) return 9;
+  if (K == 1 && N <= kMaxTeamCin) return 4;
   if (K == 1 && N <= kMaxWaveCin) return 6;
   if (K == 1 && N <= kMaxWideCin) return 1;
   if (N > 1 && ks_kpt_log2_any(N, K, aligned) >= 0) return 5;
@@ -245,6 +246,7 @@ SQ_HD int route_variant(int64_t M, int64_t N, int64_t K, bool aligned) {
     }
     return best_c == 4 ? kK9x4 : best_c == 2 ? kK9x2 : kK9x1;
   }
+  if (family == 4) return kK1Team;
   if (family == 6) return kK1Wave + k1_wave_nv(N + 3);
   if (family == 1 && N <= kMaxK1Cin) return k1_variant_of(k1_nv_for((N + 3) / 4));
   if (family == 1) {  // the fewest vectors per thread, in steps of two, that 1024 threads hold the row with
