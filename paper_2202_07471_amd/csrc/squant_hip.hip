@@ -178,6 +178,12 @@ bool mixable(const Plan& p, size_t lds_cap) {
   return p.mix_threads > 0 && p.mix_threads <= kMixedMaxThreads && p.lds <= std::min(kMixedMaxLds, lds_cap);
 }
 
+// The kernel a tensor of plan p takes in a launch of its own variant: narrow 3x3 channels by teams.
+Plan own_launch(Plan p, int64_t N, int64_t K) {
+  if (K == 9 && N > 1 && N <= kMaxK9TeamCin) return Plan{kK9Team, 4 * kWave, 16, p.mix_threads};
+  return p;
+}
+
 // Launches tensors [begin, end) of a group (at most kInlineDescs of them) as one kernel.
 int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, int output, int wtype,
                 int wave_span, hipStream_t st) {
@@ -188,6 +194,7 @@ int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, in
   bool uniform = true;
   auto items_of = [&](const TensorDesc& t) {
     if (t.K == 0) return (int64_t)1;  // a batch norm
+    if (g.variant == kK9Team) { const int per = g.threads / k9_team_lanes(t.N); return (int64_t)(t.M + per - 1) / per; }
     return route_work_items(t.M, t.N, t.K, g.threads, route_family(t.M, t.N, t.K, pointers_aligned(t.w, t.out)),
                             wave_span);
   };
@@ -232,6 +239,7 @@ int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, in
                           : g.variant == kK1Stream ? k1_stream_kernel(mode)
                           : g.variant == kStream ? stream_kernel(mode)
                           : g.variant == kDw9 ? dw9_kernel(mode)
+                          : g.variant == kK9Team ? k9_team_kernel(mode)
                           : g.variant == kDwTeam ? dw_team_kernel(mode)
                           : g.variant == kK1Team ? k1_team_kernel(mode, any)
                           : g.variant == kK9x1 ? k9_kernel(1, g.threads, mode, wtype, any)
@@ -333,8 +341,8 @@ int quantize_batched(const squant_tensor_t* h_tensors, int32_t n_tensors, squant
   std::vector<Group> groups;
   for (int32_t i = 0; i < n_tensors; ++i) {
     const squant_tensor_t& t = h_tensors[i];
-    const Plan& p = plans[(size_t)i];
-    const bool in_mixed = use_mixed && mixable(p, lds_cap);
+    const bool in_mixed = use_mixed && mixable(plans[(size_t)i], lds_cap);
+    const Plan p = in_mixed ? plans[(size_t)i] : own_launch(plans[(size_t)i], t.cin, (int64_t)t.kh * t.kw);
     const int need_threads = p.mix_threads;
     const int mixed_kind = two_classes && need_threads <= kWave ? kMixedWave : kMixed;
     Group* g = nullptr;
@@ -392,7 +400,7 @@ int squant_quantize_ex(const void* d_w, squant_wtype_t wtype, int32_t cout, int3
   const DeviceLimits lim = device_limits();
   if (!lim.ok) { (void)hipGetLastError(); return SQUANT_ERR_DEVICE; }
   const int64_t K = (int64_t)kh * kw;
-  const Plan p = plan_tensor(d_w, d_out, cout, cin, K, lim.lds_bytes);
+  const Plan p = own_launch(plan_tensor(d_w, d_out, cout, cin, K, lim.lds_bytes), cin, K);
   if (p.lds == 0) return SQUANT_ERR_UNSUPPORTED;
   Group g{p.variant, p.threads, p.lds, {}};
   g.t.push_back(TensorDesc{d_w, d_out, d_scales, cout, cin, (int32_t)K, 0});

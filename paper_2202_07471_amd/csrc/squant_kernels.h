@@ -16,6 +16,7 @@ typedef void (*kernel_t)(LaunchArgs);
 // buffer off its alignment.
 kernel_t k9_kernel(int kpt, int threads, int mode, int wtype, bool any);
 kernel_t k9_any_kernel(int kpt, int threads, int mode);
+kernel_t k9_team_kernel(int mode);
 kernel_t dw9_kernel(int mode);
 kernel_t dw_team_kernel(int mode);
 kernel_t ks_kernel(int K, int kpt, int threads, int mode);

@@ -20,6 +20,7 @@ enum Variant {
   kStream = 15,                                // any shape: nothing kept on chip, weights walked repeatedly
   kK1x16 = 16,                                 // 1x1 / FC: 16 vectors per thread
   kK1Wave = 32,                                // 1x1 / FC up to kMaxWaveCin, a wave per channel: kK1Wave + vectors per lane (2..8)
+  kK9Team = 42,                                // 3x3, 2 to 32 kernels a channel, in a launch of its own: a team of lanes per channel
   kDwTeam = 41,                                // depthwise, up to 64 elements a kernel: a team of lanes per channel
   kK1Wide = 48,                                // 1x1 / FC beyond kMaxK1Cin in one workgroup: kK1Wide + vectors per thread (10, 12, 14, 16)
   kKs = 1024                                   // small kernels in registers: kKs + 4 * K + log2(kernels per thread)
@@ -230,6 +231,12 @@ SQ_HD int route_family(int64_t M, int64_t N, int64_t K, bool aligned) {
   if (N > 1 && ks_kpt_log2_any(N, K, aligned) >= 0) return 5;
   return 0;
 }
+
+// 3x3 channels of up to 32 kernels in a launch of their own (squant_k9_team.h): lanes per channel.
+// In a mixed launch they keep the workgroup routine: there the launch is as long as its slowest
+// members and the narrow layers are few.
+constexpr int kMaxK9TeamCin = 32;
+SQ_HD int k9_team_lanes(int64_t N) { return N <= 4 ? 4 : N <= 8 ? 8 : N <= 16 ? 16 : 32; }
 
 SQ_HD int route_variant(int64_t M, int64_t N, int64_t K, bool aligned) {
   const int family = route_family(M, N, K, aligned);
