@@ -187,7 +187,7 @@ Plan own_launch(Plan p, int64_t N, int64_t K) {
 // Launches tensors [begin, end) of a group (at most kInlineDescs of them) as one kernel.
 int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, int output, int wtype,
                 int wave_span, hipStream_t st) {
-  LaunchArgs a{};
+  LaunchArgs a;  // 11 KB: only the entries in use are filled in
   a.n_sigma = g.n_sigma;
   a.act_levels_minus_1 = g.act_levels_minus_1;
   int64_t total = 0;
@@ -256,9 +256,13 @@ int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, in
       return SQUANT_ERR_DEVICE;
     }
   }
-  const unsigned grid = (unsigned)total;
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(g.threads), g.variant == kStream ? 0 : lds, st, a);
-  if (hipGetLastError() != hipSuccess) return SQUANT_ERR_DEVICE;
+  // by address: a call through the kernel's stub copies the arguments twice more
+  void* args[] = {&a};
+  if (hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3((unsigned)total), dim3(g.threads), args,
+                      g.variant == kStream ? 0 : lds, st) != hipSuccess) {
+    (void)hipGetLastError();
+    return SQUANT_ERR_DEVICE;
+  }
   return SQUANT_OK;
 }
 
