@@ -36,6 +36,7 @@ struct LaunchArgs {
   int32_t uniform_m;        // > 0: every tensor of the table takes this many workgroups
   int32_t uniform_shift;    // >= 0: uniform_m == 1 << uniform_shift
   int32_t qmax;
+  float rcp_qmax;           // 1 / qmax, correctly rounded
   int32_t mode;
   int32_t out_format;       // squant_output_t
   int32_t wtype;            // squant_wtype_t
@@ -94,6 +95,17 @@ __device__ __forceinline__ TensorDesc locate(const LaunchArgs& a, int g, int& m)
 // place of 1 / s, and one step from such an estimate gives the correctly rounded value
 // (checked for every significand and every such estimate by tests/host_reciprocal.cpp).
 __device__ __forceinline__ float reciprocal(float s) { return refine_reciprocal(s, __builtin_amdgcn_rcpf(s)); }
+
+// The scale amax / qmax of a channel (IEEE division; 1 for an all-zero channel).  `normal`: the
+// absmax is 0 or within [2^-60, 2^60], where three operations give the quotient (a division is ten
+// and its steps wait for each other).
+__device__ __forceinline__ bool scale_is_normal(float amax) {
+  return amax <= 0x1p60f && (amax >= 0x1p-60f || amax == 0.0f);
+}
+__device__ __forceinline__ float channel_scale(float amax, float qmaxf, float rcp_qmax, bool normal) {
+  if (normal) return amax > 0.0f ? div_by_reciprocal(amax, qmaxf, rcp_qmax) : 1.0f;
+  return amax > 0.0f ? amax / qmaxf : 1.0f;
+}
 
 __device__ __forceinline__ int sign_of(int64_t v) { return (v > 0) - (v < 0); }
 

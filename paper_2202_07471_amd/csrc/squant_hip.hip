@@ -217,6 +217,7 @@ int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, in
     for (int sh = 0; sh < 31; ++sh)
       if (((int64_t)1 << sh) == items0) a.uniform_shift = sh;
   a.qmax = qmax;
+  a.rcp_qmax = 1.0f / (float)qmax;
   a.mode = mode;
   a.out_format = output;
   a.wtype = wtype;

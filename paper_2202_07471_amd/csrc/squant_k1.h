@@ -430,7 +430,7 @@ __device__ __forceinline__ int64_t k1_wave_sum(int32_t v) {
 }
 
 template <int MODE, int NE, int VE, bool WAVE, typename Sh>
-__device__ __forceinline__ float k1_solve(float (&w)[NE], int N, float qmaxf, Sh& sh, uint32_t* owner,
+__device__ __forceinline__ float k1_solve(float (&w)[NE], int N, float qmaxf, float rcp_qmax, Sh& sh, uint32_t* owner,
                                           uint32_t (&code)[NE / 4]) {
   constexpr bool kChannelStage = MODE == SQUANT_MODE_EKC || MODE == SQUANT_MODE_EC;
   typedef typename std::conditional<(NE > 32), uint64_t, uint32_t>::type MaskT;
@@ -449,7 +449,7 @@ __device__ __forceinline__ float k1_solve(float (&w)[NE], int N, float qmaxf, Sh
 
   // The quotients go through the reciprocal of s, which is proven exact for an absmax within
   // [2^-60, 2^60]; a channel outside is first scaled by a power of two (see squant_k9.h).
-  float s = div_by_reciprocal(amax, qmaxf, 1.0f / qmaxf);  // 1 / qmax does not depend on the channel
+  float s = div_by_reciprocal(amax, qmaxf, rcp_qmax);
   float s2 = s;
   if (!(amax >= 0x1p-60f && amax <= 0x1p60f)) {
     s = amax > 0.0f ? amax / qmaxf : 1.0f;
@@ -592,7 +592,7 @@ __device__ __forceinline__ void k1_channel(const LaunchArgs& a, const TensorDesc
   k1_load<NE, VE, HALF, TAIL>(static_cast<const uint8_t*>(d.w) + (size_t)m * N * (HALF ? 2 : 4), N, tid, T, raw, tail);
   float w[NE];
   k1_widen<NE, VE, HALF, TAIL>(raw, tail, a.wtype == SQUANT_W_BF16, N, tid, T, w);
-  const float s = k1_solve<MODE, NE, VE, false>(w, N, (float)a.qmax, sh, reinterpret_cast<uint32_t*>(smem), code);
+  const float s = k1_solve<MODE, NE, VE, false>(w, N, (float)a.qmax, a.rcp_qmax, sh, reinterpret_cast<uint32_t*>(smem), code);
   if (tid == 0) d.scales[m] = s;
   k1_emit_as<NE, VE, TAIL>(a.out_format, code, d.out, m, N, s, tid, T);
 }

@@ -456,7 +456,8 @@ __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc
   for (int j = 0; j + 1 < 9 * KPT; j += 2) amax = fmaxf(fmaxf(amax, fabsf(w[j])), fabsf(w[j + 1]));
   if ((9 * KPT) & 1) amax = fmaxf(amax, fabsf(w[9 * KPT - 1]));
   amax = k9_block_max<NWC>(amax, sh.red_f);
-  const float s = amax > 0.0f ? amax / qmaxf : 1.0f;
+  const bool normal = scale_is_normal(amax);
+  const float s = channel_scale(amax, qmaxf, a.rcp_qmax, normal);
   if (tid == 0) d.scales[m] = s;
 
   K9Kernel kk[KPT];
@@ -468,8 +469,8 @@ __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc
   // those of the unscaled channel; an element that leaves the normal range on the way down is
   // more than 2^60 below the absmax and rounds to code 0 with perturbation 0 either way).
   // One uniform branch around all the kernels of the thread, each side one straight-line region.
-  if (amax <= 0x1p60f && (amax >= 0x1p-60f || amax == 0.0f)) {
-    const float rs = 1.0f / s;
+  if (normal) {
+    const float rs = reciprocal(s);
     // the largest quotient of the channel: no element needs the clamp unless this one does
     if (div_by_reciprocal(amax, s, rs) <= qmaxf) k9_solve_all<MODE, KPT, false, false>(w, s, rs, qmaxf, 1.0f, 1.0f, kk, esum, amin, ANY ? owned : ~0u);
     else k9_solve_all<MODE, KPT, false, true>(w, s, rs, qmaxf, 1.0f, 1.0f, kk, esum, amin, ANY ? owned : ~0u);
@@ -478,7 +479,7 @@ __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc
     const float a1 = amax * f1;
     const float f2 = a1 < 0x1p-60f ? 0x1p64f : a1 > 0x1p60f ? 0x1p-64f : 1.0f;
     const float s2 = s * f1 * f2;
-    k9_solve_all<MODE, KPT, true, true>(w, s2, 1.0f / s2, qmaxf, f1, f2, kk, esum, amin, ANY ? owned : ~0u);
+    k9_solve_all<MODE, KPT, true, true>(w, s2, reciprocal(s2), qmaxf, f1, f2, kk, esum, amin, ANY ? owned : ~0u);
   }
 
   if (kChannelStage) {

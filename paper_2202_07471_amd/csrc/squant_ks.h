@@ -232,7 +232,8 @@ __device__ __forceinline__ void ks_channel(const LaunchArgs& a, const TensorDesc
 #pragma unroll
   for (int j = 0; j < K * KPT; ++j) amax = fmaxf(amax, fabsf(w[j]));
   amax = block_max_dpp1(amax, sh.red_f);
-  const float s = amax > 0.0f ? amax / qmaxf : 1.0f;
+  const bool normal = scale_is_normal(amax);
+  const float s = channel_scale(amax, qmaxf, a.rcp_qmax, normal);
   if (tid == 0) d.scales[m] = s;
 
   int32_t esum = 0;
@@ -242,8 +243,8 @@ __device__ __forceinline__ void ks_channel(const LaunchArgs& a, const TensorDesc
   for (int q = 0; q < KPT; ++q) { cv[q] = kNoCandidate; ci[q] = 0; }
   uint32_t zero = 0;
   if (active) {
-    if (amax >= 0x1p-60f && amax <= 0x1p60f) {  // uniform over the workgroup
-      ks_solve_all<K, KPT, true, MODE>(w, s, 1.0f / s, qmaxf, code8, t, G, owned, esum, cv, ci, zero);
+    if (normal) {  // uniform over the workgroup
+      ks_solve_all<K, KPT, true, MODE>(w, s, reciprocal(s), qmaxf, code8, t, G, owned, esum, cv, ci, zero);
     } else {
       ks_solve_all<K, KPT, false, MODE>(w, s, 0.0f, qmaxf, code8, t, G, owned, esum, cv, ci, zero);
     }

@@ -1,0 +1,72 @@
+// Host-side check of the routes added around choose_variant: shapes the measured choices cover keep
+// them, every other shape a register kernel takes gets a launch that covers its channel within the
+// kernel's limits, and the variant numbers of the families do not meet.
+#include <cstdint>
+#include <cstdio>
+#include <initializer_list>
+
+#include "squant_plan.h"
+
+using namespace squant;
+
+// How many families claim a variant number.
+static int claims(int v) {
+  int n = 0;
+  n += is_k1_wave(v);
+  n += is_ks(v);
+  n += is_k1_wide(v);
+  n += k1_variant_nv(v) != 0 && !is_k1_wide(v);
+  for (int other : {(int)kGeneric, (int)kK9x1, (int)kK9x2, (int)kK9x4, (int)kK1Stream, (int)kDw9, (int)kK1Team, (int)kStream,
+                    (int)kDwTeam, (int)kK9Team})
+    n += v == other;
+  return n;
+}
+
+int main() {
+  long bad = 0, kept = 0, rerouted = 0;
+  for (int aligned = 0; aligned < 2; ++aligned)
+    for (int64_t K : {1, 2, 3, 4, 5, 6, 7, 8, 9, 16, 25, 49, 64, 65})
+      for (int64_t N = 1; N <= 70000; N += (N < 700 ? 1 : 97)) {
+        const int64_t M = 1 << 20;  // no small tensor
+        const int family = route_family(M, N, K, aligned != 0), measured = choose_family(N, K, aligned != 0);
+        const int v = route_variant(M, N, K, aligned != 0);
+        bad += claims(v) != 1;
+        if (family == measured) {
+          ++kept;
+          bad += v != choose_variant(N, K, aligned != 0);
+        } else {
+          ++rerouted;
+          bad += measured != 0 && !(measured == 2 && family == 1 && N <= kMaxWideCin);
+          if (family == 1) {
+            const int nv = k1_variant_nv(v);
+            const int64_t nvec = (N + 3) / 4;
+            const int64_t th = is_k1_wide(v) ? round_up64((nvec + nv - 1) / nv) : k1_threads(nvec, nv);
+            bad += K != 1 || nv == 0 || nv * th < nvec || th > 1024 || N > kMaxWideCin || N <= kMaxWaveCin;
+            bad += is_k1_wide(v) && nv != 10 && nv != 12 && nv != 14 && nv != 16;
+          } else if (family == 6) {
+            const int nv = v - kK1Wave;
+            bad += K != 1 || nv < 2 || nv > 8 || 64 * 4 * nv < N || N <= kMaxTeamCin;
+          } else if (family == 4) {
+            bad += K != 1 || N > 4 * team_lanes(N) * (team_lanes(N) == 16 ? 4 : 1);
+          } else if (family == 9) {
+            const int c = v == kK9x4 ? 4 : v == kK9x2 ? 2 : v == kK9x1 ? 1 : 0;
+            const int64_t th = c ? round_up64((N + c - 1) / c) : 0;
+            bad += K != 9 || N < 2 || N > kMaxK9Cin || c == 0 || th * c < N || th > 1024 || (c != 4 && th > 256);
+          } else if (family == 5) {
+            const int c = ks_variant_kpt(v), top = 1 << ks_max_kpt_log2(K);
+            const int64_t th = round_up64((N + c - 1) / c);
+            bad += !ks_has(K) || ks_variant_k(v) != K || N < 2 || c > top || th * c < N || th > 1024 || (c != top && th > 256);
+          } else if (family == 7) {
+            bad += N != 1 || K > kMaxDwK || dw_team_lanes(K) < K;
+            bad += route_work_items(130, N, K, 64, family, 1) != (130 + 64 / dw_team_lanes(K) - 1) / (64 / dw_team_lanes(K));
+          } else {
+            ++bad;
+          }
+        }
+        if (K == 9 && N > 1 && N <= kMaxK9TeamCin) bad += k9_team_lanes(N) < N || 64 % k9_team_lanes(N) != 0;
+        // small tensors off the common shapes stay generic, except depthwise ones
+        if (measured == 0 && N * K < kSmallTensor && family != 7) bad += route_family(1, N, K, aligned != 0) != 0;
+      }
+  std::printf("route_mismatches=%ld kept=%ld rerouted=%ld\n", bad, kept, rerouted);
+  return bad != 0 || rerouted == 0;
+}

@@ -51,6 +51,16 @@ def test_variant_choice_covers_every_shape(tmp_path):
     assert "plan_mismatches=0" in out.stdout
 
 
+def test_routes_cover_every_shape(tmp_path):
+    exe = str(tmp_path / "host_route_check")
+    subprocess.check_call(["g++", "-std=c++17", "-O2",
+                           "-I", os.path.join(ROOT, "paper_2202_07471_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "host_route_check.cpp"), "-o", exe])
+    out = subprocess.run([exe], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout + out.stderr
+    assert "route_mismatches=0" in out.stdout
+
+
 def test_reference_solver_under_sanitizers(tmp_path):
     """The CPU reference, compiled with the address and undefined-behaviour sanitizers, over
     assorted shapes, value patterns, modes and bit widths: nothing out of bounds, no overflow."""
