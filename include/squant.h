@@ -199,7 +199,7 @@ int squant_quantize_network(const squant_layer_t* h_layers, int32_t n_layers, in
 /* Largest cin*kh*kw one output channel may have: 2^30, the bound of the shape check (0 for an
  * invalid kernel size).  Channels that fit none of the kernels which keep a channel on chip
  * (3x3 beyond cin 4096, other kernel sizes beyond about 32 K elements, 1x1 / FC rows beyond
- * about 160 K elements or off 16-byte alignment beyond 13 K) go through a streaming kernel
+ * about 160 K elements or off 16-byte alignment beyond 64 K) go through a streaming kernel
  * that walks the weights several times: correct for any shape, a fraction of the speed. */
 int64_t squant_max_channel_elems(int32_t kh, int32_t kw);
 
