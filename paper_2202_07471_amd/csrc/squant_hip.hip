@@ -270,12 +270,21 @@ int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, in
 // A group goes out in launches of at most kInlineDescs tensors each.
 int launch_group(const Group& g, int qmax, int mode, int output, int wtype, hipStream_t st) {
   // Waves of the wave-per-channel 1x1 kernel walk several channels each where that still
-  // leaves the chip (8192 resident waves) a few rounds of them; in a mixed launch one.
+  // leaves the chip (8192 resident waves) a few rounds of them, each asking for the next
+  // channel's weights early; in a mixed launch one.  It pays while a wave holds little: rows of
+  // up to 512 elements gain with four (131 K channels of 512: binary16 62.2 -> 58.1 us, binary32
+  // 67.2 -> 65.3).  Longer 16-bit rows do best with two (131 K channels of 1024: 87.3 us with one,
+  // 83.8 with two, 85.9 with four).  Longer binary32 rows have enough bytes in flight and lose by
+  // the registers that wait (the same shape: 107.7, 117.3, 129.5 us), so they keep to one.
   int wave_span = 1;
   if (is_k1_wave(g.variant)) {
-    int64_t channels = 0;
-    for (const auto& t : g.t) channels += t.M;
-    if (channels >= (int64_t)kK1WaveSpan * 2 * 8192) wave_span = kK1WaveSpan;
+    int64_t channels = 0, longest = 0;
+    for (const auto& t : g.t) {
+      channels += t.M;
+      longest = std::max<int64_t>(longest, t.N);
+    }
+    if (channels >= (int64_t)kK1WaveSpan * 2 * 8192)
+      wave_span = longest <= 512 ? kK1WaveSpan : wtype == SQUANT_W_F32 ? 1 : 2;
   }
   for (size_t begin = 0; begin < g.t.size(); begin += kInlineDescs) {
     const size_t end = std::min(g.t.size(), begin + (size_t)kInlineDescs);

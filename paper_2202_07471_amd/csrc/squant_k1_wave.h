@@ -3,7 +3,7 @@
 // A channel of one or two thousand weights keeps a wave busy for about a microsecond, most of it
 // waiting for its weights and then for the steps of the channel stage, which follow each other.
 // With the wave as the unit (squant_k1.h with WAVE) every step runs without a workgroup barrier;
-// a wave of a large launch walks kK1WaveSpan consecutive channels and asks for the next channel's
+// a wave of a large launch walks up to kK1WaveSpan consecutive channels and asks for the next channel's
 // weights as soon as the current ones are widened or consumed, so the loads travel while the wave
 // works.  Every wave of the workgroup has an LDS area of its own; the waves never meet.
 #pragma once

@@ -31,7 +31,7 @@ constexpr int kMaxK1Cin = 32768;  // 1x1 variant: cin % 4 == 0 up to here
 constexpr int kMaxWideCin = 65536;  // 1x1 / FC rows held in one workgroup of 1024 threads
 constexpr int kMaxTeamCin = 256;  // 1x1 channels this short share a wave
 constexpr int kMaxWaveCin = 2048; // 1x1 channels up to here take a wave each (at most 8 vectors per lane)
-constexpr int kK1WaveSpan = 4;    // consecutive channels a wave of that kernel walks in a large launch (1 in others)
+constexpr int kK1WaveSpan = 4;    // the most consecutive channels a wave of that kernel walks (1 unless a launch is large)
 constexpr int kK1WaveThreads = 256;  // its workgroup in a launch of its own
 constexpr int kMixedMaxThreads = 256;  // largest workgroup of a mixed launch
 

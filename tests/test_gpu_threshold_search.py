@@ -114,3 +114,21 @@ def test_every_output_format(sq, wtype, output):
         for got, got_s in ((out, s), (batched, batched_s)):
             assert np.array_equal(got_s.cpu().numpy(), want_s)
             assert torch.equal(got.cpu().reshape(want.shape), want), (tuple(w.shape), output, wtype)
+
+
+@pytest.mark.parametrize("wtype,cin", [(torch.float32, 512), (torch.float32, 516), (torch.float16, 512), (torch.float16, 520),
+                                       (torch.bfloat16, 1032)])
+def test_channels_walked_by_one_wave(sq, wtype, cin):
+    """More than 65536 channels in one launch, with channel counts that no span divides: a wave walks four
+    channels up to 512 elements, beyond them two of 16 bits or one of 32.  Each tensor gives what it gives alone,
+    where a wave has one channel, and the reference's codes."""
+    torch.manual_seed(cin)
+    ws = [torch.randn(m, cin, device="cuda").mul_(0.05).to(wtype) for m in (32771, 32769, 1)]
+    together, scales = sq.squant_quantize_batched_ex(ws, 4, sq.MODE_EKC)
+    for w, codes, s in zip(ws, together, scales):
+        alone, alone_s = sq.squant_quantize_ex(w, 4, sq.MODE_EKC)
+        assert torch.equal(alone, codes) and torch.equal(alone_s, s)
+        ref = w[-5:].float().cpu().numpy()
+        want, want_s = oracle.quantize(ref.reshape(*ref.shape, 1, 1), 4, sq.MODE_EKC)
+        assert np.array_equal(s[-5:].cpu().numpy(), want_s)
+        assert np.array_equal(codes[-5:].cpu().numpy().reshape(want.shape), want)
