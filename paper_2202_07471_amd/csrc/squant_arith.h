@@ -149,6 +149,18 @@ SQ_HD void next2_of_9u(const Top9Rest& rest, uint32_t (&t)[5]) {
   t[4] = umax2(t2, G);
 }
 
+// The largest of key[0..NE-1] below `offer` (0 if there is none), for keys and offer below 2^31: key - offer
+// wraps to 2^32 - (offer - key), above 2^31, for the keys below the offer and stays below 2^31 for the others,
+// so the largest difference names the next key.  0 stands below every key: without it the search would come
+// back with the largest key of all once no smaller one is left.
+template <int NE>
+SQ_HD uint32_t next_key_below(const uint32_t (&key)[NE], uint32_t offer) {
+  uint32_t next = 0u - offer;
+#pragma unroll
+  for (int e = 0; e < NE; ++e) next = umax2(next, key[e] - offer);
+  return next + offer;
+}
+
 // Bits 0..8 of f (one per element of a 3x3 kernel) as 0/1 bytes in the layout of the
 // kernel's packed codes: b0 = elements 0-3, b1 = elements 4-7, b2 = element 8.  A 4-bit
 // field times 0x204081 puts bit i at positions i, i + 7, i + 14, i + 21, of which

@@ -157,21 +157,17 @@ __device__ __forceinline__ void k1_team_channels(const LaunchArgs& a, const Tens
       const int n = 4 * (l + (e >> 2) * TEAM) + (e & 3);
       key[e] = u > 0 ? ((uint32_t)u << 8) | (uint32_t)(255 - n) : 0u;
     }
-    // Every lane offers its largest key not yet taken; each step takes the largest offer of the
-    // team, and its lane moves on to its next key.  With keys below 2^31, key - offer wraps to a
-    // huge number for the keys below the offer and to a small one for the others, so the largest
-    // difference names the next key: 1.5 instructions an element and step.  (Marking the element
-    // and clearing its key in every step took four; cin 180: 26.6 -> 22.5 us for 64 x [1024, 180].)
+    // Every lane offers its largest key not yet taken, 0 when all are; each step takes the largest
+    // offer of the team, and its lane moves on to its next key: 1.5 instructions an element and step.
+    // (Marking the element and clearing its key in every step took four; cin 180: 26.6 -> 22.5 us for
+    // 64 x [1024, 180].)
     uint32_t offer = 0, taken = ~0u;  // taken: the lane's smallest key that flips
 #pragma unroll
     for (int e = 0; e < NE; ++e) offer = umax2(offer, key[e]);
     while (__ballot(need > 0) != 0ull) {
       const uint32_t m = team_max_u32<TEAM>(offer);
       const bool take = need > 0 && m != 0;
-      uint32_t next = 0;
-#pragma unroll
-      for (int e = 0; e < NE; ++e) next = umax2(next, key[e] - offer);
-      next += offer;
+      const uint32_t next = next_key_below(key, offer);
       const bool mine = take && offer == m;
       taken = mine ? m : taken;
       offer = mine ? next : offer;

@@ -41,6 +41,16 @@ def test_reciprocal_from_the_hardware_estimate(tmp_path):
     assert "reciprocal_mismatches=0" in out.stdout
 
 
+def test_selection_by_stepping_through_keys(tmp_path):
+    exe = str(tmp_path / "host_key_steps")
+    subprocess.check_call(["g++", "-std=c++17", "-O2", "-Wno-unknown-pragmas",
+                           "-I", os.path.join(ROOT, "paper_2202_07471_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "host_key_steps.cpp"), "-o", exe])
+    out = subprocess.run([exe], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout + out.stderr
+    assert "key_step_mismatches=0" in out.stdout
+
+
 def test_variant_choice_covers_every_shape(tmp_path):
     exe = str(tmp_path / "host_plan_check")
     subprocess.check_call(["g++", "-std=c++17", "-O2",
