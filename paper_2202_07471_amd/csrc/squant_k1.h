@@ -17,9 +17,10 @@
 //     per-vector bounds checks (out-of-range dwords read as 0 and are not written);
 //   * SQuant-E is 9.75 instructions an element: three for the exact quotient, rounding by a
 //     magic addition that leaves code + 128 in the sum's low byte (squant_k9.h), the biased
-//     Q23 perturbation by one FMA.  The clamp to +-qmax can only move the element that set the
-//     scale, by one rounding, so it is left out and such elements are mended afterwards in the
-//     few channels that have one;
+//     Q23 perturbation by one FMA.  While the scale is a normal number the clamp to +-qmax can
+//     only move the element that set it, by one rounding, so it is left out and such elements are
+//     mended afterwards in the few channels that have one (channels of an absmax outside
+//     [2^-60, 2^60] take a clamp: a subnormal scale has few significant bits);
 //   * SQuant-C needs the `need` = round(|sum|) elements with the largest perturbation of one
 //     sign, a handful in thousands.  It is found by threshold search: two instructions an
 //     element (compare into the carry, add-with-carry) give a mask of the elements at or above
@@ -456,18 +457,23 @@ __device__ __forceinline__ float k1_solve(float (&w)[NE], int N, float qmaxf, fl
   else amax = block_max_dpp1(amax, sh.red_f);
 
   // The quotients go through the reciprocal of s, which is proven exact for an absmax within
-  // [2^-60, 2^60]; a channel outside is first scaled by a power of two (see squant_k9.h).
+  // [2^-60, 2^60]; a channel outside is first scaled by a power of two (see squant_k9.h).  There a
+  // subnormal scale may be far below absmax / qmax, with many quotients beyond qmax, or be 0, with
+  // every one infinite (2^-40 in its place makes them at least 2^19): the weights of such a channel
+  // give way to their clamped quotients, which are then rounded with a scale of 1.
   float s = div_by_reciprocal(amax, qmaxf, rcp_qmax);
   float s2 = s;
-  if (!(amax >= 0x1p-60f && amax <= 0x1p60f)) {
+  if (__builtin_expect(!(amax >= 0x1p-60f && amax <= 0x1p60f), 0)) {
     s = amax > 0.0f ? amax / qmaxf : 1.0f;
     const float f1 = amax >= 1.0f ? 0x1p-64f : amax > 0.0f ? 0x1p64f : 1.0f;
     const float a1 = amax * f1;
     const float f2 = a1 > 0x1p60f ? 0x1p-64f : a1 < 0x1p-60f && amax > 0.0f ? 0x1p64f : 1.0f;
+    const float sp = s > 0.0f ? s * f1 * f2 : 0x1p-40f, rp = reciprocal(sp);
 #pragma unroll
-    for (int q = 0; q < NE; ++q) w[q] = w[q] * f1 * f2;
-    s2 = s * f1 * f2;
-    amax = a1 * f2;
+    for (int q = 0; q < NE; ++q)
+      w[q] = __builtin_amdgcn_fmed3f(div_by_reciprocal(w[q] * f1 * f2, sp, rp), -qmaxf, qmaxf);
+    s2 = 1.0f;
+    amax = 0.0f;  // no quotient beyond qmax is left
   }
   const float rs = reciprocal(s2);
   uint32_t B[NE];

@@ -467,7 +467,9 @@ __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc
   // under- or overflows on the way: absmax within [2^-60, 2^60].  A channel outside that range
   // is first scaled by a power of two, weights and scale alike (exact, and the quotients are
   // those of the unscaled channel; an element that leaves the normal range on the way down is
-  // more than 2^60 below the absmax and rounds to code 0 with perturbation 0 either way).
+  // more than 2^60 below the absmax and rounds to code 0 with perturbation 0 either way).  A scale
+  // that came out as 0 has infinite quotients: 2^-40 in its place makes them at least 2^19, and the
+  // clamp does the rest.
   // One uniform branch around all the kernels of the thread, each side one straight-line region.
   if (normal) {
     const float rs = reciprocal(s);
@@ -478,7 +480,7 @@ __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc
     const float f1 = amax < 1.0f ? 0x1p64f : 0x1p-64f;
     const float a1 = amax * f1;
     const float f2 = a1 < 0x1p-60f ? 0x1p64f : a1 > 0x1p60f ? 0x1p-64f : 1.0f;
-    const float s2 = s * f1 * f2;
+    const float s2 = s > 0.0f ? s * f1 * f2 : 0x1p-40f;
     k9_solve_all<MODE, KPT, true, true>(w, s2, reciprocal(s2), qmaxf, f1, f2, kk, esum, amin, ANY ? owned : ~0u);
   }
 

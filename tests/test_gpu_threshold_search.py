@@ -91,6 +91,31 @@ def test_scale_just_below_a_power_of_two(sq, cin):
     assert np.array_equal(codes.cpu().numpy().reshape(want.shape), want)
 
 
+@pytest.mark.parametrize("dtype,name", [(torch.float32, None), (torch.bfloat16, "bf16")])
+@pytest.mark.parametrize("shape", [(24, 1025, 1, 1), (24, 512, 1, 1), (24, 4096, 1, 1), (24, 40000, 1, 1),
+                                   (24, 64, 1, 1), (24, 128, 3, 3), (24, 301, 3, 3), (24, 130, 1, 3)])
+def test_subnormal_scales(sq, shape, dtype, name):
+    """Absolute maxima from 2^-149 to 2^-126: the scale has a few significant bits or is 0, so quotients far
+    beyond qmax appear in many elements and every one of them is clamped."""
+    rng = np.random.default_rng(shape[1])
+    w = rng.uniform(0.05, 1.0, shape) * rng.choice([-1.0, 1.0], shape)
+    w.reshape(24, -1)[:, 0] = 1.0
+    lowest = -133 if name else -149   # of bfloat16, of binary32
+    steps = np.ldexp(1.0, -149 + np.arange(24)).reshape(24, 1, 1, 1)
+    w = np.ldexp(np.maximum(np.round(np.abs(w) * steps * 2.0 ** -lowest), 1.0), lowest) * np.sign(w)  # no zeros
+    d = torch.from_numpy(w.astype(np.float32)).to(dtype).cuda()
+    ref = d.float().cpu().numpy()
+    assert np.all(ref != 0)
+    for bits in (2, 4, 8):
+        for mode in (sq.MODE_EKC, sq.MODE_E):
+            codes, scales = sq.squant_quantize_ex(d, bits, mode)
+            want, want_s = oracle.quantize(ref, bits, mode, threads=8)
+            what = f"{shape} {dtype} bits={bits} mode={mode}"
+            assert np.array_equal(scales.cpu().numpy().view(np.uint32), want_s.view(np.uint32)), what
+            bad = np.argwhere(codes.cpu().numpy() != want)
+            assert len(bad) == 0, f"{what}: {len(bad)} differ, first at {bad[0].tolist()}"
+
+
 @pytest.mark.parametrize("output", ["int8", "int4", "f32", "bf16"])
 @pytest.mark.parametrize("wtype", [torch.float32, torch.float16, torch.bfloat16])
 def test_every_output_format(sq, wtype, output):
