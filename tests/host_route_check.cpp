@@ -67,6 +67,9 @@ int main() {
         // small tensors off the common shapes stay generic, except depthwise ones
         if (measured == 0 && N * K < kSmallTensor && family != 7) bad += route_family(1, N, K, aligned != 0) != 0;
       }
+  // the lengths that the GPU tests of the streaming 1x1 kernel and of the one that holds a row in one workgroup use
+  for (int64_t N : {65540, 70000, 131072}) bad += route_variant(1, N, 1, true) != kK1Stream;
+  for (int64_t N : {36000, 40000, 50000, 65536}) bad += !is_k1_wide(route_variant(1, N, 1, true));
   std::printf("route_mismatches=%ld kept=%ld rerouted=%ld\n", bad, kept, rerouted);
   return bad != 0 || rerouted == 0;
 }

@@ -312,10 +312,11 @@ def test_one_sided_perturbations_have_huge_channel_sums(sq, shape):
 
 
 # ---------------------------------------------------------------------------
-# very long 1x1 / FC channels: the streaming kernel (cin beyond 32768)
+# very long 1x1 / FC channels: held in one workgroup up to cin 65536, the streaming 1x1 kernel beyond
 # ---------------------------------------------------------------------------
 @pytest.mark.parametrize("kind", ["normal", "heavy", "grid"])
-@pytest.mark.parametrize("shape", [(3, 32772, 1, 1), (2, 40000, 1, 1), (2, 65536, 1, 1), (1, 131072, 1, 1)])
+@pytest.mark.parametrize("shape", [(3, 32772, 1, 1), (2, 40000, 1, 1), (2, 65536, 1, 1), (1, 131072, 1, 1),
+                                   (2, 65540, 1, 1), (2, 70000, 1, 1)])
 def test_streaming_kernel_for_long_channels(sq, shape, kind):
     w = rand_weights(shape, 900 + shape[1] % 97, kind)
     if kind == "normal":
@@ -325,9 +326,10 @@ def test_streaming_kernel_for_long_channels(sq, shape, kind):
         assert_same(codes, scales, w, bits, mode, what=f"stream {shape} {kind} bits={bits} mode={mode}")
 
 
-def test_streaming_kernel_degenerate_channels(sq):
-    """Channels whose perturbations are all equal, all zero, or all on one side."""
-    n = 36000
+@pytest.mark.parametrize("n", [36000, 65540, 70000])
+def test_streaming_kernel_degenerate_channels(sq, n):
+    """Channels whose perturbations are all equal, all zero, or all on one side (36000: the kernel that holds
+    the row in one workgroup)."""
     rows = [np.full(n, 0.3, np.float32), np.zeros(n, np.float32), np.full(n, -1.0, np.float32)]
     half = np.full(n, 2.5, np.float32); half[0] = 7.0            # x = 2.5 everywhere: exact halves
     tiny = np.full(n, 0.01, np.float32); tiny[0] = 7.0           # every element rounds to 0, p < 0 ... same sign

@@ -109,10 +109,13 @@ def test_layer_set_batched_sixteen_bit(sq, wtype, output):
         assert np.array_equal(got.reshape(want.shape), want), f"batched {wtype} {output} {s.shape}"
 
 
+@pytest.mark.parametrize("kind", ["normal", "grid"])
+@pytest.mark.parametrize("cin", [50000, 65540, 70000])
 @pytest.mark.parametrize("wtype,output", [("f16", "int4"), ("bf16", "bf16")])
-def test_streaming_kernel_sixteen_bit_and_formats(sq, wtype, output):
-    shape = (2, 50000, 1, 1)
-    t16, bits = to16(weights(shape, 77, "normal"), wtype)
+def test_streaming_kernel_sixteen_bit_and_formats(sq, wtype, output, cin, kind):
+    """Beyond 65536 elements the streaming 1x1 kernel; 50000 is held in one workgroup."""
+    shape = (2, cin, 1, 1)
+    t16, bits = to16(weights(shape, 77, kind), wtype)
     codes, want_s = oracle.quantize(oracle.widen(bits, wtype), 4, 2, threads=8)
     got, got_s = sq.squant_quantize_ex(t16.cuda(), 4, 2, sq.OUTPUTS[output])
     torch.cuda.synchronize()
