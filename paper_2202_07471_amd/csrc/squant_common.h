@@ -92,8 +92,11 @@ __device__ __forceinline__ TensorDesc locate(const LaunchArgs& a, int g, int& m)
 }
 
 // RN(1 / s) for 2^-100 < s < 2^100: the hardware's estimate is within one unit in the last
-// place of 1 / s, and one step from such an estimate gives the correctly rounded value
-// (checked for every significand and every such estimate by tests/host_reciprocal.cpp).
+// place of 1 / s, and one step from such an estimate gives the correctly rounded value: checked
+// for every significand and every such estimate by tests/host_reciprocal.cpp, with one exception.
+// For the significand 2 - 2^-23 the step must start at the upper of the two estimates, 0.5 + 2^-24
+// (from 0.5 it ends on a tie); this hardware gives that one, which the GPU tests pin through codes
+// that differ otherwise (test_reciprocal_of_the_largest_significand).
 __device__ __forceinline__ float reciprocal(float s) { return refine_reciprocal(s, __builtin_amdgcn_rcpf(s)); }
 
 // The scale amax / qmax of a channel (IEEE division; 1 for an all-zero channel).  `normal`: the

@@ -2,7 +2,7 @@
 // of s and every binary32 estimate r0 within one unit in the last place of 1/s, one step gives
 // the correctly rounded reciprocal - except from the lower of the two estimates of the reciprocal
 // of 2 - 2^-23, for which the step ends on a tie; the hardware's estimate there is the upper one
-// (0x3f000001; the GPU parity tests run a channel with that scale).  Scaling s by a power of two scales r0 and every
+// (0x3f000001; test_reciprocal_of_the_largest_significand pins it on the GPU).  Scaling s by a power of two scales r0 and every
 // intermediate value exactly while nothing leaves the normal range, so one binade is enough.
 #include <cmath>
 #include <cstdint>

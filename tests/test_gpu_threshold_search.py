@@ -91,6 +91,22 @@ def test_scale_just_below_a_power_of_two(sq, cin):
     assert np.array_equal(codes.cpu().numpy().reshape(want.shape), want)
 
 
+@pytest.mark.parametrize("shape", [(64, 64, 1, 1), (64, 512, 1, 1), (16, 4096, 1, 1), (16, 50176, 1, 1), (64, 8, 3, 3),
+                                   (64, 128, 3, 3), (64, 301, 3, 3), (64, 128, 1, 3), (64, 64, 5, 5)])
+def test_reciprocal_of_the_largest_significand(sq, shape):
+    """With a scale of 2 - 2^-23 (at 2 bits the absmax itself) the quotient of 1.0 lies 2^-25 above a half: the
+    correctly rounded reciprocal puts it there, the one a unit below puts it on the half, and the code is 0 for 1."""
+    one = np.float32(2) - np.float32(2) ** -23
+    w = np.ones(shape, np.float32)
+    w[:, ::3] = -1.0
+    w.reshape(shape[0], -1)[:, 0] = one
+    w *= (np.float32(2) ** np.resize([0, 1, -20, 30, -40, 50], shape[0]).astype(np.float32)).reshape(-1, 1, 1, 1)
+    codes, scales = sq.squant_quantize(torch.from_numpy(w).cuda(), 2, sq.MODE_E)
+    want, want_s = oracle.quantize(w, 2, sq.MODE_E)
+    assert np.array_equal(scales.cpu().numpy(), want_s) and np.all(np.abs(want) == 1)
+    assert np.array_equal(codes.cpu().numpy(), want)
+
+
 @pytest.mark.parametrize("dtype,name", [(torch.float32, None), (torch.bfloat16, "bf16")])
 @pytest.mark.parametrize("shape", [(24, 1025, 1, 1), (24, 512, 1, 1), (24, 4096, 1, 1), (24, 40000, 1, 1),
                                    (24, 64, 1, 1), (24, 128, 3, 3), (24, 301, 3, 3), (24, 130, 1, 3)])

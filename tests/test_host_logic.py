@@ -31,7 +31,8 @@ def test_reciprocal_division_is_exact_on_every_near_midpoint_case(tmp_path):
 
 def test_reciprocal_from_the_hardware_estimate(tmp_path):
     """One refinement step from any estimate within one unit in the last place is the correctly
-    rounded reciprocal, for every significand."""
+    rounded reciprocal, for every significand; the one exception, from the lower estimate for
+    2 - 2^-23, is known (the hardware's estimate there is the upper one, pinned by a GPU test)."""
     exe = str(tmp_path / "host_reciprocal")
     subprocess.check_call(["g++", "-std=c++17", "-O2", "-mfma", "-ffp-contract=off",
                            "-I", os.path.join(ROOT, "paper_2202_07471_amd", "csrc"),
