@@ -22,9 +22,13 @@ namespace squant {
 // HALF: 16-bit weights.  ANY: carries the routines for other small kernels, for channel counts that
 // are no multiple of four and for buffers off their alignment; a launch without such members takes
 // the leaner kernel (ResNet-18 and MobileNetV2 sets 5 % faster in it).
+// The code starts on 64 KB: these launches take a few microseconds, most of their instructions run for
+// the first time on each compute unit, and the time followed the place the linker gave the kernel, which
+// any change to a kernel before it moves (the same code on the ResNet-18 set: 16.4 us at offset 0x5400 of
+// its 64 KB, 16.7 at 0x2800, 17.05 at 0x4c00; on 64 KB 16.5 whatever the code before and inside it).
 template <int MODE, bool HALF, bool ANY>
 __global__ void __launch_bounds__(kMixedMaxThreads)
-    __attribute__((amdgpu_waves_per_eu(5))) squant_channel_mixed(LaunchArgs a) {
+    __attribute__((amdgpu_waves_per_eu(5), aligned(65536))) squant_channel_mixed(LaunchArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   // one area for whichever routine the workgroup takes
   constexpr size_t kArea = sizeof(K9Shared) > sizeof(K1Shared) ? sizeof(K9Shared) : sizeof(K1Shared);
