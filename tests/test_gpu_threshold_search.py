@@ -1,6 +1,6 @@
 """GPU parity for the threshold search of the 1x1 / FC kernels: channel lengths at the edges of the
 vectors per lane and of the workgroup sizes, and values for which the search takes another way
-than its first guess: ties by the thousand, nearly empty tails, one-sided sums, quotients that the
+than its first guess: ties by the thousand, a few levels with gaps between them, nearly empty tails, one-sided sums, quotients that the
 clamp moves, a scale whose reciprocal is the hardest to round."""
 import numpy as np
 import pytest
@@ -43,6 +43,15 @@ def values(kind, shape, bits, rng):
     elif kind == "centre":      # a few large weights, the rest far below half a step
         w = rng.standard_normal(shape) * 1e-3
         w[:, ::97] = rng.standard_normal(w[:, ::97].shape)
+    elif kind == "grid4":       # requantised: a bell of fifteen levels, none of them a level of this scale
+        w = np.round(rng.standard_normal(shape) * 2.3).clip(-7, 7) / 7.0
+        w[:, 0] = 0.93
+        w[1] = np.abs(w[1])
+    elif kind == "ternary":     # three levels and the absmax
+        w = rng.integers(-1, 2, shape) * 0.37
+        w[:, 0] = 1.0
+        w[1] = np.abs(w[1])
+        w[2, :n // 2] = 0.2
     else:                       # "clamp": absmax elements of both signs with an overshooting quotient
         w = rng.uniform(-0.5, 0.5, shape)
         top = overshooting_absmax(qmax, rng)
@@ -62,7 +71,7 @@ CINS = [260, 512, 516, 1028, 2044, 2048, 2052, 3072, 4096, 6148, 8192, 16384, 24
 @pytest.mark.parametrize("bits", [2, 4, 8])
 def test_matches_the_reference(sq, cin, bits):
     rng = np.random.default_rng(1000 * bits + cin)
-    for kind in ("normal", "grid", "one_sided", "centre", "clamp"):
+    for kind in ("normal", "grid", "one_sided", "centre", "clamp", "grid4", "ternary"):
         w = values(kind, (4, cin), bits, rng)
         for dtype, name in ((torch.float32, None), (torch.float16, "f16"), (torch.bfloat16, "bf16")):
             d = torch.from_numpy(w).to(dtype).cuda()
