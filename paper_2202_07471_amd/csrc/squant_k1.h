@@ -384,7 +384,7 @@ __device__ __forceinline__ MaskT k1_channel_stage(const uint32_t (&B)[NE], int32
       hi = thr; n_hi = n; m_hi = m;
     }
     if (found) {
-      if (n_lo - n_hi <= cap || hi - lo == 1) break;
+      if (__builtin_expect(n_lo - n_hi <= cap || hi - lo == 1, 1)) break;
       if (__builtin_expect(gap, 0)) {
         k1_close_in<NE, WAVE>(B, sm, lo, hi, sh);
         if (hi - lo == 1) break;
@@ -408,10 +408,25 @@ __device__ __forceinline__ MaskT k1_channel_stage(const uint32_t (&B)[NE], int32
         thr = __builtin_amdgcn_readfirstlane(hi - (int32_t)(part * (float)(hi - lo)));
         thr = thr <= lo ? lo + 1 : thr;
       }
-    } else {  // too few: widen the distance from the top in proportion
-      const float wider = ((float)need * 1.25f + 4.0f) * __builtin_amdgcn_rcpf(fmaxf((float)n, 0.5f));
-      thr = (1 << 22) - (int32_t)fminf((float)((1 << 22) + 1 - thr) * wider, 4194304.0f);
-      thr = __builtin_amdgcn_readfirstlane(thr);
+    } else {
+      // Too few: widen the distance from the top in proportion.  Where outliers set the scale the rest
+      // crowds around 0 and that lands far below the need-th element.  About half the row lies on the
+      // wanted side, so (0, N / 2) and the count just taken give a line through logarithms as above; the
+      // nearer of the two is taken, a quarter further from the top at least.  Passes on average without
+      // and with that line, 2 bits: 1 % outliers 4.5 and 3.3 (N = 2024), Student-t 3.4 and 2.8.  Six linear
+      // layers, 49 M weights with outliers, 2 bits: binary32 62.5 -> 56.6 us, bfloat16 55.4 -> 49.4.
+      // The empty statement keeps what depends on N and need alone from being computed before the loop.
+      uint32_t half = (uint32_t)N >> 1, few = need;
+      asm volatile("" : "+s"(half), "+s"(few));
+      const float from_top = (float)((1 << 22) + 1 - thr);
+      float wider = from_top * (((float)few * 1.25f + 4.0f) * __builtin_amdgcn_rcpf(fmaxf((float)n, 0.5f)));
+      const float want = (float)few + 0.25f * (float)cap;
+      if (want < (float)half) {
+        const float base = __builtin_amdgcn_logf(fmaxf((float)n, 0.5f));
+        const float part = (__builtin_amdgcn_logf(want) - base) * __builtin_amdgcn_rcpf(__builtin_amdgcn_logf((float)half) - base);
+        wider = fminf(wider, fmaxf(1.25f * from_top, from_top + part * (float)thr));
+      }
+      thr = __builtin_amdgcn_readfirstlane((1 << 22) - (int32_t)fminf(wider, 4194304.0f));
     }
   }
   // those with u >= hi flip; `want` of the `count` with lo <= u < hi

@@ -43,6 +43,10 @@ def values(kind, shape, bits, rng):
     elif kind == "centre":      # a few large weights, the rest far below half a step
         w = rng.standard_normal(shape) * 1e-3
         w[:, ::97] = rng.standard_normal(w[:, ::97].shape)
+    elif kind == "outliers":    # one in a hundred sets the scale, the rest crowds around 0
+        w = rng.standard_normal(shape) * np.where(rng.random(shape) < 0.01, 4.0, 1.0)
+        w[1] = np.abs(w[1])
+        w[2, 5] = 60.0
     elif kind == "grid4":       # requantised: a bell of fifteen levels, none of them a level of this scale
         w = np.round(rng.standard_normal(shape) * 2.3).clip(-7, 7) / 7.0
         w[:, 0] = 0.93
@@ -71,7 +75,7 @@ CINS = [260, 512, 516, 1028, 2044, 2048, 2052, 3072, 4096, 6148, 8192, 16384, 24
 @pytest.mark.parametrize("bits", [2, 4, 8])
 def test_matches_the_reference(sq, cin, bits):
     rng = np.random.default_rng(1000 * bits + cin)
-    for kind in ("normal", "grid", "one_sided", "centre", "clamp", "grid4", "ternary"):
+    for kind in ("normal", "grid", "one_sided", "centre", "outliers", "clamp", "grid4", "ternary"):
         w = values(kind, (4, cin), bits, rng)
         for dtype, name in ((torch.float32, None), (torch.float16, "f16"), (torch.bfloat16, "bf16")):
             d = torch.from_numpy(w).to(dtype).cuda()
