@@ -150,14 +150,6 @@ __device__ __forceinline__ uint32_t load_global_u1(const uint32_t* p) {
   return *p;
 #endif
 }
-__device__ __forceinline__ vu2 load_global_u2_stream(const void* p) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  return __builtin_nontemporal_load(
-      reinterpret_cast<const __attribute__((address_space(1))) vu2*>(reinterpret_cast<uintptr_t>(p)));
-#else
-  return *reinterpret_cast<const vu2*>(p);
-#endif
-}
 // Element i of a weight tensor of the given squant_wtype_t.
 __device__ __forceinline__ float load_weight(const void* w, size_t i, int wtype) {
   if (wtype == SQUANT_W_F32) return static_cast<const float*>(w)[i];

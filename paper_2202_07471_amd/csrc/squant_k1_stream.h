@@ -1,4 +1,5 @@
-// SQuant kernel for 1x1 / FC channels too long for the register-resident kernel of squant_k1.h.
+// SQuant kernel for 1x1 / FC channels too long for the register-resident kernel of squant_k1.h: aligned
+// rows of more than kMaxWideCin elements whose codes fit in LDS.
 #pragma once
 
 #include "squant_common.h"
@@ -84,14 +85,13 @@ __device__ __forceinline__ void k1_push(SelectShared& sh, uint32_t key, int n) {
 }
 
 // ---------------------------------------------------------------------------
-// Streaming variant for channels too long for the register-resident kernel above
-// (cin > 32768, e.g. the input side of a very wide fully connected layer).  Only the
-// channel's codes live on chip (cin bytes of LDS); the weights are walked three times or
-// more - absmax, SQuant-E with the histogram, then every step of the selection - and each
-// walk recomputes the element's perturbation from the weight, which gives the same bits
+// The channel.  Only its codes live on chip (cin bytes of LDS); the weights are walked three
+// times or more - absmax, SQuant-E with the histogram, then every step of the selection - and
+// each walk recomputes the element's perturbation from the weight, which gives the same bits
 // every time.  The re-reads come from the caches (one channel is a few hundred KB).
-// Same selection as k1_channel_stage, with "the elements still undecided" expressed as a
-// prefix of u = P or ~P instead of a per-thread bit mask.
+// Selection by histogram: of the top eight bits of u = P or ~P first, then of the bits below
+// them in the bin that the last flip falls into, whose members are a prefix of u; once they are
+// few they are ranked in a list.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int32_t k1_round(float wv, float s, float rs, bool fast, float qmaxf,
                                             float& c) {

@@ -1,10 +1,9 @@
-// SQuant kernel for short 1x1 / FC channels (cin <= 256, cin % 4 == 0): several output
-// channels per wave.
+// SQuant kernel for short 1x1 / FC channels (cin <= 256, any length and alignment): several
+// output channels per wave.
 //
 // A channel of a few hundred bytes does not fill a wave, let alone a workgroup: with one
-// wave per channel the fixed work of the wave (reductions, histogram scan, barriers)
-// outweighs the channel's own, and a batch of such layers ran at 5-30 % of the memory
-// bandwidth.  Here a TEAM of 4, 8 or 16 neighbouring lanes owns a channel, so a wave works
+// wave per channel the fixed work of the wave (reductions, search, barriers) outweighs the
+// channel's own, and a batch of such layers ran at 5-30 % of the memory bandwidth.  Here a TEAM of 4, 8 or 16 neighbouring lanes owns a channel, so a wave works
 // on 16, 8 or 4 channels at once; a lane holds NV 16-byte vectors of its channel (lane l of
 // the team has vectors l, l + TEAM, ...).  Every channel-wide step is a butterfly over the
 // team's lanes with DPP (quad permutes, then the 8- and 16-lane mirrors): no LDS, no barrier,

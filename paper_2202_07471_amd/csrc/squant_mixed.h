@@ -25,7 +25,8 @@ namespace squant {
 // The code starts on 64 KB: these launches take a few microseconds, most of their instructions run for
 // the first time on each compute unit, and the time followed the place the linker gave the kernel, which
 // any change to a kernel before it moves (the same code on the ResNet-18 set: 16.4 us at offset 0x5400 of
-// its 64 KB, 16.7 at 0x2800, 17.05 at 0x4c00; on 64 KB 16.5 whatever the code before and inside it).
+// its 64 KB, 16.7 at 0x2800, 17.05 at 0x4c00).  On 64 KB the kernels before it no longer matter; changes
+// inside it still move that time between 16.3 and 16.7.
 template <int MODE, bool HALF, bool ANY>
 __global__ void __launch_bounds__(kMixedMaxThreads)
     __attribute__((amdgpu_waves_per_eu(5), aligned(65536))) squant_channel_mixed(LaunchArgs a) {

@@ -13,7 +13,7 @@ enum Variant {
   kGeneric = 0,
   kK9x1 = 1, kK9x2 = 2, kK9x4 = 3,             // 3x3 kernels per thread: 1, 2, 4
   kK1x1 = 4, kK1x2 = 5, kK1x4 = 6, kK1x8 = 7,  // 1x1 / FC: 16-byte vectors per thread: 1, 2, 4, 8
-  kK1Stream = 8,                               // 1x1 / FC beyond kMaxK1Cin: weights walked repeatedly
+  kK1Stream = 8,                               // 1x1 / FC beyond kMaxWideCin, aligned: weights walked repeatedly
   kDw9 = 9,                                    // depthwise 3x3 (cin per group = 1): one thread per channel
   kK1Team = 10,                                // 1x1 / FC up to kMaxTeamCin: 4 to 16 channels per wave
   kK1x3 = 11, kK1x5 = 12, kK1x6 = 13, kK1x7 = 14,  // 1x1 / FC: 3, 5, 6, 7 vectors per thread
@@ -26,8 +26,8 @@ enum Variant {
   kKs = 1024                                   // small kernels in registers: kKs + 4 * K + log2(kernels per thread)
 };
 
-constexpr int kMaxK9Cin = 4096;   // 3x3 variant: cin % 4 == 0 up to here
-constexpr int kMaxK1Cin = 32768;  // 1x1 variant: cin % 4 == 0 up to here
+constexpr int kMaxK9Cin = 4096;   // 3x3 variant: any cin up to here
+constexpr int kMaxK1Cin = 32768;  // 1x1 variant with the measured launch shapes: any cin up to here
 constexpr int kMaxWideCin = 65536;  // 1x1 / FC rows held in one workgroup of 1024 threads
 constexpr int kMaxTeamCin = 256;  // 1x1 channels this short share a wave
 constexpr int kMaxWaveCin = 2048; // 1x1 channels up to here take a wave each (at most 8 vectors per lane)
@@ -210,7 +210,8 @@ constexpr int kMaxDwK = 64;
 SQ_HD int dw_team_lanes(int64_t K) { return K <= 16 ? 16 : K <= 32 ? 32 : 64; }
 
 // Tensors this small (a stem with three input channels) stay with the generic routine: one of them
-// among the common shapes would otherwise send a whole network to the larger mixed kernel.
+// among the common shapes would otherwise send a whole network to the larger mixed kernel.  A small
+// tensor quantized alone has no network to protect and keeps the routine only for having one rule.
 constexpr int64_t kSmallTensor = 16384;
 
 // choose_family with those shapes, 7 = depthwise with a team of lanes per channel: 3x3 up to kMaxK9Cin, other small kernels, one-element rows
