@@ -115,10 +115,17 @@ __device__ __forceinline__ int sign_of(int64_t v) { return (v > 0) - (v < 0); }
 // k = round(|e|), an exact half rounded down (Algorithm 2, "k = round(|e|)").
 __device__ __forceinline__ int64_t flips_for(int64_t abs_sum) { return (abs_sum + kHalf - 1) >> 23; }
 
+// w / s by IEEE division.  A scale of 0 (an absmax of a few 2^-149) makes every quotient infinite, which the
+// clamp takes to +-qmax, but 0 / 0 is no number: a weight of 0 has the quotient 0 whatever the scale.
+__device__ __forceinline__ float quotient(float w, float s) {
+  const float x = w / s;
+  return w == 0.0f ? 0.0f : x;
+}
+
 // SQuant-E on one scaled weight (Algorithm 1, rounding and element perturbation):
 // returns the integer code, writes the Q23 perturbation code - x.
 __device__ __forceinline__ int round_and_perturb(float w, float s, float qmaxf, int32_t& P) {
-  float x = w / s;  // IEEE binary32 division
+  float x = quotient(w, s);
   x = fminf(fmaxf(x, -qmaxf), qmaxf);
   const float c = rintf(x);  // round half to even
   const float p = c - x;     // exact

@@ -95,7 +95,7 @@ __device__ __forceinline__ void k1_push(SelectShared& sh, uint32_t key, int n) {
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int32_t k1_round(float wv, float s, float rs, bool fast, float qmaxf,
                                             float& c) {
-  const float x = fast ? div_by_reciprocal(wv, s, rs) : wv / s;  // the IEEE quotient either way
+  const float x = fast ? div_by_reciprocal(wv, s, rs) : quotient(wv, s);  // the IEEE quotient either way
   const float xc = __builtin_amdgcn_fmed3f(x, -qmaxf, qmaxf);
   c = rintf(xc);
   const float p = c - xc;  // exact

@@ -132,7 +132,7 @@ __device__ __forceinline__ void k1_team_channels(const LaunchArgs& a, const Tens
   int32_t esum = 0;
 #pragma unroll
   for (int e = 0; e < NE; ++e) {
-    const float x = fast ? div_by_reciprocal(w[e], s, rs) : w[e] / s;  // the IEEE quotient either way
+    const float x = fast ? div_by_reciprocal(w[e], s, rs) : quotient(w[e], s);  // the IEEE quotient either way
     const float xc = __builtin_amdgcn_fmed3f(x, -qmaxf, qmaxf);
     cf[e] = rintf(xc);
     if (kChannelStage) {

@@ -88,7 +88,7 @@ __device__ __forceinline__ void k9_round(const float* w, float s, float rs, floa
 #pragma unroll
   for (int i = 0; i < 9; ++i) {
     // x = w / s: either way the IEEE binary32 quotient
-    const float x = FAST ? div_by_reciprocal(w[i], s, rs) : w[i] / s;
+    const float x = FAST ? div_by_reciprocal(w[i], s, rs) : quotient(w[i], s);
     const float xc = CLAMP ? __builtin_amdgcn_fmed3f(x, -qmaxf, qmaxf) : x;
     const float t = xc + kRoundMagic;
     const float c = t - kRoundMagic;  // round-half-even(xc), exact
@@ -205,7 +205,7 @@ __device__ __forceinline__ int3 k9_recheck_kernel(const void* w, size_t first, i
   int bi = 0;
 #pragma unroll 1
   for (int i = 0; i < 9; ++i) {
-    float x = load_weight(w, first + i, wtype) / s;
+    float x = quotient(load_weight(w, first + i, wtype), s);
     x = fminf(fmaxf(x, -qmaxf), qmaxf);
     const float p = rintf(x) - x;
     const int32_t P = __float2int_rn(p * 8388608.0f);

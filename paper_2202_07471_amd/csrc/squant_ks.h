@@ -79,7 +79,7 @@ __device__ __forceinline__ void ks_solve(const float (&w)[NW], int q, float s, f
   int32_t P[K];
 #pragma unroll
   for (int i = 0; i < K; ++i) {
-    const float x = FAST ? div_by_reciprocal(w[W0 + i], s, rs) : w[W0 + i] / s;
+    const float x = FAST ? div_by_reciprocal(w[W0 + i], s, rs) : quotient(w[W0 + i], s);
     const float xc = __builtin_amdgcn_fmed3f(x, -qmaxf, qmaxf);
     c[i] = rintf(xc);
     const float p = c[i] - xc;  // exact
@@ -171,7 +171,7 @@ __device__ __noinline__ int2 ks_zero_sum_candidate(const void* w, size_t first, 
   int32_t best = 0, bv = 0;
   int bi = 0;
   for (int i = 0; i < K; ++i) {
-    float x = load_weight(w, first + i, wtype) / s;
+    float x = quotient(load_weight(w, first + i, wtype), s);
     x = fminf(fmaxf(x, -qmaxf), qmaxf);
     const float p = rintf(x) - x;
     const int32_t P = __float2int_rn(p * 8388608.0f);

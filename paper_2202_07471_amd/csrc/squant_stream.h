@@ -50,7 +50,7 @@ struct StreamChannel {
 // SQuant-E on one weight: code and Q23 perturbation.
 __device__ __forceinline__ int32_t st_round(const StreamChannel& ch, size_t e, int& code) {
   const float wv = load_weight(ch.w, ch.first + e, ch.wtype);
-  const float x = ch.fast ? div_by_reciprocal(wv, ch.s, ch.rs) : wv / ch.s;  // the IEEE quotient either way
+  const float x = ch.fast ? div_by_reciprocal(wv, ch.s, ch.rs) : quotient(wv, ch.s);  // the IEEE quotient either way
   const float xc = fminf(fmaxf(x, -ch.qmaxf), ch.qmaxf);
   const float c = rintf(xc);
   code = (int)c;

@@ -145,6 +145,26 @@ def test_subnormal_scales(sq, shape, dtype, name):
             assert len(bad) == 0, f"{what}: {len(bad)} differ, first at {bad[0].tolist()}"
 
 
+@pytest.mark.parametrize("shape", [(24, 64, 1, 1), (24, 30, 1, 1), (24, 512, 1, 1), (24, 4096, 1, 1), (2, 40000, 1, 1),
+                                   (2, 70000, 1, 1), (24, 8, 3, 3), (24, 3, 3, 3), (24, 128, 3, 3), (24, 301, 3, 3),
+                                   (64, 130, 1, 3), (24, 64, 5, 5), (24, 1, 3, 3), (24, 1, 5, 5), (24, 16, 7, 7), (2, 5000, 3, 3)])
+def test_zero_weights_of_a_zero_scale(sq, shape):
+    """Weights of a few 2^-149 at 4 and 8 bits: the scale rounds to 0, every other weight is clamped to +-qmax, a
+    weight of 0 keeps the code 0 (0 / 0 must not reach the clamp), and no perturbation is left to flip anything."""
+    rng = np.random.default_rng(shape[1])
+    units = rng.integers(-3, 4, shape)
+    units[:, 0, 0, 0] = 3
+    d = torch.from_numpy((units * 2.0 ** -149).astype(np.float32)).cuda()
+    for bits in (4, 8):
+        want = np.sign(units) * (2 ** (bits - 1) - 1)
+        for mode in (sq.MODE_E, sq.MODE_EK, sq.MODE_EKC, sq.MODE_EC):
+            codes, scales = sq.squant_quantize(d, bits, mode)
+            together, _ = sq.squant_quantize_batched([d, torch.ones(40, 64, 3, 3, device="cuda"), torch.ones(40, 16, 1, 1, device="cuda")], bits, mode)
+            assert not scales.cpu().numpy().any()
+            assert np.array_equal(codes.cpu().numpy().reshape(shape), want), (shape, bits, mode)
+            assert np.array_equal(together[0].cpu().numpy().reshape(shape), want), ("batched", shape, bits, mode)
+
+
 @pytest.mark.parametrize("output", ["int8", "int4", "f32", "bf16"])
 @pytest.mark.parametrize("wtype", [torch.float32, torch.float16, torch.bfloat16])
 def test_every_output_format(sq, wtype, output):
