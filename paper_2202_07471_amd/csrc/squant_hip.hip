@@ -89,6 +89,7 @@ int check_shape(int32_t cout, int32_t cin, int32_t kh, int32_t kw) {
 
 constexpr int kMixed = 100;      // Group::variant of a launch of squant_channel_mixed
 constexpr int kMixedWave = 101;  // the same for the tensors whose channels take one wave each
+constexpr int kK1RowsThreads = 2 * kWave;  // workgroup of the kernel for several 1x1 / FC channels per wave
 constexpr size_t kMixedMaxLds = 16 * 1024;  // a member that wants more LDS than this stays out of it
 
 // Threads a register-kernel tensor of N kernels, up to `top` per thread, takes as a member of a
@@ -184,10 +185,13 @@ Plan own_launch(Plan p, int64_t N, int64_t K) {
   return p;
 }
 
-// Launches tensors [begin, end) of a group (at most kInlineDescs of them) as one kernel.
-int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, int output, int wtype,
+// Launches tensors [begin, end) of a group (at most kInlineDescs of them) as one kernel; rows: with the kernel for
+// several 1x1 / FC channels per wave, wave_span of them.
+int launch_part(const Group& g, bool rows, size_t begin, size_t end, int qmax, int mode, int output, int wtype,
                 int wave_span, hipStream_t st) {
   LaunchArgs a;  // 11 KB: only the entries in use are filled in
+  const int threads = rows ? kK1RowsThreads : g.threads;
+  const bool mixed = g.variant == kMixed || g.variant == kMixedWave;
   a.n_sigma = g.n_sigma;
   a.act_levels_minus_1 = g.act_levels_minus_1;
   int64_t total = 0;
@@ -195,8 +199,9 @@ int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, in
   auto items_of = [&](const TensorDesc& t) {
     if (t.K == 0) return (int64_t)1;  // a batch norm
     if (g.variant == kK9Team) { const int per = g.threads / k9_team_lanes(t.N); return (int64_t)(t.M + per - 1) / per; }
-    return route_work_items(t.M, t.N, t.K, g.threads, route_family(t.M, t.N, t.K, pointers_aligned(t.w, t.out)),
-                            wave_span);
+    const int family = route_family(t.M, t.N, t.K, pointers_aligned(t.w, t.out));
+    if (mixed) return mixed_work_items(t.M, t.N, t.K, threads, family);
+    return route_work_items(t.M, t.N, t.K, threads, family, wave_span);
   };
   const int64_t items0 = items_of(g.t[begin]);
   for (size_t i = begin; i < end; ++i) {
@@ -234,7 +239,8 @@ int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, in
     any |= family != 7 && (family != choose_family(t.N, t.K, aligned) || (family == 5 && !is_ks(g.variant)));
   }
   const kernel_t kernel = is_ks(g.variant) ? ks_kernel(ks_variant_k(g.variant), ks_variant_kpt(g.variant), g.threads, mode)
-                          : (g.variant == kMixed || g.variant == kMixedWave) ? mixed_kernel(mode, wtype, any)
+                          : mixed ? mixed_kernel(mode, wtype, any)
+                          : rows ? k1_rows_kernel(kWave / wave_span, k1_rows_nv(g.t[begin].N), mode, wtype, tail)
                           : is_k1_wave(g.variant) ? k1_wave_kernel(g.variant - kK1Wave, mode, wtype, tail)
                           : nv ? k1_kernel(nv, mode, wtype, tail)
                           : g.variant == kK1Stream ? k1_stream_kernel(mode)
@@ -249,7 +255,8 @@ int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, in
                                                : generic_kernel();
   if (!kernel) return SQUANT_ERR_UNSUPPORTED;
   size_t lds = g.lds;
-  if (g.wave_members) lds = std::max(lds, (size_t)(g.threads / kWave) * sizeof(K1WaveSel));
+  if (rows) lds = (size_t)(threads / kWave) * kK1RowsLds;
+  else if (g.wave_members) lds = std::max(lds, (size_t)(threads / kWave) * (mixed ? kK1RowsLds : sizeof(K1WaveSel)));
   if (lds > 48 * 1024) {
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
@@ -259,7 +266,7 @@ int launch_part(const Group& g, size_t begin, size_t end, int qmax, int mode, in
   }
   // by address: a call through the kernel's stub copies the arguments twice more
   void* args[] = {&a};
-  if (hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3((unsigned)total), dim3(g.threads), args,
+  if (hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3((unsigned)total), dim3(threads), args,
                       g.variant == kStream ? 0 : lds, st) != hipSuccess) {
     (void)hipGetLastError();
     return SQUANT_ERR_DEVICE;
@@ -277,18 +284,26 @@ int launch_group(const Group& g, int qmax, int mode, int output, int wtype, hipS
   // 83.8 with two, 85.9 with four).  Longer binary32 rows have enough bytes in flight and lose by
   // the registers that wait (the same shape: 107.7, 117.3, 129.5 us), so they keep to one.
   int wave_span = 1;
+  bool rows = false;
   if (is_k1_wave(g.variant)) {
     int64_t channels = 0, longest = 0;
+    rows = true;
     for (const auto& t : g.t) {
       channels += t.M;
       longest = std::max<int64_t>(longest, t.N);
+      rows &= k1_rows_pays(t.N, wtype != SQUANT_W_F32) && k1_rows_nv(t.N) == k1_rows_nv(g.t[0].N) &&
+              k1_rows_team(t.N) == k1_rows_team(g.t[0].N);  // one kernel for all
     }
-    if (channels >= (int64_t)kK1WaveSpan * 2 * 8192)
+    rows &= channels >= kK1RowsMin;
+    if (rows) {
+      wave_span = kWave / k1_rows_team(longest);
+    } else if (channels >= (int64_t)kK1WaveSpan * 2 * 8192) {
       wave_span = longest <= 512 ? kK1WaveSpan : wtype == SQUANT_W_F32 ? 1 : 2;
+    }
   }
   for (size_t begin = 0; begin < g.t.size(); begin += kInlineDescs) {
     const size_t end = std::min(g.t.size(), begin + (size_t)kInlineDescs);
-    if (int rc = launch_part(g, begin, end, qmax, mode, output, wtype, wave_span, st)) return rc;
+    if (int rc = launch_part(g, rows, begin, end, qmax, mode, output, wtype, wave_span, st)) return rc;
   }
   return SQUANT_OK;
 }

@@ -254,10 +254,7 @@ __device__ __forceinline__ uint32_t k1_team_count(Sh& sh, uint32_t wave_total, i
 // ends up in bit 0: four compares and four additions with carry.  Ordered so that at least two
 // instructions lie between a compare and the addition that reads its result, which this
 // hardware asks for where the compiler does not see the pair.
-template <bool AT_LEAST>
-__device__ __forceinline__ void push_compares(uint32_t& m, uint32_t t, const uint32_t* b) {
-  uint64_t c0, c1, c2, c3;
-#define SQ_PUSH(CMP)                                  \
+#define SQ_PUSH(CMP, T)                               \
   asm(CMP " %1, %5, %9\n\t"                           \
       CMP " %2, %5, %8\n\t"                           \
       CMP " %3, %5, %7\n\t"                           \
@@ -267,11 +264,19 @@ __device__ __forceinline__ void push_compares(uint32_t& m, uint32_t t, const uin
       "v_addc_co_u32_e64 %0, %3, %0, %0, %3\n\t"      \
       "v_addc_co_u32_e64 %0, %4, %0, %0, %4"          \
       : "+v"(m), "=&s"(c0), "=&s"(c1), "=&s"(c2), "=&s"(c3) \
-      : "s"(t), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]))
-  if (AT_LEAST) SQ_PUSH("v_cmp_le_u32_e64");
-  else SQ_PUSH("v_cmp_ge_u32_e64");
-#undef SQ_PUSH
+      : T(t), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]))
+template <bool AT_LEAST>
+__device__ __forceinline__ void push_compares(uint32_t& m, uint32_t t, const uint32_t* b) {
+  uint64_t c0, c1, c2, c3;
+  if (AT_LEAST) SQ_PUSH("v_cmp_le_u32_e64", "s");
+  else SQ_PUSH("v_cmp_ge_u32_e64", "s");
 }
+// b[i] >= t with a threshold of the lane's own.
+__device__ __forceinline__ void push_compares_lanes(uint32_t& m, uint32_t t, const uint32_t* b) {
+  uint64_t c0, c1, c2, c3;
+  SQ_PUSH("v_cmp_le_u32_e64", "v");
+}
+#undef SQ_PUSH
 
 // Moves the bounds of the search onto elements: lo to the smallest u >= lo, hi behind the largest
 // u < hi (uniform).  Four instructions an element, two passes' worth.  One barrier; that of a pass of
@@ -311,6 +316,29 @@ __device__ __forceinline__ void k1_close_in(const uint32_t (&B)[NE], int32_t sm,
   below = umin2(below, (uint32_t)(hi - lo - 1) - above);
   lo += (int32_t)above;
   hi -= (int32_t)below;
+}
+
+// The next threshold after one, `thr`, that only n < need elements reach, while no lower bound is known;
+// it aims at need + extra.
+// Widen the distance from the top in proportion.  Where outliers set the scale the rest
+// crowds around 0 and that lands far below the need-th element.  About half the row lies on the
+// wanted side, so (0, N / 2) and the count just taken give a line through logarithms; the
+// nearer of the two is taken, a quarter further from the top at least.  Passes on average without
+// and with that line, 2 bits: 1 % outliers 4.5 and 3.3 (N = 2024), Student-t 3.4 and 2.8.  Six linear
+// layers, 49 M weights with outliers, 2 bits: binary32 62.5 -> 56.6 us, bfloat16 55.4 -> 49.4.
+__device__ __forceinline__ int32_t k1_lower_threshold(int32_t thr, uint32_t n, uint32_t need, float extra, int N) {
+  // The empty statement keeps what depends on N alone from being computed before the loop.
+  uint32_t half = (uint32_t)N >> 1;
+  asm volatile("" : "+s"(half));
+  const float few = (float)need, from_top = (float)((1 << 22) + 1 - thr);
+  float wider = from_top * ((few * 1.25f + 4.0f) * __builtin_amdgcn_rcpf(fmaxf((float)n, 0.5f)));
+  const float want = few + extra;
+  if (want < (float)half) {
+    const float base = __builtin_amdgcn_logf(fmaxf((float)n, 0.5f));
+    const float part = (__builtin_amdgcn_logf(want) - base) * __builtin_amdgcn_rcpf(__builtin_amdgcn_logf((float)half) - base);
+    wider = fminf(wider, fmaxf(1.25f * from_top, from_top + part * (float)thr));
+  }
+  return (1 << 22) - (int32_t)fminf(wider, 4194304.0f);
 }
 
 // B[q] = kQ23Bias + P; sm: 0 for a positive channel sum, -1 for a negative one.  All threads of the
@@ -409,24 +437,7 @@ __device__ __forceinline__ MaskT k1_channel_stage(const uint32_t (&B)[NE], int32
         thr = thr <= lo ? lo + 1 : thr;
       }
     } else {
-      // Too few: widen the distance from the top in proportion.  Where outliers set the scale the rest
-      // crowds around 0 and that lands far below the need-th element.  About half the row lies on the
-      // wanted side, so (0, N / 2) and the count just taken give a line through logarithms as above; the
-      // nearer of the two is taken, a quarter further from the top at least.  Passes on average without
-      // and with that line, 2 bits: 1 % outliers 4.5 and 3.3 (N = 2024), Student-t 3.4 and 2.8.  Six linear
-      // layers, 49 M weights with outliers, 2 bits: binary32 62.5 -> 56.6 us, bfloat16 55.4 -> 49.4.
-      // The empty statement keeps what depends on N and need alone from being computed before the loop.
-      uint32_t half = (uint32_t)N >> 1, few = need;
-      asm volatile("" : "+s"(half), "+s"(few));
-      const float from_top = (float)((1 << 22) + 1 - thr);
-      float wider = from_top * (((float)few * 1.25f + 4.0f) * __builtin_amdgcn_rcpf(fmaxf((float)n, 0.5f)));
-      const float want = (float)few + 0.25f * (float)cap;
-      if (want < (float)half) {
-        const float base = __builtin_amdgcn_logf(fmaxf((float)n, 0.5f));
-        const float part = (__builtin_amdgcn_logf(want) - base) * __builtin_amdgcn_rcpf(__builtin_amdgcn_logf((float)half) - base);
-        wider = fminf(wider, fmaxf(1.25f * from_top, from_top + part * (float)thr));
-      }
-      thr = __builtin_amdgcn_readfirstlane((1 << 22) - (int32_t)fminf(wider, 4194304.0f));
+      thr = __builtin_amdgcn_readfirstlane(k1_lower_threshold(thr, n, need, 0.25f * (float)cap, N));
     }
   }
   // those with u >= hi flip; `want` of the `count` with lo <= u < hi
@@ -506,24 +517,19 @@ __device__ __forceinline__ int64_t k1_wave_sum(int32_t v) {
   return NE < 32 ? wave_sum_rows(v) : wave_sum_dpp(v);  // a row of 16 lanes: 16 * NE * 2^22 < 2^31
 }
 
-template <int MODE, int NE, int VE, bool WAVE, typename Sh>
-__device__ __forceinline__ float k1_solve(float (&w)[NE], int N, float qmaxf, float rcp_qmax, Sh& sh, uint32_t* owner,
-                                          uint32_t (&code)[NE / 4]) {
-  constexpr bool kChannelStage = MODE == SQUANT_MODE_EKC || MODE == SQUANT_MODE_EC;
-  typedef typename std::conditional<(NE > 32), uint64_t, uint32_t>::type MaskT;
-  const int T = k1_team<WAVE>(), tid = k1_tid<WAVE>();
-  if (kChannelStage) {  // before the first barrier
-    owner[tid] = 0;
-    if (NE > 32) owner[T + tid] = 0;
-    if constexpr (!WAVE)
-      if (tid == 0) sh.list_count = 0;
-  }
+template <int NE>
+__device__ __forceinline__ float k1_absmax(const float (&w)[NE]) {
   float amax = 0.0f;
 #pragma unroll
   for (int q = 0; q < NE; q += 2) amax = fmaxf(fmaxf(amax, fabsf(w[q])), fabsf(w[q + 1]));
-  if constexpr (WAVE) amax = wave_max_dpp(amax);
-  else amax = block_max_dpp1(amax, sh.red_f);
+  return amax;
+}
 
+// SQuant-E with the scale of a channel of absmax `amax` (the channel's, in each of its lanes); w is used up.
+// Codes and B as from k1_round_all; esum: the sum of the thread's P.  Returns the scale.
+template <int NE, bool WITH_P>
+__device__ __forceinline__ float k1_quantize(float (&w)[NE], float amax, float qmaxf, float rcp_qmax,
+                                             uint32_t (&code)[NE / 4], uint32_t (&B)[NE], int32_t& esum) {
   // The quotients go through the reciprocal of s, which is proven exact for an absmax within
   // [2^-60, 2^60]; a channel outside is first scaled by a power of two (see squant_k9.h).  There a
   // subnormal scale may be far below absmax / qmax, with many quotients beyond qmax, or be 0, with
@@ -544,8 +550,29 @@ __device__ __forceinline__ float k1_solve(float (&w)[NE], int N, float qmaxf, fl
     amax = 0.0f;  // no quotient beyond qmax is left
   }
   const float rs = reciprocal(s2);
+  esum = k1_round_all<NE, WITH_P>(w, s2, rs, qmaxf, div_by_reciprocal(amax, s2, rs), code, B);
+  return s;
+}
+
+template <int MODE, int NE, int VE, bool WAVE, typename Sh>
+__device__ __forceinline__ float k1_solve(float (&w)[NE], int N, float qmaxf, float rcp_qmax, Sh& sh, uint32_t* owner,
+                                          uint32_t (&code)[NE / 4]) {
+  constexpr bool kChannelStage = MODE == SQUANT_MODE_EKC || MODE == SQUANT_MODE_EC;
+  typedef typename std::conditional<(NE > 32), uint64_t, uint32_t>::type MaskT;
+  const int T = k1_team<WAVE>(), tid = k1_tid<WAVE>();
+  if (kChannelStage) {  // before the first barrier
+    owner[tid] = 0;
+    if (NE > 32) owner[T + tid] = 0;
+    if constexpr (!WAVE)
+      if (tid == 0) sh.list_count = 0;
+  }
+  float amax = k1_absmax(w);
+  if constexpr (WAVE) amax = wave_max_dpp(amax);
+  else amax = block_max_dpp1(amax, sh.red_f);
+
   uint32_t B[NE];
-  const int32_t esum = k1_round_all<NE, kChannelStage>(w, s2, rs, qmaxf, div_by_reciprocal(amax, s2, rs), code, B);
+  int32_t esum;
+  const float s = k1_quantize<NE, kChannelStage>(w, amax, qmaxf, rcp_qmax, code, B, esum);
 
   if (kChannelStage) {
     int64_t ec = k1_wave_sum<NE>(esum);

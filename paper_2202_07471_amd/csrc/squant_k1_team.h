@@ -25,13 +25,27 @@
 
 namespace squant {
 
-// Reductions over the TEAM (4, 8 or 16) lanes a lane belongs to; every lane gets the result.
+// Both rows' values of v in a pair of rows of 16 lanes: x from the even row, y from the odd one.
+__device__ __forceinline__ vu2 row_pair(uint32_t v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  return vu2{r[0], r[1]};
+#else
+  return vu2{v, v};
+#endif
+}
+
+// Reductions over the TEAM (4, 8, 16 or 32) lanes a lane belongs to; every lane gets the result.
 template <int TEAM>
 __device__ __forceinline__ float team_max_f32(float v) {
   v = fmaxf(v, dpp_f32<0xB1>(v));                   // quad_perm [1,0,3,2]
   v = fmaxf(v, dpp_f32<0x4E>(v));                   // quad_perm [2,3,0,1]
   if (TEAM >= 8) v = fmaxf(v, dpp_f32<0x141>(v));   // row_half_mirror
   if (TEAM >= 16) v = fmaxf(v, dpp_f32<0x140>(v));  // row_mirror
+  if (TEAM >= 32) {
+    const vu2 r = row_pair(__float_as_uint(v));
+    v = fmaxf(__uint_as_float(r.x), __uint_as_float(r.y));
+  }
   return v;
 }
 template <int TEAM>
@@ -41,14 +55,22 @@ __device__ __forceinline__ uint32_t team_max_u32(uint32_t x) {
   v = (int)max((uint32_t)v, (uint32_t)dpp_i32<0x4E>(v));
   if (TEAM >= 8) v = (int)max((uint32_t)v, (uint32_t)dpp_i32<0x141>(v));
   if (TEAM >= 16) v = (int)max((uint32_t)v, (uint32_t)dpp_i32<0x140>(v));
+  if (TEAM >= 32) {
+    const vu2 r = row_pair((uint32_t)v);
+    v = (int)max(r.x, r.y);
+  }
   return (uint32_t)v;
 }
 template <int TEAM>
-__device__ __forceinline__ int32_t team_sum_i32(int32_t v) {  // |sum| < 2^31: cin <= 256, |P| <= 2^22
+__device__ __forceinline__ int32_t team_sum_i32(int32_t v) {  // for |sum| < 2^31
   v += dpp_i32<0xB1>(v);
   v += dpp_i32<0x4E>(v);
   if (TEAM >= 8) v += dpp_i32<0x141>(v);
   if (TEAM >= 16) v += dpp_i32<0x140>(v);
+  if (TEAM >= 32) {
+    const vu2 r = row_pair((uint32_t)v);
+    v = (int)(r.x + r.y);
+  }
   return v;
 }
 

@@ -22,6 +22,7 @@ kernel_t dw_team_kernel(int mode);
 kernel_t ks_kernel(int K, int kpt, int threads, int mode);
 kernel_t k1_kernel(int nv, int mode, int wtype, bool tail);
 kernel_t k1_wave_kernel(int nv, int mode, int wtype, bool tail);
+kernel_t k1_rows_kernel(int team, int nv, int mode, int wtype, bool tail);
 kernel_t k1_stream_kernel(int mode);
 kernel_t k1_team_kernel(int mode, bool any);
 kernel_t mixed_kernel_plain(int mode);

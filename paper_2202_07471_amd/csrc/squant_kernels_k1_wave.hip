@@ -1,6 +1,7 @@
 // 1x1 / FC kernels: a wave per channel, and several channels per wave.
 #include "squant_kernels.h"
 
+#include "squant_k1_rows.h"
 #include "squant_k1_team.h"
 #include "squant_k1_wave.h"
 
@@ -17,7 +18,31 @@ kernel_t k1_wave_of(bool channel_stage, bool half, bool tail) {
   return k[channel_stage][half][tail];
 }
 
+template <int TEAM, int NV, bool HALF>
+kernel_t k1_rows_of(bool channel_stage, bool tail) {
+  static const kernel_t k[2][2] = {
+      {squant_channel_k1_rows<SQUANT_MODE_E, TEAM, NV, HALF, false>, squant_channel_k1_rows<SQUANT_MODE_E, TEAM, NV, HALF, true>},
+      {squant_channel_k1_rows<SQUANT_MODE_EKC, TEAM, NV, HALF, false>, squant_channel_k1_rows<SQUANT_MODE_EKC, TEAM, NV, HALF, true>}};
+  return k[channel_stage][tail];
+}
+template <int TEAM>
+kernel_t k1_rows_team(int nv, bool stage, bool half, bool tail) {
+  // 16-bit weights come in vectors of eight
+  if (half) return nv <= 6 ? k1_rows_of<TEAM, 6, true>(stage, tail) : k1_rows_of<TEAM, 8, true>(stage, tail);
+  switch (nv) {
+    case 5: return k1_rows_of<TEAM, 5, false>(stage, tail);
+    case 6: return k1_rows_of<TEAM, 6, false>(stage, tail);
+    case 7: return k1_rows_of<TEAM, 7, false>(stage, tail);
+    default: return k1_rows_of<TEAM, 8, false>(stage, tail);
+  }
+}
+
 }  // namespace
+
+kernel_t k1_rows_kernel(int team, int nv, int mode, int wtype, bool tail) {
+  const bool stage = mode == SQUANT_MODE_EKC || mode == SQUANT_MODE_EC, half = wtype != SQUANT_W_F32;
+  return team == 16 ? k1_rows_team<16>(nv, stage, half, tail) : k1_rows_team<32>(nv, stage, half, tail);
+}
 
 kernel_t k1_wave_kernel(int nv, int mode, int wtype, bool tail) {
   const bool stage = mode == SQUANT_MODE_EKC || mode == SQUANT_MODE_EC, half = wtype != SQUANT_W_F32;

@@ -87,6 +87,26 @@ SQ_HD int64_t k1_threads(int64_t nvec, int nv) {
 SQ_HD int k1_wave_nv(int64_t N) { return (int)((N / 4 + 63) / 64); }
 SQ_HD bool is_k1_wave(int variant) { return variant >= kK1Wave + 2 && variant <= kK1Wave + 8; }
 
+// Several 1x1 / FC channels of 257 to 1024 elements per wave (squant_k1_rows.h): lanes per channel and
+// four-element vectors per lane (5 to 8).
+constexpr int kMaxRowsCin = 1024;
+constexpr int kK1RowsLds = 4096 + 256;  // bytes a wave
+SQ_HD int k1_rows_team(int64_t N) { return N <= 512 ? 16 : 32; }
+SQ_HD int k1_rows_nv(int64_t N) { const int64_t per = 4 * k1_rows_team(N); return (int)((N + per - 1) / per); }
+// Whether a large launch of its own takes that kernel.  Up to 512 elements always (us with a wave per channel and with
+// rows: 131 K channels of 512 binary16 58.1 and 45.2, binary32 64.0 and 55.2; 65 K of 300 binary32 32.3 and 22.0).  With
+// two channels to a wave less is left to share; 65 K channels, binary32: 516 38.0 and 31.7, 640 39.7 and 36.7, 768 42.2
+// and 43.9, 1024 53.6 and 57.5, but 777, no whole number of vectors, 56.5 and 46.1, 1001 60.4 and 58.8; binary16: 516
+// 37.8 and 40.0, 700 39.5 and 41.4, 1024 44.1 and 44.9, 772 52.7 and 47.3, 1001 51.6 and 48.8.
+SQ_HD bool k1_rows_pays(int64_t N, bool half) {
+  if (N <= 512) return true;
+  if (N > kMaxRowsCin) return false;
+  return half ? N > 768 && N % 8 != 0 : N <= 640 || N % 4 != 0;
+}
+// Channels a launch must have for it: with fewer the chip holds a wave for each, and the longer chain of a wave with
+// several shows (8192 channels of 512: 7.7 us with a wave each, 8.6; of 300: 7.4 and 7.4; 16384: 11.9 and 11.5).
+constexpr int64_t kK1RowsMin = 12288;
+
 // 16-byte vectors per thread of a 1x1 / FC variant (0: not one), and back.
 SQ_HD bool is_k1_wide(int variant) { return variant > kK1Wide && variant <= kK1Wide + 16; }
 SQ_HD int k1_variant_nv(int variant) {
@@ -282,6 +302,12 @@ SQ_HD int64_t work_items(int64_t M, int64_t N, int64_t K, int64_t T, int family,
 SQ_HD int64_t route_work_items(int64_t M, int64_t N, int64_t K, int64_t T, int family, int wave_span) {
   if (family == 7) { const int64_t per = T / dw_team_lanes(K); return (M + per - 1) / per; }
   return work_items(M, N, K, T, family, wave_span);
+}
+
+// In a mixed launch.
+SQ_HD int64_t mixed_work_items(int64_t M, int64_t N, int64_t K, int64_t T, int family) {
+  if (family == 6 && N <= kMaxRowsCin) { const int64_t per = T / k1_rows_team(N); return (M + per - 1) / per; }
+  return route_work_items(M, N, K, T, family, 1);
 }
 
 SQ_HD bool pointers_aligned(const void* w, const void* out) {

@@ -1,0 +1,91 @@
+"""GPU parity for the kernel that gives four (two) 1x1 / FC channels of 257 to 512 (1024) elements to a
+wave: every count of vectors a lane holds, rows that end inside a vector, channel counts that leave
+teams of the last wave without a channel, and values whose search ends in each of its ways, in the large
+launches that take the kernel by themselves and as members of a mixed launch."""
+import numpy as np
+import pytest
+
+import oracle
+from test_gpu_one_sided_rows import KINDS as ONE_SIDED, values as one_sided_values
+from test_gpu_threshold_search import values
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+SEARCH = ("normal", "grid", "one_sided", "centre", "outliers", "clamp", "grid4", "ternary")
+
+
+@pytest.fixture(scope="module")
+def sq():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2202_07471_amd as sq
+    sq.binding.lib()
+    return sq
+
+
+def rows(kind, cin, bits, rng, m):
+    w = one_sided_values(kind, (m, cin, 1, 1), bits, rng) if kind in ONE_SIDED else values(kind, (m, cin), bits, rng)
+    return w.reshape(m, cin, 1, 1)
+
+
+def expected(d, bits, mode, output, sq):
+    ref = d.cpu().numpy() if d.dtype == torch.float32 else oracle.widen(
+        d.cpu().view(torch.int16).numpy().view(np.uint16), "f16" if d.dtype == torch.float16 else "bf16")
+    codes, scales = oracle.quantize(ref, bits, mode, threads=8)
+    if output == sq.OUT_INT4:
+        return torch.from_numpy(oracle.pack_int4(codes)), scales
+    if output == sq.OUT_INT8:
+        return torch.from_numpy(codes), scales
+    value = torch.from_numpy(codes.astype(np.float32) * scales.reshape(-1, 1, 1, 1))
+    return value if output == sq.OUT_F32 else value.to(torch.bfloat16), scales
+
+
+def same(got, want, what):
+    assert np.array_equal(got[1].cpu().numpy(), want[1]), what
+    assert torch.equal(got[0].cpu().reshape(-1), want[0].reshape(-1)), what
+
+
+# one more than a vector count holds, its largest, and between; odd rows
+@pytest.mark.parametrize("cin", [257, 260, 320, 321, 384, 388, 447, 448, 449, 511, 512, 513, 516, 640, 772, 777, 1001])
+def test_large_launch(sq, cin):
+    m = 12290   # two teams of the last wave of four have no channel
+    rng = np.random.default_rng(cin)
+    bits = (2, 3, 4, 8)[cin % 4]
+    kinds = SEARCH + ONE_SIDED
+    part = -(-m // len(kinds))
+    w = np.concatenate([rows(k, cin, bits, rng, part) for k in kinds])[:m]
+    for i, dtype in enumerate((torch.float32, torch.float16, torch.bfloat16)):
+        d = torch.from_numpy(w).to(dtype).cuda()
+        output = (sq.OUT_INT8, sq.OUT_F32, sq.OUT_BF16, sq.OUT_INT4 if bits <= 4 else sq.OUT_INT8)[(cin + i) % 4]
+        for mode in (sq.MODE_EKC, sq.MODE_E):
+            got = sq.squant_quantize_ex(d, bits, mode, output)
+            same(got, expected(d, bits, mode, output, sq), f"cin={cin} {dtype} mode={mode} output={output}")
+
+
+@pytest.mark.parametrize("cin", [257, 260, 300, 388, 509, 512, 516, 700, 897, 1022, 1024])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16])
+def test_member_of_a_mixed_launch(sq, cin, dtype):
+    rng = np.random.default_rng(cin)
+    for bits in (2, 4, 8):
+        kinds = SEARCH + ONE_SIDED
+        ws = [torch.from_numpy(rows(k, cin, bits, rng, 5)).to(dtype).cuda() for k in kinds]
+        other = torch.from_numpy(rng.standard_normal((8, 40, 3, 3)).astype(np.float32)).to(dtype).cuda()
+        for mode in (sq.MODE_EKC, sq.MODE_EC):
+            outs, scales = sq.squant_quantize_batched_ex([*ws, other], bits, mode)
+            for kind, w, out, s in zip([*kinds, "3x3"], [*ws, other], outs, scales):
+                same((out, s), expected(w, bits, mode, sq.OUT_INT8, sq), f"{kind} cin={cin} {dtype} bits={bits} mode={mode}")
+
+
+def test_scales_beyond_the_reciprocal_in_one_team_of_a_wave(sq):
+    """The teams of a wave have scales of their own: zero, subnormal and huge ones beside ordinary ones."""
+    rng = np.random.default_rng(3)
+    for cin in (400, 900):
+        w = rng.standard_normal((64, cin, 1, 1)).astype(np.float32)
+        factor = np.resize(np.float32([1, 0, 1e-42, 2.0 ** -70, 1, 2.0 ** 70, 1e-45, 1, 3e37]), 64)
+        d = torch.from_numpy((w * factor.reshape(-1, 1, 1, 1)).astype(np.float32)).cuda()
+        other = torch.from_numpy(rng.standard_normal((8, 40, 3, 3)).astype(np.float32)).cuda()
+        for bits in (2, 4, 8):
+            outs, scales = sq.squant_quantize_batched_ex([d, other], bits, sq.MODE_EKC)
+            same((outs[0], scales[0]), expected(d, bits, sq.MODE_EKC, sq.OUT_INT8, sq), f"cin={cin} bits={bits}")
