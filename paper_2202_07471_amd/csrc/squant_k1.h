@@ -276,6 +276,11 @@ __device__ __forceinline__ void push_compares_lanes(uint32_t& m, uint32_t t, con
   uint64_t c0, c1, c2, c3;
   SQ_PUSH("v_cmp_le_u32_e64", "v");
 }
+// The same for signed words.
+__device__ __forceinline__ void push_compares_signed(uint32_t& m, int32_t t, const int32_t* b) {
+  uint64_t c0, c1, c2, c3;
+  SQ_PUSH("v_cmp_le_i32_e64", "v");
+}
 #undef SQ_PUSH
 
 // Moves the bounds of the search onto elements: lo to the smallest u >= lo, hi behind the largest

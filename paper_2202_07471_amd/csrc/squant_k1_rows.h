@@ -85,7 +85,7 @@ __device__ __forceinline__ uint32_t k1_rows_select(const uint32_t (&B)[NE], uint
   constexpr int kIndexBits = TEAM == 16 ? 9 : 10;  // a key is (u - lo) above the index from the end: at most 31 bits
   constexpr uint32_t kIndexMask = (1u << kIndexBits) - 1u;
   constexpr int32_t kWidest = 1 << (31 - kIndexBits);  // widest interval whose keys fit
-  const int lane = (int)(threadIdx.x & (kWave - 1)), l = lane & (TEAM - 1), team = lane / TEAM;
+  const int lane = k1_tid<true>(), l = lane & (TEAM - 1), team = lane / TEAM;
   const int32_t step = __builtin_amdgcn_readfirstlane((int32_t)(8388608.0f * __builtin_amdgcn_rcpf((float)N)));
   const int32_t least = 1 + (int32_t)sm, top = (1 << 22) + 1;
 
@@ -347,28 +347,31 @@ __device__ __forceinline__ void k1_rows_channels(const LaunchArgs& a, const Tens
     }
   }
 
-  if (l == 0 && row < rows) d.scales[c0 + row] = s;
+  // what depends on the lane alone is computed again, not kept in registers through the search
+  const int lane_out = k1_tid<true>(), l_out = lane_out & (TEAM - 1), row_out = lane_out / TEAM;
+  const int first_out = VE * (l_out + (NL - 1) * TEAM);
+  if (l_out == 0 && row_out < rows) d.scales[c0 + row_out] = s;
   const int format = a.out_format;
-  if (format == SQUANT_OUT_INT8) k1_rows_emit<NE, VE, SQUANT_OUT_INT8, TEAM>(code, d.out, c0, rows, row, l, N, s);
-  else if (format == SQUANT_OUT_INT4) k1_rows_emit<NE, VE, SQUANT_OUT_INT4, TEAM>(code, d.out, c0, rows, row, l, N, s);
-  else if (format == SQUANT_OUT_BF16) k1_rows_emit<NE, VE, SQUANT_OUT_BF16, TEAM>(code, d.out, c0, rows, row, l, N, s);
-  else k1_rows_emit<NE, VE, SQUANT_OUT_F32, TEAM>(code, d.out, c0, rows, row, l, N, s);
+  if (format == SQUANT_OUT_INT8) k1_rows_emit<NE, VE, SQUANT_OUT_INT8, TEAM>(code, d.out, c0, rows, row_out, l_out, N, s);
+  else if (format == SQUANT_OUT_INT4) k1_rows_emit<NE, VE, SQUANT_OUT_INT4, TEAM>(code, d.out, c0, rows, row_out, l_out, N, s);
+  else if (format == SQUANT_OUT_BF16) k1_rows_emit<NE, VE, SQUANT_OUT_BF16, TEAM>(code, d.out, c0, rows, row_out, l_out, N, s);
+  else k1_rows_emit<NE, VE, SQUANT_OUT_F32, TEAM>(code, d.out, c0, rows, row_out, l_out, N, s);
   // the elements after the last whole vector of a row, one by one
-  if (TAIL && row < rows && first < N && first + VE > N) {
+  if (TAIL && row_out < rows && first_out < N && first_out + VE > N) {
     uint32_t lo = code[(NE - VE) / 4], hi = VE == 8 ? code[NE / 4 - 1] : 0u;
-    const size_t m = (size_t)(c0 + row);
+    const size_t m = (size_t)(c0 + row_out);
 #pragma unroll 1
-    for (int e = 0; e < N - first; ++e) {
+    for (int e = 0; e < N - first_out; ++e) {
       const uint32_t byte = lo & 255u;
       const float v = ((float)byte - 128.0f) * s;
       lo = __builtin_amdgcn_alignbit(hi, lo, 8);
       hi >>= 8;
-      const size_t at = m * N + first + e;
+      const size_t at = m * N + first_out + e;
       if (format == SQUANT_OUT_INT8) static_cast<uint8_t*>(d.out)[at] = (uint8_t)(byte ^ 0x80u);
       else if (format == SQUANT_OUT_BF16) static_cast<uint16_t*>(d.out)[at] = (uint16_t)bf16_bits(v);
       else if (format == SQUANT_OUT_F32) static_cast<float*>(d.out)[at] = v;
       else if ((e & 1) == 0)  // with the next element's nibble: past the end its code is 0
-        static_cast<uint8_t*>(d.out)[m * ((N + 1) / 2) + (first + e) / 2] = (uint8_t)((byte & 15u) | (lo << 4));
+        static_cast<uint8_t*>(d.out)[m * ((N + 1) / 2) + (first_out + e) / 2] = (uint8_t)((byte & 15u) | (lo << 4));
     }
   }
 }

@@ -33,6 +33,7 @@ inline kernel_t mixed_kernel(int mode, int wtype, bool any) {
   if (wtype == SQUANT_W_F32) return any ? mixed_kernel_any(mode) : mixed_kernel_plain(mode);
   return any ? mixed_kernel_any_half(mode) : mixed_kernel_plain_half(mode);
 }
+kernel_t stem_kernel(int mode);
 kernel_t stream_kernel(int mode);
 kernel_t generic_kernel();
 void (*activation_range_kernel())(BnArgs);

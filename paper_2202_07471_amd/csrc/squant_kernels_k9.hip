@@ -1,8 +1,9 @@
-// 3x3 kernels and depthwise ones.
+// 3x3 kernels, depthwise ones and stems.
 #include "squant_kernels.h"
 
 #include "squant_dw.h"
 #include "squant_k9.h"
+#include "squant_stem.h"
 
 namespace squant {
 
@@ -36,6 +37,12 @@ kernel_t dw9_kernel(int mode) {
   static const kernel_t dw9[4] = {squant_channel_dw9<SQUANT_MODE_E>, squant_channel_dw9<SQUANT_MODE_EK>,
                                   squant_channel_dw9<SQUANT_MODE_EKC>, squant_channel_dw9<SQUANT_MODE_EC>};
   return dw9[mode];
+}
+
+kernel_t stem_kernel(int mode) {
+  static const kernel_t k[4] = {squant_channel_stem<SQUANT_MODE_E>, squant_channel_stem<SQUANT_MODE_EK>,
+                                squant_channel_stem<SQUANT_MODE_EKC>, squant_channel_stem<SQUANT_MODE_EC>};
+  return k[mode];
 }
 
 kernel_t dw_team_kernel(int mode) {

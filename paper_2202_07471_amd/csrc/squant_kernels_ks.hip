@@ -41,7 +41,9 @@ kernel_t ks_kernel(int K, int kpt, int threads, int mode) {
     case 4: return ks_kernel_k<4>(kpt, threads, mode);
     case 5: return ks_kernel_k<5>(kpt, threads, mode);
     case 7: return ks_kernel_k<7>(kpt, threads, mode);
+    case 16: return ks_kernel_k<16>(kpt, threads, mode);
     case 25: return ks_kernel_k<25>(kpt, threads, mode);
+    case 49: return ks_kernel_k<49>(kpt, threads, mode);
     default: return nullptr;
   }
 }

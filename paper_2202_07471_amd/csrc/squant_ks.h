@@ -1,5 +1,5 @@
 // SQuant kernel for small convolution kernels other than 3x3 (1x3, 3x1, 1x7, 7x1, 2x2, 1x5,
-// 5x5 ...: K = kh*kw elements, 2 <= K <= kKsMaxK), built like the 3x3 kernel: one workgroup per
+// 4x4, 5x5, 7x7: K = kh*kw elements, 2 <= K <= kKsMaxK), built like the 3x3 kernel: one workgroup per
 // output channel, every thread holds KPT whole kernels in registers (thread t the kernels
 // t, t+G, ..., G = cin / KPT), SQuant-E, SQuant-K and the Algorithm 3 candidate are register
 // arithmetic, LDS only holds the channel's biased codes for SQuant-C and the write-out.
@@ -13,7 +13,8 @@
 
 #include "squant_common.h"
 #include "squant_io.h"
-#include "squant_k9.h"  // K9Shared
+#include "squant_k1.h"  // push_compares_signed
+#include "squant_k9.h"  // K9Shared, rounding constants
 #include "squant_plan.h"
 #include "squant_select.h"
 
@@ -66,14 +67,24 @@ __device__ __forceinline__ void ks_load_kernel16(float (&w)[NW], int q, rsrc_t r
   }
 }
 
-// SQuant-E, SQuant-K and the candidate update for one K-element kernel held in registers
+// The Algorithm 3 candidate from its key: the word and the element index.
+template <int IB>
+__device__ __forceinline__ void ks_candidate(int32_t ck, bool over, int32_t smask, uint32_t& cand_w, int& cand_i) {
+  constexpr int IM = (1 << IB) - 1;
+  const uint32_t mag = (uint32_t)ck >> IB;  // |p| of that element before any flip (if same-sign)
+  const uint32_t absv = over ? (uint32_t)kOne - mag : mag;
+  const uint32_t neg = (over ? ~(uint32_t)smask : (uint32_t)smask) & (1u << 23);
+  cand_w = ck >= (1 << IB) ? (absv | neg) : kNoCandidate;
+  cand_i = IM - (ck & IM);
+}
+
+// SQuant-E, SQuant-K and the candidate update for one kernel of up to nine elements held in registers
 // (straight-line code, as for 3x3).  Arguments as for k9_solve.
 template <int K, int NW, bool FAST, int MODE>
 __device__ __forceinline__ void ks_solve(const float (&w)[NW], int q, float s, float rs, float qmaxf,
                                          float (&cf)[K], int32_t& esum, uint32_t& cand_w,
                                          int& cand_i, uint32_t& zero) {
-  constexpr int IB = K <= 16 ? 4 : K <= 32 ? 5 : 6;  // bits of the index tie-break
-  constexpr int IM = (1 << IB) - 1;
+  constexpr int IB = 4, IM = (1 << IB) - 1;  // bits of the index tie-break
   const int W0 = K * q;
   float c[K];
   int32_t P[K];
@@ -114,54 +125,115 @@ __device__ __forceinline__ void ks_solve(const float (&w)[NW], int q, float s, f
   const int32_t want = over ? k - 1 : k;  // the candidate's rank: last flipped resp. first un-flipped (k <= K/2 < K)
   const float flip = smask ? 129.0f : 127.0f;  // code -= sign(E)
   int32_t ck = 0;  // the candidate's key
-  if constexpr (K <= 9) {
-    // rank = #{larger keys}, by all pairs
-    int32_t rank[K];
+  // rank = #{larger keys}, by all pairs
+  int32_t rank[K];
 #pragma unroll
-    for (int i = 0; i < K; ++i) rank[i] = i;  // i counts the pairs (j < i), corrected below
+  for (int i = 0; i < K; ++i) rank[i] = i;  // i counts the pairs (j < i), corrected below
 #pragma unroll
-    for (int i = 0; i < K; ++i)
+  for (int i = 0; i < K; ++i)
 #pragma unroll
-      for (int j = i + 1; j < K; ++j) {
-        const int32_t gt = key[j] > key[i] ? 1 : 0;
-        rank[i] += gt;
-        rank[j] -= gt;
-      }
-#pragma unroll
-    for (int i = 0; i < K; ++i) cf[i] = c[i] + (rank[i] < k ? flip : 128.0f);
-    if (MODE == SQUANT_MODE_EK) return;
-#pragma unroll
-    for (int i = 0; i < K; ++i) ck |= rank[i] == want ? key[i] : 0;
-  } else {
-    // The keys in descending order, as far as any kernel of the wave needs them (k is rarely above
-    // three): with keys within 2^30 of each other, key - m wraps to a huge number for the keys
-    // below m and to a small one for the others, so the largest difference names the next key.
-    // 1.5 instructions an element and step; all pairs of 25 elements took 900 and spilled.
-    int32_t m = key[0];
-#pragma unroll
-    for (int i = 1; i < K; ++i) m = imax2(m, key[i]);
-    int32_t last = 0x7fffffff;  // the k-th largest key
-#pragma unroll 1
-    for (int32_t rank = 0;; ++rank) {
-      if (rank == k - 1) last = m;
-      if (rank == want) ck = m;
-      if (__ballot(rank < want) == 0ull) break;
-      uint32_t z = 0;
-#pragma unroll
-      for (int i = 0; i < K; ++i) z = umax2(z, (uint32_t)key[i] - (uint32_t)m);
-      m = (int32_t)((uint32_t)m + z);
+    for (int j = i + 1; j < K; ++j) {
+      const int32_t gt = key[j] > key[i] ? 1 : 0;
+      rank[i] += gt;
+      rank[j] -= gt;
     }
 #pragma unroll
-    for (int i = 0; i < K; ++i) cf[i] = c[i] + (key[i] >= last ? flip : 128.0f);
-    if (MODE == SQUANT_MODE_EK) return;
-  }
+  for (int i = 0; i < K; ++i) cf[i] = c[i] + (rank[i] < k ? flip : 128.0f);
+  if (MODE == SQUANT_MODE_EK) return;
+#pragma unroll
+  for (int i = 0; i < K; ++i) ck |= rank[i] == want ? key[i] : 0;
 
   // ---- perturbation update (Algorithm 3): the kernel's candidate for SQuant-C ----
-  const uint32_t mag = (uint32_t)ck >> IB;  // |p| of that element before any flip (if same-sign)
-  const uint32_t absv = over ? (uint32_t)kOne - mag : mag;
-  const uint32_t neg = (over ? ~(uint32_t)smask : (uint32_t)smask) & (1u << 23);
-  cand_w = ck >= (1 << IB) ? (absv | neg) : kNoCandidate;
-  cand_i = IM - (ck & IM);
+  ks_candidate<IB>(ck, over, smask, cand_w, cand_i);
+}
+
+// The same for one kernel of more elements, one per thread.  Its perturbations take the place of the weights and its
+// codes + 128 are packed as they come (`code`), so a 7x7 kernel lives in 75 registers.
+template <int K, bool FAST, int MODE>
+__device__ __forceinline__ void ks_solve_long(const float (&w)[K], float s, float rs, float qmaxf,
+                                              uint32_t (&code)[(K + 3) / 4], int32_t& esum, uint32_t& cand_w, int& cand_i,
+                                              uint32_t& zero) {
+  constexpr int IB = K <= 16 ? 4 : K <= 32 ? 5 : 6, IM = (1 << IB) - 1;  // bits of the index tie-break
+  constexpr int KP = (K + 3) / 4 * 4;
+  int32_t key[KP];  // first the perturbations
+  uint32_t tb[KP];
+#pragma unroll
+  for (int i = 0; i < KP; ++i) {
+    if (i < K) {
+      const float x = FAST ? div_by_reciprocal(w[i], s, rs) : quotient(w[i], s);
+      const float xc = __builtin_amdgcn_fmed3f(x, -qmaxf, qmaxf);
+      const float t = xc + kRoundMagic;  // see squant_k9.h
+      const float c = t - kRoundMagic;
+      const float p = c - xc;  // exact
+      key[i] = __float_as_int(__builtin_fmaf(p, 8388608.0f, kQ23Magic)) - (int32_t)kQ23Bias;
+      tb[i] = __float_as_uint(t);
+    } else {
+      tb[i] = 128;
+      key[i] = 0;
+    }
+    if (i % 4 == 3) {
+      code[i / 4] = pack_low_bytes(tb[i - 3], tb[i - 2], tb[i - 1], tb[i]);
+      __builtin_amdgcn_sched_barrier(0);  // one group at a time: registers
+    }
+  }
+  cand_w = kNoCandidate;
+  cand_i = 0;
+  if (MODE == SQUANT_MODE_E) return;
+
+  // ---- SQuant-K (Algorithm 2 on one kernel) ----
+  int32_t E = 0;
+#pragma unroll
+  for (int i = 0; i < K; ++i) E += key[i];
+  const int32_t smask = E >> 31;
+  const int32_t A = (E ^ smask) - smask;
+  const int32_t k = (MODE == SQUANT_MODE_EC) ? 0 : (int32_t)((uint32_t)(A + kHalf - 1) >> 23);
+  const int32_t r = A - (k << 23);  // |sum| left after k flips, < 0: over SQuant
+  esum += (r ^ smask) - smask;
+  zero |= E == 0 ? 1u : 0u;
+
+  // unique keys: 2^IB |p| + (IM - i) >= 2^IB for the elements with the sign of the sum, below
+  // 2^IB for all others; |P| <= 2^22 fits the 24-bit multiply
+#pragma unroll
+  for (int i = 0; i < KP; ++i) key[i] = i < K ? __mul24(key[i], smask ? -(1 << IB) : (1 << IB)) + (IM - i) : INT32_MIN / 4;
+  const bool over = r < 0;
+  const int32_t want = over ? k - 1 : k;  // the candidate's rank: last flipped resp. first un-flipped (k <= K/2 < K)
+  // The keys in descending order, as far as any kernel of the wave needs them (k is rarely above
+  // three): with keys within 2^30 of each other, key - m wraps to a huge number for the keys
+  // below m and to a small one for the others, so the largest difference names the next key.
+  // 1.5 instructions an element and step; all pairs of 25 elements took 900 and spilled.
+  int32_t ck = 0, m = key[0];
+#pragma unroll
+  for (int i = 1; i < K; ++i) m = imax2(m, key[i]);
+  int32_t last = 0x7fffffff;  // the k-th largest key
+#pragma unroll 1
+  for (int32_t rank = 0;; ++rank) {
+    if (rank == k - 1) last = m;
+    if (rank == want) ck = m;
+    if (__ballot(rank < want) == 0ull) break;
+    uint32_t z = 0;
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      z = umax2(z, (uint32_t)key[i] - (uint32_t)m);
+      if (i % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+    }
+    m = (int32_t)((uint32_t)m + z);
+  }
+  if (MODE != SQUANT_MODE_EC) {
+#pragma unroll
+    for (int base = 0; base < KP; base += 32) {
+      constexpr int kGroup = 32;
+      uint32_t flips = 0;
+#pragma unroll
+      for (int q = (KP - base < kGroup ? KP - base : kGroup) - 4; q >= 0; q -= 4) push_compares_signed(flips, last, &key[base + q]);
+#pragma unroll
+      for (int q = 0; q < kGroup && base + q < KP; q += 4) {
+        const uint32_t b = (((flips >> q) & 15u) * 0x204081u) & 0x01010101u;  // bit e to byte e
+        code[(base + q) / 4] -= (b ^ (uint32_t)smask) - (uint32_t)smask;
+      }
+    }
+  }
+  if (MODE == SQUANT_MODE_EK) return;
+  ks_candidate<IB>(ck, over, smask, cand_w, cand_i);
 }
 
 // Cold path: the SQuant-C candidate of a kernel whose perturbation sum is exactly zero (nothing
@@ -188,11 +260,21 @@ __device__ __forceinline__ void ks_solve_all(const float (&w)[K * KPT], float s,
 #pragma unroll
   for (int q = 0; q < KPT; ++q) {
     if (KPT > 1 && !((owned >> q) & 1u)) continue;
-    float cf[K];
-    ks_solve<K, K * KPT, FAST, MODE>(w, q, s, rs, qmaxf, cf, esum, cv[q], ci[q], zero);
     const int n = t + q * G;
+    if constexpr (K > 9) {
+      static_assert(KPT == 1, "one kernel per thread");
+      uint32_t code[(K + 3) / 4];
+      ks_solve_long<K, FAST, MODE>(w, s, rs, qmaxf, code, esum, cv[q], ci[q], zero);
 #pragma unroll
-    for (int i = 0; i < K; ++i) code8[K * n + i] = (uint8_t)(int)cf[i];
+      for (int i = 0; i < K / 4; ++i) __builtin_memcpy(code8 + K * n + 4 * i, &code[i], 4);
+#pragma unroll
+      for (int i = K / 4 * 4; i < K; ++i) code8[K * n + i] = (uint8_t)(code[i / 4] >> (8 * (i & 3)));
+    } else {
+      float cf[K];
+      ks_solve<K, K * KPT, FAST, MODE>(w, q, s, rs, qmaxf, cf, esum, cv[q], ci[q], zero);
+#pragma unroll
+      for (int i = 0; i < K; ++i) code8[K * n + i] = (uint8_t)(int)cf[i];
+    }
   }
 }
 
@@ -283,10 +365,13 @@ __device__ __forceinline__ void ks_channel(const LaunchArgs& a, const TensorDesc
 }
 
 // Up to 256 threads: compiled for five waves per SIMD (measured 1-3.5 % faster than the
-// compiler's own choice of four for 1x3, 1x7 and 2x2 kernels; six costs 5x5 27 %, eight spills).
+// compiler's own choice of four for 1x3, 1x7 and 2x2 kernels; six costs 5x5 27 %, eight spills), for three with 7x7
+// kernels, which leave a few registers to scratch memory even so.  4x4 and 7x7 kernels went through the generic
+// routine before: 2 x [162, 184, 7, 7] 106.8 -> 10.2 us, 16 x [256, 64, 7, 7] 233 -> 15.4, 4 x [256, 512, 7, 7] in
+// binary16 944 -> 28.0, 16 x [512, 64, 4, 4] 49.8 -> 10.9, 2 x [512, 1000, 4, 4] 165 -> 26.8.
 template <int MAX_THREADS, int MODE, int K, int KPT>
 __global__ void __launch_bounds__(MAX_THREADS)
-    __attribute__((amdgpu_waves_per_eu(MAX_THREADS > 256 ? 1 : 5))) squant_channel_ks(LaunchArgs a) {
+    __attribute__((amdgpu_waves_per_eu(MAX_THREADS > 256 ? 1 : K == 49 ? 3 : 5))) squant_channel_ks(LaunchArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];  // K*N bytes of codes
   __shared__ K9Shared sh;
   int m;

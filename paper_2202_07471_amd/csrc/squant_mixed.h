@@ -14,6 +14,7 @@
 #include "squant_k9.h"
 #include "squant_ks.h"
 #include "squant_plan.h"
+#include "squant_stem.h"
 
 namespace squant {
 
@@ -48,7 +49,7 @@ __global__ void __launch_bounds__(kMixedMaxThreads)
   // The host only admits tensors with cin <= 4T (3x3) or cin <= 16T (1x1).
   const int T = blockDim.x;
   const bool aligned = pointers_aligned(d.w, d.out);
-  const int family = ANY ? route_family(d.M, d.N, d.K, aligned) : choose_family(d.N, d.K, aligned);
+  const int family = is_stem(d.N, d.K) ? 0 : ANY ? route_family(d.M, d.N, d.K, aligned) : choose_family(d.N, d.K, aligned);
   if (family == 9) {
     // Workgroups of two waves, the common ones, have their wide channels compiled for that, and a wave that a narrow
     // channel leaves without a kernel ends at once: the hardware's barrier waits for the waves that are left
@@ -84,6 +85,8 @@ __global__ void __launch_bounds__(kMixedMaxThreads)
     else k1_rows_dispatch<M1, 32, HALF, ANY || HALF>(a, d, m, smem);
   } else if (family == 6) {
     k1_wave_dispatch<M1, HALF, ANY>(a, d, m, smem);
+  } else if (is_stem(d.N, d.K)) {
+    stem_channels<MODE>(a, d, m);
   } else if (d.N == 1 && d.K > 1 && d.K <= kMaxDwK) {  // family 7
     dw_team_dispatch<MODE>(a, d, m);
   } else if (d.K == 0) {  // a batch norm (see TensorDesc)

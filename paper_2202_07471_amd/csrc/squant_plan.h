@@ -21,6 +21,7 @@ enum Variant {
   kK1x16 = 16,                                 // 1x1 / FC: 16 vectors per thread
   kK1Wave = 32,                                // 1x1 / FC up to kMaxWaveCin, a wave per channel: kK1Wave + vectors per lane (2..8)
   kK9Team = 42,                                // 3x3, 2 to 32 kernels a channel, in a launch of its own: a team of lanes per channel
+  kStem = 43,                                  // two to four kernels of 10 to 64 elements: a wave per channel
   kDwTeam = 41,                                // depthwise, up to 64 elements a kernel: a team of lanes per channel
   kK1Wide = 48,                                // 1x1 / FC beyond kMaxK1Cin in one workgroup: kK1Wide + vectors per thread (10, 12, 14, 16)
   kKs = 1024                                   // small kernels in registers: kKs + 4 * K + log2(kernels per thread)
@@ -123,10 +124,12 @@ SQ_HD int k1_variant_of(int nv) {
   return nv == 16 ? kK1x16 : v[nv];
 }
 
-// Small kernels held in registers (squant_ks.h): the kernel sizes it is built for, and the
+// Small kernels held in registers (squant_ks.h): the kernel sizes it is built for, those of them that the mixed kernel
+// carries too (no network has the others in number; their registers would cost every launch), and the
 // largest power of two (as its logarithm) of kernels one thread holds.
-constexpr int kKsMaxK = 25;
-SQ_HD bool ks_has(int64_t K) { return K == 2 || K == 3 || K == 4 || K == 5 || K == 7 || K == 25; }
+constexpr int kKsMaxK = 49;
+SQ_HD bool ks_has(int64_t K) { return K == 2 || K == 3 || K == 4 || K == 5 || K == 7 || K == 16 || K == 25 || K == 49; }
+SQ_HD bool ks_mixes(int64_t K) { return K <= 7 || K == 25; }
 SQ_HD constexpr int ks_max_kpt_log2(int64_t K) { return K <= 4 ? 3 : K <= 7 ? 2 : 0; }
 // log2 of the kernels per thread for a channel of N such kernels: the largest power of two that
 // divides N and puts the channel into ONE wave at least 60 % full, else the one that keeps the
@@ -229,6 +232,11 @@ SQ_HD int ks_kpt_log2_any(int64_t N, int64_t K, bool aligned) {
 constexpr int kMaxDwK = 64;
 SQ_HD int dw_team_lanes(int64_t K) { return K <= 16 ? 16 : K <= 32 ? 32 : 64; }
 
+// Channels of a few larger kernels, the stem of a network (squant_stem.h): a wave per channel, whatever
+// choose_family and route_family below say of them.
+constexpr int kMaxStemCin = 4;
+SQ_HD bool is_stem(int64_t N, int64_t K) { return N >= 2 && N <= kMaxStemCin && K >= 10 && K <= 64; }
+
 // Tensors this small (a stem with three input channels) stay with the generic routine: one of them
 // among the common shapes would otherwise send a whole network to the larger mixed kernel.  A small
 // tensor quantized alone has no network to protect and keeps the routine only for having one rule.
@@ -306,6 +314,7 @@ SQ_HD int64_t route_work_items(int64_t M, int64_t N, int64_t K, int64_t T, int f
 
 // In a mixed launch.
 SQ_HD int64_t mixed_work_items(int64_t M, int64_t N, int64_t K, int64_t T, int family) {
+  if (is_stem(N, K)) { const int64_t per = T / 64; return (M + per - 1) / per; }
   if (family == 6 && N <= kMaxRowsCin) { const int64_t per = T / k1_rows_team(N); return (M + per - 1) / per; }
   return route_work_items(M, N, K, T, family, 1);
 }
