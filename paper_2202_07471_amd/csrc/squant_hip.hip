@@ -403,6 +403,14 @@ int quantize_batched(const squant_tensor_t* h_tensors, int32_t n_tensors, squant
     g->t.push_back(TensorDesc{t.w, t.codes, t.scales, t.cout, t.cin, (int32_t)((int64_t)t.kh * t.kw), 0});
     g->wave_members |= is_k1_wave(p.variant);
   }
+  // A launch ends with its last members, and a wave that solves several 1x1 / FC channels takes longest: a classifier of
+  // such rows, the last layer of its network, goes first (ResNet-18 set 16.4 -> 16.25 us; in two launches that only
+  // lengthens the start of the second: ResNet-18 set of 1.5 times the width 35.6 and 37.0).
+  for (auto& g : groups) {
+    if (g.variant != kMixed || two_classes || g.t.size() < 2) continue;
+    const TensorDesc& last = g.t.back();
+    if (last.K == 1 && last.N > kMaxTeamCin && last.N <= kMaxRowsCin) std::rotate(g.t.begin(), g.t.end() - 1, g.t.end());
+  }
   if (bns && !bns->empty()) {
     for (auto& g : groups) {
       if (g.variant != kMixed && g.variant != kMixedWave) continue;
