@@ -54,9 +54,11 @@ __device__ __forceinline__ uint32_t team_min_u32(uint32_t x) { return ~team_max_
 // Sign (0 or ~0) and number of flips of a channel whose lanes' perturbation sums are `esum`.
 template <int TEAM>
 __device__ __forceinline__ uint32_t k1_rows_flips(int32_t esum, uint32_t& sm) {
-  if (TEAM == 16) {  // at most 511 elements of 2^22: the one that set the scale has none
+  if (TEAM == 16) {
+    // At most 512 elements of 2^22, so the sum wraps only where it is 2^31: every element is on an exact half on the
+    // same side then (a subnormal scale puts the largest there too), and the lanes' sums tell which.
     const int32_t ec = team_sum_i32<TEAM>(esum);
-    sm = (uint32_t)(ec >> 31);
+    sm = (uint32_t)((ec == INT32_MIN ? esum : ec) >> 31);
     return (((uint32_t)ec ^ sm) - sm + (uint32_t)(kHalf - 1)) >> 23;
   }
   const int32_t low = team_sum_i32<TEAM>(esum & 0xFFFF);

@@ -62,16 +62,17 @@ __device__ __forceinline__ uint32_t team_max_u32(uint32_t x) {
   return (uint32_t)v;
 }
 template <int TEAM>
-__device__ __forceinline__ int32_t team_sum_i32(int32_t v) {  // for |sum| < 2^31
-  v += dpp_i32<0xB1>(v);
-  v += dpp_i32<0x4E>(v);
-  if (TEAM >= 8) v += dpp_i32<0x141>(v);
-  if (TEAM >= 16) v += dpp_i32<0x140>(v);
+__device__ __forceinline__ int32_t team_sum_i32(int32_t x) {  // modulo 2^32
+  uint32_t v = (uint32_t)x;
+  v += (uint32_t)dpp_i32<0xB1>((int)v);
+  v += (uint32_t)dpp_i32<0x4E>((int)v);
+  if (TEAM >= 8) v += (uint32_t)dpp_i32<0x141>((int)v);
+  if (TEAM >= 16) v += (uint32_t)dpp_i32<0x140>((int)v);
   if (TEAM >= 32) {
-    const vu2 r = row_pair((uint32_t)v);
-    v = (int)(r.x + r.y);
+    const vu2 r = row_pair(v);
+    v = r.x + r.y;
   }
-  return v;
+  return (int32_t)v;
 }
 
 typedef uint32_t u32_byte __attribute__((aligned(1)));

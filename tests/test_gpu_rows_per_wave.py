@@ -89,3 +89,19 @@ def test_scales_beyond_the_reciprocal_in_one_team_of_a_wave(sq):
         for bits in (2, 4, 8):
             outs, scales = sq.squant_quantize_batched_ex([d, other], bits, sq.MODE_EKC)
             same((outs[0], scales[0]), expected(d, bits, sq.MODE_EKC, sq.OUT_INT8, sq), f"cin={cin} bits={bits}")
+
+
+# Scales of 2 * 2^-149 under which every weight is a half step from a code: each perturbation is 2^22 in units of
+# 2^-23, all of one sign, so 512 of them sum to 2^31 either way.  absmax / qmax rounds to 2 for each multiple.
+@pytest.mark.parametrize("bits, multiples", [(3, (5, 7)), (4, (11, 13)), (5, (23, 27)), (6, (47, 61)), (8, (191, 253))])
+@pytest.mark.parametrize("cin", [511, 512, 1024])
+def test_every_element_on_a_half_step(sq, bits, multiples, cin):
+    lead = np.resize(np.float32([multiples[0], -multiples[0], multiples[1], -multiples[1], 3]), 12290)
+    step = np.uint32(1).view(np.float32)   # 2^-149
+    d = torch.from_numpy(np.repeat((lead * step)[:, None], cin, axis=1).reshape(-1, cin, 1, 1)).cuda()
+    other = torch.from_numpy(np.random.default_rng(cin).standard_normal((8, 40, 3, 3)).astype(np.float32)).cuda()
+    for mode in (sq.MODE_EKC, sq.MODE_EC):
+        want = expected(d, bits, mode, sq.OUT_INT8, sq)
+        same(sq.squant_quantize_ex(d, bits, mode, sq.OUT_INT8), want, f"cin={cin} bits={bits} mode={mode}")
+        outs, scales = sq.squant_quantize_batched_ex([d[:83].contiguous(), other], bits, mode)
+        same((outs[0], scales[0]), (want[0][:83], want[1][:83]), f"mixed cin={cin} bits={bits} mode={mode}")
