@@ -25,6 +25,8 @@ struct TensorDesc {
   int32_t M, N, K;
   int32_t first;  // this tensor's first workgroup within its launch
 };
+// In a mixed launch K holds the family of squant_plan.h as well, above the kernel's elements (at most 2^20).
+constexpr int kFamilyShift = 24;
 
 // The tensor descriptors of a launch travel inside the kernel arguments (10 KB for 256 of
 // them, read with scalar loads); a batch of more tensors takes several launches.

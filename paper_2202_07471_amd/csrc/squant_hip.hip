@@ -100,11 +100,17 @@ int mixed_threads(int own, int64_t N, int top) {
   return own <= 2 * kWave || (N + top - 1) / top > 2 * kWave ? own : 2 * kWave;
 }
 
+// A tensor with its family (squant_plan.h).
+struct Member : TensorDesc {
+  int family;
+  bool any;  // see mixed_needs_any
+};
+
 struct Group {
   int variant;
   int threads;
   size_t lds;
-  std::vector<TensorDesc> t;
+  std::vector<Member> t;
   bool fixed_threads = false;  // mixed launch: a non-generic member has set the workgroup size
   float n_sigma = 0.0f;        // of the batch norms among the members
   int32_t act_levels_minus_1 = 0;
@@ -114,7 +120,7 @@ struct Group {
 // threads / lds: of a launch of the tensor's own variant.  mix_threads: what the tensor needs as
 // a member of a mixed launch (0: it cannot join one), where the per-thread work follows the
 // launch's workgroup size.
-struct Plan { int variant; int threads; size_t lds; int mix_threads; };
+struct Plan { int variant; int threads; size_t lds; int mix_threads; int family = 0; bool any = false; };
 
 inline size_t round_up(size_t v, size_t to) { return (v + to - 1) / to * to; }
 
@@ -124,10 +130,8 @@ Plan stream_plan(int64_t N) {
   return Plan{kStream, th, 16, 0};  // no dynamic LDS; 16 stands for "fits"
 }
 
-// Picks the kernel variant and launch shape for one tensor (every tensor fits one).
-Plan plan_tensor(const void* w, const void* out, int64_t M, int64_t N, int64_t K, int lds_limit) {
-  if (is_stem(N, K)) return Plan{kStem, kWave, 16, kWave};
-  const int variant = route_variant(M, N, K, pointers_aligned(w, out));
+// The launch shape of a kernel variant for one tensor (every tensor fits one).
+Plan plan_variant(int variant, int64_t N, int64_t K, int lds_limit) {
   // LDS: a selection area per wave of the launch's workgroup, added when the launch goes out
   if (is_k1_wave(variant)) return Plan{variant, kK1WaveThreads, 16, kWave};
   if (is_k1_wide(variant)) {  // LDS: the owners' masks, two words per thread
@@ -156,6 +160,7 @@ Plan plan_tensor(const void* w, const void* out, int64_t M, int64_t N, int64_t K
     case kDw9: return Plan{kDw9, kWave, 16, kWave};     // no LDS; 16 stands for "fits"
     case kDwTeam: return Plan{kDwTeam, kWave, 16, kWave};
     case kK1Team: return Plan{kK1Team, kWave, 16, kWave};
+    case kStem: return Plan{kStem, kWave, 16, kWave};
     case kK1Stream: {
       const size_t lds = round_up((size_t)N, 16);  // the channel's int8 codes
       if (lds + sizeof(K9Shared) + 64 > (size_t)lds_limit) return stream_plan(N);
@@ -174,6 +179,16 @@ Plan plan_tensor(const void* w, const void* out, int64_t M, int64_t N, int64_t K
   return Plan{kGeneric, th, lds, th};
 }
 
+// Picks the family, kernel variant and launch shape for one tensor.
+Plan plan_tensor(const void* w, const void* out, int64_t M, int64_t N, int64_t K, int lds_limit) {
+  const bool aligned = pointers_aligned(w, out);
+  const int family = tensor_family(M, N, K, aligned);
+  Plan p = plan_variant(variant_of_family(family, N, K, aligned), N, K, lds_limit);
+  p.family = family;
+  p.any = mixed_needs_any(family, N, K, aligned);
+  return p;
+}
+
 // Whether a tensor may join a launch of the mixed kernel: the mixed kernel carries a routine
 // for it that fits its workgroup size and LDS.
 bool mixable(const Plan& p, size_t lds_cap) {
@@ -182,7 +197,7 @@ bool mixable(const Plan& p, size_t lds_cap) {
 
 // The kernel a tensor of plan p takes in a launch of its own variant: narrow 3x3 channels by teams.
 Plan own_launch(Plan p, int64_t N, int64_t K) {
-  if (K == 9 && N > 1 && N <= kMaxK9TeamCin) return Plan{kK9Team, 4 * kWave, 16, p.mix_threads};
+  if (K == 9 && N > 1 && N <= kMaxK9TeamCin) { p.variant = kK9Team; p.threads = 4 * kWave; p.lds = 16; }
   return p;
 }
 
@@ -197,19 +212,22 @@ int launch_part(const Group& g, bool rows, size_t begin, size_t end, int qmax, i
   a.act_levels_minus_1 = g.act_levels_minus_1;
   int64_t total = 0;
   bool uniform = true;
-  auto items_of = [&](const TensorDesc& t) {
+  bool tail = false;  // 1x1 / FC rows: any that is no whole number of 16-byte vectors
+  bool any = false;   // any off the common channel counts and alignments (mixed: or another small kernel)
+  auto items_of = [&](const Member& t) {
     if (t.K == 0) return (int64_t)1;  // a batch norm
     if (g.variant == kK9Team) { const int per = g.threads / k9_team_lanes(t.N); return (int64_t)(t.M + per - 1) / per; }
-    if (g.variant == kStem) return (int64_t)t.M;  // workgroups of one wave
-    const int family = route_family(t.M, t.N, t.K, pointers_aligned(t.w, t.out));
-    if (mixed) return mixed_work_items(t.M, t.N, t.K, threads, family);
-    return route_work_items(t.M, t.N, t.K, threads, family, wave_span);
+    if (mixed) return mixed_work_items(t.M, t.N, t.K, threads, t.family);
+    return route_work_items(t.M, t.N, t.K, threads, t.family, wave_span);
   };
   const int64_t items0 = items_of(g.t[begin]);
   for (size_t i = begin; i < end; ++i) {
-    const TensorDesc& t = g.t[i];
+    const Member& t = g.t[i];
     const int64_t items = items_of(t);
     a.table[i - begin] = t;
+    if (mixed) a.table[i - begin].K |= t.family << kFamilyShift;
+    tail |= t.N % (wtype == SQUANT_W_F32 ? 4 : 8) != 0;
+    any |= t.any;
     a.table[i - begin].first = a.first[i - begin] = (int32_t)total;  // first workgroup within this launch
     total += items;
     uniform &= items == items0;
@@ -230,16 +248,6 @@ int launch_part(const Group& g, bool rows, size_t begin, size_t end, int qmax, i
   a.wtype = wtype;
   a.wave_span = wave_span;
   const int nv = k1_variant_nv(g.variant);
-  bool tail = false;  // 1x1 / FC rows: any that is no whole number of 16-byte vectors
-  bool any = false;   // any off the common channel counts and alignments (mixed: or another small kernel)
-  for (size_t i = begin; i < end; ++i) {
-    const TensorDesc& t = g.t[i];
-    if (t.K == 0 || is_stem(t.N, t.K)) continue;
-    const bool aligned = pointers_aligned(t.w, t.out);
-    tail |= t.N % (wtype == SQUANT_W_F32 ? 4 : 8) != 0;
-    const int family = route_family(t.M, t.N, t.K, aligned);
-    any |= family != 7 && (family != choose_family(t.N, t.K, aligned) || (family == 5 && !is_ks(g.variant)));
-  }
   const kernel_t kernel = is_ks(g.variant) ? ks_kernel(ks_variant_k(g.variant), ks_variant_kpt(g.variant), g.threads, mode)
                           : mixed ? mixed_kernel(mode, wtype, any)
                           : rows ? k1_rows_kernel(kWave / wave_span, k1_rows_nv(g.t[begin].N), mode, wtype, tail)
@@ -400,7 +408,7 @@ int quantize_batched(const squant_tensor_t* h_tensors, int32_t n_tensors, squant
       }
       g->lds = std::max(g->lds, p.lds);
     }
-    g->t.push_back(TensorDesc{t.w, t.codes, t.scales, t.cout, t.cin, (int32_t)((int64_t)t.kh * t.kw), 0});
+    g->t.push_back(Member{{t.w, t.codes, t.scales, t.cout, t.cin, (int32_t)((int64_t)t.kh * t.kw), 0}, p.family, p.any});
     g->wave_members |= is_k1_wave(p.variant);
   }
   // A launch ends with its last members, and a wave that solves several 1x1 / FC channels takes longest: a classifier of
@@ -417,7 +425,8 @@ int quantize_batched(const squant_tensor_t* h_tensors, int32_t n_tensors, squant
       g.n_sigma = act->n_sigma;
       g.act_levels_minus_1 = (int32_t)((1 << act->bits) - 1);
       for (const BnDesc& b : *bns)
-        g.t.push_back(TensorDesc{b.gamma, act->ranges + b.out_index, const_cast<float*>(b.beta), b.channels, b.relu, 0, 0});
+        g.t.push_back(Member{{b.gamma, act->ranges + b.out_index, const_cast<float*>(b.beta), b.channels, b.relu, 0, 0},
+                             kFamilyBn, false});
       bns->clear();
       break;
     }
@@ -445,7 +454,7 @@ int squant_quantize_ex(const void* d_w, squant_wtype_t wtype, int32_t cout, int3
   const Plan p = own_launch(plan_tensor(d_w, d_out, cout, cin, K, lim.lds_bytes), cin, K);
   if (p.lds == 0) return SQUANT_ERR_UNSUPPORTED;
   Group g{p.variant, p.threads, p.lds, {}};
-  g.t.push_back(TensorDesc{d_w, d_out, d_scales, cout, cin, (int32_t)K, 0});
+  g.t.push_back(Member{{d_w, d_out, d_scales, cout, cin, (int32_t)K, 0}, p.family, p.any});
   g.wave_members = is_k1_wave(p.variant);
   return launch_group(g, (1 << (bits - 1)) - 1, (int)mode, (int)output, (int)wtype,
                       (hipStream_t)stream);

@@ -1,7 +1,10 @@
 // One launch for a set of layers of different shapes (the weight tensors of a network are
 // independent problems, Section 4.2).  Every workgroup finds its tensor and output channel
-// in the descriptor table, picks the tensor's kernel variant the same way the host did and
-// runs that variant's channel routine.  The workgroup size is the largest any member tensor
+// in the descriptor table, where the host has put the tensor's family, and runs that family's
+// channel routine.  A workgroup that evaluates the rules of squant_plan.h itself starts its loads
+// behind a chain of scalar steps, the longer the more rules there are (InceptionV3-style set of 1.4
+// times the width 80.6 us, 74.5 with the family from the host; of twice the width 147 and 138;
+// ResNet-50 set with odd channel counts 22.8 and 21.2; ResNet-18 set 16.3 and 16.05).  The workgroup size is the largest any member tensor
 // needs (at most 256); the routines let surplus threads idle.
 #pragma once
 
@@ -43,13 +46,13 @@ __global__ void __launch_bounds__(kMixedMaxThreads)
                      : (MODE == SQUANT_MODE_EC) ? SQUANT_MODE_EKC : MODE;
   constexpr int kWeights = HALF ? -1 : SQUANT_W_F32;
   int m;
-  const TensorDesc d = locate(a, blockIdx.x, m);
+  TensorDesc d = locate(a, blockIdx.x, m);
+  const int family = d.K >> kFamilyShift;
+  d.K &= (1 << kFamilyShift) - 1;
   // Per-thread work is chosen from the launch's workgroup size T, not from the variant the
   // tensor would get in a launch of its own: as few kernels / vectors per thread as T allows.
   // The host only admits tensors with cin <= 4T (3x3) or cin <= 16T (1x1).
   const int T = blockDim.x;
-  const bool aligned = pointers_aligned(d.w, d.out);
-  const int family = is_stem(d.N, d.K) ? 0 : ANY ? route_family(d.M, d.N, d.K, aligned) : choose_family(d.N, d.K, aligned);
   if (family == 9) {
     // Workgroups of two waves, the common ones, have their wide channels compiled for that, and a wave that a narrow
     // channel leaves without a kernel ends at once: the hardware's barrier waits for the waves that are left
@@ -85,11 +88,11 @@ __global__ void __launch_bounds__(kMixedMaxThreads)
     else k1_rows_dispatch<M1, 32, HALF, ANY || HALF>(a, d, m, smem);
   } else if (family == 6) {
     k1_wave_dispatch<M1, HALF, ANY>(a, d, m, smem);
-  } else if (is_stem(d.N, d.K)) {
+  } else if (family == kFamilyStem) {
     stem_channels<MODE>(a, d, m);
-  } else if (d.N == 1 && d.K > 1 && d.K <= kMaxDwK) {  // family 7
+  } else if (family == 7) {
     dw_team_dispatch<MODE>(a, d, m);
-  } else if (d.K == 0) {  // a batch norm (see TensorDesc)
+  } else if (family == kFamilyBn) {  // (see TensorDesc)
     activation_range(static_cast<const float*>(d.w), d.scales, d.M, d.N != 0, a.n_sigma, a.act_levels_minus_1,
                      static_cast<squant_act_range_t*>(d.out), sh.red_f, reinterpret_cast<float*>(sh.red_i));
   } else {

@@ -1,6 +1,5 @@
-// Which kernel variant a tensor's channels go through.  One function for the host, which
-// sizes the launch from it, and for the mixed kernel, which picks the variant again per
-// workgroup from the tensor's descriptor, so the two cannot disagree.
+// Which kernel variant a tensor's channels go through.  The host decides it once per tensor, sizes the launch
+// by it and hands the mixed kernel the family in the tensor's descriptor.
 #pragma once
 
 #include <stdint.h>
@@ -261,15 +260,21 @@ SQ_HD int route_family(int64_t M, int64_t N, int64_t K, bool aligned) {
   return 0;
 }
 
+// The family a tensor is launched with: stems as well, and, among the members of a mixed launch, batch norms.
+constexpr int kFamilyStem = 8, kFamilyBn = 10;
+SQ_HD int tensor_family(int64_t M, int64_t N, int64_t K, bool aligned) {
+  return is_stem(N, K) ? kFamilyStem : route_family(M, N, K, aligned);
+}
+
 // 3x3 channels of up to 32 kernels in a launch of their own (squant_k9_team.h): lanes per channel.
 // In a mixed launch they keep the workgroup routine: there the launch is as long as its slowest
 // members and the narrow layers are few.
 constexpr int kMaxK9TeamCin = 32;
 SQ_HD int k9_team_lanes(int64_t N) { return N <= 4 ? 4 : N <= 8 ? 8 : N <= 16 ? 16 : 32; }
 
-SQ_HD int route_variant(int64_t M, int64_t N, int64_t K, bool aligned) {
-  const int family = route_family(M, N, K, aligned);
+SQ_HD int variant_of_family(int family, int64_t N, int64_t K, bool aligned) {
   if (family == 7) return kDwTeam;
+  if (family == kFamilyStem) return kStem;
   if (family == choose_family(N, K, aligned)) return choose_variant(N, K, aligned);
   if (family == 9) {  // kernels per thread by the rule of choose_variant
     int best_c = 4;
@@ -291,6 +296,14 @@ SQ_HD int route_variant(int64_t M, int64_t N, int64_t K, bool aligned) {
   }
   return ks_variant(K, ks_kpt_log2_any(N, K, aligned));
 }
+SQ_HD int route_variant(int64_t M, int64_t N, int64_t K, bool aligned) {
+  return variant_of_family(route_family(M, N, K, aligned), N, K, aligned);
+}
+
+// Whether a member of family `family` needs the mixed kernel that carries every routine (ANY in squant_mixed.h).
+SQ_HD bool mixed_needs_any(int family, int64_t N, int64_t K, bool aligned) {
+  return family != 7 && family != kFamilyStem && (family == 5 || family != choose_family(N, K, aligned));
+}
 
 // Lanes that share a short 1x1 channel (see squant_k1_team.h).
 SQ_HD int team_lanes(int64_t N) { return N <= 16 ? 4 : N <= 32 ? 8 : 16; }
@@ -309,12 +322,12 @@ SQ_HD int64_t work_items(int64_t M, int64_t N, int64_t K, int64_t T, int family,
 // The same for every family.
 SQ_HD int64_t route_work_items(int64_t M, int64_t N, int64_t K, int64_t T, int family, int wave_span) {
   if (family == 7) { const int64_t per = T / dw_team_lanes(K); return (M + per - 1) / per; }
+  if (family == kFamilyStem) { const int64_t per = T / 64; return (M + per - 1) / per; }
   return work_items(M, N, K, T, family, wave_span);
 }
 
 // In a mixed launch.
 SQ_HD int64_t mixed_work_items(int64_t M, int64_t N, int64_t K, int64_t T, int family) {
-  if (is_stem(N, K)) { const int64_t per = T / 64; return (M + per - 1) / per; }
   if (family == 6 && N <= kMaxRowsCin) { const int64_t per = T / k1_rows_team(N); return (M + per - 1) / per; }
   return route_work_items(M, N, K, T, family, 1);
 }
