@@ -266,7 +266,7 @@ int launch_part(const Group& g, bool rows, size_t begin, size_t end, int qmax, i
                                                : generic_kernel();
   if (!kernel) return SQUANT_ERR_UNSUPPORTED;
   size_t lds = g.lds;
-  if (rows) lds = (size_t)(threads / kWave) * kK1RowsLds;
+  if (rows) lds = (size_t)(threads / kWave) * (kK1RowsLds + kK1RowsListLds);
   else if (g.wave_members) lds = std::max(lds, (size_t)(threads / kWave) * (mixed ? kK1RowsLds : sizeof(K1WaveSel)));
   if (lds > 48 * 1024) {
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),

@@ -9,9 +9,9 @@
 // elements that flip (squant_k1.h) runs in all teams side by side until the last has its bounds.
 //
 // The elements between the bounds, at most kRowsListCap a team, are ranked in registers: the wave puts its
-// perturbations into LDS (in two halves: 4 KB a wave do not cost a mixed launch any of its waves), every lane
-// picks its candidates from there by index and writes their keys to the team's list, every lane takes one key
-// back, and fifteen rotations of a row compare it with the others.
+// perturbations into LDS (in two halves, 4 KB a wave), every lane picks its candidates from there by index and
+// writes their keys to the team's list, every lane takes one key back, and fifteen rotations of a row compare it
+// with the others.
 #pragma once
 
 #include "squant_k1.h"
@@ -22,13 +22,14 @@ namespace squant {
 
 constexpr int kRowsListCap = 16;  // one key a lane of a row
 
-// A wave's LDS area.
+// A wave's LDS area for its perturbations, and the keys of one team.
 template <int NE>
 struct alignas(16) K1RowsLds {
   static constexpr int kHalf = (NE / 4 + 1) / 2 * 4;  // elements a lane keeps here at a time
   uint32_t b[kHalf * kWave];  // biased perturbations, vector by vector, lane by lane; later bit q of b[lane]: element q flips
-  uint32_t list[kWave / 16][kRowsListCap];  // keys of each team
 };
+typedef uint32_t K1RowsList[kRowsListCap];
+static_assert(kWave / 16 * sizeof(K1RowsList) == kK1RowsListLds, "what the host sizes the launch by");
 
 // Keeps the compiler from moving LDS accesses of a wave across (the LDS handles them in order).
 __device__ __forceinline__ void wave_lds_fence() {
@@ -83,7 +84,7 @@ __device__ __forceinline__ uint32_t k1_rows_at_least(const uint32_t (&B)[NE], ui
 // the lane's channel.
 template <int TEAM, int NE, int VE>
 __device__ __forceinline__ uint32_t k1_rows_select(const uint32_t (&B)[NE], uint32_t sm, uint32_t need, int N,
-                                                   K1RowsLds<NE>& lds) {
+                                                   K1RowsLds<NE>& lds, K1RowsList* lists) {
   constexpr int kIndexBits = TEAM == 16 ? 9 : 10;  // a key is (u - lo) above the index from the end: at most 31 bits
   constexpr uint32_t kIndexMask = (1u << kIndexBits) - 1u;
   constexpr int32_t kWidest = 1 << (31 - kIndexBits);  // widest interval whose keys fit
@@ -192,7 +193,7 @@ __device__ __forceinline__ uint32_t k1_rows_select(const uint32_t (&B)[NE], uint
   const uint32_t incl = team_prefix_sum<TEAM>(count);
   const uint32_t total = (uint32_t)team_sum_i32<TEAM>((int32_t)count);
   constexpr int kHalf = K1RowsLds<NE>::kHalf;
-  uint32_t* put = lds.list[team] + (incl - count);
+  uint32_t* put = lists[team] + (incl - count);
   const uint32_t from = ((kQ23Bias ^ sm) - sm) + (uint32_t)lo;  // B[q] ^ sm = from + (u - lo)
 #pragma unroll
   for (int begin = 0; begin < NE; begin += kHalf) {
@@ -213,7 +214,7 @@ __device__ __forceinline__ uint32_t k1_rows_select(const uint32_t (&B)[NE], uint
   lds.b[lane] = 0;
   wave_lds_fence();
   const int at = lane & 15;  // with 32 lanes a team both rows rank the same list
-  const uint32_t listed = lds.list[team][at];
+  const uint32_t listed = lists[team][at];
   const uint32_t key = (uint32_t)at < total ? listed : 0u;
   uint32_t larger = 0;  // keys are below 2^31: the sign of a difference says which is larger
 #define SQ_ROTATE(I) larger = __builtin_amdgcn_alignbit(larger, key - (uint32_t)dpp_i32<0x120 + I>((int)key), 31)
@@ -275,9 +276,10 @@ __device__ __forceinline__ void k1_rows_emit(const uint32_t (&code)[NE / 4], voi
 // set in its mixed launch 31.5 -> 27.9 us, with odd channel counts 26.5 -> 22.4, in binary16 32.9 -> 28.3.
 // `item`: the workgroup's index within the tensor; each of its waves takes 64 / TEAM channels of N elements,
 // TEAM * (NE - VE) < N <= TEAM * NE.
+// LDS: kK1RowsLds bytes at smem and a list per team at `lists`, for each wave.
 template <int MODE, int TEAM, int NE, int VE, bool HALF, bool TAIL>
 __device__ __forceinline__ void k1_rows_channels(const LaunchArgs& a, const TensorDesc& d, int item,
-                                                 unsigned char* smem) {
+                                                 unsigned char* smem, K1RowsList* lists) {
   constexpr bool kChannelStage = MODE == SQUANT_MODE_EKC || MODE == SQUANT_MODE_EC;
   constexpr int NL = NE / VE, kRows = kWave / TEAM, kBytes = VE * (HALF ? 2 : 4);
   constexpr uint32_t kOutside = 0x40000000u;
@@ -340,7 +342,8 @@ __device__ __forceinline__ void k1_rows_channels(const LaunchArgs& a, const Tens
     uint32_t sm;
     const uint32_t need = umin2(k1_rows_flips<TEAM>(esum, sm), (uint32_t)N);
     if (__ballot(need != 0) != 0ull) {
-      const uint32_t flip = k1_rows_select<TEAM, NE, VE>(B, sm, need, N, *reinterpret_cast<K1RowsLds<NE>*>(smem + wave * kK1RowsLds));
+      K1RowsLds<NE>& lds = *reinterpret_cast<K1RowsLds<NE>*>(smem + wave * kK1RowsLds);
+      const uint32_t flip = k1_rows_select<TEAM, NE, VE>(B, sm, need, N, lds, lists + wave * (kWave / 16));
 #pragma unroll
       for (int i = 0; i < NE / 4; ++i) {
         const uint32_t b = (((flip >> (4 * i)) & 15u) * 0x204081u) & 0x01010101u;  // bit e to byte e
@@ -380,27 +383,29 @@ __device__ __forceinline__ void k1_rows_channels(const LaunchArgs& a, const Tens
 
 // For the mixed kernel.
 template <int MODE, int TEAM, bool HALF, bool TAIL>
-__device__ __forceinline__ void k1_rows_dispatch(const LaunchArgs& a, const TensorDesc& d, int item, unsigned char* smem) {
+__device__ __forceinline__ void k1_rows_dispatch(const LaunchArgs& a, const TensorDesc& d, int item, unsigned char* smem,
+                                                 K1RowsList* lists) {
   if (HALF) {
-    if (k1_rows_nv(d.N) <= 6) k1_rows_channels<MODE, TEAM, 24, 8, true, TAIL>(a, d, item, smem);
-    else k1_rows_channels<MODE, TEAM, 32, 8, true, TAIL>(a, d, item, smem);
+    if (k1_rows_nv(d.N) <= 6) k1_rows_channels<MODE, TEAM, 24, 8, true, TAIL>(a, d, item, smem, lists);
+    else k1_rows_channels<MODE, TEAM, 32, 8, true, TAIL>(a, d, item, smem, lists);
   } else {
     switch (k1_rows_nv(d.N)) {
-      case 5: k1_rows_channels<MODE, TEAM, 20, 4, false, TAIL>(a, d, item, smem); break;
-      case 6: k1_rows_channels<MODE, TEAM, 24, 4, false, TAIL>(a, d, item, smem); break;
-      case 7: k1_rows_channels<MODE, TEAM, 28, 4, false, TAIL>(a, d, item, smem); break;
-      default: k1_rows_channels<MODE, TEAM, 32, 4, false, TAIL>(a, d, item, smem); break;
+      case 5: k1_rows_channels<MODE, TEAM, 20, 4, false, TAIL>(a, d, item, smem, lists); break;
+      case 6: k1_rows_channels<MODE, TEAM, 24, 4, false, TAIL>(a, d, item, smem, lists); break;
+      case 7: k1_rows_channels<MODE, TEAM, 28, 4, false, TAIL>(a, d, item, smem, lists); break;
+      default: k1_rows_channels<MODE, TEAM, 32, 4, false, TAIL>(a, d, item, smem, lists); break;
     }
   }
 }
 
-// One kernel per team size and vector count (four elements each).  LDS: a K1RowsLds per wave.
+// One kernel per team size and vector count (four elements each).  LDS: a K1RowsLds per wave, then the lists.
 template <int MODE, int TEAM, int NV, bool HALF, bool TAIL>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) squant_channel_k1_rows(LaunchArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   int item;
   const TensorDesc d = locate(a, blockIdx.x, item);
-  k1_rows_channels<MODE, TEAM, 4 * NV, k1_ve<NV, HALF>(), HALF, TAIL>(a, d, item, smem);
+  K1RowsList* lists = reinterpret_cast<K1RowsList*>(smem + blockDim.x / kWave * kK1RowsLds);
+  k1_rows_channels<MODE, TEAM, 4 * NV, k1_ve<NV, HALF>(), HALF, TAIL>(a, d, item, smem, lists);
 }
 
 }  // namespace squant

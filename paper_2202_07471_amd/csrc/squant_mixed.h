@@ -4,8 +4,8 @@
 // channel routine.  A workgroup that evaluates the rules of squant_plan.h itself starts its loads
 // behind a chain of scalar steps, the longer the more rules there are (InceptionV3-style set of 1.4
 // times the width 80.6 us, 74.5 with the family from the host; of twice the width 147 and 138;
-// ResNet-50 set with odd channel counts 22.8 and 21.2; ResNet-18 set 16.3 and 16.05).  The workgroup size is the largest any member tensor
-// needs (at most 256); the routines let surplus threads idle.
+// ResNet-50 set with odd channel counts 22.8 and 21.2; ResNet-18 set 16.3 and 16.05).  The workgroup
+// size is the largest any member tensor needs (at most 256); the routines let surplus threads idle.
 #pragma once
 
 #include "squant_act.h"
@@ -39,6 +39,11 @@ __global__ void __launch_bounds__(kMixedMaxThreads)
   // one area for whichever routine the workgroup takes
   constexpr size_t kArea = sizeof(K9Shared) > sizeof(K1Shared) ? sizeof(K9Shared) : sizeof(K1Shared);
   __shared__ __align__(16) unsigned char shared[kArea > sizeof(GenericShared) ? kArea : sizeof(GenericShared)];
+  // The lists of rows of several channels a wave lie here too, with only the perturbations in dynamic LDS.  LDS is
+  // handed out in pieces of 1280 bytes: with the lists there as well, 18 one-wave workgroups fitted a compute unit
+  // instead of the 20 that its registers hold (MobileNetV2 set of twice the width 22.7 us, 22.1 now).
+  static_assert(sizeof(shared) >= (size_t)kMixedMaxThreads / kWave * kK1RowsListLds, "lists of every wave");
+  static_assert((sizeof(shared) + kK1RowsLds + 1279) / 1280 * 1280 * 20 <= 160 * 1024, "20 one-wave workgroups");
   K9Shared& sh = *reinterpret_cast<K9Shared*>(shared);
   GenericShared& gs = *reinterpret_cast<GenericShared*>(shared);
   // one-element kernels: E&K is E and E&C is E&K&C (SQuant-K has nothing to do, Section 3.4)
@@ -84,8 +89,9 @@ __global__ void __launch_bounds__(kMixedMaxThreads)
     ks_dispatch<MODE>(a, d, m, smem, sh);
   } else if (family == 6 && d.N <= kMaxRowsCin) {
     // 16-bit rows come in vectors of eight: a multiple of four may end in half of one
-    if (k1_rows_team(d.N) == 16) k1_rows_dispatch<M1, 16, HALF, ANY || HALF>(a, d, m, smem);
-    else k1_rows_dispatch<M1, 32, HALF, ANY || HALF>(a, d, m, smem);
+    K1RowsList* lists = reinterpret_cast<K1RowsList*>(shared);
+    if (k1_rows_team(d.N) == 16) k1_rows_dispatch<M1, 16, HALF, ANY || HALF>(a, d, m, smem, lists);
+    else k1_rows_dispatch<M1, 32, HALF, ANY || HALF>(a, d, m, smem, lists);
   } else if (family == 6) {
     k1_wave_dispatch<M1, HALF, ANY>(a, d, m, smem);
   } else if (family == kFamilyStem) {

@@ -90,7 +90,7 @@ SQ_HD bool is_k1_wave(int variant) { return variant >= kK1Wave + 2 && variant <=
 // Several 1x1 / FC channels of 257 to 1024 elements per wave (squant_k1_rows.h): lanes per channel and
 // four-element vectors per lane (5 to 8).
 constexpr int kMaxRowsCin = 1024;
-constexpr int kK1RowsLds = 4096 + 256;  // bytes a wave
+constexpr int kK1RowsLds = 4096, kK1RowsListLds = 256;  // LDS bytes a wave: perturbations, ranking lists
 SQ_HD int k1_rows_team(int64_t N) { return N <= 512 ? 16 : 32; }
 SQ_HD int k1_rows_nv(int64_t N) { const int64_t per = 4 * k1_rows_team(N); return (int)((N + per - 1) / per); }
 // Whether a large launch of its own takes that kernel.  Up to 512 elements always (us with a wave per channel and with
