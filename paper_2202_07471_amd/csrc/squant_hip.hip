@@ -115,6 +115,7 @@ struct Group {
   float n_sigma = 0.0f;        // of the batch norms among the members
   int32_t act_levels_minus_1 = 0;
   bool wave_members = false;   // holds wave-per-channel 1x1 tensors: LDS for a selection area per wave
+  bool rows_members = false;   // mixed launch: those of up to kMaxRowsCin elements go several to a wave
 };
 
 // threads / lds: of a launch of the tensor's own variant.  mix_threads: what the tensor needs as
@@ -267,7 +268,7 @@ int launch_part(const Group& g, bool rows, size_t begin, size_t end, int qmax, i
   if (!kernel) return SQUANT_ERR_UNSUPPORTED;
   size_t lds = g.lds;
   if (rows) lds = (size_t)(threads / kWave) * (kK1RowsLds + kK1RowsListLds);
-  else if (g.wave_members) lds = std::max(lds, (size_t)(threads / kWave) * (mixed ? kK1RowsLds : sizeof(K1WaveSel)));
+  else if (g.wave_members) lds = std::max(lds, (size_t)(threads / kWave) * (g.rows_members ? (size_t)kK1RowsLds : sizeof(K1WaveSel)));
   if (lds > 48 * 1024) {
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
@@ -411,13 +412,20 @@ int quantize_batched(const squant_tensor_t* h_tensors, int32_t n_tensors, squant
     g->t.push_back(Member{{t.w, t.codes, t.scales, t.cout, t.cin, (int32_t)((int64_t)t.kh * t.kw), 0}, p.family, p.any});
     g->wave_members |= is_k1_wave(p.variant);
   }
-  // A launch ends with its last members, and a wave that solves several 1x1 / FC channels takes longest: a classifier of
-  // such rows, the last layer of its network, goes first (ResNet-18 set 16.4 -> 16.25 us; in two launches that only
-  // lengthens the start of the second: ResNet-18 set of 1.5 times the width 35.6 and 37.0).
   for (auto& g : groups) {
-    if (g.variant != kMixed || two_classes || g.t.size() < 2) continue;
-    const TensorDesc& last = g.t.back();
-    if (last.K == 1 && last.N > kMaxTeamCin && last.N <= kMaxRowsCin) std::rotate(g.t.begin(), g.t.end() - 1, g.t.end());
+    if (g.variant != kMixed && g.variant != kMixedWave) continue;
+    int64_t channels = 0;
+    for (const auto& t : g.t) channels += mixed_rows_member(t.family, t.N) ? t.M : 0;
+    g.rows_members = mixed_rows_pay(channels);
+    if (!g.rows_members) continue;
+    for (auto& t : g.t)
+      if (mixed_rows_member(t.family, t.N)) t.family = kFamilyRows;
+    // A launch ends with its last members, and waves with several channels take longest: where such members come last
+    // (the classifier of a narrow network) they open the launch instead, if it is the only one (ResNet-50 sets of
+    // 0.4, 0.45 and 0.5 times the width 10.4, 11.7 and 12.7 us without, 10.1, 11.4 and 12.2 with).
+    if (g.variant == kMixed && !two_classes)
+      std::rotate(g.t.begin(), std::find_if(g.t.rbegin(), g.t.rend(), [](const Member& t) { return t.family != kFamilyRows; }).base(),
+                  g.t.end());
   }
   if (bns && !bns->empty()) {
     for (auto& g : groups) {

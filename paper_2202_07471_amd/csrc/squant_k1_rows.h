@@ -16,6 +16,7 @@
 
 #include "squant_k1.h"
 #include "squant_k1_team.h"
+#include "squant_k1_wave.h"  // K1WaveSel
 #include "squant_plan.h"
 
 namespace squant {
@@ -29,6 +30,7 @@ struct alignas(16) K1RowsLds {
   uint32_t b[kHalf * kWave];  // biased perturbations, vector by vector, lane by lane; later bit q of b[lane]: element q flips
 };
 typedef uint32_t K1RowsList[kRowsListCap];
+static_assert(sizeof(K1WaveSel) <= kK1RowsLds, "members of a wave per channel fit beside");
 static_assert(kWave / 16 * sizeof(K1RowsList) == kK1RowsListLds, "what the host sizes the launch by");
 
 // Keeps the compiler from moving LDS accesses of a wave across (the LDS handles them in order).

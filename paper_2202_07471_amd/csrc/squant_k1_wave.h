@@ -62,12 +62,15 @@ __device__ __forceinline__ void k1_wave_item(const LaunchArgs& a, const TensorDe
   k1_wave_channels<MODE, NV, VE, HALF, TAIL, PREFETCH>(a, d, c0, c1, reinterpret_cast<K1WaveSel*>(smem)[wave]);
 }
 
-// For the mixed kernel: vectors per lane from the channel's length, 5 to 8 (shorter ones go by two or four to a
-// wave there: squant_k1_rows.h); without the prefetch, whose registers that kernel does not have.
+// For the mixed kernel: vectors per lane from the channel's length, 2 to 8; without the
+// prefetch, whose registers that kernel does not have.
 template <int MODE, bool HALF, bool TAIL>
 __device__ __forceinline__ void k1_wave_dispatch(const LaunchArgs& a, const TensorDesc& d, int item,
                                                  unsigned char* smem) {
   switch (k1_wave_nv(d.N + 3)) {
+    case 2: k1_wave_item<MODE, 2, 4, HALF, TAIL, false>(a, d, item, smem); break;
+    case 3: k1_wave_item<MODE, 3, 4, HALF, TAIL, false>(a, d, item, smem); break;
+    case 4: k1_wave_item<MODE, 4, 4, HALF, TAIL, false>(a, d, item, smem); break;
     case 5: k1_wave_item<MODE, 5, 4, HALF, TAIL, false>(a, d, item, smem); break;
     case 6: k1_wave_item<MODE, 6, 4, HALF, TAIL, false>(a, d, item, smem); break;
     case 7: k1_wave_item<MODE, 7, 4, HALF, TAIL, false>(a, d, item, smem); break;

@@ -87,7 +87,7 @@ __global__ void __launch_bounds__(kMixedMaxThreads)
     k1_team_dispatch<M1, ANY>(a, d, m);
   } else if (ANY && family == 5) {
     ks_dispatch<MODE>(a, d, m, smem, sh);
-  } else if (family == 6 && d.N <= kMaxRowsCin) {
+  } else if (family == kFamilyRows) {
     // 16-bit rows come in vectors of eight: a multiple of four may end in half of one
     K1RowsList* lists = reinterpret_cast<K1RowsList*>(shared);
     if (k1_rows_team(d.N) == 16) k1_rows_dispatch<M1, 16, HALF, ANY || HALF>(a, d, m, smem, lists);

@@ -260,8 +260,9 @@ SQ_HD int route_family(int64_t M, int64_t N, int64_t K, bool aligned) {
   return 0;
 }
 
-// The family a tensor is launched with: stems as well, and, among the members of a mixed launch, batch norms.
-constexpr int kFamilyStem = 8, kFamilyBn = 10;
+// The family a tensor is launched with: stems as well, and, among the members of a mixed launch, batch norms and
+// 1x1 / FC rows that go several to a wave.
+constexpr int kFamilyStem = 8, kFamilyBn = 10, kFamilyRows = 11;
 SQ_HD int tensor_family(int64_t M, int64_t N, int64_t K, bool aligned) {
   return is_stem(N, K) ? kFamilyStem : route_family(M, N, K, aligned);
 }
@@ -326,9 +327,19 @@ SQ_HD int64_t route_work_items(int64_t M, int64_t N, int64_t K, int64_t T, int f
   return work_items(M, N, K, T, family, wave_span);
 }
 
+// Whether 1x1 / FC members of 257 to 1024 elements with `channels` channels in all go several to a wave in a mixed
+// launch.  That saves instructions but makes a wave's chain longer, which shows where few such waves end a launch.  us
+// with several and with a wave each: ResNet-18 sets of 1.35, 1.6 and 2 times the width (1688 to 2024 channels) 31.6 and
+// 30.9, 41.7 and 40.9, 54.5 and 53.7, InceptionV3-style set of twice the width (1504) 141 and 138, MobileNetV2 sets of 0.7
+// and 0.75 (1893, 1960) 9.1 and 9.0, 8.4 and 8.0; but of 0.85 (2152) 8.4 and 8.8, of 1 (2560) 9.4 and 9.8,
+// InceptionV3-style set (3504) 42.4 and 43.7, ResNet-50 (11648) 28.0 and 31.2.  A ResNet-18 set (1000) takes 16.2 with either.
+constexpr int64_t kMixedRowsMin = 2048;
+SQ_HD bool mixed_rows_member(int family, int64_t N) { return family == 6 && N <= kMaxRowsCin; }
+SQ_HD bool mixed_rows_pay(int64_t channels) { return channels >= kMixedRowsMin; }
+
 // In a mixed launch.
 SQ_HD int64_t mixed_work_items(int64_t M, int64_t N, int64_t K, int64_t T, int family) {
-  if (family == 6 && N <= kMaxRowsCin) { const int64_t per = T / k1_rows_team(N); return (M + per - 1) / per; }
+  if (family == kFamilyRows) { const int64_t per = T / k1_rows_team(N); return (M + per - 1) / per; }
   return route_work_items(M, N, K, T, family, 1);
 }
 

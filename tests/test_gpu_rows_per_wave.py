@@ -91,6 +91,30 @@ def test_scales_beyond_the_reciprocal_in_one_team_of_a_wave(sq):
             same((outs[0], scales[0]), expected(d, bits, sq.MODE_EKC, sq.OUT_INT8, sq), f"cin={cin} bits={bits}")
 
 
+MIXED_ROWS = 2051   # channels from which on a mixed launch solves several a wave, and three teams of the last one
+
+
+@pytest.mark.parametrize("cin", [257, 300, 388, 509, 512, 516, 700, 897, 1022, 1024])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16])
+def test_several_a_wave_in_a_mixed_launch(sq, cin, dtype):
+    rng = np.random.default_rng(cin + 1)
+    other = torch.from_numpy(rng.standard_normal((8, 40, 3, 3)).astype(np.float32)).to(dtype).cuda()
+    longer = torch.from_numpy(rng.standard_normal((9, 1500, 1, 1)).astype(np.float32)).to(dtype).cuda()   # a wave each
+    for bits in (2, 4, 8):
+        kinds = SEARCH + ONE_SIDED
+        part = -(-MIXED_ROWS // len(kinds))
+        w = np.concatenate([rows(k, cin, bits, rng, part) for k in kinds])[:MIXED_ROWS]
+        if dtype == torch.float32:   # scales of their own in the teams of a wave
+            factor = np.resize(np.float32([1, 0, 1e-42, 2.0 ** -70, 1, 2.0 ** 70, 1e-45, 1, 1, 1, 1]), len(w))
+            w = (w * factor.reshape(-1, 1, 1, 1)).astype(np.float32)
+        ws = [other, torch.from_numpy(w).to(dtype).cuda(), longer]
+        for mode in (sq.MODE_EKC, sq.MODE_E):
+            output = sq.OUT_INT4 if bits <= 4 and mode == sq.MODE_EKC else sq.OUT_INT8
+            outs, scales = sq.squant_quantize_batched_ex(ws, bits, mode, output)
+            for what, x, out, s in zip(("3x3", "rows", "longer"), ws, outs, scales):
+                same((out, s), expected(x, bits, mode, output, sq), f"{what} cin={cin} {dtype} bits={bits} mode={mode}")
+
+
 # Scales of 2 * 2^-149 under which every weight is a half step from a code: each perturbation is 2^22 in units of
 # 2^-23, all of one sign, so 512 of them sum to 2^31 either way.  absmax / qmax rounds to 2 for each multiple.
 @pytest.mark.parametrize("bits, multiples", [(3, (5, 7)), (4, (11, 13)), (5, (23, 27)), (6, (47, 61)), (8, (191, 253))])
@@ -103,5 +127,6 @@ def test_every_element_on_a_half_step(sq, bits, multiples, cin):
     for mode in (sq.MODE_EKC, sq.MODE_EC):
         want = expected(d, bits, mode, sq.OUT_INT8, sq)
         same(sq.squant_quantize_ex(d, bits, mode, sq.OUT_INT8), want, f"cin={cin} bits={bits} mode={mode}")
-        outs, scales = sq.squant_quantize_batched_ex([d[:83].contiguous(), other], bits, mode)
-        same((outs[0], scales[0]), (want[0][:83], want[1][:83]), f"mixed cin={cin} bits={bits} mode={mode}")
+        for m in (83, MIXED_ROWS):
+            outs, scales = sq.squant_quantize_batched_ex([d[:m].contiguous(), other], bits, mode)
+            same((outs[0], scales[0]), (want[0][:m], want[1][:m]), f"mixed, {m} of cin={cin} bits={bits} mode={mode}")
