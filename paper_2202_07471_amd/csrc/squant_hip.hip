@@ -172,7 +172,8 @@ Plan plan_variant(int variant, int64_t N, int64_t K, int lds_limit) {
   if (is_ks(variant)) {  // LDS: as for 3x3
     const int64_t kpt = ks_variant_kpt(variant);
     const int th = (int)round_up64((N + kpt - 1) / kpt);
-    return Plan{variant, th, round_up((size_t)K * N + 1, 32), ks_mixes(K) ? mixed_threads(th, N, 1 << ks_max_kpt_log2(K)) : 0};
+    const int mix = ks_mixes(N, K) ? mixed_threads(th, N, 1 << ks_max_kpt_log2(K)) : 0;
+    return Plan{variant, th, round_up((size_t)K * N + 1, 32), mix};
   }
   const size_t lds = generic_lds_bytes(N, K);
   if (lds + kStaticLds > (size_t)lds_limit) return stream_plan(N);

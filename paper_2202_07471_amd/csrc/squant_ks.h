@@ -404,6 +404,7 @@ __device__ __forceinline__ void ks_dispatch(const LaunchArgs& a, const TensorDes
     case 4: ks_channel_fit<MODE, 4>(a, d, m, smem, sh); break;
     case 5: ks_channel_fit<MODE, 5>(a, d, m, smem, sh); break;
     case 7: ks_channel_fit<MODE, 7>(a, d, m, smem, sh); break;
+    case 16: ks_channel_fit<MODE, 16>(a, d, m, smem, sh); break;
     case 25: ks_channel_fit<MODE, 25>(a, d, m, smem, sh); break;
     default: break;  // the host puts no other tensor here
   }

@@ -123,13 +123,16 @@ SQ_HD int k1_variant_of(int nv) {
   return nv == 16 ? kK1x16 : v[nv];
 }
 
-// Small kernels held in registers (squant_ks.h): the kernel sizes it is built for, those of them that the mixed kernel
-// carries too (no network has the others in number; their registers would cost every launch), and the
-// largest power of two (as its logarithm) of kernels one thread holds.
+// Small kernels held in registers (squant_ks.h): the kernel sizes it is built for, and the largest power of two (as its
+// logarithm) of kernels one thread holds.
 constexpr int kKsMaxK = 49;
 SQ_HD bool ks_has(int64_t K) { return K == 2 || K == 3 || K == 4 || K == 5 || K == 7 || K == 16 || K == 25 || K == 49; }
-SQ_HD bool ks_mixes(int64_t K) { return K <= 7 || K == 25; }
 SQ_HD constexpr int ks_max_kpt_log2(int64_t K) { return K <= 4 ? 3 : K <= 7 ? 2 : 0; }
+// Whether the mixed kernel takes channels of N such kernels too.  7x7 kernels need more registers than its five waves
+// per SIMD have.  4x4 ones join up to two waves: DCGAN and patch-discriminator layer sets 25.4 and 25.3 us in a launch per
+// width, 13.0 and 17.0 so, five small layers 10.2 and 7.3; wider ones would split a launch in two (a ResNet-18 set with
+// one 4x4 layer of 256 kernels a channel 22.5 us beside it, 25.8 in it).
+SQ_HD bool ks_mixes(int64_t N, int64_t K) { return K == 16 ? N <= 128 : K <= 25; }
 // log2 of the kernels per thread for a channel of N such kernels: the largest power of two that
 // divides N and puts the channel into ONE wave at least 60 % full, else the one that keeps the
 // waves fullest (measured: a one-wave workgroup wins down to that fill - 1x7 with cin 192 and

@@ -103,3 +103,21 @@ def test_one_kernel_per_thread(sq, k, cin):
     other = torch.from_numpy(rng.standard_normal((8, 40, 3, 3)).astype(np.float32)).to(dtype).cuda()
     outs, scales = sq.squant_quantize_batched_ex([other, w], bits, sq.MODE_EKC)
     check(sq, w, bits, sq.MODE_EKC, outs[1], scales[1], sq.OUT_INT8, what + " in a batch")
+
+
+# 4x4 kernels of up to two waves join a mixed launch, small tensors among them; wider ones and 7x7 get their own
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("cins", [(5, 8, 63, 64), (65, 100, 127, 128), (129, 256, 16, 300)])
+def test_members_of_a_batch(sq, cins, dtype):
+    rng = np.random.default_rng(cins[0])
+    kinds = KINDS if dtype == torch.float32 else KINDS[:-1]
+    for i, kind in enumerate(kinds):
+        bits = (2, 3, 4, 8)[(i + cins[0]) % 4]
+        shapes = [(5, cins[0], 4, 4), (30, cins[1], 4, 4), (9, 40, 3, 3), (5, 8, 7, 7), (3, cins[2], 4, 4), (40, cins[3], 4, 4)]
+        ws = [torch.from_numpy(values(kind, s, bits, rng)).to(dtype).cuda() for s in shapes]
+        ws[1] = at_offset(ws[1], 1)
+        for mode in (sq.MODE_E, sq.MODE_EK, sq.MODE_EKC, sq.MODE_EC):
+            output = (sq.OUT_INT8, sq.OUT_F32, sq.OUT_BF16, sq.OUT_INT4 if bits <= 4 else sq.OUT_INT8)[(i + mode) % 4]
+            outs, scales = sq.squant_quantize_batched_ex(ws, bits, mode, output)
+            for w, out, s in zip(ws, outs, scales):
+                check(sq, w, bits, mode, out, s, output, f"{kind} {tuple(w.shape)} bits={bits} {dtype} mode={mode} output={output}")
