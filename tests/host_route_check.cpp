@@ -17,7 +17,7 @@ static int claims(int v) {
   n += is_k1_wide(v);
   n += k1_variant_nv(v) != 0 && !is_k1_wide(v);
   for (int other : {(int)kGeneric, (int)kK9x1, (int)kK9x2, (int)kK9x4, (int)kK1Stream, (int)kDw9, (int)kK1Team, (int)kStream,
-                    (int)kDwTeam, (int)kK9Team})
+                    (int)kDwTeam, (int)kK9Team, (int)kStem})
     n += v == other;
   return n;
 }
@@ -70,6 +70,40 @@ int main() {
   // the lengths that the GPU tests of the streaming 1x1 kernel and of the one that holds a row in one workgroup use
   for (int64_t N : {65540, 70000, 131072}) bad += route_variant(1, N, 1, true) != kK1Stream;
   for (int64_t N : {36000, 40000, 50000, 65536}) bad += !is_k1_wide(route_variant(1, N, 1, true));
+  // what a tensor is launched with: stems ahead of the routes, everything else as routed; which members the lean mixed
+  // kernel, without small kernels, remainders and odd alignments, may take; the families fit above the kernel size
+  for (int aligned = 0; aligned < 2; ++aligned)
+    for (int64_t K : {1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 16, 25, 49, 63, 64, 65})
+      for (int64_t N = 1; N <= 2100; ++N)
+        for (int64_t M : {1, 61, 1 << 20}) {
+          const int family = tensor_family(M, N, K, aligned != 0), v = variant_of_family(family, N, K, aligned != 0);
+          const bool stem = N >= 2 && N <= 4 && K >= 10 && K <= 64;
+          bad += (family == kFamilyStem) != stem || (v == kStem) != stem || claims(v) != 1;
+          bad += !stem && (family != route_family(M, N, K, aligned != 0) || v != route_variant(M, N, K, aligned != 0));
+          bad += family == kFamilyBn || family == kFamilyRows || family < 0 || family > 127;
+          const bool needs = mixed_needs_any(family, N, K, aligned != 0);
+          bad += family == 5 && !needs;
+          bad += (family == 9 || family == 4 || family == 6 || family == 1) && needs != (N % 4 != 0 || !aligned);
+          bad += (family == kFamilyStem || family == 7 || family == 3) && needs;
+          bad += mixed_rows_member(family, N) != (K == 1 && N > kMaxTeamCin && N <= kMaxRowsCin && family == 6);
+          for (int T : {64, 128, 256}) {
+            const int64_t channels = stem ? T / 64 : family == 6 ? T / 64 : family == 7 ? T / dw_team_lanes(K)
+                                     : family == 4 ? T / team_lanes(N) : family == 3 ? T : 1;
+            bad += mixed_work_items(M, N, K, T, family) != (M + channels - 1) / channels;
+          }
+          if (ks_has(K)) bad += ks_mixes(N, K) != (K <= 7 || K == 25 || (K == 16 && N <= 128));
+        }
+  // several 1x1 / FC channels a wave: the lanes of a team hold the row and the last vector of each may be its end
+  for (int64_t N = kMaxTeamCin + 1; N <= kMaxRowsCin; ++N) {
+    const int64_t team = k1_rows_team(N), nv = k1_rows_nv(N), half = nv <= 6 ? 24 : 32;
+    bad += team != 16 && team != 32;
+    bad += nv < 5 || nv > 8 || team * (4 * nv - 4) >= N || N > team * 4 * nv;
+    bad += team * (half - 8) >= N || N > team * half;
+    for (int T : {64, 128, 256})
+      for (int64_t M : {1, 7, 2051})
+        bad += mixed_work_items(M, N, 1, T, kFamilyRows) != (M + T / team - 1) / (T / team);
+  }
+  bad += mixed_rows_pay(kMixedRowsMin - 1) || !mixed_rows_pay(kMixedRowsMin);
   std::printf("route_mismatches=%ld kept=%ld rerouted=%ld\n", bad, kept, rerouted);
   return bad != 0 || rerouted == 0;
 }

@@ -121,3 +121,17 @@ def test_members_of_a_batch(sq, cins, dtype):
             outs, scales = sq.squant_quantize_batched_ex(ws, bits, mode, output)
             for w, out, s in zip(ws, outs, scales):
                 check(sq, w, bits, mode, out, s, output, f"{kind} {tuple(w.shape)} bits={bits} {dtype} mode={mode} output={output}")
+
+
+@pytest.mark.parametrize("cout", [1, 3, 4, 61, 65])
+@pytest.mark.parametrize("cin, side", [(640, 3), (1000, 3), (700, 1), (4000, 1)])
+def test_stem_in_a_launch_of_wide_workgroups(sq, cout, cin, side):
+    """Three or four channels of a stem share a workgroup, the last of them with fewer."""
+    rng = np.random.default_rng(cout)
+    shapes = [(cout, 3, 7, 7), (10, cin, side, side), (40, 48, 3, 3), (cout, 2, 5, 5), (8, 800, 3, 3)]
+    for kind, bits in (("normal", 4), ("grid", 8), ("one_sided", 3)):
+        ws = [torch.from_numpy(values(kind, (max(s[0], 2), *s[1:]), bits, rng)[:s[0]].copy()).cuda() for s in shapes]
+        for mode in (sq.MODE_E, sq.MODE_EK, sq.MODE_EKC, sq.MODE_EC):
+            outs, scales = sq.squant_quantize_batched_ex(ws, bits, mode)
+            for w, out, s in zip(ws, outs, scales):
+                check(sq, w, bits, mode, out, s, sq.OUT_INT8, f"{kind} {tuple(w.shape)} bits={bits} mode={mode}")
