@@ -304,10 +304,11 @@ int launch_group(const Group& g, int qmax, int mode, int output, int wtype, hipS
     for (const auto& t : g.t) {
       channels += t.M;
       longest = std::max<int64_t>(longest, t.N);
-      rows &= k1_rows_pays(t.N, wtype != SQUANT_W_F32) && k1_rows_nv(t.N) == k1_rows_nv(g.t[0].N) &&
-              k1_rows_team(t.N) == k1_rows_team(g.t[0].N);  // one kernel for all
+      rows &= k1_rows_nv(t.N) == k1_rows_nv(g.t[0].N) && k1_rows_team(t.N) == k1_rows_team(g.t[0].N);  // one kernel for all
     }
-    rows &= channels >= kK1RowsMin;
+    const bool stage = mode == SQUANT_MODE_EKC || mode == SQUANT_MODE_EC;
+    const int out_bits = output == SQUANT_OUT_F32 ? 32 : output == SQUANT_OUT_BF16 ? 16 : output == SQUANT_OUT_INT4 ? 4 : 8;
+    for (const auto& t : g.t) rows = rows && channels >= k1_rows_min(t.N, wtype != SQUANT_W_F32, stage, out_bits);
     if (rows) {
       wave_span = kWave / k1_rows_team(longest);
     } else if (channels >= (int64_t)kK1WaveSpan * 2 * 8192) {

@@ -93,19 +93,40 @@ constexpr int kMaxRowsCin = 1024;
 constexpr int kK1RowsLds = 4096, kK1RowsListLds = 256;  // LDS bytes a wave: perturbations, ranking lists
 SQ_HD int k1_rows_team(int64_t N) { return N <= 512 ? 16 : 32; }
 SQ_HD int k1_rows_nv(int64_t N) { const int64_t per = 4 * k1_rows_team(N); return (int)((N + per - 1) / per); }
-// Whether a large launch of its own takes that kernel.  Up to 512 elements always (us with a wave per channel and with
-// rows: 131 K channels of 512 binary16 58.1 and 45.2, binary32 64.0 and 55.2; 65 K of 300 binary32 32.3 and 22.0).  With
-// two channels to a wave less is left to share; 65 K channels, binary32: 516 38.0 and 31.7, 640 39.7 and 36.7, 768 42.2
-// and 43.9, 1024 53.6 and 57.5, but 777, no whole number of vectors, 56.5 and 46.1, 1001 60.4 and 58.8; binary16: 516
-// 37.8 and 40.0, 700 39.5 and 41.4, 1024 44.1 and 44.9, 772 52.7 and 47.3, 1001 51.6 and 48.8.
-SQ_HD bool k1_rows_pays(int64_t N, bool half) {
-  if (N <= 512) return true;
-  if (N > kMaxRowsCin) return false;
-  return half ? N > 768 && N % 8 != 0 : N <= 640 || N % 4 != 0;
+// Channels from which on a launch of its own takes that kernel (kNoRows: never).  stage: SQuant-C runs; out_bits: of an
+// output element, 4 to 32.  Sharing a wave saves vector instructions, most of them SQuant-C's, but a row then moves in
+// pieces of a quarter or half the length: where much is written or little computed, and where rows end inside a cache
+// line, that costs more.  us with a wave a channel and with rows, 60 K channels where no other number stands:
+//   codes, SQuant-C   binary32 320 34.4 and 22.0, 512 35.0 and 29.8, 640 39.0 and 34.5, 777 53.9 and 44.6, but 1002 with 12 K
+//                     15.4 and 15.7; aligned beyond 640 no gain (1024 53.6 and 57.5); binary16 512 31.6 and 24.6, 1002 with
+//                     16 K 17.2 and 17.5, 950 with 60 K 12 % less, and up to 768 or in whole vectors no gain
+//   bfloat16 output   binary32 448 15 % less, 500 8 % more, 512 with 16 K 3 % more, 777 12 % less, 1002 2 % more;
+//                     binary16 512 15 % less, beyond 768 -5 to 7 %
+//   binary32 output   binary32 384 7 % less, 415 7 % more, 511 27 % more; binary16 320 1 % less, 333 6 and 512 50 % more
+//   SQuant-E alone    binary32 codes 384 3 % less, 480 7 and 511 22 % more; to bfloat16 320 6 % less, 333 17 % more;
+//                     binary16 codes 512 13 % less, 950 7 % less, 1002 12 % more (4-bit 7 % less); to bfloat16 448 7 % less,
+//                     480 5 % more, 500 4 % less; to binary32 in either type up to 50 % more
+// With few channels the chip holds a wave for each and the longer chain of a wave with several shows: binary32 to int8
+// 320 with 12 K 9.7 and 9.0, 448 10.3 and 10.6, with 16 K 12.0 and 11.4; 512 10.3 and 11.2, 12.1 and 12.1.
+constexpr int64_t kNoRows = INT64_MAX;
+SQ_HD int64_t k1_rows_min(int64_t N, bool half, bool stage, int out_bits) {
+  const bool codes = out_bits <= 8;
+  if (N <= 512) {  // four channels a wave
+    const int64_t longest = stage ? (codes || (half && out_bits == 16) ? 512 : out_bits == 16 ? 448 : half ? 320 : 384)
+                            : out_bits == 32 ? 0 : half ? 512 : codes ? 384 : 320;
+    if (N > longest) return kNoRows;
+    if (!stage && out_bits == 16 && (half ? N > 448 && N % 8 == 0 : N % 4 != 0)) return kNoRows;
+    return N <= 384 && out_bits != 16 ? 12288 : 16384;
+  }
+  if (N > kMaxRowsCin) return kNoRows;
+  if (half) {
+    if (N <= 768 || N % 8 == 0 || !codes) return kNoRows;
+    return stage || out_bits == 4 || N <= 960 ? 24576 : kNoRows;
+  }
+  if (!stage || (N > 640 && N % 4 == 0) || out_bits == 32) return kNoRows;
+  if (out_bits == 16) return N <= 896 ? 24576 : kNoRows;
+  return N <= 896 ? 12288 : 24576;
 }
-// Channels a launch must have for it: with fewer the chip holds a wave for each, and the longer chain of a wave with
-// several shows (8192 channels of 512: 7.7 us with a wave each, 8.6; of 300: 7.4 and 7.4; 16384: 11.9 and 11.5).
-constexpr int64_t kK1RowsMin = 12288;
 
 // 16-byte vectors per thread of a 1x1 / FC variant (0: not one), and back.
 SQ_HD bool is_k1_wide(int variant) { return variant > kK1Wide && variant <= kK1Wide + 16; }

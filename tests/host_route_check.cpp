@@ -103,6 +103,21 @@ int main() {
       for (int64_t M : {1, 7, 2051})
         bad += mixed_work_items(M, N, 1, T, kFamilyRows) != (M + T / team - 1) / (T / team);
   }
+  // and in a launch of their own: only where a kernel is built for them
+  long several = 0;
+  for (int64_t N = 1; N <= 3000; ++N)
+    for (int half = 0; half < 2; ++half)
+      for (int stage = 0; stage < 2; ++stage)
+        for (int out_bits : {4, 8, 16, 32}) {
+          const int64_t least = k1_rows_min(N, half != 0, stage != 0, out_bits);
+          if (N <= kMaxTeamCin) continue;  // these go by teams whatever it says
+          if (least == kNoRows) continue;
+          ++several;
+          bad += N > kMaxRowsCin || least < 8192;
+          const int64_t team = k1_rows_team(N), nv = k1_rows_nv(N);
+          bad += half ? team == 32 && nv <= 6 : !stage && (team != 16 || nv > 6);
+        }
+  bad += several == 0;
   bad += mixed_rows_pay(kMixedRowsMin - 1) || !mixed_rows_pay(kMixedRowsMin);
   std::printf("route_mismatches=%ld kept=%ld rerouted=%ld\n", bad, kept, rerouted);
   return bad != 0 || rerouted == 0;

@@ -115,12 +115,39 @@ def test_several_a_wave_in_a_mixed_launch(sq, cin, dtype):
                 same((out, s), expected(x, bits, mode, output, sq), f"{what} cin={cin} {dtype} bits={bits} mode={mode}")
 
 
+# every kernel of a launch of its own that takes several rows a wave, with the fewest channels it is chosen for (and
+# two more: teams of the last wave have no channel)
+@pytest.mark.parametrize("dtype, mode, cin, m, outputs", [
+    ("float32", "EKC", 257, 12290, "int8 int4 f32"), ("float32", "EKC", 320, 16386, "int4 bf16 f32"),
+    ("float32", "EC", 381, 16386, "int8 bf16 f32"), ("float32", "EKC", 448, 16386, "int8 bf16"),
+    ("float32", "EKC", 449, 16386, "int4"), ("float32", "EC", 512, 16386, "int8"),
+    ("float32", "EKC", 513, 12290, "int4"), ("float32", "EC", 640, 24578, "int8 bf16"),
+    ("float32", "EKC", 767, 12290, "int8"), ("float32", "EKC", 895, 24578, "int4 bf16"),
+    ("float32", "EKC", 1022, 24578, "int8"), ("float32", "E", 320, 16386, "int8 int4 bf16"),
+    ("float32", "E", 381, 12290, "int8"),
+    ("float16", "EKC", 257, 12290, "int4 f32"), ("bfloat16", "EC", 384, 16386, "int8 bf16"),
+    ("float16", "EKC", 509, 16386, "int4 bf16"), ("bfloat16", "EKC", 512, 16386, "int8 bf16"),
+    ("bfloat16", "EKC", 771, 24578, "int8 int4"), ("float16", "EC", 1023, 24578, "int4"),
+    ("bfloat16", "E", 383, 16386, "int8 bf16"), ("float16", "E", 511, 16386, "int4 bf16"),
+    ("float16", "E", 777, 24578, "int8"), ("bfloat16", "E", 1021, 24578, "int4")])
+def test_launch_of_its_own(sq, dtype, mode, cin, m, outputs):
+    rng = np.random.default_rng(cin + m)
+    kinds = SEARCH + ONE_SIDED
+    part = -(-m // len(kinds))
+    for output in outputs.split():
+        bits = {"int4": 4, "int8": 8, "f32": 3, "bf16": 2}[output]
+        w = np.concatenate([rows(k, cin, bits, rng, part) for k in kinds])[:m]
+        d = torch.from_numpy(w).to(getattr(torch, dtype)).cuda()
+        got = sq.squant_quantize_ex(d, bits, sq.MODES[mode], sq.OUTPUTS[output])
+        same(got, expected(d, bits, sq.MODES[mode], sq.OUTPUTS[output], sq), f"cin={cin} {dtype} mode={mode} output={output}")
+
+
 # Scales of 2 * 2^-149 under which every weight is a half step from a code: each perturbation is 2^22 in units of
 # 2^-23, all of one sign, so 512 of them sum to 2^31 either way.  absmax / qmax rounds to 2 for each multiple.
 @pytest.mark.parametrize("bits, multiples", [(3, (5, 7)), (4, (11, 13)), (5, (23, 27)), (6, (47, 61)), (8, (191, 253))])
 @pytest.mark.parametrize("cin", [511, 512, 1024])
 def test_every_element_on_a_half_step(sq, bits, multiples, cin):
-    lead = np.resize(np.float32([multiples[0], -multiples[0], multiples[1], -multiples[1], 3]), 12290)
+    lead = np.resize(np.float32([multiples[0], -multiples[0], multiples[1], -multiples[1], 3]), 16386)
     step = np.uint32(1).view(np.float32)   # 2^-149
     d = torch.from_numpy(np.repeat((lead * step)[:, None], cin, axis=1).reshape(-1, cin, 1, 1)).cuda()
     other = torch.from_numpy(np.random.default_rng(cin).standard_normal((8, 40, 3, 3)).astype(np.float32)).cuda()
