@@ -19,12 +19,54 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
   return __float_as_uint(wave_max_dpp(__uint_as_float(v)));  // compares the bits as integers
 }
 
+// SQuant-E alone knows no kernels: the channel's elements side by side, at most four a lane.  A lane per element of a kernel
+// left 48 of 64 idle with 4x4 kernels (200 K channels of [3, 4, 4]: 57.2 us, 50.0 through the generic routine).
+__device__ __forceinline__ void stem_round_channel(const LaunchArgs& a, const TensorDesc& d, int m) {
+  constexpr int kMost = kMaxStemCin;  // kernels of up to 64 elements
+  const int lane = (int)(threadIdx.x & (kWave - 1)), L = d.N * d.K;
+  const float qmaxf = (float)a.qmax;
+  const size_t base = (size_t)m * L;
+  float w[kMost], amax = 0.0f;
+#pragma unroll
+  for (int i = 0; i < kMost; ++i) {
+    const int e = lane + i * kWave;
+    w[i] = e < L ? load_weight(d.w, base + e, a.wtype) : 0.0f;
+  }
+#pragma unroll
+  for (int i = 0; i < kMost; ++i) amax = fmaxf(amax, fabsf(w[i]));
+  amax = wave_max_dpp(amax);
+  const float s = amax > 0.0f ? amax / qmaxf : 1.0f;
+  if (lane == 0) d.scales[m] = s;
+#pragma unroll
+  for (int i = 0; i < kMost; ++i) {
+    if (i * kWave >= L) break;
+    const int e = lane + i * kWave;
+    int32_t P;
+    const int code = round_and_perturb(w[i], s, qmaxf, P);  // past the channel: 0
+    if (a.out_format == SQUANT_OUT_INT4) {
+      // even elements store their own nibble and the next one's, which is the next lane's
+      const uint32_t next = (uint32_t)dpp_i32<0xB1>(code);
+      if (e < L && (e & 1) == 0)
+        static_cast<uint8_t*>(d.out)[(size_t)m * ((L + 1) / 2) + e / 2] = (uint8_t)((code & 15) | ((next & 15u) << 4));
+    } else if (e >= L) {
+      continue;
+    } else if (a.out_format == SQUANT_OUT_INT8) {
+      static_cast<int8_t*>(d.out)[base + e] = (int8_t)code;
+    } else if (a.out_format == SQUANT_OUT_BF16) {
+      static_cast<uint16_t*>(d.out)[base + e] = (uint16_t)bf16_bits((float)code * s);
+    } else {  // SQUANT_OUT_F32
+      static_cast<float*>(d.out)[base + e] = (float)code * s;
+    }
+  }
+}
+
 // `item` is the workgroup's index within the tensor: one channel a wave.
 template <int MODE>
 __device__ __forceinline__ void stem_channels(const LaunchArgs& a, const TensorDesc& d, int item) {
   constexpr bool kChannelStage = MODE == SQUANT_MODE_EKC || MODE == SQUANT_MODE_EC;
   const int m = item * ((int)blockDim.x / kWave) + __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
   if (m >= d.M) return;  // no step of the workgroup follows
+  if constexpr (MODE == SQUANT_MODE_E) return stem_round_channel(a, d, m);
   const int lane = (int)(threadIdx.x & (kWave - 1)), K = d.K, N = d.N;
   const bool in = lane < K;
   const float qmaxf = (float)a.qmax;
