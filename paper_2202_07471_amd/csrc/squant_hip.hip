@@ -191,6 +191,11 @@ Plan plan_tensor(const void* w, const void* out, int64_t M, int64_t N, int64_t K
   return p;
 }
 
+bool has_channel_stage(int mode) { return mode == SQUANT_MODE_EKC || mode == SQUANT_MODE_EC; }
+int output_bits(int output) {
+  return output == SQUANT_OUT_F32 ? 32 : output == SQUANT_OUT_BF16 ? 16 : output == SQUANT_OUT_INT4 ? 4 : 8;
+}
+
 // Whether a tensor may join a launch of the mixed kernel: the mixed kernel carries a routine
 // for it that fits its workgroup size and LDS.
 bool mixable(const Plan& p, size_t lds_cap) {
@@ -306,9 +311,8 @@ int launch_group(const Group& g, int qmax, int mode, int output, int wtype, hipS
       longest = std::max<int64_t>(longest, t.N);
       rows &= k1_rows_nv(t.N) == k1_rows_nv(g.t[0].N) && k1_rows_team(t.N) == k1_rows_team(g.t[0].N);  // one kernel for all
     }
-    const bool stage = mode == SQUANT_MODE_EKC || mode == SQUANT_MODE_EC;
-    const int out_bits = output == SQUANT_OUT_F32 ? 32 : output == SQUANT_OUT_BF16 ? 16 : output == SQUANT_OUT_INT4 ? 4 : 8;
-    for (const auto& t : g.t) rows = rows && channels >= k1_rows_min(t.N, wtype != SQUANT_W_F32, stage, out_bits);
+    for (const auto& t : g.t)
+      rows = rows && channels >= k1_rows_min(t.N, wtype != SQUANT_W_F32, has_channel_stage(mode), output_bits(output));
     if (rows) {
       wave_span = kWave / k1_rows_team(longest);
     } else if (channels >= (int64_t)kK1WaveSpan * 2 * 8192) {
@@ -418,7 +422,7 @@ int quantize_batched(const squant_tensor_t* h_tensors, int32_t n_tensors, squant
     if (g.variant != kMixed && g.variant != kMixedWave) continue;
     int64_t channels = 0;
     for (const auto& t : g.t) channels += mixed_rows_member(t.family, t.N) ? t.M : 0;
-    g.rows_members = mixed_rows_pay(channels);
+    g.rows_members = mixed_rows_pay(channels, wtype != SQUANT_W_F32, has_channel_stage((int)mode), output_bits((int)output));
     if (!g.rows_members) continue;
     for (auto& t : g.t)
       if (mixed_rows_member(t.family, t.N)) t.family = kFamilyRows;

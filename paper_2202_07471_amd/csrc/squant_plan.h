@@ -357,9 +357,17 @@ SQ_HD int64_t route_work_items(int64_t M, int64_t N, int64_t K, int64_t T, int f
 // 30.9, 41.7 and 40.9, 54.5 and 53.7, InceptionV3-style set of twice the width (1504) 141 and 138, MobileNetV2 sets of 0.7
 // and 0.75 (1893, 1960) 9.1 and 9.0, 8.4 and 8.0; but of 0.85 (2152) 8.4 and 8.8, of 1 (2560) 9.4 and 9.8,
 // InceptionV3-style set (3504) 42.4 and 43.7, ResNet-50 (11648) 28.0 and 31.2.  A ResNet-18 set (1000) takes 16.2 with either.
+// Rows of a shared wave are written in shorter pieces, which binary32 output shows: with SQuant-C where there is much of it
+// (ResNet-50 sets from bfloat16, of 1.5 times the width, 22080 channels, 82.6 and 83.3, of 1.9 times, 27960, 138 and 127), with
+// SQuant-E alone throughout from 16 bits (ResNet-50 32.5 and 28.3) and from binary32 but for the middle (MobileNetV2 set of 1.9
+// times the width, 8795, 20.5 and 21.4; InceptionV3-style set of half the width, 3944, 15.7 and 13.3; ResNet-50 of 1.9 133 and 128).
 constexpr int64_t kMixedRowsMin = 2048;
 SQ_HD bool mixed_rows_member(int family, int64_t N) { return family == 6 && N <= kMaxRowsCin; }
-SQ_HD bool mixed_rows_pay(int64_t channels) { return channels >= kMixedRowsMin; }
+SQ_HD bool mixed_rows_pay(int64_t channels, bool half, bool stage, int out_bits) {
+  if (out_bits < 32) return channels >= kMixedRowsMin;
+  if (stage) return channels >= kMixedRowsMin && channels < 24576;
+  return !half && channels >= 8192 && channels < 20480;
+}
 
 // In a mixed launch.
 SQ_HD int64_t mixed_work_items(int64_t M, int64_t N, int64_t K, int64_t T, int family) {

@@ -118,7 +118,15 @@ int main() {
           bad += half ? team == 32 && nv <= 6 : !stage && (team != 16 || nv > 6);
         }
   bad += several == 0;
-  bad += mixed_rows_pay(kMixedRowsMin - 1) || !mixed_rows_pay(kMixedRowsMin);
+  for (int half = 0; half < 2; ++half)
+    for (int stage = 0; stage < 2; ++stage) {
+      for (int out_bits : {4, 8, 16, 32}) bad += mixed_rows_pay(kMixedRowsMin - 1, half != 0, stage != 0, out_bits);
+      for (int out_bits : {4, 8, 16})
+        for (int64_t channels : {2048, 8192, 30000}) bad += !mixed_rows_pay(channels, half != 0, stage != 0, out_bits);
+      bad += mixed_rows_pay(2048, half != 0, stage != 0, 32) != (stage != 0);
+      bad += mixed_rows_pay(8192, half != 0, stage != 0, 32) != (stage != 0 || half == 0);
+      bad += mixed_rows_pay(24576, half != 0, stage != 0, 32);
+    }
   std::printf("route_mismatches=%ld kept=%ld rerouted=%ld\n", bad, kept, rerouted);
   return bad != 0 || rerouted == 0;
 }
