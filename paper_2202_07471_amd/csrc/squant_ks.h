@@ -67,6 +67,35 @@ __device__ __forceinline__ void ks_load_kernel16(float (&w)[NW], int q, rsrc_t r
   }
 }
 
+// Bits of a key's index tie-break.
+template <int K>
+constexpr int ks_index_bits() { return K <= 16 ? 4 : K <= 32 ? 5 : 6; }
+
+// The k-th largest key (0x7fffffff: k = 0) and the one of rank `want`, by the keys in descending order as far as any
+// kernel of the wave needs them (k is rarely above three): with keys within 2^30 of each other, key - m wraps to a huge
+// number for the keys below m and to a small one for the others, so the largest difference names the next key.
+// 1.5 instructions an element and step; all pairs of 25 elements took 900 and spilled.  FENCED: eight at a time, for registers.
+template <int K, bool FENCED, int KP>
+__device__ __forceinline__ void ks_step_keys(const int32_t (&key)[KP], int32_t k, int32_t want, int32_t& last, int32_t& ck) {
+  int32_t m = key[0];
+#pragma unroll
+  for (int i = 1; i < K; ++i) m = imax2(m, key[i]);
+  last = 0x7fffffff;
+#pragma unroll 1
+  for (int32_t rank = 0;; ++rank) {
+    if (rank == k - 1) last = m;
+    if (rank == want) ck = m;
+    if (__ballot(rank < want) == 0ull) break;
+    uint32_t z = 0;
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      z = umax2(z, (uint32_t)key[i] - (uint32_t)m);
+      if (FENCED && i % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+    }
+    m = (int32_t)((uint32_t)m + z);
+  }
+}
+
 // The Algorithm 3 candidate from its key: the word and the element index.
 template <int IB>
 __device__ __forceinline__ void ks_candidate(int32_t ck, bool over, int32_t smask, uint32_t& cand_w, int& cand_i) {
@@ -78,13 +107,13 @@ __device__ __forceinline__ void ks_candidate(int32_t ck, bool over, int32_t smas
   cand_i = IM - (ck & IM);
 }
 
-// SQuant-E, SQuant-K and the candidate update for one kernel of up to nine elements held in registers
-// (straight-line code, as for 3x3).  Arguments as for k9_solve.
+// SQuant-E, SQuant-K and the candidate update for one kernel held in registers (straight-line code, as
+// for 3x3).  Arguments as for k9_solve.
 template <int K, int NW, bool FAST, int MODE>
 __device__ __forceinline__ void ks_solve(const float (&w)[NW], int q, float s, float rs, float qmaxf,
                                          float (&cf)[K], int32_t& esum, uint32_t& cand_w,
                                          int& cand_i, uint32_t& zero) {
-  constexpr int IB = 4, IM = (1 << IB) - 1;  // bits of the index tie-break
+  constexpr int IB = ks_index_bits<K>(), IM = (1 << IB) - 1;
   const int W0 = K * q;
   float c[K];
   int32_t P[K];
@@ -125,35 +154,47 @@ __device__ __forceinline__ void ks_solve(const float (&w)[NW], int q, float s, f
   const int32_t want = over ? k - 1 : k;  // the candidate's rank: last flipped resp. first un-flipped (k <= K/2 < K)
   const float flip = smask ? 129.0f : 127.0f;  // code -= sign(E)
   int32_t ck = 0;  // the candidate's key
-  // rank = #{larger keys}, by all pairs
-  int32_t rank[K];
+  if constexpr (K <= 9) {
+    // rank = #{larger keys}, by all pairs
+    int32_t rank[K];
 #pragma unroll
-  for (int i = 0; i < K; ++i) rank[i] = i;  // i counts the pairs (j < i), corrected below
+    for (int i = 0; i < K; ++i) rank[i] = i;  // i counts the pairs (j < i), corrected below
 #pragma unroll
-  for (int i = 0; i < K; ++i)
+    for (int i = 0; i < K; ++i)
 #pragma unroll
-    for (int j = i + 1; j < K; ++j) {
-      const int32_t gt = key[j] > key[i] ? 1 : 0;
-      rank[i] += gt;
-      rank[j] -= gt;
-    }
+      for (int j = i + 1; j < K; ++j) {
+        const int32_t gt = key[j] > key[i] ? 1 : 0;
+        rank[i] += gt;
+        rank[j] -= gt;
+      }
 #pragma unroll
-  for (int i = 0; i < K; ++i) cf[i] = c[i] + (rank[i] < k ? flip : 128.0f);
-  if (MODE == SQUANT_MODE_EK) return;
+    for (int i = 0; i < K; ++i) cf[i] = c[i] + (rank[i] < k ? flip : 128.0f);
+    if (MODE == SQUANT_MODE_EK) return;
 #pragma unroll
-  for (int i = 0; i < K; ++i) ck |= rank[i] == want ? key[i] : 0;
+    for (int i = 0; i < K; ++i) ck |= rank[i] == want ? key[i] : 0;
+  } else {
+    int32_t last;
+    ks_step_keys<K, false>(key, k, want, last, ck);
+#pragma unroll
+    for (int i = 0; i < K; ++i) cf[i] = c[i] + (key[i] >= last ? flip : 128.0f);
+    if (MODE == SQUANT_MODE_EK) return;
+  }
 
   // ---- perturbation update (Algorithm 3): the kernel's candidate for SQuant-C ----
   ks_candidate<IB>(ck, over, smask, cand_w, cand_i);
 }
 
 // The same for one kernel of more elements, one per thread.  Its perturbations take the place of the weights and its
-// codes + 128 are packed as they come (`code`), so a 7x7 kernel lives in 75 registers.
+// codes + 128 are packed as they come (`code`), so a 7x7 kernel lives in 75 registers.  5x5 kernels take it where SQuant-K
+// flips nothing: 4 x [512, 300, 5, 5] in binary16 24.7 us above and 19.9 here with E&C, 12.1 and 11.4 with E, but [512, 200, 5, 5]
+// 14.7 and 15.4 with E&K&C, 12.7 and 13.0 with E&K.
+template <int K, int MODE>
+constexpr bool ks_packed() { return K > 25 || K == 16 || (K == 25 && (MODE == SQUANT_MODE_E || MODE == SQUANT_MODE_EC)); }
 template <int K, bool FAST, int MODE>
 __device__ __forceinline__ void ks_solve_long(const float (&w)[K], float s, float rs, float qmaxf,
                                               uint32_t (&code)[(K + 3) / 4], int32_t& esum, uint32_t& cand_w, int& cand_i,
                                               uint32_t& zero) {
-  constexpr int IB = K <= 16 ? 4 : K <= 32 ? 5 : 6, IM = (1 << IB) - 1;  // bits of the index tie-break
+  constexpr int IB = ks_index_bits<K>(), IM = (1 << IB) - 1;
   constexpr int KP = (K + 3) / 4 * 4;
   int32_t key[KP];  // first the perturbations
   uint32_t tb[KP];
@@ -197,28 +238,13 @@ __device__ __forceinline__ void ks_solve_long(const float (&w)[K], float s, floa
   for (int i = 0; i < KP; ++i) key[i] = i < K ? __mul24(key[i], smask ? -(1 << IB) : (1 << IB)) + (IM - i) : INT32_MIN / 4;
   const bool over = r < 0;
   const int32_t want = over ? k - 1 : k;  // the candidate's rank: last flipped resp. first un-flipped (k <= K/2 < K)
-  // The keys in descending order, as far as any kernel of the wave needs them (k is rarely above
-  // three): with keys within 2^30 of each other, key - m wraps to a huge number for the keys
-  // below m and to a small one for the others, so the largest difference names the next key.
-  // 1.5 instructions an element and step; all pairs of 25 elements took 900 and spilled.
-  int32_t ck = 0, m = key[0];
+  int32_t ck = 0, last;
+  if (MODE == SQUANT_MODE_EC) {  // nothing flips: the candidate is the largest
+    ck = key[0];
 #pragma unroll
-  for (int i = 1; i < K; ++i) m = imax2(m, key[i]);
-  int32_t last = 0x7fffffff;  // the k-th largest key
-#pragma unroll 1
-  for (int32_t rank = 0;; ++rank) {
-    if (rank == k - 1) last = m;
-    if (rank == want) ck = m;
-    if (__ballot(rank < want) == 0ull) break;
-    uint32_t z = 0;
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      z = umax2(z, (uint32_t)key[i] - (uint32_t)m);
-      if (i % 8 == 7) __builtin_amdgcn_sched_barrier(0);
-    }
-    m = (int32_t)((uint32_t)m + z);
-  }
-  if (MODE != SQUANT_MODE_EC) {
+    for (int i = 1; i < K; ++i) ck = imax2(ck, key[i]);
+  } else {
+    ks_step_keys<K, true>(key, k, want, last, ck);
 #pragma unroll
     for (int base = 0; base < KP; base += 32) {
       constexpr int kGroup = 32;
@@ -261,7 +287,7 @@ __device__ __forceinline__ void ks_solve_all(const float (&w)[K * KPT], float s,
   for (int q = 0; q < KPT; ++q) {
     if (KPT > 1 && !((owned >> q) & 1u)) continue;
     const int n = t + q * G;
-    if constexpr (K > 9) {
+    if constexpr (ks_packed<K, MODE>()) {
       static_assert(KPT == 1, "one kernel per thread");
       uint32_t code[(K + 3) / 4];
       ks_solve_long<K, FAST, MODE>(w, s, rs, qmaxf, code, esum, cv[q], ci[q], zero);
