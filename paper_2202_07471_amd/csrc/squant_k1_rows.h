@@ -274,8 +274,9 @@ __device__ __forceinline__ void k1_rows_emit(const uint32_t (&code)[NE / 4], voi
 }
 
 // Vector instructions a channel of 512 binary16 weights, a wave per channel and here: 256 and 206; scalar ones 181 and 39.
-// 131 K such channels: 58.1 -> 45.2 us (2.6 -> 4.5 TB/s; SIMDs issue vector instructions 85 % of the time); the ResNet-50
-// set in its mixed launch 31.5 -> 27.9 us, with odd channel counts 26.5 -> 22.4, in binary16 32.9 -> 28.3.
+// 131 K such channels to int8: 58.2 -> 45.3 us (3.5 -> 4.4 TB/s; SIMDs issue vector instructions 85 % of the time); the
+// ResNet-50 set in its mixed launch 31.2 us with a wave a channel, 27.5 here, with odd channel counts 24.8 and 21.2.
+// Where it is taken: k1_rows_min and mixed_rows_pay in squant_plan.h.
 // `item`: the workgroup's index within the tensor; each of its waves takes 64 / TEAM channels of N elements,
 // TEAM * (NE - VE) < N <= TEAM * NE.
 // LDS: kK1RowsLds bytes at smem and a list per team at `lists`, for each wave.

@@ -393,8 +393,8 @@ __device__ __forceinline__ void ks_channel(const LaunchArgs& a, const TensorDesc
 // Up to 256 threads: compiled for five waves per SIMD (measured 1-3.5 % faster than the
 // compiler's own choice of four for 1x3, 1x7 and 2x2 kernels; six costs 5x5 27 %, eight spills), for three with 7x7
 // kernels, which leave a few registers to scratch memory even so.  4x4 and 7x7 kernels went through the generic
-// routine before: 2 x [162, 184, 7, 7] 106.8 -> 10.2 us, 16 x [256, 64, 7, 7] 233 -> 15.4, 4 x [256, 512, 7, 7] in
-// binary16 944 -> 28.0, 16 x [512, 64, 4, 4] 49.8 -> 10.9, 2 x [512, 1000, 4, 4] 165 -> 26.8.
+// routine before: 2 x [162, 184, 7, 7] 106 -> 10.2 us, 16 x [256, 64, 7, 7] 234 -> 16.0, 4 x [256, 512, 7, 7] in
+// binary16 941 -> 30, 16 x [512, 64, 4, 4] 49.9 -> 11.1, 2 x [512, 1000, 4, 4] 129 -> 22.3, all to int8.
 template <int MAX_THREADS, int MODE, int K, int KPT>
 __global__ void __launch_bounds__(MAX_THREADS)
     __attribute__((amdgpu_waves_per_eu(MAX_THREADS > 256 ? 1 : K == 49 ? 3 : 5))) squant_channel_ks(LaunchArgs a) {

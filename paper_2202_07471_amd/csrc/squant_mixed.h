@@ -31,7 +31,7 @@ namespace squant {
 // the first time on each compute unit, and the time followed the place the linker gave the kernel, which
 // any change to a kernel before it moves (the same code on the ResNet-18 set: 16.4 us at offset 0x5400 of
 // its 64 KB, 16.7 at 0x2800, 17.05 at 0x4c00).  On 64 KB the kernels before it no longer matter; changes
-// inside it still move that time between 16.3 and 16.7.
+// inside it still move that time by 2 to 3 % (ResNet-18 sets of 1.1 to 1.35 times the width likewise).
 template <int MODE, bool HALF, bool ANY>
 __global__ void __launch_bounds__(kMixedMaxThreads)
     __attribute__((amdgpu_waves_per_eu(5), aligned(65536))) squant_channel_mixed(LaunchArgs a) {
@@ -61,7 +61,7 @@ __global__ void __launch_bounds__(kMixedMaxThreads)
   if (family == 9) {
     // Workgroups of two waves, the common ones, have their wide channels compiled for that, and a wave that a narrow
     // channel leaves without a kernel ends at once: the hardware's barrier waits for the waves that are left
-    // (ResNet-18 set 16.8 -> 16.3 us).
+    // (ResNet-18 set 16.5 to 16.9 us without the two, 16.1 to 16.3 with).
     if (d.N <= kWave) {
       if (__builtin_amdgcn_readfirstlane((int)threadIdx.x) >= kWave) return;
       k9_channel<MODE, 1, kWeights, 1, ANY>(a, d, m, smem, sh);

@@ -260,9 +260,10 @@ SQ_HD int dw_team_lanes(int64_t K) { return K <= 16 ? 16 : K <= 32 ? 32 : 64; }
 constexpr int kMaxStemCin = 4;
 SQ_HD bool is_stem(int64_t N, int64_t K) { return N >= 2 && N <= kMaxStemCin && K >= 10 && K <= 64; }
 
-// Tensors this small (a stem with three input channels) stay with the generic routine: one of them
-// among the common shapes would otherwise send a whole network to the larger mixed kernel.  A small
-// tensor quantized alone has no network to protect and keeps the routine only for having one rule.
+// Tensors this small off the common shapes (a narrow layer with an odd channel count) stay with the generic
+// routine: one of them among the common shapes would otherwise send a whole network to the larger mixed
+// kernel.  A small tensor quantized alone has no network to protect and keeps the routine only for having
+// one rule.  Stems are no part of this, whatever their size.
 constexpr int64_t kSmallTensor = 16384;
 
 // choose_family with those shapes, 7 = depthwise with a team of lanes per channel: 3x3 up to kMaxK9Cin, other small kernels, one-element rows
