@@ -1,7 +1,9 @@
 """GPU parity for the kernel that gives four (two) 1x1 / FC channels of 257 to 512 (1024) elements to a
 wave: every count of vectors a lane holds, rows that end inside a vector, channel counts that leave
 teams of the last wave without a channel, and values whose search ends in each of its ways, in the large
-launches that take the kernel by themselves and as members of a mixed launch."""
+launches that take the kernel by themselves (test_launch_of_its_own; the other lengths and outputs of
+test_large_launch take a wave per channel) and as members of a mixed launch (from MIXED_ROWS channels on; fewer
+take a wave each)."""
 import numpy as np
 import pytest
 
