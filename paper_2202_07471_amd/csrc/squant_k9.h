@@ -61,6 +61,7 @@ __device__ __forceinline__ uint32_t pack_low_bytes(uint32_t a, uint32_t b, uint3
 // scheduled in.
 typedef uint64_t lanemask_t;
 __device__ __forceinline__ lanemask_t lanes_uge(uint32_t a, uint32_t b) { return __builtin_amdgcn_uicmp(a, b, 35); }
+__device__ __forceinline__ lanemask_t lanes_eq(uint32_t a, uint32_t b) { return __builtin_amdgcn_uicmp(a, b, 32); }
 __device__ __forceinline__ lanemask_t lanes_slt(int32_t a, int32_t b) { return __builtin_amdgcn_sicmp(a, b, 40); }
 __device__ __forceinline__ lanemask_t lanes_sge(int32_t a, int32_t b) { return __builtin_amdgcn_sicmp(a, b, 39); }
 __device__ __forceinline__ uint32_t vsel(lanemask_t m, uint32_t if_set, uint32_t if_clear) {
@@ -103,19 +104,41 @@ __device__ __forceinline__ void k9_round(const float* w, float s, float rs, floa
   kk.d2 = tb[8];
 }
 
+// The sign a kernel whose perturbations add up to 0 exactly takes (all ones: negative).  Nothing is masked in
+// such a kernel (Algorithm 3 on a sum of 0): its candidate is the largest |p| of either sign, lowest index first,
+// and flipping it moves the element against its own sign.  So the sign of that element stands in for the sum's,
+// and the largest key of that side is the candidate.
+__device__ __forceinline__ uint32_t k9_zero_sum_sign(const uint32_t (&pb)[9]) {
+  int32_t pos = 0, neg = 0;  // 32 |p| + (31 - index) of the largest on each side
+#pragma unroll
+  for (int i = 0; i < 9; ++i) {
+    const int32_t p = (int32_t)(pb[i] - kQ23Bias) << 5;
+    pos = imax2(pos, p + (31 - i));
+    neg = imax2(neg, (31 - i) - p);
+  }
+  return neg > pos ? ~0u : 0u;
+}
+
 // SQuant-K and the perturbation update for one kernel (Algorithm 2 on the kernel,
 // Algorithm 3): the flip mask, the sign, the candidate; esum += the kernel's Q23
-// perturbation sum after SQuant-K; returns |sum before SQuant-K| (0: the candidate of such
-// a kernel is worked out separately, see k9_recheck_kernel).
+// perturbation sum after SQuant-K.  real: the lanes that hold a kernel; the others (zeros) are kept
+// from the work on sums of 0, which is rare otherwise: one kernel in 800 with bfloat16 weights, in
+// 25 thousand with binary16, next to none with binary32.  (Such candidates were worked out from the weights in memory
+// before, one load after the other, in a loop over the thread's kernels: 64 x [512, 512, 3, 3] bfloat16 to 4 bit
+// 107 -> 101.6 us, 4 x [255, 248, 3, 3] binary16 10.2 -> 6.6, ResNet-18 set in bfloat16 17.9 -> 14.5.)
 template <int MODE>
-__device__ __forceinline__ uint32_t k9_flip(const uint32_t (&pb)[9], K9Kernel& kk, int32_t& esum) {
+__device__ __forceinline__ void k9_flip(const uint32_t (&pb)[9], K9Kernel& kk, int32_t& esum, lanemask_t real) {
   constexpr bool kCand = MODE == SQUANT_MODE_EKC || MODE == SQUANT_MODE_EC;
   uint32_t eb = 0;
 #pragma unroll
   for (int i = 0; i < 9; ++i) eb += pb[i];
   const int32_t E = (int32_t)(eb - 9u * kQ23Bias);
-  const uint32_t sm = (uint32_t)(E >> 31);  // all ones when the sum is negative
+  uint32_t sm = (uint32_t)(E >> 31);  // all ones when the sum is negative
   const uint32_t A = ((uint32_t)E ^ sm) - sm;  // |E|
+  if (kCand) {
+    const lanemask_t zero = lanes_eq(A, 0u) & real;
+    if (__builtin_expect(zero != 0, 0)) sm = vsel(zero, k9_zero_sum_sign(pb), sm);
+  }
   kk.sm = sm;
 
   // unique keys, larger = flips earlier.  For a positive sum (pb << 5) = base + 32 P, for a
@@ -136,7 +159,7 @@ __device__ __forceinline__ uint32_t k9_flip(const uint32_t (&pb)[9], K9Kernel& k
     const int32_t rel = (int32_t)(ck - base);
     kk.cand = vsel(lanes_sge(rel, 32), ((uint32_t)rel >> 5) | (sm & (1u << 23)), kNoCandidate);
     kk.cand_bit = 0x80000000u >> (ck & 31u);
-    return A;
+    return;
   }
 
   const uint32_t tt = A + (uint32_t)(kHalf - 1);  // k = tt >> 23 (an exact half rounds down)
@@ -170,7 +193,7 @@ __device__ __forceinline__ uint32_t k9_flip(const uint32_t (&pb)[9], K9Kernel& k
     }
   }
   kk.flips = flips;
-  if (!kCand) return A;
+  if (!kCand) return;
 
   // ---- perturbation update (Algorithm 3): the kernel's candidate for SQuant-C ----
   const lanemask_t over = lanes_slt(r, 0);
@@ -183,7 +206,6 @@ __device__ __forceinline__ uint32_t k9_flip(const uint32_t (&pb)[9], K9Kernel& k
   const uint32_t word = vsel(over, ((2u << 23) - sbit) - mag, mag | sbit);
   kk.cand = vsel(lanes_sge(rel, 32), word, kNoCandidate);
   kk.cand_bit = 0x80000000u >> (ck & 31u);
-  return A;
 }
 
 // Moves the elements named by the flip mask one step against the kernel's sign: on the
@@ -194,35 +216,6 @@ __device__ __forceinline__ void k9_apply_flips(K9Kernel& kk) {
   kk.d0 -= (b0 ^ kk.sm) - kk.sm;
   kk.d1 -= (b1 ^ kk.sm) - kk.sm;
   kk.d2 -= (b2 ^ kk.sm) - kk.sm;
-}
-
-// Cold path (a rolled loop) for a thread that saw a kernel whose perturbation sum is exactly zero.  Nothing
-// is masked in such a kernel: its candidate is the largest |p| of either sign, lowest index
-// first.  It has k = 0, so its perturbations are those of plain rounding and are recomputed
-// here from the weights in memory; returns (sum is zero, candidate perturbation, element index).
-__device__ __forceinline__ int3 k9_recheck_kernel(const void* w, size_t first, int wtype, float s, float qmaxf) {
-  int32_t best = 0, bv = 0, sum = 0;
-  int bi = 0;
-#pragma unroll 1
-  for (int i = 0; i < 9; ++i) {
-    float x = quotient(load_weight(w, first + i, wtype), s);
-    x = fminf(fmaxf(x, -qmaxf), qmaxf);
-    const float p = rintf(x) - x;
-    const int32_t P = __float2int_rn(p * 8388608.0f);
-    const int32_t ap = P < 0 ? -P : P;
-    sum += P;
-    if (ap > best) { best = ap; bv = P; bi = i; }
-  }
-  return make_int3(sum == 0 ? 1 : 0, bv, bi);
-}
-
-// The candidate of a zero-sum kernel into the kernel's record: flipping it moves the element
-// against its own sign, so that sign becomes the kernel's (the flip mask is empty, so the
-// sign has had no other use).
-__device__ __forceinline__ void k9_set_zero_sum_candidate(K9Kernel& kk, int32_t v, int index) {
-  kk.cand = candidate_word(v);
-  kk.cand_bit = 1u << index;
-  kk.sm = v < 0 ? ~0u : 0u;
 }
 
 // Kernel q of a thread: nine floats at `base` (uniform, the channel's kernels q*G ...)
@@ -251,14 +244,21 @@ __device__ __forceinline__ void k9_load_kernel_row(float (&w)[NW], int q, rsrc_t
 
 // The same for 16-bit weights (binary16 or bfloat16): nine half-words, 16 bytes and two, at any
 // half-word (five aligned dwords shifted into place cost ten vector instructions a kernel more).
-template <int NW>
-__device__ __forceinline__ void k9_load_kernel16(float (&w)[NW], int q, rsrc_t row, uint32_t lane_off, uint32_t off,
-                                                 bool bf16) {
-  const vu4 v = buffer_load_u4(row, lane_off, off);
-  const uint32_t last = buffer_load_u16(row, lane_off + 16u, off);
+// All kernels of a thread are asked for before the first is widened: with the type decided kernel by
+// kernel, the loads of the next one waited for the last (4 x [255, 248, 3, 3] binary16 to int8
+// 11.6 us, binary32 6.5).
+struct K9Raw16 { vu4 head; uint32_t last; };
+__device__ __forceinline__ K9Raw16 k9_load_kernel16(rsrc_t row, uint32_t lane_off, uint32_t off) {
+  return {buffer_load_u4(row, lane_off, off), buffer_load_u16(row, lane_off + 16u, off)};
+}
+template <bool BF16, int KPT>
+__device__ __forceinline__ void k9_widen16(const K9Raw16 (&raw)[KPT], float (&w)[9 * KPT]) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) widen_pair(v[j], bf16, w[9 * q + 2 * j], w[9 * q + 2 * j + 1]);
-  w[9 * q + 8] = bf16 ? widen_bf16(last) : widen_f16(last);
+  for (int q = 0; q < KPT; ++q) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) widen_pair(raw[q].head[j], BF16, w[9 * q + 2 * j], w[9 * q + 2 * j + 1]);
+    w[9 * q + 8] = BF16 ? widen_bf16(raw[q].last) : widen_f16(raw[q].last);
+  }
 }
 
 // Sum over the wave of values with |v| <= 2^25 (the 16 lanes of a row add up to at most 2^29).
@@ -378,11 +378,11 @@ __device__ __forceinline__ void k9_channel_flip(K9Kernel (&kk)[KPT], int64_t ec,
 // SQuant-E and SQuant-K on all the kernels of a thread.
 //   PRESCALE  the weights are first multiplied by the powers of two f1 and f2 (and s, rs are
 //             those of the scaled channel): see k9_channel
-//   owned     bit q: the thread has a kernel q (others hold zeros and leave no trace)
+//   real      lanes that have a kernel q of their own (others hold zeros and leave no trace)
 template <int MODE, int KPT, bool PRESCALE, bool CLAMP>
 __device__ __forceinline__ void k9_solve_all(const float (&w)[9 * KPT], float s, float rs, float qmaxf,
                                              float f1, float f2, K9Kernel (&kk)[KPT], int32_t& esum,
-                                             uint32_t& amin, uint32_t owned = ~0u) {
+                                             const lanemask_t (&real)[KPT]) {
 #pragma unroll
   for (int q = 0; q < KPT; ++q) {
     // A branch that is always taken (s is finite) but that the compiler cannot fold: it makes
@@ -400,17 +400,19 @@ __device__ __forceinline__ void k9_solve_all(const float (&w)[9 * KPT], float s,
     uint32_t pb[9];
     k9_round<true, CLAMP>(x, s, rs, qmaxf, kk[q], pb);
     if (MODE != SQUANT_MODE_E) {
-      const uint32_t sum = k9_flip<MODE>(pb, kk[q], esum);
-      amin = umin2(amin, (owned >> q) & 1u ? sum : ~0u);
+      k9_flip<MODE>(pb, kk[q], esum, real[q]);
       if (MODE == SQUANT_MODE_EK) k9_apply_flips(kk[q]);
     }
   }
 }
 
+constexpr int kWHalf = 3;
+
 // One workgroup per output channel.  Thread t owns the KPT 3x3 kernels t, t + G, t + 2G, ...
 // (G = cin / KPT); KPT is 4 for wide layers and 2 or 1 for narrow ones, so that the waves
 // stay full.
-//   WT   the weight type when it is known at compile time (squant_wtype_t), -1: the launch's
+//   WT   the weight type when it is known at compile time (squant_wtype_t; kWHalf: one of the
+//        16-bit types), -1: the launch's
 //   NWC  the waves per workgroup when known at compile time, 0: the launch's
 //   ANY  any cin and any alignment: G = ceil(cin / KPT), the kernels past the channel's end read
 //        as zeros through the range of the row's descriptor, and the row is written through one.
@@ -420,7 +422,7 @@ __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc
                                            unsigned char* smem, K9Shared& sh) {
   constexpr bool kChannelStage = MODE == SQUANT_MODE_EKC || MODE == SQUANT_MODE_EC;
   const int T = NWC ? NWC * kWave : (int)blockDim.x, tid = threadIdx.x;
-  const int wtype = WT >= 0 ? WT : a.wtype;
+  const int wtype = WT == kWHalf ? (a.wtype == SQUANT_W_BF16 ? SQUANT_W_BF16 : SQUANT_W_F16) : WT >= 0 ? WT : a.wtype;
   const float qmaxf = (float)a.qmax;
   uint8_t* code8 = reinterpret_cast<uint8_t*>(smem);  // biased codes: code + 128
 
@@ -442,11 +444,15 @@ __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc
     const uint32_t each = wtype == SQUANT_W_F32 ? 36u : 18u;  // bytes of a kernel
     const rsrc_t row = make_rsrc(static_cast<const uint8_t*>(d.w) + (size_t)m * N * each, each * (uint32_t)N);
     const uint32_t lane_off = active ? each * (uint32_t)tid : 0x40000000u;  // idle threads: out of range
-    const bool bf16 = wtype == SQUANT_W_BF16;
+    if (wtype == SQUANT_W_F32) {
 #pragma unroll
-    for (int q = 0; q < KPT; ++q) {
-      if (wtype == SQUANT_W_F32) k9_load_kernel_row(w, q, row, lane_off, each * (uint32_t)(q * G));
-      else k9_load_kernel16(w, q, row, lane_off, each * (uint32_t)(q * G), bf16);
+      for (int q = 0; q < KPT; ++q) k9_load_kernel_row(w, q, row, lane_off, each * (uint32_t)(q * G));
+    } else {
+      K9Raw16 raw[KPT];
+#pragma unroll
+      for (int q = 0; q < KPT; ++q) raw[q] = k9_load_kernel16(row, lane_off, each * (uint32_t)(q * G));
+      if (wtype == SQUANT_W_BF16) k9_widen16<true>(raw, w);
+      else k9_widen16<false>(raw, w);
     }
   }
   if (kChannelStage) k9_select_reset<NWC>(sh.sel);  // before the first barrier
@@ -462,7 +468,9 @@ __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc
 
   K9Kernel kk[KPT];
   int32_t esum = 0;
-  uint32_t amin = ~0u;  // smallest |kernel sum| of this thread: 0 flags an exact-zero kernel
+  lanemask_t real[KPT];
+#pragma unroll
+  for (int q = 0; q < KPT; ++q) real[q] = ANY ? __ballot((owned >> q) & 1u) : wtype == SQUANT_W_F32 ? ~0ull : __ballot(active);
   // The quotients w / s go through the reciprocal of s, which is proven exact while nothing
   // under- or overflows on the way: absmax within [2^-60, 2^60].  A channel outside that range
   // is first scaled by a power of two, weights and scale alike (exact, and the quotients are
@@ -474,25 +482,17 @@ __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc
   if (normal) {
     const float rs = reciprocal(s);
     // the largest quotient of the channel: no element needs the clamp unless this one does
-    if (div_by_reciprocal(amax, s, rs) <= qmaxf) k9_solve_all<MODE, KPT, false, false>(w, s, rs, qmaxf, 1.0f, 1.0f, kk, esum, amin, ANY ? owned : ~0u);
-    else k9_solve_all<MODE, KPT, false, true>(w, s, rs, qmaxf, 1.0f, 1.0f, kk, esum, amin, ANY ? owned : ~0u);
+    if (div_by_reciprocal(amax, s, rs) <= qmaxf) k9_solve_all<MODE, KPT, false, false>(w, s, rs, qmaxf, 1.0f, 1.0f, kk, esum, real);
+    else k9_solve_all<MODE, KPT, false, true>(w, s, rs, qmaxf, 1.0f, 1.0f, kk, esum, real);
   } else {
     const float f1 = amax < 1.0f ? 0x1p64f : 0x1p-64f;
     const float a1 = amax * f1;
     const float f2 = a1 < 0x1p-60f ? 0x1p64f : a1 > 0x1p60f ? 0x1p-64f : 1.0f;
     const float s2 = s > 0.0f ? s * f1 * f2 : 0x1p-40f;
-    k9_solve_all<MODE, KPT, true, true>(w, s2, reciprocal(s2), qmaxf, f1, f2, kk, esum, amin, ANY ? owned : ~0u);
+    k9_solve_all<MODE, KPT, true, true>(w, s2, reciprocal(s2), qmaxf, f1, f2, kk, esum, real);
   }
 
   if (kChannelStage) {
-    if (amin == 0u && active) {
-#pragma unroll
-      for (int q = 0; q < KPT; ++q) {
-        if (ANY && !((owned >> q) & 1u)) continue;
-        const int3 z = k9_recheck_kernel(d.w, (size_t)m * L + 9 * (t + q * G), wtype, s, qmaxf);
-        if (z.x) k9_set_zero_sum_candidate(kk[q], z.y, z.z);
-      }
-    }
     // candidates into the histogram before the wanted sign is known: one barrier then
     // publishes the partial sums and the histogram
     if (active) {
@@ -571,7 +571,7 @@ __device__ __forceinline__ void dw9_channels(const LaunchArgs& a, const TensorDe
   k9_round<false>(w, s, 0.0f, qmaxf, kk, pb);
   if (MODE != SQUANT_MODE_E) {
     int32_t esum = 0;
-    k9_flip<KM>(pb, kk, esum);
+    k9_flip<KM>(pb, kk, esum, 0ull);  // a sum of 0 flips nothing here
     if (MODE == SQUANT_MODE_EC) {
       // the channel is this kernel: its candidate has the sign of the sum (none if the sum is 0)
       const int32_t mag = esum < 0 ? -esum : esum;

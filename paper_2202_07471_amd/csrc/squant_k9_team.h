@@ -53,8 +53,13 @@ __device__ __forceinline__ void k9_team_channels(const LaunchArgs& a, const Tens
     const uint32_t each = a.wtype == SQUANT_W_F32 ? 36u : 18u;
     const rsrc_t range = make_rsrc(static_cast<const uint8_t*>(d.w) + (size_t)first * N * each, each * (uint32_t)(rows * N));
     const uint32_t at = live ? each * (uint32_t)(r * N + n) : 0x40000000u;
-    if (a.wtype == SQUANT_W_F32) k9_load_kernel_row(w, 0, range, at, 0);
-    else k9_load_kernel16(w, 0, range, at, 0, a.wtype == SQUANT_W_BF16);
+    if (a.wtype == SQUANT_W_F32) {
+      k9_load_kernel_row(w, 0, range, at, 0);
+    } else {
+      const K9Raw16 raw[1] = {k9_load_kernel16(range, at, 0)};
+      if (a.wtype == SQUANT_W_BF16) k9_widen16<true>(raw, w);
+      else k9_widen16<false>(raw, w);
+    }
   }
   float amax = 0.0f;
 #pragma unroll
@@ -71,12 +76,8 @@ __device__ __forceinline__ void k9_team_channels(const LaunchArgs& a, const Tens
   else k9_round<false>(w, s, 0.0f, qmaxf, kk, pb);
   if (MODE != SQUANT_MODE_E) {
     int32_t esum = 0;
-    const uint32_t sum = k9_flip<MODE>(pb, kk, esum);
+    k9_flip<MODE>(pb, kk, esum, __ballot(live));
     if (kChannelStage) {
-      if (live && sum == 0u) {
-        const int3 z = k9_recheck_kernel(d.w, 9 * ((size_t)(first + r) * N + n), a.wtype, s, qmaxf);
-        if (z.x) k9_set_zero_sum_candidate(kk, z.y, z.z);
-      }
       const int32_t ec = k9_team_sum<TEAM>(esum);  // lanes without a kernel: 0
       const int32_t smask = ec >> 31;
       const int32_t mag = (ec ^ smask) - smask;

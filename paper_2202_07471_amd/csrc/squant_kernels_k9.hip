@@ -24,12 +24,12 @@ kernel_t k9_kernel(int kpt, int threads, int mode, int wtype, bool any) {
    squant_channel_k9<256, SQUANT_MODE_EKC, 4, WT, NWC>, squant_channel_k9<256, SQUANT_MODE_EC, 4, WT, NWC>}
   static const kernel_t k9x4_two_waves[3][4] = {SQ_K9_ROW_X(SQUANT_W_F32, 2), SQ_K9_ROW_X(SQUANT_W_F16, 2),
                                                 SQ_K9_ROW_X(SQUANT_W_BF16, 2)};
-  static const kernel_t k9x4_one_wave[4] = SQ_K9_ROW_X(SQUANT_W_F32, 1);
+  static const kernel_t k9x4_one_wave[2][4] = {SQ_K9_ROW_X(SQUANT_W_F32, 1), SQ_K9_ROW_X(kWHalf, 1)};
 #undef SQ_K9_ROW_X
   if (kpt == 1) return k9x1[mode];
   if (kpt == 2) return k9x2[mode];
   if (threads == 2 * kWave) return k9x4_two_waves[wtype][mode];
-  if (threads == kWave && wtype == SQUANT_W_F32) return k9x4_one_wave[mode];
+  if (threads == kWave) return k9x4_one_wave[wtype != SQUANT_W_F32][mode];
   return threads <= 256 ? k9x4[mode] : k9x4_large[mode];
 }
 

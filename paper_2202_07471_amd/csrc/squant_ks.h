@@ -42,11 +42,10 @@ __device__ __forceinline__ void ks_load_kernel(float (&w)[NW], int q, rsrc_t row
     w[K * q + 4 * V4] = __uint_as_float(buffer_load_u1(row, lane_off + 16u * V4, off));
   }
 }
-template <int K, int NW>
-__device__ __forceinline__ void ks_load_kernel16(float (&w)[NW], int q, rsrc_t row, uint32_t lane_off, uint32_t off,
-                                                 bool bf16) {
+// The dwords of K 16-bit weights; the type is looked at once, after all loads of a thread are on their way.
+template <int K>
+__device__ __forceinline__ void ks_load_kernel16(uint32_t (&d)[(K + 1) / 2], rsrc_t row, uint32_t lane_off, uint32_t off) {
   constexpr int V8 = K / 8;
-  uint32_t d[(K + 1) / 2];
 #pragma unroll
   for (int j = 0; j < V8; ++j) {
     const vu4 v = buffer_load_u4(row, lane_off + 16u * j, off);
@@ -59,12 +58,17 @@ __device__ __forceinline__ void ks_load_kernel16(float (&w)[NW], int q, rsrc_t r
   }
   if (K & 2) d[(K & ~3) / 2] = buffer_load_u1(row, lane_off + 2u * (K & ~3), off);
   if (K & 1) d[K / 2] = buffer_load_u16(row, lane_off + 2u * (K - 1), off);
+}
+template <int K, int KPT, bool BF16>
+__device__ __forceinline__ void ks_widen16(const uint32_t (&d)[KPT][(K + 1) / 2], float (&w)[K * KPT]) {
 #pragma unroll
-  for (int i = 0; i < K; ++i) {
-    float lo, hi;
-    widen_pair(d[i / 2], bf16, lo, hi);
-    w[K * q + i] = i & 1 ? hi : lo;
-  }
+  for (int q = 0; q < KPT; ++q)
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      float lo, hi;
+      widen_pair(d[q][i / 2], BF16, lo, hi);
+      w[K * q + i] = i & 1 ? hi : lo;
+    }
 }
 
 // Bits of a key's index tie-break.
@@ -107,12 +111,26 @@ __device__ __forceinline__ void ks_candidate(int32_t ck, bool over, int32_t smas
   cand_i = IM - (ck & IM);
 }
 
+// The sign a kernel whose perturbations P add up to 0 exactly takes, that of its largest |p| (lowest index first):
+// see k9_zero_sum_sign.
+template <int K, int KP>
+__device__ __forceinline__ int32_t ks_zero_sum_sign(const int32_t (&P)[KP]) {
+  constexpr int IB = ks_index_bits<K>(), IM = (1 << IB) - 1;
+  int32_t pos = 0, neg = 0;
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    const int32_t p = P[i] << IB;
+    pos = imax2(pos, p + (IM - i));
+    neg = imax2(neg, (IM - i) - p);
+  }
+  return neg > pos ? -1 : 0;
+}
+
 // SQuant-E, SQuant-K and the candidate update for one kernel held in registers (straight-line code, as
 // for 3x3).  Arguments as for k9_solve.
 template <int K, int NW, bool FAST, int MODE>
 __device__ __forceinline__ void ks_solve(const float (&w)[NW], int q, float s, float rs, float qmaxf,
-                                         float (&cf)[K], int32_t& esum, uint32_t& cand_w,
-                                         int& cand_i, uint32_t& zero) {
+                                         float (&cf)[K], int32_t& esum, uint32_t& cand_w, int& cand_i) {
   constexpr int IB = ks_index_bits<K>(), IM = (1 << IB) - 1;
   const int W0 = K * q;
   float c[K];
@@ -138,12 +156,12 @@ __device__ __forceinline__ void ks_solve(const float (&w)[NW], int q, float s, f
   int32_t E = 0;
 #pragma unroll
   for (int i = 0; i < K; ++i) E += P[i];
-  const int32_t smask = E >> 31;
+  int32_t smask = E >> 31;
   const int32_t A = (E ^ smask) - smask;
   const int32_t k = (MODE == SQUANT_MODE_EC) ? 0 : (int32_t)((uint32_t)(A + kHalf - 1) >> 23);
   const int32_t r = A - (k << 23);  // |sum| left after k flips, < 0: over SQuant
   esum += (r ^ smask) - smask;
-  zero |= (E == 0 ? 1u : 0u) << q;
+  if (MODE != SQUANT_MODE_EK && __builtin_expect(__ballot(E == 0) != 0ull, 0)) smask = E == 0 ? ks_zero_sum_sign<K>(P) : smask;
 
   // unique keys: 2^IB |p| + (IM - i) >= 2^IB for the elements with the sign of the sum, below
   // 2^IB for all others; |P| <= 2^22 fits the 24-bit multiply
@@ -192,8 +210,7 @@ template <int K, int MODE>
 constexpr bool ks_packed() { return K > 25 || K == 16 || (K == 25 && (MODE == SQUANT_MODE_E || MODE == SQUANT_MODE_EC)); }
 template <int K, bool FAST, int MODE>
 __device__ __forceinline__ void ks_solve_long(const float (&w)[K], float s, float rs, float qmaxf,
-                                              uint32_t (&code)[(K + 3) / 4], int32_t& esum, uint32_t& cand_w, int& cand_i,
-                                              uint32_t& zero) {
+                                              uint32_t (&code)[(K + 3) / 4], int32_t& esum, uint32_t& cand_w, int& cand_i) {
   constexpr int IB = ks_index_bits<K>(), IM = (1 << IB) - 1;
   constexpr int KP = (K + 3) / 4 * 4;
   int32_t key[KP];  // first the perturbations
@@ -225,12 +242,12 @@ __device__ __forceinline__ void ks_solve_long(const float (&w)[K], float s, floa
   int32_t E = 0;
 #pragma unroll
   for (int i = 0; i < K; ++i) E += key[i];
-  const int32_t smask = E >> 31;
+  int32_t smask = E >> 31;
   const int32_t A = (E ^ smask) - smask;
   const int32_t k = (MODE == SQUANT_MODE_EC) ? 0 : (int32_t)((uint32_t)(A + kHalf - 1) >> 23);
   const int32_t r = A - (k << 23);  // |sum| left after k flips, < 0: over SQuant
   esum += (r ^ smask) - smask;
-  zero |= E == 0 ? 1u : 0u;
+  if (MODE != SQUANT_MODE_EK && __builtin_expect(__ballot(E == 0) != 0ull, 0)) smask = E == 0 ? ks_zero_sum_sign<K>(key) : smask;
 
   // unique keys: 2^IB |p| + (IM - i) >= 2^IB for the elements with the sign of the sum, below
   // 2^IB for all others; |P| <= 2^22 fits the 24-bit multiply
@@ -262,27 +279,10 @@ __device__ __forceinline__ void ks_solve_long(const float (&w)[K], float s, floa
   ks_candidate<IB>(ck, over, smask, cand_w, cand_i);
 }
 
-// Cold path: the SQuant-C candidate of a kernel whose perturbation sum is exactly zero (nothing
-// masked: the largest |p| of either sign, lowest index first), recomputed from memory.
-__device__ __noinline__ int2 ks_zero_sum_candidate(const void* w, size_t first, int K, int wtype,
-                                                   float s, float qmaxf) {
-  int32_t best = 0, bv = 0;
-  int bi = 0;
-  for (int i = 0; i < K; ++i) {
-    float x = quotient(load_weight(w, first + i, wtype), s);
-    x = fminf(fmaxf(x, -qmaxf), qmaxf);
-    const float p = rintf(x) - x;
-    const int32_t P = __float2int_rn(p * 8388608.0f);
-    const int32_t ap = P < 0 ? -P : P;
-    if (ap > best) { best = ap; bv = P; bi = i; }
-  }
-  return make_int2(bv, bi);
-}
-
 template <int K, int KPT, bool FAST, int MODE>
 __device__ __forceinline__ void ks_solve_all(const float (&w)[K * KPT], float s, float rs, float qmaxf,
                                              uint8_t* code8, int t, int G, uint32_t owned, int32_t& esum,
-                                             uint32_t (&cv)[KPT], int (&ci)[KPT], uint32_t& zero) {
+                                             uint32_t (&cv)[KPT], int (&ci)[KPT]) {
 #pragma unroll
   for (int q = 0; q < KPT; ++q) {
     if (KPT > 1 && !((owned >> q) & 1u)) continue;
@@ -290,14 +290,14 @@ __device__ __forceinline__ void ks_solve_all(const float (&w)[K * KPT], float s,
     if constexpr (ks_packed<K, MODE>()) {
       static_assert(KPT == 1, "one kernel per thread");
       uint32_t code[(K + 3) / 4];
-      ks_solve_long<K, FAST, MODE>(w, s, rs, qmaxf, code, esum, cv[q], ci[q], zero);
+      ks_solve_long<K, FAST, MODE>(w, s, rs, qmaxf, code, esum, cv[q], ci[q]);
 #pragma unroll
       for (int i = 0; i < K / 4; ++i) __builtin_memcpy(code8 + K * n + 4 * i, &code[i], 4);
 #pragma unroll
       for (int i = K / 4 * 4; i < K; ++i) code8[K * n + i] = (uint8_t)(code[i / 4] >> (8 * (i & 3)));
     } else {
       float cf[K];
-      ks_solve<K, K * KPT, FAST, MODE>(w, q, s, rs, qmaxf, cf, esum, cv[q], ci[q], zero);
+      ks_solve<K, K * KPT, FAST, MODE>(w, q, s, rs, qmaxf, cf, esum, cv[q], ci[q]);
 #pragma unroll
       for (int i = 0; i < K; ++i) code8[K * n + i] = (uint8_t)(int)cf[i];
     }
@@ -328,10 +328,15 @@ __device__ __forceinline__ void ks_channel(const LaunchArgs& a, const TensorDesc
     const uint32_t each = K * (a.wtype == SQUANT_W_F32 ? 4u : 2u);  // bytes of a kernel
     const rsrc_t row = make_rsrc(static_cast<const uint8_t*>(d.w) + (size_t)m * N * each, each * (uint32_t)N);
     const uint32_t lane_off = active ? each * (uint32_t)t : 0x40000000u;  // idle threads: out of range
+    if (a.wtype == SQUANT_W_F32) {
 #pragma unroll
-    for (int q = 0; q < KPT; ++q) {
-      if (a.wtype == SQUANT_W_F32) ks_load_kernel<K>(w, q, row, lane_off, each * (uint32_t)(q * G));
-      else ks_load_kernel16<K>(w, q, row, lane_off, each * (uint32_t)(q * G), a.wtype == SQUANT_W_BF16);
+      for (int q = 0; q < KPT; ++q) ks_load_kernel<K>(w, q, row, lane_off, each * (uint32_t)(q * G));
+    } else {
+      uint32_t raw[KPT][(K + 1) / 2];
+#pragma unroll
+      for (int q = 0; q < KPT; ++q) ks_load_kernel16<K>(raw[q], row, lane_off, each * (uint32_t)(q * G));
+      if (a.wtype == SQUANT_W_BF16) ks_widen16<K, KPT, true>(raw, w);
+      else ks_widen16<K, KPT, false>(raw, w);
     }
   }
   if (kChannelStage) select_reset(sh.sel);  // before the first barrier
@@ -349,22 +354,11 @@ __device__ __forceinline__ void ks_channel(const LaunchArgs& a, const TensorDesc
   int ci[KPT];
 #pragma unroll
   for (int q = 0; q < KPT; ++q) { cv[q] = kNoCandidate; ci[q] = 0; }
-  uint32_t zero = 0;
   if (active) {
     if (normal) {  // uniform over the workgroup
-      ks_solve_all<K, KPT, true, MODE>(w, s, reciprocal(s), qmaxf, code8, t, G, owned, esum, cv, ci, zero);
+      ks_solve_all<K, KPT, true, MODE>(w, s, reciprocal(s), qmaxf, code8, t, G, owned, esum, cv, ci);
     } else {
-      ks_solve_all<K, KPT, false, MODE>(w, s, 0.0f, qmaxf, code8, t, G, owned, esum, cv, ci, zero);
-    }
-    if (kChannelStage && zero != 0) {
-#pragma unroll
-      for (int q = 0; q < KPT; ++q)
-        if (zero & (1u << q)) {
-          const int2 z = ks_zero_sum_candidate(d.w, (size_t)m * L + (size_t)K * (size_t)(t + q * G), K,
-                                               a.wtype, s, qmaxf);
-          cv[q] = candidate_word(z.x);
-          ci[q] = z.y;
-        }
+      ks_solve_all<K, KPT, false, MODE>(w, s, 0.0f, qmaxf, code8, t, G, owned, esum, cv, ci);
     }
   }
   if (kChannelStage) {

@@ -49,7 +49,7 @@ __global__ void __launch_bounds__(kMixedMaxThreads)
   // one-element kernels: E&K is E and E&C is E&K&C (SQuant-K has nothing to do, Section 3.4)
   constexpr int M1 = (MODE == SQUANT_MODE_EK) ? SQUANT_MODE_E
                      : (MODE == SQUANT_MODE_EC) ? SQUANT_MODE_EKC : MODE;
-  constexpr int kWeights = HALF ? -1 : SQUANT_W_F32;
+  constexpr int kWeights = HALF ? kWHalf : SQUANT_W_F32;
   int m;
   TensorDesc d = locate(a, blockIdx.x, m);
   const int family = d.K >> kFamilyShift;
