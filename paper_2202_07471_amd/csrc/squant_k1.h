@@ -645,9 +645,14 @@ __device__ __forceinline__ void k1_emit(const uint32_t (&code)[NE / 4], void* ou
         buffer_store_u4_stream(vu4{o0, o1, bf16_bits(u.x) | (bf16_bits(u.y) << 16),
                                    bf16_bits(u.z) | (bf16_bits(u.w) << 16)}, row, at, step);
       }
-    } else {
+    } else if (VE == 4) {
       buffer_store_u4_stream(__builtin_bit_cast(vu4, dequant4(c0, s)), row, at, step);
-      if (VE == 8) buffer_store_u4_stream(__builtin_bit_cast(vu4, dequant4(c1, s)), row, at + 16u, step);
+    } else {
+      const int lane = tid & (kWave - 1);
+      const vu2 c = team_interleave<kWave>(c0, c1, lane);
+      const uint32_t piece = (uint32_t)(tid - lane) * kUnit + (uint32_t)lane * 16u;
+      buffer_store_u4_stream(__builtin_bit_cast(vu4, dequant4(c.x, s)), row, piece, step);
+      buffer_store_u4_stream(__builtin_bit_cast(vu4, dequant4(c.y, s)), row, piece + 16u * kWave, step);
     }
   }
 }

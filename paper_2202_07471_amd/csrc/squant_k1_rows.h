@@ -266,9 +266,17 @@ __device__ __forceinline__ void k1_rows_emit(const uint32_t (&code)[NE / 4], voi
         buffer_store_u4_stream(vu4{o0, o1, bf16_bits(u.x) | (bf16_bits(u.y) << 16),
                                    bf16_bits(u.z) | (bf16_bits(u.w) << 16)}, range, at, step);
       }
-    } else {
+    } else if (VE == 4) {
       buffer_store_u4_stream(__builtin_bit_cast(vu4, dequant4(c0w, s)), range, at, step);
-      if (VE == 8) buffer_store_u4_stream(__builtin_bit_cast(vu4, dequant4(c1w, s)), range, at + 16u, step);
+    } else {
+      const vu2 c = team_interleave<TEAM>(c0w, c1w, (int)(threadIdx.x & (kWave - 1)));
+      const int v = (l >> 1) + j * TEAM;  // the vector the first piece belongs to; the second: TEAM / 2 later
+      const uint32_t piece = (uint32_t)row * row_bytes + (uint32_t)l * 16u;
+      const bool in = row < rows;
+      buffer_store_u4_stream(__builtin_bit_cast(vu4, dequant4(c.x, s)), range,
+                             in && (j < NL - 1 || v < N / VE) ? piece : kOutside, step);
+      buffer_store_u4_stream(__builtin_bit_cast(vu4, dequant4(c.y, s)), range,
+                             in && (j < NL - 1 || v + TEAM / 2 < N / VE) ? piece + 16u * TEAM : kOutside, step);
     }
   }
 }
