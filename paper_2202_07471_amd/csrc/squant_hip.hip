@@ -224,8 +224,10 @@ int launch_part(const Group& g, bool rows, size_t begin, size_t end, int qmax, i
   auto items_of = [&](const Member& t) {
     if (t.K == 0) return (int64_t)1;  // a batch norm
     if (g.variant == kK9Team) { const int per = g.threads / k9_team_lanes(t.N); return (int64_t)(t.M + per - 1) / per; }
-    if (mixed) return mixed_work_items(t.M, t.N, t.K, threads, t.family);
-    return route_work_items(t.M, t.N, t.K, threads, t.family, wave_span);
+    const int64_t items = mixed ? mixed_work_items(t.M, t.N, t.K, threads, t.family)
+                                : route_work_items(t.M, t.N, t.K, threads, t.family, wave_span);
+    const int each = items_per_workgroup(t.family);
+    return (items + each - 1) / each;
   };
   const int64_t items0 = items_of(g.t[begin]);
   for (size_t i = begin; i < end; ++i) {

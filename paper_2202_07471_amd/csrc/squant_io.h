@@ -110,8 +110,12 @@ __device__ __forceinline__ void buffer_store_u1_stream(uint32_t v, rsrc_t r, uin
 __device__ __forceinline__ void buffer_store_u16_stream(uint16_t v, rsrc_t r, uint32_t lane_off, uint32_t off) {
   __builtin_amdgcn_raw_buffer_store_b16(v, r, (int)lane_off, (int)off, kNonTemporal);
 }
+__device__ __forceinline__ void buffer_store_u8(uint32_t v, rsrc_t r, uint32_t lane_off) {
+  __builtin_amdgcn_raw_buffer_store_b8((uint8_t)v, r, (int)lane_off, 0, 0);
+}
 #else  // the host pass only parses the kernels
 struct rsrc_t {};
+__device__ void buffer_store_u8(uint32_t, rsrc_t, uint32_t);
 __device__ rsrc_t make_rsrc(const void*, uint32_t);
 __device__ uint32_t buffer_load_u1(rsrc_t, uint32_t, uint32_t);
 __device__ vu2 buffer_load_u2(rsrc_t, uint32_t, uint32_t);

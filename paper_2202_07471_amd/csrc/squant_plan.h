@@ -251,8 +251,8 @@ SQ_HD int ks_kpt_log2_any(int64_t N, int64_t K, bool aligned) {
   return best;
 }
 
-// Depthwise kernels other than 3x3 (squant_dw.h): lanes per channel.
-constexpr int kMaxDwK = 64;
+// Depthwise kernels other than 3x3 (squant_dw.h): places for elements in a channel's team of lanes, and elements a lane.
+constexpr int kMaxDwK = 64, kDwLaneElems = 4;
 SQ_HD int dw_team_lanes(int64_t K) { return K <= 16 ? 16 : K <= 32 ? 32 : 64; }
 
 // Channels of a few larger kernels, the stem of a network (squant_stem.h): a wave per channel, whatever
@@ -369,6 +369,9 @@ SQ_HD bool mixed_rows_pay(int64_t channels, bool half, bool stage, int out_bits)
   if (stage) return channels >= kMixedRowsMin && channels < 24576;
   return !half && channels >= 8192 && channels < 20480;
 }
+
+// Work items, as the functions here count them, that a workgroup takes: a lane of a depthwise team has several elements.
+SQ_HD int items_per_workgroup(int family) { return family == 7 ? kDwLaneElems : 1; }
 
 // In a mixed launch.
 SQ_HD int64_t mixed_work_items(int64_t M, int64_t N, int64_t K, int64_t T, int family) {
