@@ -87,6 +87,51 @@ SQ_HD int64_t k1_threads(int64_t nvec, int nv) {
 SQ_HD int k1_wave_nv(int64_t N) { return (int)((N / 4 + 63) / 64); }
 SQ_HD bool is_k1_wave(int variant) { return variant >= kK1Wave + 2 && variant <= kK1Wave + 8; }
 
+// Launch shape of the 1x1 / FC kernel with SQuant-C in a launch of its own: T threads of NV vectors, the fewest whole waves
+// that hold a row of nvec vectors for each NV the kernel is built for.  `rows`, `bytes`: of the launch, read and written.
+// The shape is the one of the least time by a model with three terms:
+//   * what a row takes from its load to its store when nothing else runs: it grows with the vectors a thread holds;
+//   * instructions, for all T * NV vector slots (an idle vector still runs SQuant-E).  Few vectors a thread leave the fixed
+//     work of a wave to few weights; from ten on a SIMD holds four or five waves instead of seven or eight; five, six and
+//     seven waves share out badly over four SIMDs; and a compute unit holds whole workgroups: of more than eight waves
+//     of ten vectors or more, or sixteen of eight, only one;
+//   * memory, at 7.1 TB/s (launches that fit the caches in part), joined with the second as a 4-norm.
+// Its numbers were fitted to 3900 times: every NV at 95 lengths from 2100 to 65536, 1 M to 130 M weights, binary32 and
+// bfloat16, four outputs.  Over these the model's shape takes 1.2 % more than the best one; k1_shape, whose weights are older
+// than the threshold search, 7 % more.  us of some, best ones first, k1_shape's last, bfloat16 to int8 / binary32 to int8:
+//   30 M weights  cin  4096  8 x 128 21.8 / 26.6   4 x 256 24.5 / 26.7   16 x 64  24.8 / 30.4
+//                 cin  7168  7 x 256 21.8 / 26.4   8 x 256 23.2 / 27.1   16 x 128 25.9 / 30.3
+//                 cin 12288 12 x 256 22.9 / 27.3   6 x 512 24.3 / 26.8   16 x 192 24.8 / 29.1
+//    4 M weights  cin  4096  4 x 256  8.0 /  8.3   5 x 256  8.9 /  8.8   16 x 64  12.5 / 12.8
+//                 cin  8192  4 x 512  7.9 /  8.3  10 x 256  9.0 /  9.2   16 x 128 11.7 / 12.4
+//   45 M weights  cin 36412 12 x 768 57.1 / 65.8  14 x 704 60.9 / 68.2   10 x 960 61.1 / 70.7 (the fewest vectors a thread)
+// Thirteen to fifteen waves are left out below 32768 elements (76 rows of 26001 17.3 with 7 x 960, 13.9 with 14 x 512), and so
+// are nine to eleven and sixteen of eight vectors (90 rows of 22001 12.6 with 8 x 704, 10.9 with 12 x 512).
+inline K1Shape k1_launch_shape(int64_t nvec, int64_t rows, int64_t bytes) {
+  const bool wide = nvec > kMaxK1Cin / 4;
+  struct Vectors { int nv; float row_us, slot; };  // slot: relative instructions of a vector slot
+  const Vectors built[9] = {{4, 1.7f, 1.25f}, {5, 2.0f, 1.12f}, {6, 2.4f, 1.02f}, {7, 2.6f, 1.00f}, {8, 3.1f, 1.12f},
+                            {10, 3.3f, 1.25f}, {12, 4.1f, 1.17f}, {14, 4.6f, 1.25f}, {16, 5.2f, 1.22f}};
+  // by waves, for up to seven, eight and more vectors a thread
+  const float of_waves[3][16] = {
+      {1.00f, 0.63f, 0.66f, 0.68f, 0.95f, 0.99f, 1.01f, 0.82f, 1.08f, 1.15f, 1.12f, 1.07f, 1.43f, 1.47f, 1.34f, 1.06f},
+      {1.00f, 0.52f, 0.61f, 0.63f, 0.87f, 0.84f, 0.86f, 0.76f, 1.15f, 1.14f, 1.07f, 0.96f, 1.77f, 1.77f, 1.75f, 1.60f},
+      {0.48f, 0.51f, 0.61f, 0.56f, 0.99f, 1.01f, 0.91f, 0.79f, 1.52f, 1.46f, 1.45f, 1.41f, 1.46f, 1.41f, 1.35f, 1.26f}};
+  const float memory_us = (float)bytes / 7.1e6f;
+  K1Shape best = {16, 1024};
+  float best_us = 3.0e38f;
+  for (const Vectors& v : built) {
+    const int64_t T = round_up64((nvec + v.nv - 1) / v.nv);
+    const int waves = (int)(T / 64);
+    if (T > 1024 || (wide ? v.nv < 10 : (waves > 12 && waves < 16) || (v.nv == 8 && waves > 8 && waves != 12))) continue;
+    const float work_us = (float)rows * (float)(v.nv * T) * v.slot * of_waves[v.nv <= 7 ? 0 : v.nv == 8 ? 1 : 2][waves - 1] * 2.955e-6f;
+    const float w2 = work_us * work_us, m2 = memory_us * memory_us;
+    const float us = v.row_us + __builtin_sqrtf(__builtin_sqrtf(w2 * w2 + m2 * m2));
+    if (us < best_us) { best_us = us; best.nv = v.nv; best.threads = (int)T; }
+  }
+  return best;
+}
+
 // Several 1x1 / FC channels of 257 to 1024 elements per wave (squant_k1_rows.h): lanes per channel and
 // four-element vectors per lane (5 to 8).
 constexpr int kMaxRowsCin = 1024;
