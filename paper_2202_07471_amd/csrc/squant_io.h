@@ -213,6 +213,86 @@ __device__ __forceinline__ vu2 team_interleave(uint32_t c0, uint32_t c1, int lan
   return lane & 1 ? vu2{a1, b1} : vu2{a0, b0};
 }
 
+// The K codes (biased bytes in d0, d1, d2) of a thread's kernels tid, tid + G, ... of a channel into the channel's
+// bytes in LDS.  A store that is not aligned to its size costs the LDS dearly (a wave's 8 bytes at 9 n and one more byte 43 ns,
+// nine single bytes 17, aligned dwords 2 each), so where the four lanes of a quad hold four consecutive kernels from a
+// multiple of four on, whose 4 K bytes are K dwords, each lane puts together the dwords that begin in its
+// kernel: its own bytes and, behind them, the first of the next lane's.  owned, bit q: the thread has kernel q.
+// Whole quads call this.  A row's last dword may take up to three bytes behind it, from the next lane's kernel:
+// 128, as a kernel without weights has.
+// ALL: a thread has all of its kernels or none.
+template <int K, bool ALL, int KPT, typename Kernel>
+__device__ __forceinline__ void store_kernel_codes(uint8_t* code8, int tid, int G, uint32_t owned, const Kernel (&kk)[KPT],
+                                                   bool quads = true) {
+  static_assert(K == 2 || K == 3 || K == 4 || K == 5 || K == 7 || K == 9, "kernel sizes with a pattern of dwords");
+  if (!quads || (K != 4 && KPT > 1 && (G & 3) != 0)) {
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) {
+      if (!((owned >> q) & 1u)) continue;
+      uint8_t* dst = code8 + K * (tid + q * G);
+      if (K > 4) {
+        const uint64_t lo = (uint64_t)kk[q].d0 | ((uint64_t)kk[q].d1 << 32);
+        __builtin_memcpy(dst, &lo, K < 8 ? 4 : 8);
+      }
+      const uint32_t rest = K == 9 ? kk[q].d2 : K > 4 ? kk[q].d1 : kk[q].d0;
+#pragma unroll
+      for (int i = 0; i < K % 4; ++i) dst[K / 4 * 4 + i] = (uint8_t)(rest >> (8 * i));
+    }
+    return;
+  }
+  const uint32_t i = (uint32_t)tid & 3u, before = (4u - i) & 3u;  // the lane within its quad
+  // where the lane's first whole dword begins: `before` bytes into its kernel (9, 5), or i bytes (7, 3)
+  const uint32_t first = K == 9 ? 2 * i + (i > 0 ? 1 : 0) : K == 7 ? 2 * i : K == 5 ? i + (i > 0 ? 1 : 0) : K == 2 ? i >> 1 : i;
+  uint8_t* base = K == 4 ? code8 + 4 * tid : code8 + K * (tid & ~3) + 4 * first;
+  uint32_t w0[KPT], w1[KPT], last[KPT];
+#pragma unroll
+  for (int q = 0; q < KPT; ++q) {
+    const uint32_t d0 = kk[q].d0, d1 = kk[q].d1;
+    const uint32_t next = (uint32_t)__builtin_amdgcn_mov_dpp((int)d0, 0xF9, 0xf, 0xf, true);  // quad_perm [1, 2, 3, 3]
+    w1[q] = last[q] = 0;
+    if (K == 9) {
+      last[q] = __builtin_amdgcn_perm(next, kk[q].d2, 0x06050400u);
+      w0[q] = __builtin_amdgcn_alignbyte(d1, d0, before);
+      w1[q] = __builtin_amdgcn_alignbyte(last[q], d1, before);
+    } else if (K == 7) {
+      const uint32_t end = __builtin_amdgcn_perm(next, d1, 0x04020100u);
+      w0[q] = __builtin_amdgcn_alignbyte(end, d0, i);
+      w1[q] = __builtin_amdgcn_alignbyte(next >> 8, end, i);
+    } else if (K == 5) {
+      last[q] = __builtin_amdgcn_perm(next, d1, 0x06050400u);
+      w0[q] = __builtin_amdgcn_alignbyte(last[q], d0, before);
+    } else if (K == 4) {
+      w0[q] = d0;
+    } else if (K == 3) {
+      w0[q] = __builtin_amdgcn_alignbyte(next >> 8, __builtin_amdgcn_perm(next, d0, 0x04020100u), i);
+    } else {
+      w0[q] = __builtin_amdgcn_perm(next, d0, 0x05040100u);
+    }
+  }
+  auto at = [&](int q) { return reinterpret_cast<uint32_t*>(base + q * (K * G)); };
+  auto put = [&](int q) {
+    at(q)[0] = w0[q];
+    if (K == 9) at(q)[1] = w1[q];
+  };
+  const bool begins = (K != 3 || i < 3) && (K != 2 || (i & 1u) == 0);  // a dword begins in the lane's kernel
+  if (ALL) {
+    if (owned != 0 && begins) {
+#pragma unroll
+      for (int q = 0; q < KPT; ++q) put(q);
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < KPT; ++q)
+      if (((owned >> q) & 1u) && begins) put(q);
+  }
+  const bool more = K == 7 ? i < 3 : (K == 9 || K == 5) && i == 0;
+  if (owned != 0 && more) {
+#pragma unroll
+    for (int q = 0; q < KPT; ++q)
+      if (ALL || ((owned >> q) & 1u)) at(q)[K == 9 ? 2 : 1] = K == 7 ? w1[q] : last[q];
+  }
+}
+
 // Writes output channel m of a tensor from its biased codes in LDS (nvec dwords, so the
 // channel has 4 * nvec elements) in the requested format (squant_output_t).  Called by the
 // whole workgroup after a barrier; 16-byte stores where the channel's row is aligned.

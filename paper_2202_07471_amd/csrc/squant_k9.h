@@ -348,11 +348,11 @@ __device__ __forceinline__ void k9_channel_flip(K9Kernel (&kk)[KPT], int64_t ec,
   }
   if (!rank) return;
   // Rank the candidates of bin `lo` among themselves: they agree in the top eight bits of
-  // |v|, so the low fifteen above "4095 - kernel index" order them (cin <= 4096).
+  // |v|, so the low fifteen above "8191 - kernel index" order them (cin <= 4096; 8192 in squant_ks.h).
   uint32_t comp[KPT];
 #pragma unroll
   for (int q = 0; q < KPT; ++q) {
-    comp[q] = ((kk[q].cand & 0x7FFFu) << 12) | (uint32_t)(4095 - (t + q * G));
+    comp[q] = ((kk[q].cand & 0x7FFFu) << 13) | (uint32_t)(8191 - (t + q * G));
     if (at[q]) list[atomicAdd(&sel.list_count, 1u)] = comp[q];
   }
   bool any = false;

@@ -2,13 +2,15 @@
 // 4x4, 5x5, 7x7: K = kh*kw elements, 2 <= K <= kKsMaxK), built like the 3x3 kernel: one workgroup per
 // output channel, every thread holds KPT whole kernels in registers (thread t the kernels
 // t, t+G, ..., G = cin / KPT), SQuant-E, SQuant-K and the Algorithm 3 candidate are register
-// arithmetic, LDS only holds the channel's biased codes for SQuant-C and the write-out.
+// arithmetic, LDS holds the histogram of SQuant-C and the channel's biased codes for the write-out.
 //
-// The k largest same-sign perturbations of a kernel (Algorithm 2's top-k, k <= K/2) are found
-// by ranking (up to nine elements; larger kernels step through their keys from the top): with unique integer keys (|p| in Q23 above an "index from the end" tie-break,
-// elements of the other sign below all same-sign ones) the rank of an element is the number of
-// larger keys, K(K-1)/2 comparisons in all; an element flips when its rank is below k, and the
-// candidate is the element of rank k-1 (over SQuant) or k (under SQuant).
+// Up to seven elements the arithmetic is the 3x3 kernel's (squant_k9.h): rounding by a magic addition, codes
+// packed as they come, biased perturbations, unique keys, a mask of flips that SQuant-C toggles, all with a selection
+// network of its own per K.  Larger kernels step through their keys from the top.
+// The version before ranked all pairs of keys (three instructions a pair), clamped and converted every
+// code, stored it by itself and flipped SQuant-C's through LDS atomics.  20 M weights in channels of 192 kernels, to int8, us before and
+// now: 1x7 29.1 and 22.0, 1x5 28.9 and 24.2, 1x3 33.0 and 28.6, 2x2 30.5 and 24.7; 16 x [1024, 192, 1, 7] binary16 with E&C 34.2
+// and 21.6, with E&K 24.6 and 19.0; an InceptionV3-style set of 1.39 times the width, binary16, E&C 74.7 and 67.6.
 #pragma once
 
 #include "squant_common.h"
@@ -172,31 +174,11 @@ __device__ __forceinline__ void ks_solve(const float (&w)[NW], int q, float s, f
   const int32_t want = over ? k - 1 : k;  // the candidate's rank: last flipped resp. first un-flipped (k <= K/2 < K)
   const float flip = smask ? 129.0f : 127.0f;  // code -= sign(E)
   int32_t ck = 0;  // the candidate's key
-  if constexpr (K <= 9) {
-    // rank = #{larger keys}, by all pairs
-    int32_t rank[K];
+  int32_t last;
+  ks_step_keys<K, false>(key, k, want, last, ck);
 #pragma unroll
-    for (int i = 0; i < K; ++i) rank[i] = i;  // i counts the pairs (j < i), corrected below
-#pragma unroll
-    for (int i = 0; i < K; ++i)
-#pragma unroll
-      for (int j = i + 1; j < K; ++j) {
-        const int32_t gt = key[j] > key[i] ? 1 : 0;
-        rank[i] += gt;
-        rank[j] -= gt;
-      }
-#pragma unroll
-    for (int i = 0; i < K; ++i) cf[i] = c[i] + (rank[i] < k ? flip : 128.0f);
-    if (MODE == SQUANT_MODE_EK) return;
-#pragma unroll
-    for (int i = 0; i < K; ++i) ck |= rank[i] == want ? key[i] : 0;
-  } else {
-    int32_t last;
-    ks_step_keys<K, false>(key, k, want, last, ck);
-#pragma unroll
-    for (int i = 0; i < K; ++i) cf[i] = c[i] + (key[i] >= last ? flip : 128.0f);
-    if (MODE == SQUANT_MODE_EK) return;
-  }
+  for (int i = 0; i < K; ++i) cf[i] = c[i] + (key[i] >= last ? flip : 128.0f);
+  if (MODE == SQUANT_MODE_EK) return;
 
   // ---- perturbation update (Algorithm 3): the kernel's candidate for SQuant-C ----
   ks_candidate<IB>(ck, over, smask, cand_w, cand_i);
@@ -304,8 +286,227 @@ __device__ __forceinline__ void ks_solve_all(const float (&w)[K * KPT], float s,
   }
 }
 
+// ---- kernels of up to seven elements: the 3x3 kernel's arithmetic ----
+template <int K>
+constexpr bool ks_short() { return K <= 7; }
+
+// The K / 2 + 1 largest of K unique keys, largest first: k <= K / 2 elements flip and the next one may be wanted.  Three
+// are sorted, the others inserted: a median of three gives each place.
+template <int K>
+__device__ __forceinline__ void ks_top(const uint32_t (&x)[K], uint32_t (&t)[K / 2 + 1]) {
+  if constexpr (K == 2) {
+    t[0] = umax2(x[0], x[1]);
+    t[1] = umin2(x[0], x[1]);
+  } else {
+    constexpr int R = K / 2 + 1;
+    uint32_t top[4] = {umax3(x[0], x[1], x[2]), umed3(x[0], x[1], x[2]), umin3(x[0], x[1], x[2]), 0};
+#pragma unroll
+    for (int i = 3; i < K; ++i) {
+      uint32_t next[4];
+      next[0] = umax2(top[0], x[i]);
+      next[1] = umed3(top[0], top[1], x[i]);
+      next[2] = umed3(top[1], top[2], x[i]);
+      next[3] = i == 3 ? umin2(top[2], x[i]) : umed3(top[2], top[3], x[i]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) top[r] = next[r];
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) t[r] = top[r];
+  }
+}
+
+// SQuant-E on one kernel: see k9_round.
+template <int K, bool CLAMP>
+__device__ __forceinline__ void ks_round(const float (&w)[K], float s, float rs, float qmaxf, K9Kernel& kk, uint32_t (&pb)[K]) {
+  uint32_t tb[8];
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    const float x = div_by_reciprocal(w[i], s, rs);  // the IEEE quotient
+    const float xc = CLAMP ? __builtin_amdgcn_fmed3f(x, -qmaxf, qmaxf) : x;
+    const float t = xc + kRoundMagic;
+    pb[i] = __float_as_uint(__builtin_fmaf((t - kRoundMagic) - xc, 8388608.0f, kQ23Magic));
+    tb[i] = __float_as_uint(t);
+  }
+  kk.d0 = K == 2 ? __builtin_amdgcn_perm(tb[1], tb[0], 0x0c0c0400u) : pack_low_bytes(tb[0], tb[1], tb[2], tb[K > 3 ? 3 : 2]);
+  if (K == 5) kk.d1 = tb[4];  // its upper bytes are not codes
+  if (K == 7) kk.d1 = pack_low_bytes(tb[4], tb[5], tb[6], tb[6]);
+}
+
+// See k9_zero_sum_sign.
+template <int K>
+__device__ __forceinline__ uint32_t ks_zero_sum_bits(const uint32_t (&pb)[K]) {
+  int32_t P[K];
+#pragma unroll
+  for (int i = 0; i < K; ++i) P[i] = (int32_t)(pb[i] - kQ23Bias);
+  return (uint32_t)ks_zero_sum_sign<K>(P);
+}
+
+// SQuant-K and the perturbation update for one kernel: see k9_flip, whose words these are.
+template <int MODE, int K>
+__device__ __forceinline__ void ks_flip(const uint32_t (&pb)[K], K9Kernel& kk, int32_t& esum, lanemask_t real) {
+  constexpr bool kCand = MODE == SQUANT_MODE_EKC || MODE == SQUANT_MODE_EC;
+  constexpr int R = K / 2 + 1;
+  uint32_t eb = 0;
+#pragma unroll
+  for (int i = 0; i < K; ++i) eb += pb[i];
+  const int32_t E = (int32_t)(eb - (uint32_t)K * kQ23Bias);
+  uint32_t sm = (uint32_t)(E >> 31);
+  const uint32_t A = ((uint32_t)E ^ sm) - sm;
+  if (kCand) {
+    const lanemask_t zero = lanes_eq(A, 0u) & real;
+    if (__builtin_expect(zero != 0, 0)) sm = vsel(zero, ks_zero_sum_bits<K>(pb), sm);
+  }
+  kk.sm = sm;
+  uint32_t key[K];
+#pragma unroll
+  for (int i = 0; i < K; ++i) key[i] = ((pb[i] ^ sm) << 5) | (uint32_t)(31 - i);
+  const uint32_t base = (kQ23Bias << 5) + (sm & (((~kQ23Bias) << 5) - (kQ23Bias << 5)));
+
+  if (MODE == SQUANT_MODE_EC) {
+    esum += E;
+    uint32_t ck = key[0];
+#pragma unroll
+    for (int i = 1; i < K; i += 2) ck = umax3(ck, key[i], key[i + 1 < K ? i + 1 : i]);
+    const int32_t rel = (int32_t)(ck - base);
+    kk.cand = vsel(lanes_sge(rel, 32), ((uint32_t)rel >> 5) | (sm & (1u << 23)), kNoCandidate);
+    kk.cand_bit = 0x80000000u >> (ck & 31u);
+    return;
+  }
+
+  const uint32_t tt = A + (uint32_t)(kHalf - 1);  // k = tt >> 23
+  const int32_t r = (int32_t)(tt & 0x7FFFFFu) - (kHalf - 1);
+  esum += (int32_t)(((uint32_t)r ^ sm) - sm);
+  uint32_t top[R];
+  ks_top<K>(key, top);
+  uint32_t mask = 0x80000000u >> (top[0] & 31u);
+  lanemask_t at_least = lanes_uge(tt, 1u << 23);
+  uint32_t flips = vsel0(at_least, mask), thr = top[0], nxt = 0;  // thr: the k-th largest, k >= 1; nxt: the next one
+  if (kCand) nxt = vsel(at_least, top[1], top[0]);
+#pragma unroll
+  for (int k = 2; k < R; ++k) {
+    at_least = lanes_uge(tt, (uint32_t)k << 23);
+    mask |= 0x80000000u >> (top[k - 1] & 31u);
+    flips = vsel(at_least, mask, flips);
+    if (kCand) {
+      thr = vsel(at_least, top[k - 1], thr);
+      nxt = vsel(at_least, top[k], nxt);
+    }
+  }
+  kk.flips = flips;
+  if (!kCand) return;
+
+  const lanemask_t over = lanes_slt(r, 0);
+  const uint32_t ck = vsel(over, thr, nxt);
+  const int32_t rel = (int32_t)(ck - base);
+  const uint32_t mag = (uint32_t)rel >> 5, sbit = sm & (1u << 23);
+  const uint32_t word = vsel(over, ((2u << 23) - sbit) - mag, mag | sbit);
+  kk.cand = vsel(lanes_sge(rel, 32), word, kNoCandidate);
+  kk.cand_bit = 0x80000000u >> (ck & 31u);
+}
+
+template <int K>
+__device__ __forceinline__ void ks_apply_flips(K9Kernel& kk) {
+  const uint32_t b0 = ((kk.flips & 15u) * 0x204081u) & 0x01010101u;  // bit e to byte e
+  kk.d0 -= (b0 ^ kk.sm) - kk.sm;
+  if (K > 4) {
+    const uint32_t b1 = ((kk.flips >> 4) * 0x204081u) & 0x01010101u;
+    kk.d1 -= (b1 ^ kk.sm) - kk.sm;
+  }
+}
+
+// SQuant-E and SQuant-K on all the kernels of a thread: see k9_solve_all.
+template <int MODE, int K, int KPT, bool GENERAL>
+__device__ __forceinline__ void ks_solve_short(const float (&w)[K * KPT], float s, float rs, float qmaxf, float f1, float f2,
+                                               K9Kernel (&kk)[KPT], int32_t& esum, const lanemask_t (&real)[KPT]) {
+#pragma unroll
+  for (int q = 0; q < KPT; ++q) {
+    kk[q].d0 = kk[q].d1 = kk[q].flips = kk[q].sm = kk[q].cand_bit = 0;
+    kk[q].cand = kNoCandidate;
+    if (__float_as_uint(s) + (uint32_t)q == 0xFFFFFFF0u) continue;  // never: a basic block for each kernel
+    float x[K];
+#pragma unroll
+    for (int i = 0; i < K; ++i) x[i] = GENERAL ? w[K * q + i] * f1 * f2 : w[K * q + i];
+    uint32_t pb[K];
+    ks_round<K, GENERAL>(x, s, rs, qmaxf, kk[q], pb);
+    if (MODE != SQUANT_MODE_E) {
+      ks_flip<MODE, K>(pb, kk[q], esum, real[q]);
+      if (MODE == SQUANT_MODE_EK) ks_apply_flips<K>(kk[q]);
+    }
+  }
+}
+
+// A channel of such kernels from its weights in w on: codes into `code8`.  As in k9_channel.
+template <int MODE, int K, int KPT>
+__device__ __forceinline__ void ks_channel_short(const float (&w)[K * KPT], float amax, float s, bool normal, float qmaxf, int N, int t,
+                                                 int G, uint32_t owned, uint8_t* code8, K9Shared& sh) {
+  constexpr bool kChannelStage = MODE == SQUANT_MODE_EKC || MODE == SQUANT_MODE_EC;
+  K9Kernel kk[KPT];
+  int32_t esum = 0;
+  lanemask_t real[KPT];
+#pragma unroll
+  for (int q = 0; q < KPT; ++q) real[q] = __ballot((owned >> q) & 1u);
+  const float rs0 = reciprocal(s);
+  if (normal && div_by_reciprocal(amax, s, rs0) <= qmaxf) {
+    ks_solve_short<MODE, K, KPT, false>(w, s, rs0, qmaxf, 1.0f, 1.0f, kk, esum, real);
+  } else {  // a quotient beyond qmax, or an absmax outside the range of the reciprocal: scaled by powers of two
+    const float f1 = normal ? 1.0f : amax < 1.0f ? 0x1p64f : 0x1p-64f;
+    const float a1 = amax * f1;
+    const float f2 = normal ? 1.0f : a1 < 0x1p-60f ? 0x1p64f : a1 > 0x1p60f ? 0x1p-64f : 1.0f;
+    const float s2 = s > 0.0f ? s * f1 * f2 : 0x1p-40f;
+    ks_solve_short<MODE, K, KPT, true>(w, s2, reciprocal(s2), qmaxf, f1, f2, kk, esum, real);
+  }
+  if (kChannelStage) {
+#pragma unroll
+    for (int q = 0; q < KPT; ++q)
+      if ((owned >> q) & 1u) count_candidate(sh.sel, kk[q].cand);
+    // after SQuant-K a kernel's sum is at most a half, eight of a thread 2^25; without it up to 3.5
+    const int64_t ws = MODE == SQUANT_MODE_EC ? wave_sum_dpp(owned ? esum : 0) : wave_sum_rows(owned ? esum : 0);
+    const int64_t ec = k9_block_sum<0>(ws, sh.red_i);
+    k9_channel_flip<KPT, true>(kk, ec, N, t, G, owned, reinterpret_cast<uint32_t*>(code8), sh.sel);
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) ks_apply_flips<K>(kk[q]);
+  }
+  store_kernel_codes<K, KPT == 1>(code8, t, G, owned, kk);
+}
+
+// The same for larger kernels.
+template <int MODE, int K, int KPT>
+__device__ __forceinline__ void ks_channel_long(const float (&w)[K * KPT], float s, bool normal, float qmaxf, int N, int t, int G,
+                                                uint32_t owned, uint8_t* code8, K9Shared& sh) {
+  constexpr bool kChannelStage = MODE == SQUANT_MODE_EKC || MODE == SQUANT_MODE_EC;
+  int32_t esum = 0;
+  uint32_t cv[KPT];
+  int ci[KPT];
+#pragma unroll
+  for (int q = 0; q < KPT; ++q) { cv[q] = kNoCandidate; ci[q] = 0; }
+  if (owned) {
+    if (normal) {  // uniform over the workgroup
+      ks_solve_all<K, KPT, true, MODE>(w, s, reciprocal(s), qmaxf, code8, t, G, owned, esum, cv, ci);
+    } else {
+      ks_solve_all<K, KPT, false, MODE>(w, s, 0.0f, qmaxf, code8, t, G, owned, esum, cv, ci);
+    }
+  }
+  if (kChannelStage) {
+    if (owned) {
+#pragma unroll
+      for (int q = 0; q < KPT; ++q)
+        if ((owned >> q) & 1u) count_candidate(sh.sel, cv[q]);
+    }
+    const int64_t ec = block_sum_dpp1(esum, sh.red_i);
+    const int sgn = sign_of(ec);
+    const int64_t kc = flips_for(ec < 0 ? -ec : ec);
+    if (kc > 0) {
+      int cpos[KPT], cn[KPT];
+#pragma unroll
+      for (int q = 0; q < KPT; ++q) { cn[q] = t + q * G; cpos[q] = K * cn[q] + ci[q]; }
+      channel_stage<KPT, 1>(cv, cpos, cn, sgn, (uint32_t)(kc > N ? N : kc),
+                            reinterpret_cast<uint32_t*>(code8), sh.sel);
+    }
+  }
+}
+
 // One workgroup per output channel of N kernels, any N and any alignment; thread t takes kernels
-// t, t + G, ..., G = ceil(N / KPT).
+// t, t + G, ..., G = ceil(N / KPT) in whole fours.
 template <int MODE, int K, int KPT>
 __device__ __forceinline__ void ks_channel(const LaunchArgs& a, const TensorDesc& d, int m,
                                            unsigned char* smem, K9Shared& sh) {
@@ -314,14 +515,14 @@ __device__ __forceinline__ void ks_channel(const LaunchArgs& a, const TensorDesc
   const float qmaxf = (float)a.qmax;
   uint8_t* code8 = reinterpret_cast<uint8_t*>(smem);  // biased codes: code + 128
 
-  const int N = d.N, G = (N + KPT - 1) / KPT;
+  const int N = d.N, G = KPT == 1 ? N : ((N + KPT - 1) / KPT + 3) & ~3;  // whole quads: see store_kernel_codes
   const int L = K * N;
   const bool active = tid < G;
   const int t = tid;
   uint32_t owned = active ? ~0u : 0u;  // bit q: kernel t + q * G exists and is this thread's
   if (active) {
 #pragma unroll
-    for (int q = 1; q < KPT; ++q) owned &= t + q * G < N ? ~0u : ~(1u << q);
+    for (int q = KPT == 1 ? 1 : 0; q < KPT; ++q) owned &= t + q * G < N ? ~0u : ~(1u << q);
   }
   float w[K * KPT];
   {
@@ -349,34 +550,10 @@ __device__ __forceinline__ void ks_channel(const LaunchArgs& a, const TensorDesc
   const float s = channel_scale(amax, qmaxf, a.rcp_qmax, normal);
   if (tid == 0) d.scales[m] = s;
 
-  int32_t esum = 0;
-  uint32_t cv[KPT];
-  int ci[KPT];
-#pragma unroll
-  for (int q = 0; q < KPT; ++q) { cv[q] = kNoCandidate; ci[q] = 0; }
-  if (active) {
-    if (normal) {  // uniform over the workgroup
-      ks_solve_all<K, KPT, true, MODE>(w, s, reciprocal(s), qmaxf, code8, t, G, owned, esum, cv, ci);
-    } else {
-      ks_solve_all<K, KPT, false, MODE>(w, s, 0.0f, qmaxf, code8, t, G, owned, esum, cv, ci);
-    }
-  }
-  if (kChannelStage) {
-    if (active) {
-#pragma unroll
-      for (int q = 0; q < KPT; ++q)
-        if ((owned >> q) & 1u) count_candidate(sh.sel, cv[q]);
-    }
-    const int64_t ec = block_sum_dpp1(esum, sh.red_i);
-    const int sgn = sign_of(ec);
-    const int64_t kc = flips_for(ec < 0 ? -ec : ec);
-    if (kc > 0) {
-      int cpos[KPT], cn[KPT];
-#pragma unroll
-      for (int q = 0; q < KPT; ++q) { cn[q] = t + q * G; cpos[q] = K * cn[q] + ci[q]; }
-      channel_stage<KPT, 1>(cv, cpos, cn, sgn, (uint32_t)(kc > N ? N : kc),
-                            reinterpret_cast<uint32_t*>(smem), sh.sel);
-    }
+  if constexpr (ks_short<K>()) {
+    ks_channel_short<MODE, K, KPT>(w, amax, s, normal, qmaxf, N, t, G, owned, code8, sh);
+  } else {
+    ks_channel_long<MODE, K, KPT>(w, s, normal, qmaxf, N, t, G, owned, code8, sh);
   }
   if (tid == 0) code8[L] = 128;  // the element a packed row of odd length is short of
   __syncthreads();

@@ -1,0 +1,86 @@
+"""GPU parity for kernels of 2, 3, 4, 5, 7 and 9 elements whose codes go to the write-out as whole dwords of four
+lanes: channel counts around whole quads and around each number of kernels a thread, packed rows of odd length, values
+that make all of a channel's candidates equal, alone and in a mixed launch."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def sq():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2202_07471_amd as sq
+    sq.binding.lib()
+    return sq
+
+
+def weights(shape, kind, gen):
+    if kind == "normal":
+        return torch.randn(shape, generator=gen)
+    if kind == "levels":      # equal keys, sums of exactly 0 and of exact halves
+        return torch.round(torch.randn(shape, generator=gen) * 3) / 4
+    w = torch.full(shape, 0.3)   # every kernel the same: all candidates of a channel are equal
+    w[:, 0] = 7.0 if shape[0] % 2 else -7.0
+    return w
+
+
+def check(sq, w, out, s, mode, output):
+    host = w.cpu().numpy() if w.dtype == torch.float32 else oracle.widen(w.cpu().view(torch.int16).numpy().view(np.uint16), "f16")
+    codes, want_s = oracle.quantize(host, 4, mode, threads=8)
+    want = oracle.pack_int4(codes) if output == sq.OUT_INT4 else codes
+    assert np.array_equal(s.cpu().numpy(), want_s) and np.array_equal(out.cpu().numpy(), want), (tuple(w.shape), w.dtype, mode, output)
+
+
+COUNTS = [2, 3, 5, 6, 7, 31, 62, 63, 65, 66, 127, 129, 130, 131, 135, 152, 200, 254, 257, 260, 300, 511, 513, 600, 1021, 1030, 2047, 4095]
+
+
+@pytest.mark.parametrize("kh,kw", [(1, 2), (3, 1), (2, 2), (1, 5), (7, 1), (3, 3)])
+@pytest.mark.parametrize("kind", ["normal", "levels", "equal"])
+def test_alone(sq, kh, kw, kind):
+    gen = torch.Generator().manual_seed(kh * 8 + kw)
+    for i, cin in enumerate(COUNTS):
+        cout = max(3, min(40, -(-17000 // (cin * kh * kw))))   # no small tensor: those may go elsewhere
+        if i % 3 == 0:
+            cout |= 1
+        w = weights((cout, cin, kh, kw), kind, gen).to(torch.float32 if i % 2 else torch.float16).cuda()
+        for mode in (sq.MODE_E, sq.MODE_EK, sq.MODE_EKC, sq.MODE_EC):
+            output = sq.OUT_INT4 if (i + mode) % 2 else sq.OUT_INT8
+            out, s = sq.squant_quantize_ex(w, 4, mode, output)
+            check(sq, w, out, s, mode, output)
+
+
+def test_most_kernels_a_thread(sq):
+    gen = torch.Generator().manual_seed(1)
+    for shape in ((3, 8192, 1, 2), (3, 8189, 1, 3), (3, 8190, 2, 2), (3, 4094, 1, 7)):
+        for kind in ("normal", "equal"):
+            w = weights(shape, kind, gen).cuda()
+            out, s = sq.squant_quantize_ex(w, 4, sq.MODE_EKC, sq.OUT_INT4)
+            check(sq, w, out, s, sq.MODE_EKC, sq.OUT_INT4)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+def test_in_a_mixed_launch(sq, dtype):
+    gen = torch.Generator().manual_seed(2)
+    shapes = [(20, n, 1, k) for n in (67, 130, 258, 301, 500) for k in (2, 3, 5, 7)] + [(20, n, 3, 3) for n in (5, 66, 131, 255, 512)]
+    for kind in ("normal", "levels"):
+        ws = [weights(s, kind, gen).to(dtype).cuda() for s in shapes]
+        for mode in (sq.MODE_EK, sq.MODE_EKC, sq.MODE_EC):
+            codes, scales = sq.BatchPlan(ws, sq.OUT_INT4).run(4, mode)
+            for w, c, s in zip(ws, codes, scales):
+                check(sq, w, c, s, mode, sq.OUT_INT4)
+
+
+def test_a_launch_of_many_channels(sq):
+    """From 32768 binary32 channels on, the 3x3 kernel stores single kernels."""
+    w = torch.randn((33000, 272, 3, 3), generator=torch.Generator().manual_seed(4)).cuda()
+    out, s = sq.squant_quantize_ex(w, 4, sq.MODE_EKC, sq.OUT_INT8)
+    few, few_s = sq.squant_quantize_ex(w[:500], 4, sq.MODE_EKC, sq.OUT_INT8)
+    check(sq, w[:500], few, few_s, sq.MODE_EKC, sq.OUT_INT8)
+    check(sq, w[-500:], out[-500:], s[-500:], sq.MODE_EKC, sq.OUT_INT8)
+    assert torch.equal(out[:500], few) and torch.equal(s[:500], few_s)
