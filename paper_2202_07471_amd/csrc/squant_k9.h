@@ -414,7 +414,7 @@ constexpr int kWHalf = 3;
 //   WT   the weight type when it is known at compile time (squant_wtype_t; kWHalf: one of the
 //        16-bit types), -1: the launch's
 //   NWC  the waves per workgroup when known at compile time, 0: the launch's
-//   ANY  any cin and any alignment: G = ceil(cin / KPT), the kernels past the channel's end read
+//   ANY  any cin and any alignment: G = ceil(cin / KPT), in whole fours, the kernels past the channel's end read
 //        as zeros through the range of the row's descriptor, and the row is written through one.
 //        (Otherwise cin is a multiple of four, weights start on 16 bytes and codes on four.)
 template <int MODE, int KPT, int WT = -1, int NWC = 0, bool ANY = false>
@@ -426,14 +426,15 @@ __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc
   const float qmaxf = (float)a.qmax;
   uint8_t* code8 = reinterpret_cast<uint8_t*>(smem);  // biased codes: code + 128
 
-  const int N = d.N, G = ANY ? (N + KPT - 1) / KPT : N / KPT;
+  // (ANY: whole quads of threads, as store_kernel_codes likes them)
+  const int N = d.N, G = !ANY ? N / KPT : KPT == 1 ? N : ((N + KPT - 1) / KPT + 3) & ~3;
   const int L = 9 * N, nvec = L >> 2;  // dwords of codes (cin % 4 == 0)
   const bool active = tid < G;
   const int t = active ? tid : 0;  // idle threads shadow thread 0's loads and write nothing
   uint32_t owned = active ? ~0u : 0u;  // bit q: kernel t + q * G exists and is this thread's
   if (ANY && active) {
 #pragma unroll
-    for (int q = 1; q < KPT; ++q) owned &= tid + q * G < N ? ~0u : ~(1u << q);
+    for (int q = KPT == 1 ? 1 : 0; q < KPT; ++q) owned &= tid + q * G < N ? ~0u : ~(1u << q);
   }
   float w[9 * KPT];
   if (wtype == SQUANT_W_F32 && !ANY) {
@@ -509,16 +510,11 @@ __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc
     for (int q = 0; q < KPT; ++q) k9_apply_flips(kk[q]);
   }
 
-  if (active) {
-#pragma unroll
-    for (int q = 0; q < KPT; ++q) {
-      if (ANY && !((owned >> q) & 1u)) continue;
-      uint8_t* dst = code8 + 9 * (t + q * G);
-      const uint64_t lo = (uint64_t)kk[q].d0 | ((uint64_t)kk[q].d1 << 32);
-      __builtin_memcpy(dst, &lo, 8);
-      dst[8] = (uint8_t)kk[q].d2;
-    }
-  }
+  // Putting dwords together costs vector instructions where the LDS has time to spare: the largest binary32 launches,
+  // bound by memory and the power that it and the arithmetic share, keep to stores that are not aligned (256 x [512, 512, 3, 3] 492 us
+  // so, 500 with dwords, with E&C 64 of them 125 and 129; but 32 59.2 and 58.4, two 7.6 and 7.0, and bfloat16 to 4 bit 64 104 and 96).
+  const bool quads = !(WT == SQUANT_W_F32 && NWC == 2 && !ANY) || a.total < 32768;
+  store_kernel_codes<9, !ANY>(code8, tid, G, owned, kk, quads);
   if (ANY && tid == 0) code8[L] = 128;  // the element a packed row of odd length is short of
   __syncthreads();
 
