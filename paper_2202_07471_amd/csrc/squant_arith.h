@@ -27,6 +27,13 @@ SQ_HD float div_by_reciprocal(float w, float s, float r) {
   return __builtin_fmaf(e0, r, q0);
 }
 
+// The same for a weight of binary16 or bfloat16 and the scale that such an absmax gives, s = RN(amax / qmax) with qmax =
+// 2^(b-1) - 1, b = 2 ... 8: r and rl = RN((1 - s r) r) are together 1 / s to 2^-48, and RN(w r + RN(w rl)) is the
+// quotient for each of the 1024 significands of w, 1024 of amax and seven qmax (tests/host_half_quotient.cpp tries
+// all 7.3 million; bfloat16 values are among them).  With any significand of s 28 of 2^33 pairs differ.
+SQ_HD float reciprocal_low(float s, float r) { return __builtin_fmaf(-s, r, 1.0f) * r; }
+SQ_HD float half_quotient(float w, float r, float rl) { return __builtin_fmaf(w, r, w * rl); }
+
 // One step from an estimate r0 of 1 / s: r0 (2 - s r0), the residual 1 - s r0 in one FMA.
 SQ_HD float refine_reciprocal(float s, float r0) {
   const float e = __builtin_fmaf(-s, r0, 1.0f);

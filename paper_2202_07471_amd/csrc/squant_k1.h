@@ -15,7 +15,9 @@
 //   * loads and stores are buffer instructions on a descriptor of the channel's row: one
 //     address register for all vectors, and the hardware's range check takes the place of the
 //     per-vector bounds checks (out-of-range dwords read as 0 and are not written);
-//   * SQuant-E is 9.75 instructions an element: three for the exact quotient, rounding by a
+//   * SQuant-E is 9.75 instructions an element: three for the exact quotient (two for 16-bit weights, whose quotients
+//     by the scales they can have are exact so: six linear layers in bfloat16 118.4 -> 117.0 us, 16 x [4096, 2048] 87.8 -> 86.2;
+//     rows beyond 45000 elements, one workgroup a compute unit, lose 1 to 2 %: the code is laid out otherwise), rounding by a
 //     magic addition that leaves code + 128 in the sum's low byte (squant_k9.h), the biased
 //     Q23 perturbation by one FMA.  While the scale is a normal number the clamp to +-qmax can
 //     only move the element that set it, by one rounding, so it is left out and such elements are
@@ -151,16 +153,19 @@ __device__ __forceinline__ void k1_widen(uint32_t (&raw)[HALF ? NE / 2 : NE], ui
 // x = w / s for the NE elements of a thread: the packed biased codes (code + 128, four to a
 // dword) and, WITH_P, the Q23 perturbations in biased form (kQ23Bias + P).  `over` (uniform):
 // the quotient of the absmax element exceeds qmax.  Returns the sum of the P.
-template <int NE, bool WITH_P>
+// HALF: 16-bit weights.
+template <int NE, bool WITH_P, bool HALF>
 __device__ __forceinline__ int32_t k1_round_all(const float (&w)[NE], float s, float rs, float qmaxf,
                                                 float xmax, uint32_t (&code)[NE / 4], uint32_t (&B)[NE]) {
   uint32_t biased = 0;
+  const float rl = HALF ? reciprocal_low(s, rs) : 0.0f;
 #pragma unroll
   for (int i = 0; i < NE / 4; ++i) {
     uint32_t tb[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const float x = div_by_reciprocal(w[4 * i + e], s, rs);  // the IEEE quotient
+      // the IEEE quotient
+      const float x = HALF ? half_quotient(w[4 * i + e], rs, rl) : div_by_reciprocal(w[4 * i + e], s, rs);
       const float t = x + kRoundMagic;  // round half to even; code + 128 in the low byte
       tb[e] = __float_as_uint(t);
       if (WITH_P) {
@@ -532,7 +537,7 @@ __device__ __forceinline__ float k1_absmax(const float (&w)[NE]) {
 
 // SQuant-E with the scale of a channel of absmax `amax` (the channel's, in each of its lanes); w is used up.
 // Codes and B as from k1_round_all; esum: the sum of the thread's P.  Returns the scale.
-template <int NE, bool WITH_P>
+template <int NE, bool WITH_P, bool HALF>
 __device__ __forceinline__ float k1_quantize(float (&w)[NE], float amax, float qmaxf, float rcp_qmax,
                                              uint32_t (&code)[NE / 4], uint32_t (&B)[NE], int32_t& esum) {
   // The quotients go through the reciprocal of s, which is proven exact for an absmax within
@@ -555,11 +560,11 @@ __device__ __forceinline__ float k1_quantize(float (&w)[NE], float amax, float q
     amax = 0.0f;  // no quotient beyond qmax is left
   }
   const float rs = reciprocal(s2);
-  esum = k1_round_all<NE, WITH_P>(w, s2, rs, qmaxf, div_by_reciprocal(amax, s2, rs), code, B);
+  esum = k1_round_all<NE, WITH_P, HALF>(w, s2, rs, qmaxf, div_by_reciprocal(amax, s2, rs), code, B);
   return s;
 }
 
-template <int MODE, int NE, int VE, bool WAVE, typename Sh>
+template <int MODE, int NE, int VE, bool WAVE, bool HALF, typename Sh>
 __device__ __forceinline__ float k1_solve(float (&w)[NE], int N, float qmaxf, float rcp_qmax, Sh& sh, uint32_t* owner,
                                           uint32_t (&code)[NE / 4]) {
   constexpr bool kChannelStage = MODE == SQUANT_MODE_EKC || MODE == SQUANT_MODE_EC;
@@ -577,7 +582,7 @@ __device__ __forceinline__ float k1_solve(float (&w)[NE], int N, float qmaxf, fl
 
   uint32_t B[NE];
   int32_t esum;
-  const float s = k1_quantize<NE, kChannelStage>(w, amax, qmaxf, rcp_qmax, code, B, esum);
+  const float s = k1_quantize<NE, kChannelStage, HALF>(w, amax, qmaxf, rcp_qmax, code, B, esum);
 
   if (kChannelStage) {
     int64_t ec = k1_wave_sum<NE>(esum);
@@ -711,7 +716,7 @@ __device__ __forceinline__ void k1_channel(const LaunchArgs& a, const TensorDesc
   k1_load<NE, VE, HALF, TAIL>(static_cast<const uint8_t*>(d.w) + (size_t)m * N * (HALF ? 2 : 4), N, tid, T, raw, tail);
   float w[NE];
   k1_widen<NE, VE, HALF, TAIL>(raw, tail, a.wtype == SQUANT_W_BF16, N, tid, T, w);
-  const float s = k1_solve<MODE, NE, VE, false>(w, N, (float)a.qmax, a.rcp_qmax, sh, reinterpret_cast<uint32_t*>(smem), code);
+  const float s = k1_solve<MODE, NE, VE, false, HALF>(w, N, (float)a.qmax, a.rcp_qmax, sh, reinterpret_cast<uint32_t*>(smem), code);
   if (tid == 0) d.scales[m] = s;
   k1_emit_as<NE, VE, TAIL>(a.out_format, code, d.out, m, N, s, tid, T);
 }

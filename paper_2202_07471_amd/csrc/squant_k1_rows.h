@@ -348,7 +348,7 @@ __device__ __forceinline__ void k1_rows_channels(const LaunchArgs& a, const Tens
   const float amax = team_max_f32<TEAM>(k1_absmax(w));
   uint32_t code[NE / 4], B[NE];
   int32_t esum;
-  const float s = k1_quantize<NE, kChannelStage>(w, amax, (float)a.qmax, a.rcp_qmax, code, B, esum);
+  const float s = k1_quantize<NE, kChannelStage, HALF>(w, amax, (float)a.qmax, a.rcp_qmax, code, B, esum);
   if (kChannelStage) {
     uint32_t sm;
     const uint32_t need = umin2(k1_rows_flips<TEAM>(esum, sm), (uint32_t)N);

@@ -36,7 +36,7 @@ __device__ __forceinline__ void k1_wave_channels(const LaunchArgs& a, const Tens
     uint32_t code[NE / 4];
     k1_widen<NE, VE, HALF, TAIL>(raw, tail, a.wtype == SQUANT_W_BF16, N, k1_tid<true>(), kWave, w);
     if (PREFETCH && m + 1 < c1) load(m + 1);
-    const float s = k1_solve<MODE, NE, VE, true>(w, N, (float)a.qmax, a.rcp_qmax, sel, sel.owner, code);
+    const float s = k1_solve<MODE, NE, VE, true, HALF>(w, N, (float)a.qmax, a.rcp_qmax, sel, sel.owner, code);
     k1_sync<true>();  // the channel's last LDS access
     // The next channel's weights are waited for here, before this one's stores: loads and stores
     // complete in one order, so a wait at the loop's head would also wait for the stores.

@@ -82,14 +82,15 @@ __device__ __forceinline__ uint32_t vsel0(lanemask_t m, uint32_t if_set) {  // e
 //   CLAMP  clamp the quotients to [-qmax, qmax] (Section 2.2).  Only the quotient of the
 //          absmax element itself can lie outside, by one rounding of s; the caller leaves the
 //          clamp out for a channel whose absmax / s does not exceed qmax.
-template <bool FAST, bool CLAMP = true>
+//   HALF   16-bit weights, whose quotients take an operation less
+template <bool FAST, bool CLAMP = true, bool HALF = false>
 __device__ __forceinline__ void k9_round(const float* w, float s, float rs, float qmaxf, K9Kernel& kk,
-                                         uint32_t (&pb)[9]) {
+                                         uint32_t (&pb)[9], float rl = 0.0f) {
   uint32_t tb[9];
 #pragma unroll
   for (int i = 0; i < 9; ++i) {
     // x = w / s: either way the IEEE binary32 quotient
-    const float x = FAST ? div_by_reciprocal(w[i], s, rs) : quotient(w[i], s);
+    const float x = HALF ? half_quotient(w[i], rs, rl) : FAST ? div_by_reciprocal(w[i], s, rs) : quotient(w[i], s);
     const float xc = CLAMP ? __builtin_amdgcn_fmed3f(x, -qmaxf, qmaxf) : x;
     const float t = xc + kRoundMagic;
     const float c = t - kRoundMagic;  // round-half-even(xc), exact
@@ -379,10 +380,11 @@ __device__ __forceinline__ void k9_channel_flip(K9Kernel (&kk)[KPT], int64_t ec,
 //   PRESCALE  the weights are first multiplied by the powers of two f1 and f2 (and s, rs are
 //             those of the scaled channel): see k9_channel
 //   real      lanes that have a kernel q of their own (others hold zeros and leave no trace)
-template <int MODE, int KPT, bool PRESCALE, bool CLAMP>
+template <int MODE, int KPT, bool PRESCALE, bool CLAMP, bool HALF>
 __device__ __forceinline__ void k9_solve_all(const float (&w)[9 * KPT], float s, float rs, float qmaxf,
                                              float f1, float f2, K9Kernel (&kk)[KPT], int32_t& esum,
                                              const lanemask_t (&real)[KPT]) {
+  const float rl = HALF ? reciprocal_low(s, rs) : 0.0f;
 #pragma unroll
   for (int q = 0; q < KPT; ++q) {
     // A branch that is always taken (s is finite) but that the compiler cannot fold: it makes
@@ -398,7 +400,7 @@ __device__ __forceinline__ void k9_solve_all(const float (&w)[9 * KPT], float s,
       x[i] = PRESCALE ? w[9 * q + i] * f1 * f2 : w[9 * q + i];
     }
     uint32_t pb[9];
-    k9_round<true, CLAMP>(x, s, rs, qmaxf, kk[q], pb);
+    k9_round<true, CLAMP, HALF>(x, s, rs, qmaxf, kk[q], pb, rl);
     if (MODE != SQUANT_MODE_E) {
       k9_flip<MODE>(pb, kk[q], esum, real[q]);
       if (MODE == SQUANT_MODE_EK) k9_apply_flips(kk[q]);
@@ -421,6 +423,7 @@ template <int MODE, int KPT, int WT = -1, int NWC = 0, bool ANY = false>
 __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc& d, int m,
                                            unsigned char* smem, K9Shared& sh) {
   constexpr bool kChannelStage = MODE == SQUANT_MODE_EKC || MODE == SQUANT_MODE_EC;
+  constexpr bool kHalf = WT == SQUANT_W_F16 || WT == SQUANT_W_BF16 || WT == kWHalf;
   const int T = NWC ? NWC * kWave : (int)blockDim.x, tid = threadIdx.x;
   const int wtype = WT == kWHalf ? (a.wtype == SQUANT_W_BF16 ? SQUANT_W_BF16 : SQUANT_W_F16) : WT >= 0 ? WT : a.wtype;
   const float qmaxf = (float)a.qmax;
@@ -483,14 +486,14 @@ __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc
   if (normal) {
     const float rs = reciprocal(s);
     // the largest quotient of the channel: no element needs the clamp unless this one does
-    if (div_by_reciprocal(amax, s, rs) <= qmaxf) k9_solve_all<MODE, KPT, false, false>(w, s, rs, qmaxf, 1.0f, 1.0f, kk, esum, real);
-    else k9_solve_all<MODE, KPT, false, true>(w, s, rs, qmaxf, 1.0f, 1.0f, kk, esum, real);
+    if (div_by_reciprocal(amax, s, rs) <= qmaxf) k9_solve_all<MODE, KPT, false, false, kHalf>(w, s, rs, qmaxf, 1.0f, 1.0f, kk, esum, real);
+    else k9_solve_all<MODE, KPT, false, true, kHalf>(w, s, rs, qmaxf, 1.0f, 1.0f, kk, esum, real);
   } else {
     const float f1 = amax < 1.0f ? 0x1p64f : 0x1p-64f;
     const float a1 = amax * f1;
     const float f2 = a1 < 0x1p-60f ? 0x1p64f : a1 > 0x1p60f ? 0x1p-64f : 1.0f;
     const float s2 = s > 0.0f ? s * f1 * f2 : 0x1p-40f;
-    k9_solve_all<MODE, KPT, true, true>(w, s2, reciprocal(s2), qmaxf, f1, f2, kk, esum, real);
+    k9_solve_all<MODE, KPT, true, true, false>(w, s2, reciprocal(s2), qmaxf, f1, f2, kk, esum, real);
   }
 
   if (kChannelStage) {
