@@ -226,8 +226,7 @@ int launch_part(const Group& g, bool rows, size_t begin, size_t end, int qmax, i
     if (g.variant == kK9Team) { const int per = g.threads / k9_team_lanes(t.N); return (int64_t)(t.M + per - 1) / per; }
     const int64_t items = mixed ? mixed_work_items(t.M, t.N, t.K, threads, t.family)
                                 : route_work_items(t.M, t.N, t.K, threads, t.family, wave_span);
-    const int each = items_per_workgroup(t.family);
-    return (items + each - 1) / each;
+    return ceil_div(items, items_per_workgroup(t.family));
   };
   const int64_t items0 = items_of(g.t[begin]);
   for (size_t i = begin; i < end; ++i) {
@@ -378,14 +377,23 @@ int quantize_batched(const squant_tensor_t* h_tensors, int32_t n_tensors, squant
   const size_t lds_cap = (size_t)lim.lds_bytes - kStaticLds - sizeof(K9Shared) - sizeof(GenericShared);
   int small_kinds = 0;
   Plan small_first{};
+  // Networks repeat their shapes: the plans of the last few are kept for the call.
+  struct Seen { int64_t N = 0, K = 0; bool aligned = false, small = false; Plan p{}; } seen[16];
   for (int32_t i = 0; i < n_tensors; ++i) {
     const squant_tensor_t& t = h_tensors[i];
-    Plan p = plan_tensor(t.w, t.codes, t.cout, t.cin, (int64_t)t.kh * t.kw, lim.lds_bytes);
-    if (p.lds == 0) return SQUANT_ERR_UNSUPPORTED;
-    // LDS size classes: next power of two >= 2 KB keeps the number of launches small
-    size_t cls = 2048;
-    while (cls < p.lds) cls <<= 1;
-    p.lds = std::max(std::min(cls, lds_cap), p.lds);
+    const int64_t N = t.cin, K = (int64_t)t.kh * t.kw;
+    const bool aligned = pointers_aligned(t.w, t.codes), small = t.cout * N * K < kSmallTensor;  // what a plan depends on
+    Seen& last = seen[((uint32_t)N >> 2 ^ (uint32_t)N >> 6 ^ (uint32_t)K ^ (uint32_t)aligned) & 15u];
+    if (last.N != N || last.K != K || last.aligned != aligned || last.small != small) {
+      Plan p = plan_tensor(t.w, t.codes, t.cout, N, K, lim.lds_bytes);
+      if (p.lds == 0) return SQUANT_ERR_UNSUPPORTED;
+      // LDS size classes: next power of two >= 2 KB keeps the number of launches small
+      size_t cls = 2048;
+      while (cls < p.lds) cls <<= 1;
+      p.lds = std::max(std::min(cls, lds_cap), p.lds);
+      last.N = N; last.K = K; last.aligned = aligned; last.small = small; last.p = p;
+    }
+    const Plan& p = last.p;
     plans[(size_t)i] = p;
     if (mixable(p, lds_cap)) {
       if (small_kinds == 0) { small_first = p; small_kinds = 1; }
@@ -421,6 +429,7 @@ int quantize_batched(const squant_tensor_t* h_tensors, int32_t n_tensors, squant
     if (!g) {
       groups.push_back(Group{in_mixed ? mixed_kind : p.variant, in_mixed ? need_threads : p.threads, p.lds, {}});
       g = &groups.back();
+      g->t.reserve((size_t)(n_tensors - i) + (bns ? bns->size() : 0));
     }
     if (in_mixed) {
       // the workgroup size follows the specialised routines (their kernels / vectors per thread

@@ -35,7 +35,9 @@ constexpr int kK1WaveSpan = 4;    // the most consecutive channels a wave of tha
 constexpr int kK1WaveThreads = 256;  // its workgroup in a launch of its own
 constexpr int kMixedMaxThreads = 256;  // largest workgroup of a mixed launch
 
-SQ_HD int64_t round_up64(int64_t v) { return (v + 63) / 64 * 64; }
+SQ_HD int64_t round_up64(int64_t v) { return (v + 63) & ~(int64_t)63; }  // v >= 0
+// ceil(a / b) for 0 <= a < 2^31, 0 < b <= 1024: 32-bit divisions take a host a third of the time of 64-bit ones
+SQ_HD int64_t ceil_div(int64_t a, int64_t b) { return ((uint32_t)a + (uint32_t)b - 1u) / (uint32_t)b; }
 
 // Launch shape of the 1x1 / FC kernel for a channel of nvec 16-byte vectors (at most 8192):
 // T threads of NV vectors each, NV in 1..8 or 16.  Candidates: workgroups of one or two waves
@@ -212,12 +214,11 @@ SQ_HD int ks_kpt_log2(int64_t N, int64_t K) {
   int best = -1;
   int64_t best_num = 0, best_den = 1;
   for (int lg = top; lg >= 0; --lg) {
-    const int64_t c = (int64_t)1 << lg;
-    if (N % c != 0) continue;
-    const int64_t th = round_up64(N / c);
+    if ((N & ((1 << lg) - 1)) != 0) continue;
+    const int64_t num = N >> lg, th = round_up64(num);
     if (th > 1024 || (th > 256 && lg != top)) continue;
-    if (th == 64 && (N / c) * 10 >= th * 6) return lg;
-    if ((N / c) * best_den > best_num * th) { best_num = N / c; best_den = th; best = lg; }
+    if (th == 64 && num * 10 >= th * 6) return lg;
+    if (num * best_den > best_num * th) { best_num = num; best_den = th; best = lg; }
   }
   return best;
 }
@@ -251,10 +252,10 @@ SQ_HD int choose_variant(int64_t N, int64_t K, bool aligned) {
     // (fill = (N / c) / round_up64(N / c), compared by cross-multiplication)
     int best_c = 4;
     int64_t best_num = 0, best_den = 1;
-    for (int c = 4; c >= 1; c >>= 1) {
-      const int64_t th = round_up64(N / c);
+    for (int lg = 2; lg >= 0; --lg) {
+      const int c = 1 << lg;
+      const int64_t num = N >> lg, th = round_up64(num);
       if (th > 256 && c != 4) continue;
-      const int64_t num = N / c;
       if (th == 64 && num * 10 >= th * 6) { best_c = c; break; }
       if (num * best_den > best_num * th) { best_num = num; best_den = th; best_c = c; }
     }
@@ -350,8 +351,9 @@ SQ_HD int variant_of_family(int family, int64_t N, int64_t K, bool aligned) {
   if (family == 9) {  // kernels per thread by the rule of choose_variant
     int best_c = 4;
     int64_t best_num = 0, best_den = 1;
-    for (int c = 4; c >= 1; c >>= 1) {
-      const int64_t used = (N + c - 1) / c, th = round_up64(used);
+    for (int lg = 2; lg >= 0; --lg) {
+      const int c = 1 << lg;
+      const int64_t used = (N + c - 1) >> lg, th = round_up64(used);
       if (th > 256 && c != 4) continue;
       if (th == 64 && used * 10 >= th * 6) { best_c = c; break; }
       if (used * best_den > best_num * th) { best_num = used; best_den = th; best_c = c; }
@@ -383,17 +385,17 @@ SQ_HD int team_lanes(int64_t N) { return N <= 16 ? 4 : N <= 32 ? 8 : 16; }
 // one per channel, except depthwise 3x3 (every thread has a channel of its own), short 1x1
 // channels (one per team of lanes) and 1x1 channels of a wave each (wave_span per wave).  `family` as from choose_family.
 SQ_HD int64_t work_items(int64_t M, int64_t N, int64_t K, int64_t T, int family, int wave_span) {
-  if (family == 3) return (M + T - 1) / T;
-  if (family == 4) { const int64_t per = T / team_lanes(N); return (M + per - 1) / per; }
-  if (family == 6) { const int64_t per = T / 64 * wave_span; return (M + per - 1) / per; }
+  if (family == 3) return ceil_div(M, T);
+  if (family == 4) return ceil_div(M, (uint32_t)T / (uint32_t)team_lanes(N));
+  if (family == 6) return ceil_div(M, (T >> 6) * wave_span);
   (void)K;
   return M;
 }
 
 // The same for every family.
 SQ_HD int64_t route_work_items(int64_t M, int64_t N, int64_t K, int64_t T, int family, int wave_span) {
-  if (family == 7) { const int64_t per = T / dw_team_lanes(K); return (M + per - 1) / per; }
-  if (family == kFamilyStem) { const int64_t per = T / 64; return (M + per - 1) / per; }
+  if (family == 7) return ceil_div(M, (uint32_t)T / (uint32_t)dw_team_lanes(K));
+  if (family == kFamilyStem) return ceil_div(M, T >> 6);
   return work_items(M, N, K, T, family, wave_span);
 }
 
@@ -420,7 +422,7 @@ SQ_HD int items_per_workgroup(int family) { return family == 7 ? kDwLaneElems : 
 
 // In a mixed launch.
 SQ_HD int64_t mixed_work_items(int64_t M, int64_t N, int64_t K, int64_t T, int family) {
-  if (family == kFamilyRows) { const int64_t per = T / k1_rows_team(N); return (M + per - 1) / per; }
+  if (family == kFamilyRows) return ceil_div(M, (uint32_t)T / (uint32_t)k1_rows_team(N));
   return route_work_items(M, N, K, T, family, 1);
 }
 
