@@ -39,7 +39,8 @@ SQ_HD int64_t round_up64(int64_t v) { return (v + 63) & ~(int64_t)63; }  // v >=
 // ceil(a / b) for 0 <= a < 2^31, 0 < b <= 1024: 32-bit divisions take a host a third of the time of 64-bit ones
 SQ_HD int64_t ceil_div(int64_t a, int64_t b) { return ((uint32_t)a + (uint32_t)b - 1u) / (uint32_t)b; }
 
-// Launch shape of the 1x1 / FC kernel for a channel of nvec 16-byte vectors (at most 8192):
+// Launch shape of the 1x1 / FC kernel for a channel of nvec 16-byte vectors (at most 8192), in launches of their own that
+// do without SQuant-C (with it: k1_launch_shape) and where it is asked whether a channel fits a mixed launch:
 // T threads of NV vectors each, NV in 1..8 or 16.  Candidates: workgroups of one or two waves
 // or a whole multiple of four (which spread evenly over the four SIMDs of a compute unit) with
 // NV = ceil(nvec / T) up to 8, and sixteen vectors in the fewest waves that cover the channel
