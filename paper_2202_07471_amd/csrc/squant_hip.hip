@@ -429,7 +429,7 @@ int quantize_batched(const squant_tensor_t* h_tensors, int32_t n_tensors, squant
     if (!g) {
       groups.push_back(Group{in_mixed ? mixed_kind : p.variant, in_mixed ? need_threads : p.threads, p.lds, {}});
       g = &groups.back();
-      g->t.reserve((size_t)(n_tensors - i) + (bns ? bns->size() : 0));
+      g->t.reserve(std::min((size_t)(n_tensors - i) + (bns ? bns->size() : 0), (size_t)kInlineDescs));
     }
     if (in_mixed) {
       // the workgroup size follows the specialised routines (their kernels / vectors per thread
