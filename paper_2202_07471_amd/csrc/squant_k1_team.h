@@ -17,10 +17,16 @@
 // team-wide maximum, and the lane that holds it moves on to its next key.  The
 // wave loops until every one of its teams has its `need` elements or runs out of
 // candidates (typically 2-6 steps: need = round(|sum of cin perturbations|)).
+//
+// Bound by vector instructions.  The scale, its reciprocal, rounding, packing and keys are those of the 3x3 kernel (three-operation
+// forms, a magic addition that leaves the code in a byte, biased perturbations); with divisions, a conversion per code and
+// element-wise 16-bit stores before, 20 M weights took, us before and now: cin 128 bfloat16 to 4 bit 27.2 and 24.7, 200 to int8 32.9 and
+// 29.9, 256 27.3 and 24.4, 181 binary32 25.3 and 22.9, 64 25.8 and 25.0; ResNet-50 set of 0.71 times the width 21.0 and 20.7.
 #pragma once
 
 #include "squant_common.h"
 #include "squant_io.h"
+#include "squant_k9.h"  // rounding constants, pack_low_bytes
 #include "squant_plan.h"
 
 namespace squant {
@@ -76,6 +82,7 @@ __device__ __forceinline__ int32_t team_sum_i32(int32_t x) {  // modulo 2^32
 }
 
 typedef uint32_t u32_byte __attribute__((aligned(1)));
+typedef uint32_t u32_half __attribute__((aligned(2)));
 typedef uint16_t u16_byte __attribute__((aligned(1)));
 
 // `item` is the workgroup's index within the tensor: it covers blockDim.x / TEAM channels.
@@ -141,63 +148,76 @@ __device__ __forceinline__ void k1_team_channels(const LaunchArgs& a, const Tens
 
   float amax = 0.0f;
 #pragma unroll
-  for (int e = 0; e < NE; ++e) amax = fmaxf(amax, fabsf(w[e]));
+  for (int e = 0; e < NE; e += 2) amax = fmaxf(fmaxf(amax, fabsf(w[e])), fabsf(w[e + 1]));
   amax = team_max_f32<TEAM>(amax);
-  const float s = amax > 0.0f ? amax / qmaxf : 1.0f;
-  if (live && l == 0) d.scales[channel] = s;
   // the reciprocal path only where every team of the wave is in its range (same quotients
   // either way; the choice must be the same for the whole wave)
-  const bool fast = __ballot(!(amax >= 0x1p-60f && amax <= 0x1p60f) && amax > 0.0f) == 0ull;
-  const float rs = 1.0f / s;
-
-  float cf[NE];      // codes
-  int32_t P[NE];     // perturbations, Q23
-  int32_t esum = 0;
+  const bool fast = __ballot(!scale_is_normal(amax)) == 0ull;
+  const float s = channel_scale(amax, qmaxf, a.rcp_qmax, fast);
+  if (live && l == 0) d.scales[channel] = s;
+  if (fast) {
+    const float rs = reciprocal(s);
 #pragma unroll
-  for (int e = 0; e < NE; ++e) {
-    const float x = fast ? div_by_reciprocal(w[e], s, rs) : quotient(w[e], s);  // the IEEE quotient either way
-    const float xc = __builtin_amdgcn_fmed3f(x, -qmaxf, qmaxf);
-    cf[e] = rintf(xc);
-    if (kChannelStage) {
-      const float p = cf[e] - xc;  // exact
-      P[e] = __float_as_int(__builtin_fmaf(p, 8388608.0f, 12582912.0f)) - 0x4B400000;
-      esum += P[e];
+    for (int e = 0; e < NE; ++e) w[e] = div_by_reciprocal(w[e], s, rs);  // the IEEE quotient either way
+  } else {
+#pragma unroll
+    for (int e = 0; e < NE; ++e) w[e] = quotient(w[e], s);
+  }
+
+  // SQuant-E as in k9_round: codes + 128, four to a dword, and biased perturbations
+  uint32_t code[NV], pb[NE], biased = 0;
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    uint32_t tb[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float xc = __builtin_amdgcn_fmed3f(w[4 * j + e], -qmaxf, qmaxf);
+      const float t = xc + kRoundMagic;
+      tb[e] = __float_as_uint(t);
+      if (kChannelStage) {
+        pb[4 * j + e] = __float_as_uint(__builtin_fmaf((t - kRoundMagic) - xc, 8388608.0f, kQ23Magic));
+        biased += pb[4 * j + e];
+      }
     }
+    code[j] = pack_low_bytes(tb[0], tb[1], tb[2], tb[3]);
   }
 
   if (kChannelStage) {
-    const int32_t ec = team_sum_i32<TEAM>(esum);
+    const int32_t ec = team_sum_i32<TEAM>((int32_t)(biased - (uint32_t)NE * kQ23Bias));
     const int32_t mag = ec < 0 ? -ec : ec;
     const int32_t kc = (int32_t)flips_for(mag);
     uint32_t need = (uint32_t)(kc > N ? N : kc);  // the same in every lane of a team
-    const int32_t smask = ec >> 31;
-    // unique keys: |P| above 255 - index for the elements with the sign of the sum, else 0
+    // unique keys: |P| above 255 - index for the elements with the sign of the sum, below 256 for the others
+    const uint32_t sm = (uint32_t)(ec >> 31), zero = kQ23Bias ^ sm;  // pb ^ sm - zero: P for a positive sum, -P for a negative one
     uint32_t key[NE];
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
-      const int32_t u = (P[e] ^ smask) - smask;  // P for a positive sum, -P for a negative one
-      const int n = 4 * (l + (e >> 2) * TEAM) + (e & 3);
-      key[e] = u > 0 ? ((uint32_t)u << 8) | (uint32_t)(255 - n) : 0u;
+      const uint32_t n = 4 * (uint32_t)(l + (e >> 2) * TEAM) + (e & 3);
+      key[e] = (__builtin_elementwise_sub_sat(pb[e] ^ sm, zero) << 8) | (255u - n);
     }
-    // Every lane offers its largest key not yet taken, 0 when all are; each step takes the largest
+    // Every lane offers its largest key not yet taken; each step takes the largest
     // offer of the team, and its lane moves on to its next key: 1.5 instructions an element and step.
     // (Marking the element and clearing its key in every step took four; cin 180: 26.6 -> 22.5 us for
     // 64 x [1024, 180].)
     uint32_t offer = 0, taken = ~0u;  // taken: the lane's smallest key that flips
 #pragma unroll
-    for (int e = 0; e < NE; ++e) offer = umax2(offer, key[e]);
+    for (int e = 0; e < NE; e += 2) offer = umax3(offer, key[e], key[e + 1]);
     while (__ballot(need > 0) != 0ull) {
       const uint32_t m = team_max_u32<TEAM>(offer);
-      const bool take = need > 0 && m != 0;
+      const bool take = need > 0 && m >= 256u;
       const uint32_t next = next_key_below(key, offer);
       const bool mine = take && offer == m;
       taken = mine ? m : taken;
       offer = mine ? next : offer;
       need = take ? need - 1 : 0u;  // out of candidates: this team is done
     }
-    const float step = smask ? 1.0f : -1.0f;  // one step against the sum
 #pragma unroll
-    for (int e = 0; e < NE; ++e) cf[e] += key[e] >= taken ? step : 0.0f;
+    for (int j = 0; j < NV; ++j) {
+      uint32_t hit = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) hit |= key[4 * j + e] >= taken ? 1u << (8 * e) : 0u;
+      code[j] -= (hit ^ sm) - sm;  // one step against the sum; no carry leaves a biased byte
+    }
   }
 
   if (!live) return;
@@ -207,34 +227,39 @@ __device__ __forceinline__ void k1_team_channels(const LaunchArgs& a, const Tens
     if (idx >= nvec) continue;
     const size_t at = (size_t)channel * N + 4 * (size_t)idx;  // first element of this vector
     const int left = TAIL ? N - 4 * idx : 4;                  // elements of it inside the row
+    const bool whole = !TAIL || left >= 4;
     if (a.out_format == SQUANT_OUT_INT8) {
-      uint32_t packed = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) packed = __builtin_amdgcn_cvt_pk_u8_f32(cf[4 * j + e] + 128.0f, e, packed);
-      packed ^= 0x80808080u;
+      uint32_t packed = code[j] ^ 0x80808080u;
       int8_t* out = static_cast<int8_t*>(d.out) + at;
       if (!TAIL) store_global_u1(out, packed);
-      else if (left >= 4) *reinterpret_cast<u32_byte*>(out) = packed;
+      else if (whole) *reinterpret_cast<u32_byte*>(out) = packed;
       else
         for (int e = 0; e < left; ++e) out[e] = (int8_t)(packed >> (8 * e));
     } else if (a.out_format == SQUANT_OUT_INT4) {
-      uint32_t packed = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) packed |= ((uint32_t)(int)cf[4 * j + e] & 0xFu) << (4 * e);
+      const uint32_t packed = pack_nibbles4(code[j]);
       uint8_t* out = static_cast<uint8_t*>(d.out) + (size_t)channel * ((N + 1) / 2) + 2 * (size_t)idx;
       if (!TAIL) store_global_u16(out, (uint16_t)packed);
       else if (left >= 3) *reinterpret_cast<u16_byte*>(out) = (uint16_t)packed;
       else out[0] = (uint8_t)packed;
-    } else if (a.out_format == SQUANT_OUT_BF16) {
-      uint16_t* out = static_cast<uint16_t*>(d.out) + at;
+    } else {
+      const vf4 v = dequant4(code[j], s);
+      if (a.out_format == SQUANT_OUT_BF16) {
+        uint16_t* out = static_cast<uint16_t*>(d.out) + at;
+        if (whole) {
+          const uint32_t lo = bf16_bits(v.x) | (bf16_bits(v.y) << 16), hi = bf16_bits(v.z) | (bf16_bits(v.w) << 16);
+          reinterpret_cast<u32_half*>(out)[0] = lo;
+          reinterpret_cast<u32_half*>(out)[1] = hi;
+        } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (!TAIL || e < left) out[e] = (uint16_t)bf16_bits((cf[4 * j + e] + 0.0f) * s);  // code -0 is 0
-    } else {  // SQUANT_OUT_F32
-      float* out = static_cast<float*>(d.out) + at;
+          for (int e = 0; e < 3; ++e)
+            if (e < left) out[e] = (uint16_t)bf16_bits(v[e]);
+        }
+      } else {  // SQUANT_OUT_F32
+        float* out = static_cast<float*>(d.out) + at;
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (!TAIL || e < left) out[e] = (cf[4 * j + e] + 0.0f) * s;  // code -0 is 0
+        for (int e = 0; e < 4; ++e)
+          if (whole || e < left) out[e] = v[e];
+      }
     }
   }
 }
