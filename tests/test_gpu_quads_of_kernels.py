@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import oracle
+import routes
 
 pytestmark = pytest.mark.gpu
 
@@ -76,11 +77,21 @@ def test_in_a_mixed_launch(sq, dtype):
                 check(sq, w, c, s, mode, sq.OUT_INT4)
 
 
-def test_a_launch_of_many_channels(sq):
-    """From 32768 binary32 channels on, the 3x3 kernel stores single kernels."""
-    w = torch.randn((33000, 272, 3, 3), generator=torch.Generator().manual_seed(4)).cuda()
+@pytest.mark.parametrize("cin", [400, 512])
+def test_a_launch_of_many_channels(sq, cin):
+    """From 32768 workgroups on, aligned binary32 channels of four kernels a thread in two waves are stored kernel by
+    kernel: in a launch of their own and in a mixed one."""
+    most = 32768
+    assert routes.routes([(most, cin, 3, 3)]) == [(routes.K9, 4, 128)]
+    w = torch.randn((most, cin, 3, 3), generator=torch.Generator(device="cuda").manual_seed(cin), device="cuda")
     out, s = sq.squant_quantize_ex(w, 4, sq.MODE_EKC, sq.OUT_INT8)
-    few, few_s = sq.squant_quantize_ex(w[:500], 4, sq.MODE_EKC, sq.OUT_INT8)
-    check(sq, w[:500], few, few_s, sq.MODE_EKC, sq.OUT_INT8)
-    check(sq, w[-500:], out[-500:], s[-500:], sq.MODE_EKC, sq.OUT_INT8)
-    assert torch.equal(out[:500], few) and torch.equal(s[:500], few_s)
+    few, few_s = sq.squant_quantize_ex(w[:most - 1], 4, sq.MODE_EKC, sq.OUT_INT8)   # whole dwords
+    assert torch.equal(out[:most - 1], few) and torch.equal(s[:most - 1], few_s)
+    other = torch.randn((64, 256, 1, 1), device="cuda")
+    for mode in (sq.MODE_E, sq.MODE_EK, sq.MODE_EKC, sq.MODE_EC):
+        codes, scales = sq.BatchPlan([w, other]).run(4, mode)
+        check(sq, other, codes[1], scales[1], mode, sq.OUT_INT8)
+        out, s = sq.squant_quantize_ex(w, 4, mode, sq.OUT_INT8)
+        assert torch.equal(out, codes[0]) and torch.equal(s, scales[0])
+        for rows in (slice(0, 200), slice(most - 200, most)):
+            check(sq, w[rows], out[rows], s[rows], mode, sq.OUT_INT8)
