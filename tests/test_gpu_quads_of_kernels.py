@@ -45,11 +45,11 @@ COUNTS = [2, 3, 5, 6, 7, 31, 62, 63, 65, 66, 127, 129, 130, 131, 135, 152, 200, 
 @pytest.mark.parametrize("kind", ["normal", "levels", "equal"])
 def test_alone(sq, kh, kw, kind):
     gen = torch.Generator().manual_seed(kh * 8 + kw)
-    for i, cin in enumerate(COUNTS):
-        cout = max(3, min(40, -(-17000 // (cin * kh * kw))))   # no small tensor: those may go elsewhere
-        if i % 3 == 0:
-            cout |= 1
-        w = weights((cout, cin, kh, kw), kind, gen).to(torch.float32 if i % 2 else torch.float16).cuda()
+    # no small tensor: odd counts of those stay with the generic routine
+    shapes = [(routes.enough(cin, kh * kw, 3) | (1 if i % 3 == 0 else 0), cin, kh, kw) for i, cin in enumerate(COUNTS)]
+    assert {family for family, _, _ in routes.routes(shapes)} == {routes.K9 if kh * kw == 9 else routes.SMALL}
+    for i, shape in enumerate(shapes):
+        w = weights(shape, kind, gen).to(torch.float32 if i % 2 else torch.float16).cuda()
         for mode in (sq.MODE_E, sq.MODE_EK, sq.MODE_EKC, sq.MODE_EC):
             output = sq.OUT_INT4 if (i + mode) % 2 else sq.OUT_INT8
             out, s = sq.squant_quantize_ex(w, 4, mode, output)
@@ -68,7 +68,9 @@ def test_most_kernels_a_thread(sq):
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
 def test_in_a_mixed_launch(sq, dtype):
     gen = torch.Generator().manual_seed(2)
-    shapes = [(20, n, 1, k) for n in (67, 130, 258, 301, 500) for k in (2, 3, 5, 7)] + [(20, n, 3, 3) for n in (5, 66, 131, 255, 512)]
+    shapes = [(routes.enough(n, k, 20), n, 1, k) for n in (3, 31, 67, 130, 258, 301, 500) for k in (2, 3, 5, 7)]
+    shapes += [(routes.enough(n, 9, 20), n, 3, 3) for n in (5, 66, 131, 255, 512)]
+    assert [family for family, _, _ in routes.routes(shapes)] == [routes.SMALL] * 28 + [routes.K9] * 5
     for kind in ("normal", "levels"):
         ws = [weights(s, kind, gen).to(dtype).cuda() for s in shapes]
         for mode in (sq.MODE_EK, sq.MODE_EKC, sq.MODE_EC):
