@@ -20,5 +20,5 @@ int main() {
         ++shapes;
       }
   std::printf("shape_mismatches=%ld shapes=%ld\n", bad, shapes);
-  return 0;
+  return bad != 0;
 }
