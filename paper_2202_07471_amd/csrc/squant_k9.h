@@ -122,13 +122,16 @@ __device__ __forceinline__ uint32_t k9_zero_sum_sign(const uint32_t (&pb)[9]) {
 
 // SQuant-K and the perturbation update for one kernel (Algorithm 2 on the kernel,
 // Algorithm 3): the flip mask, the sign, the candidate; esum += the kernel's Q23
-// perturbation sum after SQuant-K.  real: the lanes that hold a kernel; the others (zeros) are kept
-// from the work on sums of 0, which is rare otherwise: one kernel in 800 with bfloat16 weights, in
-// 25 thousand with binary16, next to none with binary32.  (Such candidates were worked out from the weights in memory
-// before, one load after the other, in a loop over the thread's kernels: 64 x [512, 512, 3, 3] bfloat16 to 4 bit
-// 107 -> 101.6 us, 4 x [255, 248, 3, 3] binary16 10.2 -> 6.6, ResNet-18 set in bfloat16 17.9 -> 14.5.)
-template <int MODE>
-__device__ __forceinline__ void k9_flip(const uint32_t (&pb)[9], K9Kernel& kk, int32_t& esum, lanemask_t real) {
+// perturbation sum after SQuant-K; returns |sum before SQuant-K|.
+//   ZERO   the candidate of a kernel whose sum is 0 is settled here, from registers.  Such kernels are one in 800
+//          with bfloat16 weights, one in 25 thousand with binary16 and next to none with binary32.  In 16 bits
+//          k9_recheck_kernel would come often and waits for one load after the other (64 x [512, 512, 3, 3] bfloat16 to
+//          4 bit 107 us with it, 101.6 so, 4 x [255, 248, 3, 3] binary16 10.2 and 6.6, ResNet-18 set in bfloat16 17.9 and
+//          14.5); in 32 bits the branch per kernel costs more (100 M weights in channels of 181 kernels, E&C, 88.0 us with
+//          it and 84.5 with neither).
+//   real   the lanes that hold a kernel; the others (zeros) are kept from that work.
+template <int MODE, bool ZERO>
+__device__ __forceinline__ uint32_t k9_flip(const uint32_t (&pb)[9], K9Kernel& kk, int32_t& esum, lanemask_t real = 0) {
   constexpr bool kCand = MODE == SQUANT_MODE_EKC || MODE == SQUANT_MODE_EC;
   uint32_t eb = 0;
 #pragma unroll
@@ -136,7 +139,7 @@ __device__ __forceinline__ void k9_flip(const uint32_t (&pb)[9], K9Kernel& kk, i
   const int32_t E = (int32_t)(eb - 9u * kQ23Bias);
   uint32_t sm = (uint32_t)(E >> 31);  // all ones when the sum is negative
   const uint32_t A = ((uint32_t)E ^ sm) - sm;  // |E|
-  if (kCand) {
+  if (kCand && ZERO) {
     const lanemask_t zero = lanes_eq(A, 0u) & real;
     if (__builtin_expect(zero != 0, 0)) sm = vsel(zero, k9_zero_sum_sign(pb), sm);
   }
@@ -160,7 +163,7 @@ __device__ __forceinline__ void k9_flip(const uint32_t (&pb)[9], K9Kernel& kk, i
     const int32_t rel = (int32_t)(ck - base);
     kk.cand = vsel(lanes_sge(rel, 32), ((uint32_t)rel >> 5) | (sm & (1u << 23)), kNoCandidate);
     kk.cand_bit = 0x80000000u >> (ck & 31u);
-    return;
+    return A;
   }
 
   const uint32_t tt = A + (uint32_t)(kHalf - 1);  // k = tt >> 23 (an exact half rounds down)
@@ -194,7 +197,7 @@ __device__ __forceinline__ void k9_flip(const uint32_t (&pb)[9], K9Kernel& kk, i
     }
   }
   kk.flips = flips;
-  if (!kCand) return;
+  if (!kCand) return A;
 
   // ---- perturbation update (Algorithm 3): the kernel's candidate for SQuant-C ----
   const lanemask_t over = lanes_slt(r, 0);
@@ -207,6 +210,7 @@ __device__ __forceinline__ void k9_flip(const uint32_t (&pb)[9], K9Kernel& kk, i
   const uint32_t word = vsel(over, ((2u << 23) - sbit) - mag, mag | sbit);
   kk.cand = vsel(lanes_sge(rel, 32), word, kNoCandidate);
   kk.cand_bit = 0x80000000u >> (ck & 31u);
+  return A;
 }
 
 // Moves the elements named by the flip mask one step against the kernel's sign: on the
@@ -217,6 +221,32 @@ __device__ __forceinline__ void k9_apply_flips(K9Kernel& kk) {
   kk.d0 -= (b0 ^ kk.sm) - kk.sm;
   kk.d1 -= (b1 ^ kk.sm) - kk.sm;
   kk.d2 -= (b2 ^ kk.sm) - kk.sm;
+}
+
+// Cold path (a rolled loop) for a thread of binary32 weights that saw a kernel whose perturbation sum is exactly
+// zero (see k9_zero_sum_sign): such a kernel has k = 0, so its perturbations are those of plain rounding and are
+// recomputed here from the weights in memory; returns (sum is zero, candidate perturbation, element index).
+__device__ __forceinline__ int3 k9_recheck_kernel(const float* w, float s, float qmaxf) {
+  int32_t best = 0, bv = 0, sum = 0;
+  int bi = 0;
+#pragma unroll 1
+  for (int i = 0; i < 9; ++i) {
+    int32_t P;
+    round_and_perturb(w[i], s, qmaxf, P);
+    const int32_t ap = P < 0 ? -P : P;
+    sum += P;
+    if (ap > best) { best = ap; bv = P; bi = i; }
+  }
+  return make_int3(sum == 0 ? 1 : 0, bv, bi);
+}
+
+// The candidate of a zero-sum kernel into the kernel's record: flipping it moves the element
+// against its own sign, so that sign becomes the kernel's (the flip mask is empty, so the
+// sign has had no other use).
+__device__ __forceinline__ void k9_set_zero_sum_candidate(K9Kernel& kk, int32_t v, int index) {
+  kk.cand = candidate_word(v);
+  kk.cand_bit = 1u << index;
+  kk.sm = v < 0 ? ~0u : 0u;
 }
 
 // Kernel q of a thread: nine floats at `base` (uniform, the channel's kernels q*G ...)
@@ -379,12 +409,14 @@ __device__ __forceinline__ void k9_channel_flip(K9Kernel (&kk)[KPT], int64_t ec,
 // SQuant-E and SQuant-K on all the kernels of a thread.
 //   PRESCALE  the weights are first multiplied by the powers of two f1 and f2 (and s, rs are
 //             those of the scaled channel): see k9_channel
+//   TWO       quotients in two operations: 16-bit weights under a scale in the range of the proof
+//   HALF      16-bit weights; binary32: amin becomes the smallest |sum| before SQuant-K of the `owned` kernels (bit q)
 //   real      lanes that have a kernel q of their own (others hold zeros and leave no trace)
-template <int MODE, int KPT, bool PRESCALE, bool CLAMP, bool HALF>
+template <int MODE, int KPT, bool PRESCALE, bool CLAMP, bool TWO, bool HALF>
 __device__ __forceinline__ void k9_solve_all(const float (&w)[9 * KPT], float s, float rs, float qmaxf,
                                              float f1, float f2, K9Kernel (&kk)[KPT], int32_t& esum,
-                                             const lanemask_t (&real)[KPT]) {
-  const float rl = HALF ? reciprocal_low(s, rs) : 0.0f;
+                                             const lanemask_t (&real)[KPT], uint32_t owned, uint32_t& amin) {
+  const float rl = TWO ? reciprocal_low(s, rs) : 0.0f;
 #pragma unroll
   for (int q = 0; q < KPT; ++q) {
     // A branch that is always taken (s is finite) but that the compiler cannot fold: it makes
@@ -400,32 +432,35 @@ __device__ __forceinline__ void k9_solve_all(const float (&w)[9 * KPT], float s,
       x[i] = PRESCALE ? w[9 * q + i] * f1 * f2 : w[9 * q + i];
     }
     uint32_t pb[9];
-    k9_round<true, CLAMP, HALF>(x, s, rs, qmaxf, kk[q], pb, rl);
+    k9_round<true, CLAMP, TWO>(x, s, rs, qmaxf, kk[q], pb, rl);
     if (MODE != SQUANT_MODE_E) {
-      k9_flip<MODE>(pb, kk[q], esum, real[q]);
+      const uint32_t sum = k9_flip<MODE, HALF>(pb, kk[q], esum, real[q]);
+      if (!HALF) amin = umin2(amin, (owned >> q) & 1u ? sum : ~0u);
       if (MODE == SQUANT_MODE_EK) k9_apply_flips(kk[q]);
     }
   }
 }
 
-constexpr int kWHalf = 3;
+constexpr int kWHalf = 3;  // weight type of a kernel: binary16 or bfloat16, the launch says which
 
 // One workgroup per output channel.  Thread t owns the KPT 3x3 kernels t, t + G, t + 2G, ...
 // (G = cin / KPT); KPT is 4 for wide layers and 2 or 1 for narrow ones, so that the waves
 // stay full.
-//   WT   the weight type when it is known at compile time (squant_wtype_t; kWHalf: one of the
-//        16-bit types), -1: the launch's
+//   WT   the weight type: SQUANT_W_F32, one of the 16-bit types, or kWHalf.  One routine for both widths waits for the
+//        weights before it clears the histogram (registers of one width's loads are written under the other's) and takes 65
+//        instead of 63 registers with SQuant-E alone, one workgroup of 1024 threads a compute unit instead of two: 20 M binary32
+//        weights in channels of 33 kernels, E&K&C, 37.9 us with one routine and 36.5 so, of 48 28.1 and 27.1, 100 M with E in
+//        channels of 4096 kernels 77.2 and 68.2, binary16 63.5 and 49.5.
 //   NWC  the waves per workgroup when known at compile time, 0: the launch's
 //   ANY  any cin and any alignment: G = ceil(cin / KPT), in whole fours, the kernels past the channel's end read
 //        as zeros through the range of the row's descriptor, and the row is written through one.
 //        (Otherwise cin is a multiple of four, weights start on 16 bytes and codes on four.)
-template <int MODE, int KPT, int WT = -1, int NWC = 0, bool ANY = false>
+template <int MODE, int KPT, int WT, int NWC = 0, bool ANY = false>
 __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc& d, int m,
                                            unsigned char* smem, K9Shared& sh) {
   constexpr bool kChannelStage = MODE == SQUANT_MODE_EKC || MODE == SQUANT_MODE_EC;
-  constexpr bool kHalf = WT == SQUANT_W_F16 || WT == SQUANT_W_BF16 || WT == kWHalf;
+  constexpr bool kHalf = WT != SQUANT_W_F32;
   const int T = NWC ? NWC * kWave : (int)blockDim.x, tid = threadIdx.x;
-  const int wtype = WT == kWHalf ? (a.wtype == SQUANT_W_BF16 ? SQUANT_W_BF16 : SQUANT_W_F16) : WT >= 0 ? WT : a.wtype;
   const float qmaxf = (float)a.qmax;
   uint8_t* code8 = reinterpret_cast<uint8_t*>(smem);  // biased codes: code + 128
 
@@ -440,26 +475,27 @@ __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc
     for (int q = KPT == 1 ? 1 : 0; q < KPT; ++q) owned &= tid + q * G < N ? ~0u : ~(1u << q);
   }
   float w[9 * KPT];
-  if (wtype == SQUANT_W_F32 && !ANY) {
+  K9Raw16 raw[KPT];
+  if (!kHalf && !ANY) {
     const float* src = static_cast<const float*>(d.w) + (size_t)m * L;
 #pragma unroll
     for (int q = 0; q < KPT; ++q) k9_load_kernel(w, q, src + (size_t)q * (9 * G), 9u * (uint32_t)t);
   } else {
-    const uint32_t each = wtype == SQUANT_W_F32 ? 36u : 18u;  // bytes of a kernel
+    constexpr uint32_t each = kHalf ? 18u : 36u;  // bytes of a kernel
     const rsrc_t row = make_rsrc(static_cast<const uint8_t*>(d.w) + (size_t)m * N * each, each * (uint32_t)N);
     const uint32_t lane_off = active ? each * (uint32_t)tid : 0x40000000u;  // idle threads: out of range
-    if (wtype == SQUANT_W_F32) {
 #pragma unroll
-      for (int q = 0; q < KPT; ++q) k9_load_kernel_row(w, q, row, lane_off, each * (uint32_t)(q * G));
-    } else {
-      K9Raw16 raw[KPT];
-#pragma unroll
-      for (int q = 0; q < KPT; ++q) raw[q] = k9_load_kernel16(row, lane_off, each * (uint32_t)(q * G));
-      if (wtype == SQUANT_W_BF16) k9_widen16<true>(raw, w);
-      else k9_widen16<false>(raw, w);
+    for (int q = 0; q < KPT; ++q) {
+      if (kHalf) raw[q] = k9_load_kernel16(row, lane_off, each * (uint32_t)(q * G));
+      else k9_load_kernel_row(w, q, row, lane_off, each * (uint32_t)(q * G));
     }
   }
-  if (kChannelStage) k9_select_reset<NWC>(sh.sel);  // before the first barrier
+  if (kChannelStage) k9_select_reset<NWC>(sh.sel);  // before the first barrier, and while the weights are on their way
+  if (kHalf) {
+    if (WT == SQUANT_W_BF16 || (WT == kWHalf && a.wtype == SQUANT_W_BF16)) k9_widen16<true>(raw, w);
+    else k9_widen16<false>(raw, w);
+    weights_are_here();
+  }
 
   float amax = 0.0f;
 #pragma unroll
@@ -472,9 +508,10 @@ __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc
 
   K9Kernel kk[KPT];
   int32_t esum = 0;
+  uint32_t amin = ~0u;  // binary32: the smallest |kernel sum| of this thread, 0 flags an exact-zero kernel
   lanemask_t real[KPT];
 #pragma unroll
-  for (int q = 0; q < KPT; ++q) real[q] = ANY ? __ballot((owned >> q) & 1u) : wtype == SQUANT_W_F32 ? ~0ull : __ballot(active);
+  for (int q = 0; q < KPT; ++q) real[q] = !kHalf ? 0ull : ANY ? __ballot((owned >> q) & 1u) : __ballot(active);
   // The quotients w / s go through the reciprocal of s, which is proven exact while nothing
   // under- or overflows on the way: absmax within [2^-60, 2^60].  A channel outside that range
   // is first scaled by a power of two, weights and scale alike (exact, and the quotients are
@@ -486,17 +523,25 @@ __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc
   if (normal) {
     const float rs = reciprocal(s);
     // the largest quotient of the channel: no element needs the clamp unless this one does
-    if (div_by_reciprocal(amax, s, rs) <= qmaxf) k9_solve_all<MODE, KPT, false, false, kHalf>(w, s, rs, qmaxf, 1.0f, 1.0f, kk, esum, real);
-    else k9_solve_all<MODE, KPT, false, true, kHalf>(w, s, rs, qmaxf, 1.0f, 1.0f, kk, esum, real);
+    if (div_by_reciprocal(amax, s, rs) <= qmaxf) k9_solve_all<MODE, KPT, false, false, kHalf, kHalf>(w, s, rs, qmaxf, 1.0f, 1.0f, kk, esum, real, ANY ? owned : ~0u, amin);
+    else k9_solve_all<MODE, KPT, false, true, kHalf, kHalf>(w, s, rs, qmaxf, 1.0f, 1.0f, kk, esum, real, ANY ? owned : ~0u, amin);
   } else {
     const float f1 = amax < 1.0f ? 0x1p64f : 0x1p-64f;
     const float a1 = amax * f1;
     const float f2 = a1 < 0x1p-60f ? 0x1p64f : a1 > 0x1p60f ? 0x1p-64f : 1.0f;
     const float s2 = s > 0.0f ? s * f1 * f2 : 0x1p-40f;
-    k9_solve_all<MODE, KPT, true, true, false>(w, s2, reciprocal(s2), qmaxf, f1, f2, kk, esum, real);
+    k9_solve_all<MODE, KPT, true, true, false, kHalf>(w, s2, reciprocal(s2), qmaxf, f1, f2, kk, esum, real, ANY ? owned : ~0u, amin);
   }
 
   if (kChannelStage) {
+    if (!kHalf && amin == 0u && active) {
+#pragma unroll
+      for (int q = 0; q < KPT; ++q) {
+        if (ANY && !((owned >> q) & 1u)) continue;
+        const int3 z = k9_recheck_kernel(static_cast<const float*>(d.w) + (size_t)m * L + 9 * (t + q * G), s, qmaxf);
+        if (z.x) k9_set_zero_sum_candidate(kk[q], z.y, z.z);
+      }
+    }
     // candidates into the histogram before the wanted sign is known: one barrier then
     // publishes the partial sums and the histogram
     if (active) {
@@ -527,7 +572,7 @@ __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc
 
 // Compiled for five waves per SIMD (at most 102 VGPRs): left alone, the scheduler interleaves
 // the four kernels of a thread further than the register file pays for.
-template <int MAX_THREADS, int MODE, int KPT, int WT = -1, int NWC = 0, bool ANY = false>
+template <int MAX_THREADS, int MODE, int KPT, int WT, int NWC = 0, bool ANY = false>
 __global__ void __launch_bounds__(MAX_THREADS) __attribute__((amdgpu_waves_per_eu(5)))
     squant_channel_k9(LaunchArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];  // 9*N bytes of codes
@@ -570,7 +615,7 @@ __device__ __forceinline__ void dw9_channels(const LaunchArgs& a, const TensorDe
   k9_round<false>(w, s, 0.0f, qmaxf, kk, pb);
   if (MODE != SQUANT_MODE_E) {
     int32_t esum = 0;
-    k9_flip<KM>(pb, kk, esum, 0ull);  // a sum of 0 flips nothing here
+    k9_flip<KM, false>(pb, kk, esum);  // a sum of 0 flips nothing here
     if (MODE == SQUANT_MODE_EC) {
       // the channel is this kernel: its candidate has the sign of the sum (none if the sum is 0)
       const int32_t mag = esum < 0 ? -esum : esum;

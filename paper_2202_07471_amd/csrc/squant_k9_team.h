@@ -76,7 +76,7 @@ __device__ __forceinline__ void k9_team_channels(const LaunchArgs& a, const Tens
   else k9_round<false>(w, s, 0.0f, qmaxf, kk, pb);
   if (MODE != SQUANT_MODE_E) {
     int32_t esum = 0;
-    k9_flip<MODE>(pb, kk, esum, __ballot(live));
+    k9_flip<MODE, true>(pb, kk, esum, __ballot(live));
     if (kChannelStage) {
       const int32_t ec = k9_team_sum<TEAM>(esum);  // lanes without a kernel: 0
       const int32_t smask = ec >> 31;

@@ -15,7 +15,7 @@ typedef void (*kernel_t)(LaunchArgs);
 // no whole number of 16-byte vectors, any: some channel count is no multiple of four or some
 // buffer off its alignment.
 kernel_t k9_kernel(int kpt, int threads, int mode, int wtype, bool any);
-kernel_t k9_any_kernel(int kpt, int threads, int mode);
+kernel_t k9_any_kernel(int kpt, int threads, int mode, int wtype);
 kernel_t k9_team_kernel(int mode);
 kernel_t dw9_kernel(int mode);
 kernel_t dw_team_kernel(int mode);
