@@ -256,7 +256,7 @@ int launch_part(const Group& g, bool rows, size_t begin, size_t end, int qmax, i
   a.wtype = wtype;
   a.wave_span = wave_span;
   const int nv = k1_variant_nv(g.variant);
-  const kernel_t kernel = is_ks(g.variant) ? ks_kernel(ks_variant_k(g.variant), ks_variant_kpt(g.variant), g.threads, mode)
+  const kernel_t kernel = is_ks(g.variant) ? ks_kernel(ks_variant_k(g.variant), ks_variant_kpt(g.variant), g.threads, mode, wtype)
                           : mixed ? mixed_kernel(mode, wtype, any)
                           : rows ? k1_rows_kernel(kWave / wave_span, k1_rows_nv(g.t[begin].N), mode, wtype, tail)
                           : is_k1_wave(g.variant) ? k1_wave_kernel(g.variant - kK1Wave, mode, wtype, tail)

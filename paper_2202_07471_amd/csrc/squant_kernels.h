@@ -19,7 +19,7 @@ kernel_t k9_any_kernel(int kpt, int threads, int mode, int wtype);
 kernel_t k9_team_kernel(int mode);
 kernel_t dw9_kernel(int mode);
 kernel_t dw_team_kernel(int mode);
-kernel_t ks_kernel(int K, int kpt, int threads, int mode);
+kernel_t ks_kernel(int K, int kpt, int threads, int mode, int wtype);
 kernel_t k1_kernel(int nv, int mode, int wtype, bool tail);
 kernel_t k1_wave_kernel(int nv, int mode, int wtype, bool tail);
 kernel_t k1_rows_kernel(int team, int nv, int mode, int wtype, bool tail);

@@ -506,8 +506,10 @@ __device__ __forceinline__ void ks_channel_long(const float (&w)[K * KPT], float
 }
 
 // One workgroup per output channel of N kernels, any N and any alignment; thread t takes kernels
-// t, t + G, ..., G = ceil(N / KPT) in whole fours.
-template <int MODE, int K, int KPT>
+// t, t + G, ..., G = ceil(N / KPT) in whole fours.  HALF: 16-bit weights.  (One routine for both widths waits for the weights
+// before it clears the histogram, see squant_k9.h: 7x7 kernels, 192 a channel, 20 M binary32 weights with E 28.3 us and
+// 25.5 so; 1x2, 64 a channel, 20 M bfloat16 to 4 bit 69.1 and 63.9)
+template <int MODE, int K, int KPT, bool HALF>
 __device__ __forceinline__ void ks_channel(const LaunchArgs& a, const TensorDesc& d, int m,
                                            unsigned char* smem, K9Shared& sh) {
   constexpr bool kChannelStage = MODE == SQUANT_MODE_EKC || MODE == SQUANT_MODE_EC;
@@ -525,22 +527,23 @@ __device__ __forceinline__ void ks_channel(const LaunchArgs& a, const TensorDesc
     for (int q = KPT == 1 ? 1 : 0; q < KPT; ++q) owned &= t + q * G < N ? ~0u : ~(1u << q);
   }
   float w[K * KPT];
+  uint32_t raw[KPT][(K + 1) / 2];
   {
-    const uint32_t each = K * (a.wtype == SQUANT_W_F32 ? 4u : 2u);  // bytes of a kernel
+    constexpr uint32_t each = K * (HALF ? 2u : 4u);  // bytes of a kernel
     const rsrc_t row = make_rsrc(static_cast<const uint8_t*>(d.w) + (size_t)m * N * each, each * (uint32_t)N);
     const uint32_t lane_off = active ? each * (uint32_t)t : 0x40000000u;  // idle threads: out of range
-    if (a.wtype == SQUANT_W_F32) {
 #pragma unroll
-      for (int q = 0; q < KPT; ++q) ks_load_kernel<K>(w, q, row, lane_off, each * (uint32_t)(q * G));
-    } else {
-      uint32_t raw[KPT][(K + 1) / 2];
-#pragma unroll
-      for (int q = 0; q < KPT; ++q) ks_load_kernel16<K>(raw[q], row, lane_off, each * (uint32_t)(q * G));
-      if (a.wtype == SQUANT_W_BF16) ks_widen16<K, KPT, true>(raw, w);
-      else ks_widen16<K, KPT, false>(raw, w);
+    for (int q = 0; q < KPT; ++q) {
+      if (HALF) ks_load_kernel16<K>(raw[q], row, lane_off, each * (uint32_t)(q * G));
+      else ks_load_kernel<K>(w, q, row, lane_off, each * (uint32_t)(q * G));
     }
   }
-  if (kChannelStage) select_reset(sh.sel);  // before the first barrier
+  if (kChannelStage) select_reset(sh.sel);  // before the first barrier, and while the weights are on their way
+  if (HALF) {
+    if (a.wtype == SQUANT_W_BF16) ks_widen16<K, KPT, true>(raw, w);
+    else ks_widen16<K, KPT, false>(raw, w);
+    weights_are_here();
+  }
 
   float amax = 0.0f;
 #pragma unroll
@@ -566,43 +569,43 @@ __device__ __forceinline__ void ks_channel(const LaunchArgs& a, const TensorDesc
 // kernels, which leave a few registers to scratch memory even so.  4x4 and 7x7 kernels went through the generic
 // routine before: 2 x [162, 184, 7, 7] 106 -> 10.2 us, 16 x [256, 64, 7, 7] 234 -> 16.0, 4 x [256, 512, 7, 7] in
 // binary16 941 -> 30, 16 x [512, 64, 4, 4] 49.9 -> 11.1, 2 x [512, 1000, 4, 4] 129 -> 22.3, all to int8.
-template <int MAX_THREADS, int MODE, int K, int KPT>
+template <int MAX_THREADS, int MODE, int K, int KPT, bool HALF>
 __global__ void __launch_bounds__(MAX_THREADS)
     __attribute__((amdgpu_waves_per_eu(MAX_THREADS > 256 ? 1 : K == 49 ? 3 : 5))) squant_channel_ks(LaunchArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];  // K*N bytes of codes
   __shared__ K9Shared sh;
   int m;
   const TensorDesc d = locate(a, blockIdx.x, m);
-  ks_channel<MODE, K, KPT>(a, d, m, smem, sh);
+  ks_channel<MODE, K, KPT, HALF>(a, d, m, smem, sh);
 }
 
 // The routine for a channel of N kernels of K elements in a workgroup of T threads: as few kernels
 // per thread as T allows.
-template <int MODE, int K>
+template <int MODE, int K, bool HALF>
 __device__ __forceinline__ void ks_channel_fit(const LaunchArgs& a, const TensorDesc& d, int m, unsigned char* smem,
                                                K9Shared& sh) {
   constexpr int top = ks_max_kpt_log2(K);
   const int N = d.N, T = blockDim.x;
-  if (N <= T || top < 1) { ks_channel<MODE, K, 1>(a, d, m, smem, sh); return; }
+  if (N <= T || top < 1) { ks_channel<MODE, K, 1, HALF>(a, d, m, smem, sh); return; }
   if constexpr (top >= 1)
-    if (N <= 2 * T) { ks_channel<MODE, K, 2>(a, d, m, smem, sh); return; }
+    if (N <= 2 * T) { ks_channel<MODE, K, 2, HALF>(a, d, m, smem, sh); return; }
   if constexpr (top >= 2)
-    if (N <= 4 * T) { ks_channel<MODE, K, 4>(a, d, m, smem, sh); return; }
-  if constexpr (top >= 3) ks_channel<MODE, K, 8>(a, d, m, smem, sh);
+    if (N <= 4 * T) { ks_channel<MODE, K, 4, HALF>(a, d, m, smem, sh); return; }
+  if constexpr (top >= 3) ks_channel<MODE, K, 8, HALF>(a, d, m, smem, sh);
 }
 
 // For the mixed kernel.
-template <int MODE>
+template <int MODE, bool HALF>
 __device__ __forceinline__ void ks_dispatch(const LaunchArgs& a, const TensorDesc& d, int m, unsigned char* smem,
                                             K9Shared& sh) {
   switch (d.K) {
-    case 2: ks_channel_fit<MODE, 2>(a, d, m, smem, sh); break;
-    case 3: ks_channel_fit<MODE, 3>(a, d, m, smem, sh); break;
-    case 4: ks_channel_fit<MODE, 4>(a, d, m, smem, sh); break;
-    case 5: ks_channel_fit<MODE, 5>(a, d, m, smem, sh); break;
-    case 7: ks_channel_fit<MODE, 7>(a, d, m, smem, sh); break;
-    case 16: ks_channel_fit<MODE, 16>(a, d, m, smem, sh); break;
-    case 25: ks_channel_fit<MODE, 25>(a, d, m, smem, sh); break;
+    case 2: ks_channel_fit<MODE, 2, HALF>(a, d, m, smem, sh); break;
+    case 3: ks_channel_fit<MODE, 3, HALF>(a, d, m, smem, sh); break;
+    case 4: ks_channel_fit<MODE, 4, HALF>(a, d, m, smem, sh); break;
+    case 5: ks_channel_fit<MODE, 5, HALF>(a, d, m, smem, sh); break;
+    case 7: ks_channel_fit<MODE, 7, HALF>(a, d, m, smem, sh); break;
+    case 16: ks_channel_fit<MODE, 16, HALF>(a, d, m, smem, sh); break;
+    case 25: ks_channel_fit<MODE, 25, HALF>(a, d, m, smem, sh); break;
     default: break;  // the host puts no other tensor here
   }
 }

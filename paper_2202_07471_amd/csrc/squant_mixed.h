@@ -86,7 +86,7 @@ __global__ void __launch_bounds__(kMixedMaxThreads)
   } else if (family == 4) {
     k1_team_dispatch<M1, ANY>(a, d, m);
   } else if (ANY && family == 5) {
-    ks_dispatch<MODE>(a, d, m, smem, sh);
+    ks_dispatch<MODE, HALF>(a, d, m, smem, sh);
   } else if (family == kFamilyRows) {
     // 16-bit rows come in vectors of eight: a multiple of four may end in half of one
     K1RowsList* lists = reinterpret_cast<K1RowsList*>(shared);
