@@ -128,18 +128,50 @@ __device__ __forceinline__ int32_t ks_zero_sum_sign(const int32_t (&P)[KP]) {
   return neg > pos ? -1 : 0;
 }
 
+// Cold path for kernels of 16 elements and more: the candidate of a kernel whose perturbations add up to 0, from its
+// weights read once more.  Settled before the keys take the place of the perturbations, as for short kernels, it costs
+// registers in every launch: 7x7, 868 a channel, 20 M binary32 weights with E&C 41.1 us so and 31.8 with this, 5x5, 300 a
+// channel, binary16 23.1 and 18.3.  With E&K&C the keys are kept anyway, and 16-bit weights meet such kernels often (with one
+// load after the other for each, 5x5, 192 a channel, 2 M bfloat16 weights 9.2 us, settled before 6.7): there, and for 16 elements,
+// whose registers suffice, 16-bit kernels settle it before (kHere in ks_channel_long).
+template <int K, bool HALF>
+__device__ __forceinline__ void ks_zero_sum_candidate(rsrc_t row, uint32_t lane_off, bool bf16, float s, float qmaxf, uint32_t& cand_w,
+                                                      int& cand_i) {
+  int32_t best = 0, bv = 0;
+  cand_i = 0;
+  auto offer = [&](float w, int i) {
+    int32_t P;
+    round_and_perturb(w, s, qmaxf, P);
+    const int32_t ap = P < 0 ? -P : P;
+    if (ap > best) { best = ap; bv = P; cand_i = i; }
+  };
+  if (HALF) {
+    uint32_t raw[(K + 1) / 2];
+    ks_load_kernel16<K>(raw, row, lane_off, 0);
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      const uint32_t h = i & 1 ? raw[i / 2] >> 16 : raw[i / 2] & 0xFFFFu;
+      offer(bf16 ? widen_bf16(h) : widen_f16(h), i);
+      __builtin_amdgcn_sched_barrier(0);  // one after the other: registers
+    }
+  } else {
+#pragma unroll 1
+    for (int i = 0; i < K; ++i) offer(__uint_as_float(buffer_load_u1(row, lane_off + 4u * i, 0)), i);
+  }
+  cand_w = candidate_word(bv);
+}
+
 // SQuant-E, SQuant-K and the candidate update for one kernel held in registers (straight-line code, as
-// for 3x3).  Arguments as for k9_solve.
-template <int K, int NW, bool FAST, int MODE>
-__device__ __forceinline__ void ks_solve(const float (&w)[NW], int q, float s, float rs, float qmaxf,
-                                         float (&cf)[K], int32_t& esum, uint32_t& cand_w, int& cand_i) {
+// for 3x3); zero: its perturbations add up to 0, the candidate is not settled.
+template <int K, bool FAST, int MODE, bool HERE>
+__device__ __forceinline__ void ks_solve(const float (&w)[K], float s, float rs, float qmaxf,
+                                         float (&cf)[K], int32_t& esum, uint32_t& cand_w, int& cand_i, bool& zero) {
   constexpr int IB = ks_index_bits<K>(), IM = (1 << IB) - 1;
-  const int W0 = K * q;
   float c[K];
   int32_t P[K];
 #pragma unroll
   for (int i = 0; i < K; ++i) {
-    const float x = FAST ? div_by_reciprocal(w[W0 + i], s, rs) : quotient(w[W0 + i], s);
+    const float x = FAST ? div_by_reciprocal(w[i], s, rs) : quotient(w[i], s);
     const float xc = __builtin_amdgcn_fmed3f(x, -qmaxf, qmaxf);
     c[i] = rintf(xc);
     const float p = c[i] - xc;  // exact
@@ -163,7 +195,8 @@ __device__ __forceinline__ void ks_solve(const float (&w)[NW], int q, float s, f
   const int32_t k = (MODE == SQUANT_MODE_EC) ? 0 : (int32_t)((uint32_t)(A + kHalf - 1) >> 23);
   const int32_t r = A - (k << 23);  // |sum| left after k flips, < 0: over SQuant
   esum += (r ^ smask) - smask;
-  if (MODE != SQUANT_MODE_EK && __builtin_expect(__ballot(E == 0) != 0ull, 0)) smask = E == 0 ? ks_zero_sum_sign<K>(P) : smask;
+  if (!HERE) zero = E == 0;
+  else if (__builtin_expect(__ballot(E == 0) != 0ull, 0)) smask = E == 0 ? ks_zero_sum_sign<K>(P) : smask;
 
   // unique keys: 2^IB |p| + (IM - i) >= 2^IB for the elements with the sign of the sum, below
   // 2^IB for all others; |P| <= 2^22 fits the 24-bit multiply
@@ -190,9 +223,10 @@ __device__ __forceinline__ void ks_solve(const float (&w)[NW], int q, float s, f
 // 14.7 and 15.4 with E&K&C, 12.7 and 13.0 with E&K.
 template <int K, int MODE>
 constexpr bool ks_packed() { return K > 25 || K == 16 || (K == 25 && (MODE == SQUANT_MODE_E || MODE == SQUANT_MODE_EC)); }
-template <int K, bool FAST, int MODE>
+template <int K, bool FAST, int MODE, bool HERE>
 __device__ __forceinline__ void ks_solve_long(const float (&w)[K], float s, float rs, float qmaxf,
-                                              uint32_t (&code)[(K + 3) / 4], int32_t& esum, uint32_t& cand_w, int& cand_i) {
+                                              uint32_t (&code)[(K + 3) / 4], int32_t& esum, uint32_t& cand_w, int& cand_i,
+                                              bool& zero) {
   constexpr int IB = ks_index_bits<K>(), IM = (1 << IB) - 1;
   constexpr int KP = (K + 3) / 4 * 4;
   int32_t key[KP];  // first the perturbations
@@ -229,7 +263,8 @@ __device__ __forceinline__ void ks_solve_long(const float (&w)[K], float s, floa
   const int32_t k = (MODE == SQUANT_MODE_EC) ? 0 : (int32_t)((uint32_t)(A + kHalf - 1) >> 23);
   const int32_t r = A - (k << 23);  // |sum| left after k flips, < 0: over SQuant
   esum += (r ^ smask) - smask;
-  if (MODE != SQUANT_MODE_EK && __builtin_expect(__ballot(E == 0) != 0ull, 0)) smask = E == 0 ? ks_zero_sum_sign<K>(key) : smask;
+  if (!HERE) zero = E == 0;
+  else if (__builtin_expect(__ballot(E == 0) != 0ull, 0)) smask = E == 0 ? ks_zero_sum_sign<K>(key) : smask;
 
   // unique keys: 2^IB |p| + (IM - i) >= 2^IB for the elements with the sign of the sum, below
   // 2^IB for all others; |P| <= 2^22 fits the 24-bit multiply
@@ -261,28 +296,22 @@ __device__ __forceinline__ void ks_solve_long(const float (&w)[K], float s, floa
   ks_candidate<IB>(ck, over, smask, cand_w, cand_i);
 }
 
-template <int K, int KPT, bool FAST, int MODE>
-__device__ __forceinline__ void ks_solve_all(const float (&w)[K * KPT], float s, float rs, float qmaxf,
-                                             uint8_t* code8, int t, int G, uint32_t owned, int32_t& esum,
-                                             uint32_t (&cv)[KPT], int (&ci)[KPT]) {
+// The kernel of a thread: SQuant-E, SQuant-K and its candidate, codes into its bytes of the channel.
+template <int K, bool FAST, int MODE, bool HERE>
+__device__ __forceinline__ void ks_solve_kernel(const float (&w)[K], float s, float rs, float qmaxf, uint8_t* code8, int32_t& esum,
+                                                uint32_t& cand_w, int& cand_i, bool& zero) {
+  if constexpr (ks_packed<K, MODE>()) {
+    uint32_t code[(K + 3) / 4];
+    ks_solve_long<K, FAST, MODE, HERE>(w, s, rs, qmaxf, code, esum, cand_w, cand_i, zero);
 #pragma unroll
-  for (int q = 0; q < KPT; ++q) {
-    if (KPT > 1 && !((owned >> q) & 1u)) continue;
-    const int n = t + q * G;
-    if constexpr (ks_packed<K, MODE>()) {
-      static_assert(KPT == 1, "one kernel per thread");
-      uint32_t code[(K + 3) / 4];
-      ks_solve_long<K, FAST, MODE>(w, s, rs, qmaxf, code, esum, cv[q], ci[q]);
+    for (int i = 0; i < K / 4; ++i) __builtin_memcpy(code8 + 4 * i, &code[i], 4);
 #pragma unroll
-      for (int i = 0; i < K / 4; ++i) __builtin_memcpy(code8 + K * n + 4 * i, &code[i], 4);
+    for (int i = K / 4 * 4; i < K; ++i) code8[i] = (uint8_t)(code[i / 4] >> (8 * (i & 3)));
+  } else {
+    float cf[K];
+    ks_solve<K, FAST, MODE, HERE>(w, s, rs, qmaxf, cf, esum, cand_w, cand_i, zero);
 #pragma unroll
-      for (int i = K / 4 * 4; i < K; ++i) code8[K * n + i] = (uint8_t)(code[i / 4] >> (8 * (i & 3)));
-    } else {
-      float cf[K];
-      ks_solve<K, K * KPT, FAST, MODE>(w, q, s, rs, qmaxf, cf, esum, cv[q], ci[q]);
-#pragma unroll
-      for (int i = 0; i < K; ++i) code8[K * n + i] = (uint8_t)(int)cf[i];
-    }
+    for (int i = 0; i < K; ++i) code8[i] = (uint8_t)(int)cf[i];
   }
 }
 
@@ -469,38 +498,31 @@ __device__ __forceinline__ void ks_channel_short(const float (&w)[K * KPT], floa
   store_kernel_codes<K, KPT == 1>(code8, t, G, owned, kk);
 }
 
-// The same for larger kernels.
-template <int MODE, int K, int KPT>
-__device__ __forceinline__ void ks_channel_long(const float (&w)[K * KPT], float s, bool normal, float qmaxf, int N, int t, int G,
-                                                uint32_t owned, uint8_t* code8, K9Shared& sh) {
+// The same for larger kernels, one a thread; `row`, `lane_off`: where the kernel's weights lie.
+template <int MODE, int K, bool HALF>
+__device__ __forceinline__ void ks_channel_long(const float (&w)[K], float s, bool normal, float qmaxf, int N, int t, bool active,
+                                                uint8_t* code8, K9Shared& sh, rsrc_t row, uint32_t lane_off, bool bf16) {
   constexpr bool kChannelStage = MODE == SQUANT_MODE_EKC || MODE == SQUANT_MODE_EC;
+  constexpr bool kHere = HALF && (MODE == SQUANT_MODE_EKC || K == 16);  // see ks_zero_sum_candidate
   int32_t esum = 0;
-  uint32_t cv[KPT];
-  int ci[KPT];
-#pragma unroll
-  for (int q = 0; q < KPT; ++q) { cv[q] = kNoCandidate; ci[q] = 0; }
-  if (owned) {
-    if (normal) {  // uniform over the workgroup
-      ks_solve_all<K, KPT, true, MODE>(w, s, reciprocal(s), qmaxf, code8, t, G, owned, esum, cv, ci);
-    } else {
-      ks_solve_all<K, KPT, false, MODE>(w, s, 0.0f, qmaxf, code8, t, G, owned, esum, cv, ci);
-    }
+  uint32_t cv[1] = {kNoCandidate};
+  int ci = 0;
+  bool zero = false;
+  if (active) {
+    if (normal) ks_solve_kernel<K, true, MODE, kHere>(w, s, reciprocal(s), qmaxf, code8 + K * t, esum, cv[0], ci, zero);  // uniform
+    else ks_solve_kernel<K, false, MODE, kHere>(w, s, 0.0f, qmaxf, code8 + K * t, esum, cv[0], ci, zero);
   }
   if (kChannelStage) {
-    if (owned) {
-#pragma unroll
-      for (int q = 0; q < KPT; ++q)
-        if ((owned >> q) & 1u) count_candidate(sh.sel, cv[q]);
+    if (active) {
+      if (!kHere && zero) ks_zero_sum_candidate<K, HALF>(row, lane_off, bf16, s, qmaxf, cv[0], ci);
+      count_candidate(sh.sel, cv[0]);
     }
     const int64_t ec = block_sum_dpp1(esum, sh.red_i);
     const int sgn = sign_of(ec);
     const int64_t kc = flips_for(ec < 0 ? -ec : ec);
     if (kc > 0) {
-      int cpos[KPT], cn[KPT];
-#pragma unroll
-      for (int q = 0; q < KPT; ++q) { cn[q] = t + q * G; cpos[q] = K * cn[q] + ci[q]; }
-      channel_stage<KPT, 1>(cv, cpos, cn, sgn, (uint32_t)(kc > N ? N : kc),
-                            reinterpret_cast<uint32_t*>(code8), sh.sel);
+      const int cpos[1] = {K * t + ci}, cn[1] = {t};
+      channel_stage<1, 1>(cv, cpos, cn, sgn, (uint32_t)(kc > N ? N : kc), reinterpret_cast<uint32_t*>(code8), sh.sel);
     }
   }
 }
@@ -528,15 +550,13 @@ __device__ __forceinline__ void ks_channel(const LaunchArgs& a, const TensorDesc
   }
   float w[K * KPT];
   uint32_t raw[KPT][(K + 1) / 2];
-  {
-    constexpr uint32_t each = K * (HALF ? 2u : 4u);  // bytes of a kernel
-    const rsrc_t row = make_rsrc(static_cast<const uint8_t*>(d.w) + (size_t)m * N * each, each * (uint32_t)N);
-    const uint32_t lane_off = active ? each * (uint32_t)t : 0x40000000u;  // idle threads: out of range
+  constexpr uint32_t each = K * (HALF ? 2u : 4u);  // bytes of a kernel
+  const rsrc_t row = make_rsrc(static_cast<const uint8_t*>(d.w) + (size_t)m * N * each, each * (uint32_t)N);
+  const uint32_t lane_off = active ? each * (uint32_t)t : 0x40000000u;  // idle threads: out of range
 #pragma unroll
-    for (int q = 0; q < KPT; ++q) {
-      if (HALF) ks_load_kernel16<K>(raw[q], row, lane_off, each * (uint32_t)(q * G));
-      else ks_load_kernel<K>(w, q, row, lane_off, each * (uint32_t)(q * G));
-    }
+  for (int q = 0; q < KPT; ++q) {
+    if (HALF) ks_load_kernel16<K>(raw[q], row, lane_off, each * (uint32_t)(q * G));
+    else ks_load_kernel<K>(w, q, row, lane_off, each * (uint32_t)(q * G));
   }
   if (kChannelStage) select_reset(sh.sel);  // before the first barrier, and while the weights are on their way
   if (HALF) {
@@ -556,7 +576,8 @@ __device__ __forceinline__ void ks_channel(const LaunchArgs& a, const TensorDesc
   if constexpr (ks_short<K>()) {
     ks_channel_short<MODE, K, KPT>(w, amax, s, normal, qmaxf, N, t, G, owned, code8, sh);
   } else {
-    ks_channel_long<MODE, K, KPT>(w, s, normal, qmaxf, N, t, G, owned, code8, sh);
+    static_assert(KPT == 1, "larger kernels: one a thread");
+    ks_channel_long<MODE, K, HALF>(w, s, normal, qmaxf, N, t, active, code8, sh, row, lane_off, a.wtype == SQUANT_W_BF16);
   }
   if (tid == 0) code8[L] = 128;  // the element a packed row of odd length is short of
   __syncthreads();
@@ -571,7 +592,7 @@ __device__ __forceinline__ void ks_channel(const LaunchArgs& a, const TensorDesc
 // binary16 941 -> 30, 16 x [512, 64, 4, 4] 49.9 -> 11.1, 2 x [512, 1000, 4, 4] 129 -> 22.3, all to int8.
 template <int MAX_THREADS, int MODE, int K, int KPT, bool HALF>
 __global__ void __launch_bounds__(MAX_THREADS)
-    __attribute__((amdgpu_waves_per_eu(MAX_THREADS > 256 ? 1 : K == 49 ? 3 : 5))) squant_channel_ks(LaunchArgs a) {
+    __attribute__((amdgpu_waves_per_eu(K == 16 ? 8 : K == 25 ? 5 : MAX_THREADS > 256 ? 1 : K == 49 ? 3 : 5))) squant_channel_ks(LaunchArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];  // K*N bytes of codes
   __shared__ K9Shared sh;
   int m;
