@@ -495,7 +495,9 @@ __device__ __forceinline__ void ks_channel_short(const float (&w)[K * KPT], floa
 #pragma unroll
     for (int q = 0; q < KPT; ++q) ks_apply_flips<K>(kk[q]);
   }
-  store_kernel_codes<K, KPT == 1>(code8, t, G, owned, kk);
+  // with SQuant-E alone, one kernel of two or three elements a thread: the few bytes one by one (3x1, 64 a channel, 20 M
+  // weights to bfloat16 34.8 us as dwords, 34.4 so)
+  store_kernel_codes<K, KPT == 1>(code8, t, G, owned, kk, !(MODE == SQUANT_MODE_E && K <= 3 && KPT == 1));
 }
 
 // The same for larger kernels, one a thread; `row`, `lane_off`: where the kernel's weights lie.
