@@ -16,8 +16,7 @@
 //     address register for all vectors, and the hardware's range check takes the place of the
 //     per-vector bounds checks (out-of-range dwords read as 0 and are not written);
 //   * SQuant-E is 9.75 instructions an element: three for the exact quotient (two for 16-bit weights, whose quotients
-//     by the scales they can have are exact so: six linear layers in bfloat16 118.4 -> 117.0 us, 16 x [4096, 2048] 87.8 -> 86.2;
-//     rows beyond 45000 elements, one workgroup a compute unit, lose 1 to 2 %: the code is laid out otherwise), rounding by a
+//     by the scales they can have are exact so: six linear layers in bfloat16 118.4 -> 117.0 us, 16 x [4096, 2048] 87.8 -> 86.2), rounding by a
 //     magic addition that leaves code + 128 in the sum's low byte (squant_k9.h), the biased
 //     Q23 perturbation by one FMA.  While the scale is a normal number the clamp to +-qmax can
 //     only move the element that set it, by one rounding, so it is left out and such elements are
@@ -162,15 +161,29 @@ __device__ __forceinline__ int32_t k1_round_all(const float (&w)[NE], float s, f
 #pragma unroll
   for (int i = 0; i < NE / 4; ++i) {
     uint32_t tb[4];
+    float x[4];  // the IEEE quotients
+    // The two operations of 16-bit weights in stages of four elements: left alone the compiler takes one element to its end
+    // before it begins the next, every instruction waits for the one before, and with the two to four waves a SIMD that long
+    // rows have nothing hides that.  64 M weights bfloat16 to int8, us with three operations, with two one element after
+    // the other, and so: cin 24576 52.7, 50.3, 48.0, 32768 49.1, 50.5, 48.3, 50176 79.2, 80.7, 78.6; binary16 to 4 bit 40960 65.6, 65.5, 63.1.
+    if (HALF) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = w[4 * i + e] * rl;
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = __builtin_fmaf(w[4 * i + e], rs, x[e]);  // half_quotient
+      __builtin_amdgcn_sched_barrier(0);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = div_by_reciprocal(w[4 * i + e], s, rs);
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      // the IEEE quotient
-      const float x = HALF ? half_quotient(w[4 * i + e], rs, rl) : div_by_reciprocal(w[4 * i + e], s, rs);
-      const float t = x + kRoundMagic;  // round half to even; code + 128 in the low byte
+      const float t = x[e] + kRoundMagic;  // round half to even; code + 128 in the low byte
       tb[e] = __float_as_uint(t);
       if (WITH_P) {
         const float c = t - kRoundMagic;
-        const float p = c - x;  // exact
+        const float p = c - x[e];  // exact
         const uint32_t pb = __float_as_uint(__builtin_fmaf(p, 8388608.0f, kQ23Magic));
         biased += pb;
         B[4 * i + e] = pb;

@@ -130,7 +130,7 @@ __device__ __forceinline__ int32_t ks_zero_sum_sign(const int32_t (&P)[KP]) {
 
 // Cold path for kernels of 16 elements and more: the candidate of a kernel whose perturbations add up to 0, from its
 // weights read once more.  Settled before the keys take the place of the perturbations, as for short kernels, it costs
-// registers in every launch: 7x7, 868 a channel, 20 M binary32 weights with E&C 41.1 us so and 31.8 with this, 5x5, 300 a
+// registers in every launch: 7x7, 868 a channel, 20 M binary32 weights with E&C 41.1 us so and 31.4 with this, 5x5, 300 a
 // channel, binary16 23.1 and 18.3.  With E&K&C the keys are kept anyway, and 16-bit weights meet such kernels often (with one
 // load after the other for each, 5x5, 192 a channel, 2 M bfloat16 weights 9.2 us, settled before 6.7): there, and for 16 elements,
 // whose registers suffice, 16-bit kernels settle it before (kHere in ks_channel_long).
