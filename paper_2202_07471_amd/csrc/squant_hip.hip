@@ -303,7 +303,7 @@ void shape_rows(Group& g, int wtype, int out_bits) {
     rows += t.M;
     weights += (int64_t)t.M * t.N;
   }
-  const K1Shape sh = k1_launch_shape(nvec, rows, weights * ((wtype == SQUANT_W_F32 ? 32 : 16) + out_bits) / 8);
+  const K1Shape sh = k1_launch_shape(nvec, rows, weights * ((wtype == SQUANT_W_F32 ? 32 : 16) + out_bits) / 8, out_bits == 32);
   g.variant = sh.nv <= 8 ? k1_variant_of(sh.nv) : kK1Wide + sh.nv;
   g.threads = sh.threads;
   g.lds = (size_t)(sh.nv > 8 ? 8 : 4) * sh.threads;  // the owners' masks

@@ -86,50 +86,69 @@ SQ_HD int64_t k1_threads(int64_t nvec, int nv) {
   return round_up64((nvec + nv - 1) / nv);
 }
 
+// The shape of any row held in one workgroup where nothing else is known: beyond kMaxK1Cin elements the fewest vectors per
+// thread, in steps of two, that 1024 threads hold the row with.
+SQ_HD K1Shape k1_usual_shape(int64_t nvec) {
+  if (nvec <= kMaxK1Cin / 4) return k1_shape(nvec);
+  const int64_t least = (nvec + 1023) / 1024, nv = least <= 10 ? 10 : (least + 1) / 2 * 2;
+  return {(int)nv, (int)round_up64((nvec + nv - 1) / nv)};
+}
+
 // The wave-per-channel 1x1 / FC kernel: 16-byte vectors per lane of a channel of N elements.
 SQ_HD int k1_wave_nv(int64_t N) { return (int)((N / 4 + 63) / 64); }
 SQ_HD bool is_k1_wave(int variant) { return variant >= kK1Wave + 2 && variant <= kK1Wave + 8; }
 
 // Launch shape of the 1x1 / FC kernel with SQuant-C in a launch of its own: T threads of NV vectors, the fewest whole waves
-// that hold a row of nvec vectors for each NV the kernel is built for.  `rows`, `bytes`: of the launch, read and written.
-// The shape is the one of the least time by a model with three terms:
-//   * what a row takes from its load to its store when nothing else runs: it grows with the vectors a thread holds;
+// that hold a row of nvec vectors for each NV the kernel is built for, or the shape that a launch without SQuant-C would get.
+// `rows`, `bytes`: of the launch, read and written; wide_out: to binary32.  The shape is the one of the least time by a model:
+//   * what a row takes from its load to its store when nothing else runs: it grows with the vectors a thread holds and with
+//     the waves, whose steps wait for each other;
 //   * instructions, for all T * NV vector slots (an idle vector still runs SQuant-E).  Few vectors a thread leave the fixed
-//     work of a wave to few weights; from ten on a SIMD holds four or five waves instead of seven or eight; five, six and
-//     seven waves share out badly over four SIMDs; and a compute unit holds whole workgroups: of more than eight waves
-//     of ten vectors or more, or sixteen of eight, only one;
-//   * memory, at 7.1 TB/s (launches that fit the caches in part), joined with the second as a 4-norm.
-// Its numbers were fitted to 3900 times: every NV at 95 lengths from 2100 to 65536, 1 M to 130 M weights, binary32 and
-// bfloat16, four outputs.  Over these the model's shape takes 1.2 % more than the best one; k1_shape, whose weights are older
-// than the threshold search, 7 % more.  us of some, best ones first, k1_shape's last, bfloat16 to int8 / binary32 to int8:
+//     work of a wave to few weights; from ten on a SIMD holds four or five waves instead of seven or eight; and numbers of waves
+//     that are no multiple of four share out badly over four SIMDs;
+//   * memory, at 7.33 TB/s (launches that fit the caches in part), joined with the second as a 4-norm;
+//   * where more rows are launched than the chip holds at once, a few percent more, a third with binary32 output (its
+//     workgroups all write at their end): 976 rows of 16384 bfloat16 to binary32 8 x 512, 768 at once, 24.1 us, 16 x 256, 1024, 18.6.
+// A shape other than the usual one has to be two percent better by the model, which is not exact: of 3840 launches (60 lengths
+// from 2052 to 65536, a third of them odd, 0.4 M to 130 M weights, binary32 and bfloat16, four outputs, every NV) 64 are
+// slower by more than 1.2 % than the usual shape, which is 5.4 % slower than the best one in the mean; this choice is 0.6 %.
+// The numbers were fitted to the choice itself on these launches: on half of them, the other half's choice was 0.8 % off the best.
+// (A model fitted to times alone, with some shapes struck out by hand and nothing in favour of the usual one, was 1.4 % off
+// and slower than the usual shape by more than 1.2 % in 388 of them: 2052 bfloat16 to int8, 16 M weights 16.9 us and 18.7, 975
+// rows of 4100 8.7 and 9.9, 549 rows of 16384 binary32 to binary32 16.2 and 21.1.)
+// us of some, best ones first, the usual one last, bfloat16 to int8 / binary32 to int8:
 //   30 M weights  cin  4096  8 x 128 21.8 / 26.6   4 x 256 24.5 / 26.7   16 x 64  24.8 / 30.4
 //                 cin  7168  7 x 256 21.8 / 26.4   8 x 256 23.2 / 27.1   16 x 128 25.9 / 30.3
 //                 cin 12288 12 x 256 22.9 / 27.3   6 x 512 24.3 / 26.8   16 x 192 24.8 / 29.1
 //    4 M weights  cin  4096  4 x 256  8.0 /  8.3   5 x 256  8.9 /  8.8   16 x 64  12.5 / 12.8
 //                 cin  8192  4 x 512  7.9 /  8.3  10 x 256  9.0 /  9.2   16 x 128 11.7 / 12.4
-//   45 M weights  cin 36412 12 x 768 57.1 / 65.8  14 x 704 60.9 / 68.2   10 x 960 61.1 / 70.7 (the fewest vectors a thread)
-// Thirteen to fifteen waves are left out below 32768 elements (76 rows of 26001 17.3 with 7 x 960, 13.9 with 14 x 512), and so
-// are nine to eleven and sixteen of eight vectors (90 rows of 22001 12.6 with 8 x 704, 10.9 with 12 x 512).
-inline K1Shape k1_launch_shape(int64_t nvec, int64_t rows, int64_t bytes) {
-  const bool wide = nvec > kMaxK1Cin / 4;
-  struct Vectors { int nv; float row_us, slot; };  // slot: relative instructions of a vector slot
-  const Vectors built[9] = {{4, 1.7f, 1.25f}, {5, 2.0f, 1.12f}, {6, 2.4f, 1.02f}, {7, 2.6f, 1.00f}, {8, 3.1f, 1.12f},
-                            {10, 3.3f, 1.25f}, {12, 4.1f, 1.17f}, {14, 4.6f, 1.25f}, {16, 5.2f, 1.22f}};
-  // by waves, for up to seven, eight and more vectors a thread
-  const float of_waves[3][16] = {
-      {1.00f, 0.63f, 0.66f, 0.68f, 0.95f, 0.99f, 1.01f, 0.82f, 1.08f, 1.15f, 1.12f, 1.07f, 1.43f, 1.47f, 1.34f, 1.06f},
-      {1.00f, 0.52f, 0.61f, 0.63f, 0.87f, 0.84f, 0.86f, 0.76f, 1.15f, 1.14f, 1.07f, 0.96f, 1.77f, 1.77f, 1.75f, 1.60f},
-      {0.48f, 0.51f, 0.61f, 0.56f, 0.99f, 1.01f, 0.91f, 0.79f, 1.52f, 1.46f, 1.45f, 1.41f, 1.46f, 1.41f, 1.35f, 1.26f}};
-  const float memory_us = (float)bytes / 7.1e6f;
-  K1Shape best = {16, 1024};
+//   45 M weights  cin 36412 12 x 768 57.1 / 65.8  14 x 704 60.9 / 68.2   10 x 960 61.1 / 70.7
+struct K1Built { int nv; float row_us, slot; int waves; };  // slot: relative instructions of a vector slot; waves: a compute unit holds
+constexpr K1Built kK1Built[9] = {{4, 6.24f, 1.09f, 32}, {5, 6.61f, 0.95f, 32}, {6, 6.97f, 0.88f, 32}, {7, 7.33f, 0.78f, 32}, {8, 7.65f, 0.92f, 28},
+                                 {10, 8.25f, 1.10f, 20}, {12, 8.58f, 1.04f, 20}, {14, 8.73f, 1.14f, 16}, {16, 10.60f, 1.16f, 16}};
+inline float k1_launch_us(const K1Built& v, int64_t T, int64_t rows, int64_t bytes, bool wide_out) {
+  // relative instructions by waves, for up to seven, eight and more vectors a thread
+  constexpr float of_waves[3][16] = {
+      {1.04f, 0.61f, 0.57f, 0.60f, 1.12f, 1.15f, 0.95f, 0.72f, 1.17f, 1.45f, 1.03f, 0.95f, 1.43f, 1.43f, 2.08f, 0.86f},
+      {0.84f, 0.46f, 0.65f, 0.54f, 0.80f, 1.08f, 0.82f, 0.75f, 1.29f, 0.99f, 1.05f, 0.88f, 2.08f, 1.59f, 2.18f, 1.36f},
+      {0.41f, 0.40f, 0.52f, 0.46f, 0.92f, 0.97f, 0.77f, 0.51f, 2.37f, 1.55f, 1.21f, 1.15f, 2.00f, 1.65f, 1.98f, 1.27f}};
+  const int waves = (int)(T / 64);
+  const float work = (float)rows * (float)(v.nv * T) * v.slot * of_waves[v.nv <= 7 ? 0 : v.nv == 8 ? 1 : 2][waves - 1] * 2.955e-6f;
+  const float memory = (float)bytes / 7.33e6f, w2 = work * work, m2 = memory * memory;
+  const float us = v.row_us + 2.78f * (float)waves / 16.0f + __builtin_sqrtf(__builtin_sqrtf(w2 * w2 + m2 * m2));
+  const int at_once = v.waves / waves;  // workgroups of a compute unit
+  const float rounds = (float)rows / (256.0f * (float)(at_once > 0 ? at_once : 1));
+  return rounds > 1.0f ? us * (1.0f + (wide_out ? 0.34f : 0.06f) / (1.0f + 0.09f * (rounds - 1.0f))) : us;
+}
+inline K1Shape k1_launch_shape(int64_t nvec, int64_t rows, int64_t bytes, bool wide_out) {
+  K1Shape best = k1_usual_shape(nvec);
   float best_us = 3.0e38f;
-  for (const Vectors& v : built) {
+  for (const K1Built& v : kK1Built)
+    if (v.nv == best.nv) best_us = 0.98f * k1_launch_us(v, best.threads, rows, bytes, wide_out);
+  for (const K1Built& v : kK1Built) {
     const int64_t T = round_up64((nvec + v.nv - 1) / v.nv);
-    const int waves = (int)(T / 64);
-    if (T > 1024 || (wide ? v.nv < 10 : (waves > 12 && waves < 16) || (v.nv == 8 && waves > 8 && waves != 12))) continue;
-    const float work_us = (float)rows * (float)(v.nv * T) * v.slot * of_waves[v.nv <= 7 ? 0 : v.nv == 8 ? 1 : 2][waves - 1] * 2.955e-6f;
-    const float w2 = work_us * work_us, m2 = memory_us * memory_us;
-    const float us = v.row_us + __builtin_sqrtf(__builtin_sqrtf(w2 * w2 + m2 * m2));
+    if (T > 1024) continue;
+    const float us = k1_launch_us(v, T, rows, bytes, wide_out);
     if (us < best_us) { best_us = us; best.nv = v.nv; best.threads = (int)T; }
   }
   return best;
@@ -364,10 +383,7 @@ SQ_HD int variant_of_family(int family, int64_t N, int64_t K, bool aligned) {
   if (family == 4) return kK1Team;
   if (family == 6) return kK1Wave + k1_wave_nv(N + 3);
   if (family == 1 && N <= kMaxK1Cin) return k1_variant_of(k1_nv_for((N + 3) / 4));
-  if (family == 1) {  // the fewest vectors per thread, in steps of two, that 1024 threads hold the row with
-    const int64_t nv = ((N + 3) / 4 + 1023) / 1024;
-    return kK1Wide + (int)(nv <= 10 ? 10 : (nv + 1) / 2 * 2);
-  }
+  if (family == 1) return kK1Wide + k1_usual_shape((N + 3) / 4).nv;
   return ks_variant(K, ks_kpt_log2_any(N, K, aligned));
 }
 SQ_HD int route_variant(int64_t M, int64_t N, int64_t K, bool aligned) {

@@ -12,8 +12,8 @@ int main() {
   long bad = 0, shapes = 0;
   for (int64_t n = kMaxWaveCin + 1; n <= kMaxWideCin; ++n)
     for (int64_t rows : {1, 64, 300, 2000, 40000})
-      for (int64_t half_bytes : {5, 6, 10, 16}) {  // per weight, read and written
-        const K1Shape s = k1_launch_shape((n + 3) / 4, rows, rows * n * half_bytes / 2);
+      for (int64_t half_bytes : {5, 6, 10, 12, 16}) {  // per weight, read and written
+        const K1Shape s = k1_launch_shape((n + 3) / 4, rows, rows * n * half_bytes / 2, half_bytes >= 12);
         bool built = false;
         for (int nv : {4, 5, 6, 7, 8, 10, 12, 14, 16}) built |= s.nv == nv;
         bad += !built || s.threads % 64 != 0 || s.threads < 64 || s.threads > 1024 || (int64_t)s.nv * s.threads < (n + 3) / 4;

@@ -1,7 +1,7 @@
 // Prints, for each line "cout cin elements aligned" on standard input, how the planner routes such a tensor: its family,
 // and for the kernels that hold whole channels of small kernels in registers (families 5 and 9) the kernels and threads
-// of a launch of its own.  With an argument "rows" the lines are "longest rows bytes" and the answer is the launch shape
-// of 1x1 / FC rows with SQuant-C: vectors and threads.
+// of a launch of its own.  With an argument "rows" the lines are "longest rows bytes wide" (wide: 1 for
+// binary32 output) and the answer is the launch shape of 1x1 / FC rows with SQuant-C: vectors and threads.
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
@@ -13,8 +13,8 @@ using namespace squant;
 int main(int argc, char** argv) {
   long long a, b, c, d;
   if (argc > 1 && std::strcmp(argv[1], "rows") == 0) {
-    while (std::scanf("%lld %lld %lld", &a, &b, &c) == 3) {
-      const K1Shape s = k1_launch_shape((a + 3) / 4, b, c);
+    while (std::scanf("%lld %lld %lld %lld", &a, &b, &c, &d) == 4) {
+      const K1Shape s = k1_launch_shape((a + 3) / 4, b, c, d != 0);
       std::printf("%d %d\n", s.nv, s.threads);
     }
     return 0;

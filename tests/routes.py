@@ -29,7 +29,8 @@ def routes(shapes, aligned=True):
 
 
 def row_shapes(launches):
-    """(vectors a thread, threads) of launches of 1x1 / FC rows with SQuant-C: (longest row, rows, bytes moved) each."""
+    """(vectors a thread, threads) of launches of 1x1 / FC rows with SQuant-C: (longest row, rows, bytes moved, binary32
+    output) each."""
     return _ask(launches, "rows")
 
 

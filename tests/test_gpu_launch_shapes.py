@@ -46,7 +46,7 @@ def launches(dtype, tail, out_bits):
     sizes = [(n // 8 * 8 + off, rows) for n in LENGTHS for off in offs
              for rows in sorted({8, 300, 2_000_000 // n, 6_000_000 // n, 16_000_000 // n})]
     found = {}
-    for size, (nv, _) in zip(sizes, routes.row_shapes([(n, rows, n * rows * (bits + out_bits) // 8) for n, rows in sizes])):
+    for size, (nv, _) in zip(sizes, routes.row_shapes([(n, rows, n * rows * (bits + out_bits) // 8, out_bits == 32) for n, rows in sizes])):
         found.setdefault(nv, size)
     assert set(found) == set(VECTORS)
     return found
