@@ -4,18 +4,24 @@
 
 #include "squant_k1.h"
 #include "squant_k1_stream.h"
+#include "squant_plan.h"
 
 namespace squant {
 namespace {
 
+template <int NV, int MODE>
+kernel_t k1_of(bool half, bool tail) {
+  static const kernel_t k[2][2] = {{squant_channel_k1<MODE, NV, false, false>, squant_channel_k1<MODE, NV, false, true>},
+                                   {squant_channel_k1<MODE, NV, true, false>, squant_channel_k1<MODE, NV, true, true>}};
+  return k[half][tail];
+}
 template <int NV>
-kernel_t k1_of(bool channel_stage, bool half, bool tail) {
-  static const kernel_t k[2][2][2] = {
-      {{squant_channel_k1<SQUANT_MODE_E, NV, false, false>, squant_channel_k1<SQUANT_MODE_E, NV, false, true>},
-       {squant_channel_k1<SQUANT_MODE_E, NV, true, false>, squant_channel_k1<SQUANT_MODE_E, NV, true, true>}},
-      {{squant_channel_k1<SQUANT_MODE_EKC, NV, false, false>, squant_channel_k1<SQUANT_MODE_EKC, NV, false, true>},
-       {squant_channel_k1<SQUANT_MODE_EKC, NV, true, false>, squant_channel_k1<SQUANT_MODE_EKC, NV, true, true>}}};
-  return k[channel_stage][half][tail];
+kernel_t k1_of_nv(bool stage, bool half, bool tail) {
+  if constexpr (k1_built(NV, true))
+    if (stage) return k1_of<NV, SQUANT_MODE_EKC>(half, tail);
+  if constexpr (k1_built(NV, false))
+    if (!stage) return k1_of<NV, SQUANT_MODE_E>(half, tail);
+  return nullptr;
 }
 
 }  // namespace
@@ -23,18 +29,15 @@ kernel_t k1_of(bool channel_stage, bool half, bool tail) {
 kernel_t k1_kernel(int nv, int mode, int wtype, bool tail) {
   const bool stage = mode == SQUANT_MODE_EKC || mode == SQUANT_MODE_EC, half = wtype != SQUANT_W_F32;
   switch (nv) {
-    case 1: return k1_of<1>(stage, half, tail);
-    case 2: return k1_of<2>(stage, half, tail);
-    case 3: return k1_of<3>(stage, half, tail);
-    case 4: return k1_of<4>(stage, half, tail);
-    case 5: return k1_of<5>(stage, half, tail);
-    case 6: return k1_of<6>(stage, half, tail);
-    case 7: return k1_of<7>(stage, half, tail);
-    case 8: return k1_of<8>(stage, half, tail);
-    case 10: return k1_of<10>(stage, half, tail);
-    case 12: return k1_of<12>(stage, half, tail);
-    case 14: return k1_of<14>(stage, half, tail);
-    case 16: return k1_of<16>(stage, half, tail);
+    case 4: return k1_of_nv<4>(stage, half, tail);
+    case 5: return k1_of_nv<5>(stage, half, tail);
+    case 6: return k1_of_nv<6>(stage, half, tail);
+    case 7: return k1_of_nv<7>(stage, half, tail);
+    case 8: return k1_of_nv<8>(stage, half, tail);
+    case 10: return k1_of_nv<10>(stage, half, tail);
+    case 12: return k1_of_nv<12>(stage, half, tail);
+    case 14: return k1_of_nv<14>(stage, half, tail);
+    case 16: return k1_of_nv<16>(stage, half, tail);
     default: return nullptr;
   }
 }

@@ -126,6 +126,10 @@ SQ_HD bool is_k1_wave(int variant) { return variant >= kK1Wave + 2 && variant <=
 struct K1Built { int nv; float row_us, slot; int waves; };  // slot: relative instructions of a vector slot; waves: a compute unit holds
 constexpr K1Built kK1Built[9] = {{4, 6.24f, 1.09f, 32}, {5, 6.61f, 0.95f, 32}, {6, 6.97f, 0.88f, 32}, {7, 7.33f, 0.78f, 32}, {8, 7.65f, 0.92f, 28},
                                  {10, 8.25f, 1.10f, 20}, {12, 8.58f, 1.04f, 20}, {14, 8.73f, 1.14f, 16}, {16, 10.60f, 1.16f, 16}};
+// Vectors per thread that launches of their own are built for: with SQuant-C those above, without it what k1_usual_shape gives.
+SQ_HD constexpr bool k1_built(int nv, bool stage) {
+  return stage ? nv >= 4 && nv <= 16 && (nv <= 8 || nv % 2 == 0) : nv == 5 || nv == 6 || (nv >= 10 && nv <= 16 && nv % 2 == 0);
+}
 inline float k1_launch_us(const K1Built& v, int64_t T, int64_t rows, int64_t bytes, bool wide_out) {
   // relative instructions by waves, for up to seven, eight and more vectors a thread
   constexpr float of_waves[3][16] = {
