@@ -169,11 +169,11 @@ Plan plan_variant(int variant, int64_t N, int64_t K, int lds_limit) {
     }
     default: break;
   }
-  if (is_ks(variant)) {  // LDS: as for 3x3, and a dword per kernel for SQuant-C's ranking list before
+  if (is_ks(variant)) {  // LDS: as for 3x3, or a dword per kernel for SQuant-C's ranking list before
     const int64_t kpt = ks_variant_kpt(variant);
     const int th = (int)round_up64((N + kpt - 1) / kpt);
     const int mix = ks_mixes(N, K) ? mixed_threads(th, N, 1 << ks_max_kpt_log2(K)) : 0;
-    return Plan{variant, th, round_up((size_t)std::max<int64_t>(K, 4) * N + 1, 32), mix};
+    return Plan{variant, th, ks_lds_bytes(N, K), mix};
   }
   const size_t lds = generic_lds_bytes(N, K);
   if (lds + kStaticLds > (size_t)lds_limit) return stream_plan(N);

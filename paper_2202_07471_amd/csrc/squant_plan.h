@@ -2,6 +2,7 @@
 // by it and hands the mixed kernel the family in the tensor's descriptor.
 #pragma once
 
+#include <stddef.h>
 #include <stdint.h>
 
 #include "squant_arith.h"  // SQ_HD
@@ -245,6 +246,12 @@ SQ_HD int ks_kpt_log2(int64_t N, int64_t K) {
     if (num * best_den > best_num * th) { best_num = num; best_den = th; best = lg; }
   }
   return best;
+}
+// LDS of a channel: its codes and one more, and before them a dword per kernel for SQuant-C's ranking list (they take the same
+// place).  Whole chunks of 32, so 512 kernels of two elements stay in a class of 2 KB, 1024 in 4 KB.
+SQ_HD size_t ks_lds_bytes(int64_t N, int64_t K) {
+  const int64_t codes = K * N + 1, list = 4 * N, most = codes > list ? codes : list;
+  return (size_t)((most + 31) / 32 * 32);
 }
 SQ_HD bool is_ks(int variant) { return variant >= kKs && variant < kKs + 4 * (kKsMaxK + 1); }
 SQ_HD int ks_variant(int64_t K, int kpt_log2) { return kKs + 4 * (int)K + kpt_log2; }

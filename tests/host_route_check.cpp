@@ -56,6 +56,8 @@ int main() {
             const int c = ks_variant_kpt(v), top = 1 << ks_max_kpt_log2(K);
             const int64_t th = round_up64((N + c - 1) / c);
             bad += !ks_has(K) || ks_variant_k(v) != K || N < 2 || c > top || th * c < N || th > 1024 || (c != top && th > 256);
+            const int64_t lds = (int64_t)ks_lds_bytes(N, K);   // the codes and one more, or the ranking list, and no more
+            bad += lds < K * N + 1 || lds < 4 * N || lds >= (K * N + 1 > 4 * N ? K * N + 1 : 4 * N) + 32;
           } else if (family == 7) {
             bad += N != 1 || K > kMaxDwK || dw_team_lanes(K) < K;
             bad += route_work_items(130, N, K, 64, family, 1) != (130 + 64 / dw_team_lanes(K) - 1) / (64 / dw_team_lanes(K));
