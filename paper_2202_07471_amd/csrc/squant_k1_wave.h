@@ -79,10 +79,12 @@ __device__ __forceinline__ void k1_wave_dispatch(const LaunchArgs& a, const Tens
 }
 
 // One kernel per vector count.  The next channel's weights share the registers with the
-// current channel's perturbations and codes.
+// current channel's perturbations and codes.  Five vectors are held to
+// 80 VGPRs, 72 in 16 bits: the compiler left at five waves a SIMD takes 79 or 85, 71 or 79, as small changes elsewhere have it
+// (to int8, us with 85 / 79 and so: 32 x [1224, 1224] binary32 45.4, 43.4; 32 x [1100, 1100] binary32 39.3, 37.9, bfloat16 33.9, 31.9).
 template <int MODE, int NV, bool HALF, bool TAIL>
 __global__ void __launch_bounds__(256)
-    __attribute__((amdgpu_waves_per_eu(NV <= 3 ? 8 : NV <= 4 ? 6 : NV <= 6 ? 5 : 4)))
+    __attribute__((amdgpu_waves_per_eu(NV <= 3 ? 8 : NV == 4 ? 6 : NV == 5 ? (HALF ? 7 : 6) : NV <= 6 ? 5 : 4)))
     squant_channel_k1_wave(LaunchArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];  // one K1WaveSel per wave
   int item;
