@@ -455,7 +455,8 @@ constexpr int kWHalf = 3;  // weight type of a kernel: binary16 or bfloat16, the
 //   ANY  any cin and any alignment: G = ceil(cin / KPT), in whole fours, the kernels past the channel's end read
 //        as zeros through the range of the row's descriptor, and the row is written through one.
 //        (Otherwise cin is a multiple of four, weights start on 16 bytes and codes on four.)
-template <int MODE, int KPT, int WT, int NWC = 0, bool ANY = false>
+//   OWN  a launch of 3x3 kernels only
+template <int MODE, int KPT, int WT, int NWC = 0, bool ANY = false, bool OWN = false>
 __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc& d, int m,
                                            unsigned char* smem, K9Shared& sh) {
   constexpr bool kChannelStage = MODE == SQUANT_MODE_EKC || MODE == SQUANT_MODE_EC;
@@ -558,10 +559,16 @@ __device__ __forceinline__ void k9_channel(const LaunchArgs& a, const TensorDesc
     for (int q = 0; q < KPT; ++q) k9_apply_flips(kk[q]);
   }
 
-  // Putting dwords together costs vector instructions where the LDS has time to spare: the largest binary32 launches,
-  // bound by memory and the power that it and the arithmetic share, keep to stores that are not aligned (256 x [512, 512, 3, 3] 492 us
-  // so, 500 with dwords, with E&C 64 of them 125 and 129; but 32 59.2 and 58.4, two 7.6 and 7.0, and bfloat16 to 4 bit 64 104 and 96).
-  const bool quads = !(WT == SQUANT_W_F32 && NWC == 2 && !ANY) || a.total < 32768;
+  // Putting dwords together costs vector instructions where the LDS has time to spare.  Two kinds of binary32 launches keep to
+  // stores that are not aligned.  The largest of two waves a channel, bound by memory and the power that it and the arithmetic
+  // share: 256 x [512, 512, 3, 3] 492 us so, 500 with dwords, but 32 59.2 and 58.4, two 7.6 and 7.0.  And layers of fewer than 64 kernels a
+  // channel in a launch of their own, 20 M weights to int8: 33 a channel 36.0 and 36.8 us, 36 33.3 and 33.8, 48 26.2 and 26.6.  Everywhere else dwords
+  // are as fast or faster, 20 M and 100 M weights: 64 21.3 and 21.3, 100.2 and 100.4, 128 18.8 and 18.7, 83.2 and 82.9, 256 18.8 and 18.3, 87.5 and 87.5,
+  // 1024 21.1 and 19.6, 86.4 and 86.5, 2048 28.4 and 24.3, 111 and 94.7, except four a thread in one wave of less than 60 lanes, 160
+  // 21.1 and 21.2, 97.8 and 98.9, 200 20.3 and 20.3, 89.2 and 89.7.
+  bool quads = true;
+  if (WT == SQUANT_W_F32 && NWC == 2 && !ANY) quads = a.total < 32768;
+  if (WT == SQUANT_W_F32 && KPT == 1 && OWN) quads = N >= kWave;
   store_kernel_codes<9, !ANY>(code8, tid, G, owned, kk, quads);
   if (ANY && tid == 0) code8[L] = 128;  // the element a packed row of odd length is short of
   __syncthreads();
@@ -579,7 +586,7 @@ __global__ void __launch_bounds__(MAX_THREADS) __attribute__((amdgpu_waves_per_e
   __shared__ K9Shared sh;
   int m;
   const TensorDesc d = locate(a, blockIdx.x, m);
-  k9_channel<MODE, KPT, WT, NWC, ANY>(a, d, m, smem, sh);
+  k9_channel<MODE, KPT, WT, NWC, ANY, true>(a, d, m, smem, sh);
 }
 
 // ---------------------------------------------------------------------------
