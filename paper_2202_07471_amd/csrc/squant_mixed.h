@@ -70,6 +70,11 @@ __global__ void __launch_bounds__(kMixedMaxThreads)
     } else if (d.N <= 2 * T) {
       k9_channel<MODE, 2, kWeights, 0, ANY>(a, d, m, smem, sh);
     } else if (T == 2 * kWave) {
+      // Keeps the two routines of four kernels a thread apart: the compiler otherwise joins their 16-bit loads ahead of the
+      // branch, which took 82 registers for 62 with SQuant-E alone, 96 and 24 bytes of scratch memory for 78 with E&K and 56 bytes
+      // with E&K&C (binary16, us so joined and now: ResNet-18 set with E 9.6 and 9.2, with E&K 11.4 and 10.6, of twice the width with
+      // E&K&C 52.8 and 43.8, ResNet-50 set of twice the width 90.8 and 83.3; ResNet-18 set with E&K&C 13.6 and 13.7).
+      if (HALF) asm volatile("");
       k9_channel<MODE, 4, kWeights, 2, ANY>(a, d, m, smem, sh);
     } else {
       k9_channel<MODE, 4, kWeights, 0, ANY>(a, d, m, smem, sh);
