@@ -56,6 +56,25 @@ def test_alone(sq, kh, kw, kind):
             check(sq, w, out, s, mode, output)
 
 
+@pytest.mark.parametrize("output", ["INT8", "INT4", "F32"])
+def test_narrow_binary32(sq, output):
+    """Fewer than 64 kernels a channel: stores that are not aligned, and dwords from 64 on."""
+    gen = torch.Generator().manual_seed(5)
+    shapes = [(routes.enough(cin, 9, 65), cin, 3, 3) for cin in (33, 35, 36, 48, 60, 61, 63, 64)]
+    assert {(family, kpt) for family, kpt, _ in routes.routes(shapes)} == {(routes.K9, 1)}
+    for shape in shapes:
+        for kind in ("normal", "equal"):
+            w = weights(shape, kind, gen).cuda()
+            for mode in (sq.MODE_E, sq.MODE_EK, sq.MODE_EKC, sq.MODE_EC):
+                out, s = sq.squant_quantize_ex(w, 4, mode, getattr(sq, "OUT_" + output))
+                if output == "F32":
+                    codes, want_s = oracle.quantize(w.cpu().numpy(), 4, mode, threads=8)
+                    want = codes.astype(np.float32) * want_s.reshape(-1, 1, 1, 1)
+                    assert np.array_equal(out.cpu().numpy(), want.reshape(shape)), (shape, kind, mode)
+                else:
+                    check(sq, w, out, s, mode, getattr(sq, "OUT_" + output))
+
+
 def test_most_kernels_a_thread(sq):
     gen = torch.Generator().manual_seed(1)
     for shape in ((3, 8192, 1, 2), (3, 8189, 1, 3), (3, 8190, 2, 2), (3, 4094, 1, 7)):
